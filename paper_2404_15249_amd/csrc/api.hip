@@ -5,7 +5,6 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
-#include <queue>
 #include <cstring>
 #include <new>
 #include <string>
@@ -79,7 +78,7 @@ struct kfbi_prob {
     int N = 0, n = 0, M = 0, Q = 0, I = 0;
     int Rm = 8, G = 1;           // sine modes per sparse-fast-solve workgroup; workgroups = ceil(n / Rm)
     DevPlan dp{};                // the double-layer operator's view (see plan_view)
-    const double* cp_wn = nullptr;   // 6 M: weights of d_n v+ at the samples (the Neumann operator)
+    const double* cp_wn = nullptr;   // 6 x M: weights of d_n v+ at the samples (the Neumann operator)
     std::vector<void*> allocs;
     size_t bytes = 0;
     // work buffers
@@ -736,7 +735,9 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         return set_err(KFBI_ERR_UNSUPPORTED, "more than " + std::to_string(kMaxSamples) + " samples");
     }
     // modes per workgroup of the sparse fast solve: the most the LDS holds that
-    // still leaves a workgroup for at least half of the compute units
+    // still leaves a workgroup for every compute unit (at 1024^2, 8 modes in 128
+    // workgroups take 28.4 us a GMRES step and 4 in 256 take 27.3; at 2048^2 4 in
+    // 512 take 40.1 and 8 in 256 31.3), never 1: a pair shares its sines
     {
         int rmax = 0;
         for (int r = kMaxModesPerGroup; r >= 1 && !rmax; r /= 2)
@@ -745,9 +746,9 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
             delete p;
             return set_err(KFBI_ERR_UNSUPPORTED, "problem too large for the local data share");
         }
-        p->Rm = 1;
-        for (int r = rmax; r >= 1; r /= 2)
-            if ((p->n + r - 1) / r >= ctx->num_cu / 2 || r == 1) {
+        p->Rm = 2;
+        for (int r = rmax; r >= 2; r /= 2)
+            if ((p->n + r - 1) / r >= ctx->num_cu) {
                 p->Rm = r;
                 break;
             }
@@ -788,83 +789,87 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     const int K = 30;
     dp.K = K;
     std::vector<int> colptr(P.col_ptr.begin(), P.col_ptr.end());
-    // node table of the sparse sine sums: kModeWaves sub-tables of 64 lanes
-    // (512 workers).  A column's nodes form one piece, or several pieces of at
-    // most `cap` nodes when the column is long (its extra pieces' sums are added
-    // to the first piece's in a fixed order); pieces go largest first to the
-    // least loaded worker, each worker's pieces in order, and sub-table w's rows
-    // are the longest worker list among its lanes
+    // node table of the sparse sine sums (see DevPlan::il_ij).  A column's nodes
+    // with even j and those with odd j are summed apart (the mirrored modes l and
+    // N - l share their sines up to the sign (-1)^(j+1)): each half forms one
+    // piece, or several of at most `cap` nodes when it is long (its extra pieces'
+    // sums are added to the first piece's in a fixed order).  Pieces go by
+    // falling length into steps of 64, the steps, longest first, to the
+    // wavefront (sub-table) with the fewest rows so far
     std::vector<int> sub_off(kModeWaves + 1, 0), il_ij, il_pos(std::max(p->I, 1), 0), split;
     {
         constexpr int NW = kModeWaves * 64;
-        auto xpos_of = [&](int i) { return i + (i - 1) / (n / 64); };
+        auto xpos_of = [&](int i) { return i + (i - 1) / modes_chunk(n); };
+        std::vector<std::vector<int>> half(2 * (n + 1));      // parity q, column i: nodes at q (n + 1) + i
+        for (int i = 0; i <= n; ++i)
+            for (int r = colptr[i]; r < colptr[i + 1]; ++r) half[(P.irr_j[r] & 1) * (n + 1) + i].push_back(r);
         int cap = std::max(1, (p->I + NW - 1) / NW);
         for (;;) {
             long extra = 0;
-            for (int i = 0; i <= n; ++i) extra += std::max(0, (colptr[i + 1] - colptr[i] + cap - 1) / cap - 1);
+            for (const auto& v : half) extra += std::max(0, ((int)v.size() + cap - 1) / cap - 1);
             if (extra <= kMaxExtra) break;
             cap *= 2;
         }
         struct Piece {
-            int first, count, dest;
+            const int* first;
+            int count, dest;
         };
         std::vector<Piece> pieces;
         int n_extra = 0;
-        for (int i = 0; i <= n; ++i) {
-            const int cnt = colptr[i + 1] - colptr[i];
+        for (int c = 0; c < (int)half.size(); ++c) {
+            const int cnt = (int)half[c].size(), pos = xpos_of(c % (n + 1)) + c / (n + 1) * modes_stride_of(n);
             if (cnt == 0) continue;
             const int np = (cnt + cap - 1) / cap;
             if (np > 1) {
-                split.push_back(xpos_of(i));
+                split.push_back(pos);
                 split.push_back(n_extra);
                 split.push_back(np - 1);
             }
-            for (int k = 0; k < np; ++k) {
-                const int a = colptr[i] + k * cap, b = std::min(colptr[i + 1], a + cap);
-                pieces.push_back({a, b - a, k == 0 ? xpos_of(i) : (kExtraFlag | n_extra++)});
-            }
+            for (int k = 0; k < np; ++k)
+                pieces.push_back({half[c].data() + k * cap, std::min(cnt - k * cap, cap),
+                                  k == 0 ? pos : 2 * modes_stride_of(n) + n_extra++});
         }
-        std::vector<int> order(pieces.size());
-        for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int a, int b) { return pieces[a].count > pieces[b].count; });
-        using Load = std::pair<int, int>;               // (nodes so far, worker)
-        std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-        for (int w = 0; w < NW; ++w) heap.push({0, w});
-        std::vector<std::vector<int>> wpieces(NW);
-        std::vector<int> load(NW, 0);
-        for (int k : order) {
-            const Load top = heap.top();
-            heap.pop();
-            wpieces[top.second].push_back(k);
-            load[top.second] += pieces[k].count;
-            heap.push({load[top.second], top.second});
+        std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& b) { return a.count > b.count; });
+        const int n_steps = ((int)pieces.size() + 63) / 64;
+        std::vector<std::vector<int>> wsteps(kModeWaves);
+        std::vector<int> load(kModeWaves, 0);
+        for (int s = 0; s < n_steps; ++s) {
+            const int w = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            wsteps[w].push_back(s);
+            load[w] += pieces[64 * s].count;
         }
-        for (int w = 0; w < kModeWaves; ++w) {
-            int t = 0;
-            for (int L = 0; L < 64; ++L) t = std::max(t, load[w * 64 + L]);
-            sub_off[w + 1] = sub_off[w] + (t + kSlots - 1) / kSlots * kSlots;
-        }
+        for (int w = 0; w < kModeWaves; ++w) sub_off[w + 1] = sub_off[w] + (load[w] + kSlots - 1) / kSlots * kSlots;
         const int T = std::max(sub_off[kModeWaves], kSlots);
         dp.T = T;
         il_ij.assign((size_t)T * 64, 0);
-        for (int w = 0; w < NW; ++w) {
-            const int sub = w / 64, L = w % 64;
-            int t = sub_off[sub];
-            for (int k : wpieces[w]) {
-                const Piece& pc = pieces[k];
-                for (int r = pc.first; r < pc.first + pc.count; ++r, ++t) {
-                    const size_t slot = (size_t)t * 64 + L;
-                    const bool last = r + 1 == pc.first + pc.count;
-                    il_ij[slot] = (last ? (int)0x80000000u : 0) | (pc.dest << 16) | P.irr_j[r];
-                    il_pos[r] = (int)slot;
+        for (int w = 0; w < kModeWaves; ++w) {
+            int t = sub_off[w];
+            for (int s : wsteps[w]) {
+                const int len = pieces[64 * s].count;
+                for (int L = 0; L < 64; ++L) {
+                    const bool has = 64 * s + L < (int)pieces.size();
+                    const Piece pc = has ? pieces[64 * s + L] : Piece{nullptr, 0, 0};
+                    for (int q = 0; q < pc.count; ++q) {
+                        const int r = pc.first[q], j = P.irr_j[r];
+                        const size_t slot = (size_t)(t + q) * 64 + L;
+                        il_ij[slot] = modes_row_place(std::min(j, n - j), n) << 4 | (j > n / 2 ? (int)0x80000000u : 0);
+                        il_pos[r] = (int)slot;
+                    }
+                    il_ij[(size_t)(t + len - 1) * 64 + L] |= kIlLast | pc.dest << 16;
                 }
+                t += len;
             }
         }
         dp.n_split = (int)split.size() / 3;
     }
-    std::vector<int4> cpk(p->M);
-    for (int k = 0; k < p->M; ++k) cpk[k] = make_int4(P.cp_i0[k], P.cp_j0[k], sxy[k], 0);
+    auto by_node = [&](const std::vector<double>& w) {       // 6 per sample to one row per stencil node
+        std::vector<double> t(w.size());
+        for (int k = 0; k < p->M; ++k)
+            for (int c = 0; c < 6; ++c) t[(size_t)c * p->M + k] = w[6 * (size_t)k + c];
+        return t;
+    };
+    std::vector<int> cpk(p->M);
+    for (int k = 0; k < p->M; ++k) cpk[k] = P.cp_i0[k] | P.cp_j0[k] << 13 | (sxy[k] & 1) << 26 | (sxy[k] >> 1) << 27;
     // correction chunks: irregular nodes in the order of their first crossing
     // along Gamma, cut where a chunk would exceed kCorrChunk nodes or its
     // crossings' segments (with the spline filter's reach) a window of
@@ -938,7 +943,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         (st = upload(p, &dp.sub_off, sub_off)) || (st = upload(p, &dp.split, split)) || (st = upload(p, &dp.il_ij, il_ij)) ||
         (st = upload(p, &dp.il_pos, il_pos)) || (st = upload(p, &dp.cp_pack, cpk)) ||
         (st = upload(p, &dp.cp_i0, P.cp_i0)) || (st = upload(p, &dp.cp_j0, P.cp_j0)) ||
-        (st = upload(p, &dp.cp_sxy, sxy)) || (st = upload(p, &dp.cp_w, P.cp_w)) || (st = upload(p, &p->cp_wn, P.cp_wn)) ||
+        (st = upload(p, &dp.cp_sxy, sxy)) || (st = upload(p, &dp.cp_w, by_node(P.cp_w))) || (st = upload(p, &p->cp_wn, by_node(P.cp_wn))) ||
         (st = upload(p, &dp.cp_out, P.cp_out)) || (st = upload(p, &dp.inside, P.inside)) ||
         (st = upload(p, &dp.sinq, sinq)) || (st = upload(p, &dp.modes, mode_constants(n, P.h, p->kappa))) ||
         (st = upload(p, &dp.taps, spline_filter_taps(K))))

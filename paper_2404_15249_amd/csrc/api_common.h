@@ -40,6 +40,8 @@ inline ModeConst row_solve_constants(double d, int N) {
     c.rinv = 1.0 / r;
     c.logr = std::log1p(0.5 * d - 0.5 * sq);
     c.rC = std::pow(r, C);
+    c.rH = std::pow(r, modes_chunk(N));
+    c.rN1 = std::exp((N - 1.0) * c.logr);
     const double r2N = std::exp(2.0 * N * c.logr);
     c.smc = -r / (1.0 - r2N);
     return c;

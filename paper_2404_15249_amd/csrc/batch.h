@@ -8,16 +8,16 @@
 namespace kfbi {
 
 constexpr int kBatchNmax = 4096;    // largest grid a batch serves
-// LDS of the batched fast solve holds this many doubles of mode solutions
-// (and, after them, kMaxModesPerGroup x kMaxExtra sums of extra pieces):
-// eight padded modes of the 2048^2 grid, four of the 4096^2 grid
-constexpr int kBatchXs = 8 * (2048 + 64);
+// LDS of the batched fast solve holds this many doubles of mode solutions and sums
+// of extra pieces: eight modes of the 2048^2 grid, four of the 4096^2 grid
+constexpr int kBatchXs = 4 * (2 * modes_stride_of(2048) + kMaxExtra);
+constexpr int kBatchTable = 96 * 32 + 4;   // the largest table of sines and cosines (modes_table_len at 2048)
 
 // Modes per workgroup of a batched problem with grid N: the largest power of two
 // up to kMaxModesPerGroup whose padded solutions fit kBatchXs.
 __host__ __device__ constexpr int batch_modes_per_group(int N) {
     int R = kMaxModesPerGroup;
-    while (R > 1 && R * (N + 64) > kBatchXs) R /= 2;
+    while (R > 2 && R / 2 * (2 * modes_stride_of(N) + kMaxExtra) > kBatchXs) R /= 2;
     return R;
 }
 

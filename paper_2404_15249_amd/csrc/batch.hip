@@ -35,27 +35,20 @@ template <int C>
 __device__ __forceinline__ void modes_item(const DevPlan& p, const double* corr, int row, const ModesLds& L,
                                            double* part) {
     constexpr int R = batch_modes_per_group(64 * C);
-    modes_round<C, R>(p, corr, row * R, L, [&](int cp, double s) { part[(size_t)row * p.M + cp] = s; });
+    modes_round<C, R, false>(p, corr, row, L, [&](int cp, double s) { part[(size_t)row * p.M + cp] = s; });
 }
 
 __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __restrict__ slots, BatchWork w) {
     extern __shared__ double smem[];
     ModesLds L;
     L.sq = smem;
-    L.xs = smem + (kBatchNmax / 2 + 2);
-    L.ex = L.xs + kBatchXs;
+    L.xs = smem + kBatchTable;
     const int n_items = w.counts[1];
-    int curN = -1;
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 item = w.mode_items[it];
         const SlotDev& S = slots[item.x];
         if (slot_done(S)) continue;
         const DevPlan& p = S.p;
-        if (p.N != curN) {
-            __syncthreads();
-            for (int k = threadIdx.x; k <= p.N / 2; k += kModeWaves * 64) L.sq[k] = p.sinq[k];
-            curN = p.N;
-        }
         switch (p.N) {
             case 64: modes_item<1>(p, S.corr_il, item.y, L, S.partial); break;
             case 128: modes_item<2>(p, S.corr_il, item.y, L, S.partial); break;
@@ -100,7 +93,7 @@ __global__ __launch_bounds__(kGmChunk) void k_gm_vec_b(const SlotDev* __restrict
 }  // namespace
 
 size_t modes_b_lds_bytes() {
-    return sizeof(double) * ((size_t)(kBatchNmax / 2 + 2) + (size_t)kBatchXs + (size_t)kMaxModesPerGroup * kMaxExtra);
+    return sizeof(double) * ((size_t)kBatchTable + (size_t)kBatchXs);
 }
 
 hipError_t launch_batch_step(const SlotDev* slots, BatchWork w, int n_cu, hipStream_t s) {

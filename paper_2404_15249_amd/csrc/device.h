@@ -158,21 +158,24 @@ __device__ __forceinline__ double wave_allsum(double v) {
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
-// base^k for 0 <= k < 256 by repeated squaring (eight fixed steps)
-__device__ __forceinline__ double pow_u8(double base, int k) {
+// base^k for 0 <= k < 2^BITS by repeated squaring (BITS fixed steps)
+template <int BITS>
+__device__ __forceinline__ double pow_u(double base, int k) {
     double res = 1.0;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < BITS; ++b) {
         if ((k >> b) & 1) res *= base;
         base *= base;
     }
     return res;
 }
+__device__ __forceinline__ double pow_u8(double base, int k) { return pow_u<8>(base, k); }
 
 // Weighted inclusive scans over the wavefront, v_L <- sum_k m^|L-k| v_k over
 // k <= L (up) or k >= L (down): inside each row of 16 lanes by four DPP row
 // shifts, then across the rows from the row ends read as scalars.
-__device__ __forceinline__ double wave_scan_up(double v, double m, int lane) {
+// pl: m^((lane & 15) + 1) (up), m^(16 - (lane & 15)) (down).
+__device__ __forceinline__ double wave_scan_up(double v, double m, double pl, int lane) {
     const double m2 = m * m, m4 = m2 * m2, m8 = m4 * m4, m16 = m8 * m8;
     v = fma(m, dpp_f64<kDppRowShr1>(v), v);
     v = fma(m2, dpp_f64<kDppRowShr1 + 1>(v), v);
@@ -183,10 +186,10 @@ __device__ __forceinline__ double wave_scan_up(double v, double m, int lane) {
     const double p2 = fma(m16, p1, readlane_f64(v, 47));
     const int row = lane >> 4;
     const double before = row == 0 ? 0.0 : row == 1 ? p0 : row == 2 ? p1 : p2;
-    return fma(pow_u8(m, (lane & 15) + 1), before, v);
+    return fma(pl, before, v);
 }
 
-__device__ __forceinline__ double wave_scan_down(double v, double m, int lane) {
+__device__ __forceinline__ double wave_scan_down(double v, double m, double pl, int lane) {
     const double m2 = m * m, m4 = m2 * m2, m8 = m4 * m4, m16 = m8 * m8;
     v = fma(m, dpp_f64<kDppRowShl1>(v), v);
     v = fma(m2, dpp_f64<kDppRowShl1 + 1>(v), v);
@@ -197,7 +200,7 @@ __device__ __forceinline__ double wave_scan_down(double v, double m, int lane) {
     const double q1 = fma(m16, q2, readlane_f64(v, 16));
     const int row = lane >> 4;
     const double after = row == 3 ? 0.0 : row == 2 ? q3 : row == 1 ? q2 : q1;
-    return fma(pow_u8(m, 16 - (lane & 15)), after, v);
+    return fma(pl, after, v);
 }
 
 template <int C>
@@ -212,7 +215,7 @@ __device__ __forceinline__ void mode_solve(double (&e)[C], const ModeConst& mc, 
         e[c] = w;
     }
     // the lanes' carries: the weighted prefix of the chunk ends, from lane L-1
-    double carry = dpp_f64<kDppWaveShr1>(wave_scan_up(w, mc.rC, lane));
+    double carry = dpp_f64<kDppWaveShr1>(wave_scan_up(w, mc.rC, pow_u8(mc.rC, (lane & 15) + 1), lane));
     // e[c] += r^(c+1) carry; the powers in four interleaved chains
     const double r2 = r * r, r4 = r2 * r2;
     double pw[4] = {r, r2, r2 * r, r4};
@@ -228,7 +231,7 @@ __device__ __forceinline__ void mode_solve(double (&e)[C], const ModeConst& mc, 
         y = fma(r, y, e[c]);
         e[c] = y;
     }
-    carry = dpp_f64<kDppWaveShl1>(wave_scan_down(y, mc.rC, lane));
+    carry = dpp_f64<kDppWaveShl1>(wave_scan_down(y, mc.rC, pow_u8(mc.rC, 16 - (lane & 15)), lane));
     // e[c] += r^(C-c) carry
     pw[0] = r;
     pw[1] = r2;
@@ -259,67 +262,20 @@ __device__ __forceinline__ void mode_solve(double (&e)[C], const ModeConst& mc, 
     if (lane == 63) e[C - 1] = 0.0;
 }
 
-// mode_solve on a wavefront's padded solution in LDS (node i at
-// i + (i - 1) / C, values scaled by h2 on the way in), for chunks too long to
-// keep in registers: the same steps, streamed through LDS.
-template <int C>
-__device__ __forceinline__ void mode_solve_lds(double* x, const ModeConst& mc, int lane, int N, double h2) {
-    double* e = x + lane * (C + 1) + 1;
-    const double r = mc.r;
-    double w = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < C; ++c) {
-        w = r * (w - e[c] * h2);
-        e[c] = w;
-    }
-    double carry = dpp_f64<kDppWaveShr1>(wave_scan_up(w, mc.rC, lane));
-    double pw = r;
-#pragma unroll 8
-    for (int c = 0; c < C; ++c) {
-        e[c] += pw * carry;
-        pw *= r;
-    }
-    if (lane == 63) e[C - 1] = 0.0;
-    double y = 0.0;
-#pragma unroll 8
-    for (int c = C - 1; c >= 0; --c) {
-        y = e[c] + r * y;
-        e[c] = y;
-    }
-    carry = dpp_f64<kDppWaveShl1>(wave_scan_down(y, mc.rC, lane));
-    pw = r;
-#pragma unroll 8
-    for (int c = C - 1; c >= 0; --c) {
-        e[c] += pw * carry;
-        pw *= r;
-    }
-    const double y1 = readlane_f64(e[0], 0);
-    double p1 = r * pow_u8(mc.rC, lane);                    // r^(lane C + 1)
-    double p2 = mc.rinv * pow_u8(mc.rC, 128 - lane);        // r^(2N - lane C - 1), 2N = 128 C
-    const double coef = y1 * mc.smc;
-#pragma unroll 8
-    for (int c = 0; c < C; ++c) {
-        e[c] += coef * (p1 - p2);
-        p1 *= r;
-        p2 *= mc.rinv;
-    }
-    if (lane == 63) e[C - 1] = 0.0;
-}
-
 // Jump terms of the stencil nodes outside Omega: the far-side value is moved to
 // the Omega side with the Taylor expansion of the jumps at the sample.  Every
 // load is issued before any is used: sample cp is the knot that starts spline
 // segment cp (u = 0, as the plan builds it), so the density's values there do
 // not wait for the sample's geometry.
 __device__ inline double outside_terms(const DevPlan& p, const JumpSrc& js, int cp, const int (&ni)[6], const int (&nj)[6],
-                                const double* __restrict__ w) {
+                                const double* __restrict__ w, int ldw) {
     const unsigned char* o6 = p.cp_out + 6 * (size_t)cp;
     unsigned char o[6];
     double wk[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         o[k] = o6[k];
-        wk[k] = w[k];
+        wk[k] = w[(size_t)k * ldw];
     }
     const PointGeom g = p.z_geo[cp];
     const double zx = p.zx[cp], zy = p.zy[cp];
@@ -418,7 +374,7 @@ __device__ inline bool reduce_samples64(const DevPlan& p, const JumpSrc& js, con
         if (wave == kOutsideWave) {
             int ni[6], nj[6];
             stencil_nodes(p, cp, ni, nj);
-            outside[lane] = outside_terms(p, js, cp, ni, nj, p.cp_w + 6 * (size_t)cp);
+            outside[lane] = outside_terms(p, js, cp, ni, nj, p.cp_w + cp, M);
         } else {
             // every row is loaded from a row that exists (then selected), so no
             // load waits under its own condition before the next is requested
@@ -451,214 +407,398 @@ __device__ inline bool reduce_samples64(const DevPlan& p, const JumpSrc& js, con
 
 // ---------------------------------------------------------------- sparse fast solve, R modes per workgroup
 //
-// LDS of the sparse fast solve: the quarter sine table and R padded mode
-// solutions (node i at i + (i - 1) / C, so the lanes' chunk-strided accesses
-// fall in different banks).
+// LDS of the sparse fast solve: the block's row sines (two per row up to N/2) and
+// the rows' 2 cos(pi j / N); at N = 4096, where they would not fit beside the
+// solutions, the quarter-period table sin(pi m / N), m <= N/2, they are looked up
+// in, and the carries between a mode's wavefronts.  Then the
+// padded mode solutions (node i at i + (i - 1) / CH with CH nodes a lane, so the
+// lanes' chunk-strided accesses fall in different banks).
 struct ModesLds {
-    double* sq;   // N/2 + 2
-    double* xs;   // R x (N + 64)
-    double* ex;   // R x kMaxExtra: sums of the extra pieces of long columns
+    double* sq;   // modes_table_len
+    double* xs;   // modes_pairs<R> x modes_pair_len<C>
 };
 
+template <int C>
+constexpr bool kRowSines = C <= 32;
+template <int C>
+constexpr int modes_table_len() { return kRowSines<C> ? 96 * C + 4 : 32 * C + 2 + 3 * kModeWaves; }
+// the rows' cosines in the table, after the 32 C + 1 pairs of sines
+template <int C>
+constexpr int modes_cos_at() { return 64 * C + 2; }
+// doubles of one padded solution: CH = modes_chunk(N) nodes a lane
+template <int C>
+constexpr int modes_stride() { return modes_stride_of(64 * C); }
+// a pair of mirrored modes: the sums over even rows, those over odd rows (then the
+// two solutions) and the sums of the extra pieces of long column halves
+template <int C>
+constexpr int modes_pair_len() { return 2 * modes_stride<C>() + kMaxExtra; }
 template <int R>
-__device__ __forceinline__ ModesLds modes_lds(double* smem, int N) {
+constexpr int modes_pairs() { return R >= 2 ? R / 2 : 1; }
+template <int C, int R>
+constexpr size_t modes_lds_len() {
+    return (size_t)modes_table_len<C>() + (size_t)modes_pairs<R>() * modes_pair_len<C>();
+}
+
+template <int C>
+__device__ __forceinline__ ModesLds modes_lds(double* smem) {
     ModesLds L;
     L.sq = smem;
-    L.xs = smem + (N / 2 + 2);
-    L.ex = L.xs + (size_t)R * (N + 64);
+    L.xs = smem + modes_table_len<C>();
     return L;
 }
 
-// Sine modes l = base + 1 .. base + R (those <= n) by a workgroup of
-// kModeWaves wavefronts.
+// v with its sign flipped where bit 31 of `sign` is set
+__device__ __forceinline__ double flip_sign(double v, unsigned sign) {
+    return __hiloint2double(__double2hiint(v) ^ (int)sign, __double2loint(v));
+}
+
+// (sin(l0 t), sin((l0 + 1) t)), t = pi j / N, 0 <= j <= N/2, N = 64 C, at16 = 16
+// modes_row_place(j): from the block's row sines in LDS, at N = 4096 by two lookups in the
+// quarter-period table.
+template <int C>
+__device__ __forceinline__ double2 row_sines(const double* sq, int at16, int l0) {
+    constexpr int N = 64 * C;
+    if constexpr (kRowSines<C>) return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(sq) + at16);
+    const int j = at16 >> 4;
+    const int m0 = (int)(__umul24((unsigned)j, (unsigned)l0) & (2 * N - 1));
+    return make_double2(sinpi_n(sq, m0, N), sinpi_n(sq, (m0 + j) & (2 * N - 1), N));
+}
+
+// 2 cos(pi j / N) of the row at the same place.
+template <int C>
+__device__ __forceinline__ double row_c2(const double* sq, int at16) {
+    if constexpr (kRowSines<C>)
+        return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(sq + modes_cos_at<C>()) + (at16 >> 1));
+    return 2.0 * sq[32 * C - (at16 >> 4)];
+}
+
+// The block's row sines into LDS (every node's and every sample's sines are then
+// one 16-byte read at its row, nearly free of bank conflicts because the lanes'
+// rows follow the curve; a table indexed by j l mod 2N, which scatters them, took
+// three reads of three passes each and bounded the sums), or at N = 4096 the
+// quarter-period table.
+template <int C>
+__device__ __forceinline__ void modes_load_table(double* sq, const double* __restrict__ sinq, int l0, int tid) {
+    constexpr int N = 64 * C;
+    if constexpr (kRowSines<C>) {
+        if (tid == 0) {
+            reinterpret_cast<double2*>(sq)[0] = make_double2(0.0, 0.0);
+            sq[modes_cos_at<C>()] = 2.0;
+        }
+        for (int j = 1 + tid; j <= N / 2; j += kModeWaves * 64) {
+            const int m0 = (int)(__umul24((unsigned)j, (unsigned)l0) & (2 * N - 1));
+            sq[modes_cos_at<C>() + modes_row_place(j, N)] = 2.0 * sinq[N / 2 - j];
+            reinterpret_cast<double2*>(sq)[modes_row_place(j, N)] =
+                make_double2(sinpi(m0 * (1.0 / N)), sinpi(((m0 + j) & (2 * N - 1)) * (1.0 / N)));
+        }
+    } else {
+        for (int k = tid; k <= N / 2; k += kModeWaves * 64) sq[k] = sinq[k];
+    }
+}
+
+// The sine modes of block g by a workgroup of kModeWaves wavefronts: the H = R/2
+// mirrored pairs (l, N - l) for l = g H + 1 .. g H + H (N/2 is its own mirror),
+// or with R = 1 the one mode l = g + 1.
 //  1. Sparse sine sums of the corrected right-hand side along y: wavefront w
-//     walks sub-table w of the interleaved node table (each lane owns whole
-//     columns); per node the sines of all R modes come from three table
-//     lookups and the recurrence sin((l+1)t) = 2 cos t sin(lt) - sin((l-1)t),
-//     and a column's R sums are stored when its last node is reached.
-//  2. The tridiagonal solve along x of each mode (one wavefront per mode).
-//  3. The weighted six-point gather at every sample (the row sines by the same
-//     recurrence): emit(cp, s) with s the sum over the R modes, for
-//     cp = tid, tid + 64 kModeWaves, ...
-// L.sq must hold the sine table of p.N, or sinq (the table in device memory)
-// is given and loaded here; must be called by the whole workgroup.  The round
-// does nothing while *skip is nonzero (skip may be null); the flag is checked
-// after the first requests and the clear, so its latency overlaps theirs.
-template <int C, int R, class Emit>
-__device__ __forceinline__ void modes_round(const DevPlan& p, const double* __restrict__ corr, int base,
-                                            const ModesLds& L, Emit emit, const double* __restrict__ sinq = nullptr,
-                                            const int* __restrict__ skip = nullptr) {
-    constexpr int XS = 64 * (C + 1);
+//     walks sub-table w of the interleaved node table: steps of 64 column halves
+//     (the nodes of one column and one parity of j) of about equal length, one a
+//     lane, so all lanes end and store their H sums together.  Per node the sines
+//     of the H modes l are two values of its row (modes_load_table) and the
+//     recurrence sin((l+1)t) = 2 cos t sin(lt) - sin((l-1)t).  With E and O the sums over even
+//     and odd j, mode l has E + O and mode N - l, whose sine at row j is
+//     (-1)^(j+1) that of mode l, has O - E: a pair costs the sines and the
+//     multiply-adds of one mode.
+//  2. The tridiagonal solve along x of each mode (mode_solve's steps) by S = C / CH
+//     wavefronts: a lane holds CH <= 32 nodes in registers, and the S wavefronts'
+//     carries are joined through LDS (a row of 4096 nodes would not fit one
+//     wavefront's registers beside sixteen wavefronts' worth of the rest).
+//  3. The weighted six-point gather at every sample: the row sines by the same
+//     recurrence, again one set per pair (the rows j0 and j0 +- 1 have opposite
+//     signs in the mirrored mode).  emit(cp, s) gets the sum s over the block's
+//     modes, for cp = tid, tid + 64 kModeWaves, ...
+// What bounds it: a compute unit's intake of the node and sample tables from L2
+// (64 bytes a clock, 12 bytes a node) until the sums are done, then LDS and issue;
+// the R padded solutions fill the LDS, so it holds one workgroup, and sixteen
+// wavefronts hide more latency than eight.  At 2048^2 with 7656 nodes (256
+// workgroups) one launch went from 16.7 us (eight wavefronts, every mode summed
+// by itself with three lookups a node, powers recomputed in the solve) to 12.3 us,
+// at 1024^2 from 10.6 to 7.6 us.
+// Must be called by the whole workgroup; N = 64 C.  The round does nothing while *skip is nonzero (skip may be null);
+// the flag is checked after the first requests and the clear, so its latency
+// overlaps theirs.
+// EARLY: the wavefront's mode constants and the thread's first stencil are
+// requested ahead of their phases (off where the registers are short: the
+// batched kernel holds every grid size's code).
+template <int C, int R, bool EARLY, class Emit>
+__device__ __forceinline__ void modes_round(const DevPlan& p, const double* __restrict__ corr, int g,
+                                            const ModesLds& L, Emit emit, const int* __restrict__ skip = nullptr) {
+    constexpr int N = 64 * C, XS = modes_stride<C>(), PS = modes_pair_len<C>();
+    constexpr int CH = modes_chunk(N), S = C / CH;
+    static_assert(R * S <= kModeWaves, "S wavefronts for each mode");
+    static_assert(S == 1 || !kRowSines<C>, "the carries' place");
+    double* carry_up = L.sq + 32 * C + 2;               // S > 1: one value a wavefront each, after the table
+    double* carry_dn = carry_up + kModeWaves;
+    double* carry_g = carry_dn + kModeWaves;
     constexpr int NT = kModeWaves * 64;
-    const int N = p.N, n = p.n, M = p.M, mask2 = 2 * N - 1, half = N / 2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int H = modes_pairs<R>();
+    const int M = p.M;
+    int tid = threadIdx.x;
+    // in the batched kernel's item loop the thread's addresses for every grid size
+    // would otherwise be kept in registers across the loop
+    if (!EARLY) asm volatile("" : "+v"(tid));
+    // the wavefront's index as a scalar: its branches are then uniform
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double* sq = L.sq;
-    const int l0 = base + 1;
-    const int nact = min(R, n - base);                  // modes of this round that exist
+    const int l0 = g * H + 1;
     const int skipped = load_flag_or_zero(skip);
     // the first rows of this wavefront's node table are requested before
     // anything waits, so their latency overlaps the table load and the clear;
     // the sub-table's bounds come with the plan's fields, not from memory
-    const int wu = __builtin_amdgcn_readfirstlane(wave);
-    int t_beg = p.sub_offv[0], t_end = p.sub_offv[1];  // multiples of kSlots
+    int t_beg, t_end;                                  // multiples of kSlots
+    if constexpr (EARLY) {
+        t_beg = p.sub_offv[0];
+        t_end = p.sub_offv[1];
 #pragma unroll
-    for (int w = 1; w < kModeWaves; ++w)               // constant indices: loaded with the other fields
-        if (wu == w) {
-            t_beg = p.sub_offv[w];
-            t_end = p.sub_offv[w + 1];
-        }
-    int pk[kSlots], pkn[kSlots];
-    double cv[kSlots], cvn[kSlots];
-    if (t_beg < t_end) {
+        for (int w = 1; w < kModeWaves; ++w)           // constant indices: loaded with the other fields
+            if (wave == w) {
+                t_beg = p.sub_offv[w];
+                t_end = p.sub_offv[w + 1];
+            }
+    } else {                                           // the plan is in memory: no gain, and seventeen registers
+        t_beg = p.sub_off[wave];
+        t_end = p.sub_off[wave + 1];
+    }
+    struct Rows {                                       // kSlots rows of the node table
+        int pk[kSlots];
+        double cv[kSlots];
+    };
+    auto load_rows = [&](Rows& n, int t0) {
 #pragma unroll
         for (int q = 0; q < kSlots; ++q) {
-            pk[q] = p.il_ij[(size_t)(t_beg + q) * 64 + lane];
-            cv[q] = corr[(size_t)(t_beg + q) * 64 + lane];
+            n.pk[q] = p.il_ij[(unsigned)(t0 + q) * 64u + (unsigned)lane];
+            n.cv[q] = corr[(unsigned)(t0 + q) * 64u + (unsigned)lane];
         }
-    }
-    // also requested now: this wavefront's mode constants (phase 2) and the
-    // stencil data of the thread's first kPre samples (phase 3)
-    constexpr int kPre = 2;
+    };
+    Rows ra, rb;
+    if (t_beg < t_end) load_rows(ra, t_beg);
+    if (EARLY && t_beg + kSlots < t_end) load_rows(rb, t_beg + kSlots);
+    // also requested now: this wavefront's mode constants (phase 2)
+    const int mode = wave / S, sub = wave % S;          // mode of the block (pairs' l first, then their mirrors)
+    const bool mirror = R >= 2 && mode >= H, solves = mode < R;
+    const int lw = mirror ? N - (l0 + mode - H) : l0 + mode;
     ModeConst mcw{};
-    if (wave < nact) mcw = p.modes[l0 + wave];
-    int4 pre_pk[kPre];
-    double2 pre_w[kPre][3];
-#pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const int cp = tid + q * NT;
-        if (cp < M) {
-            pre_pk[q] = p.cp_pack[cp];
-            const double2* w2 = reinterpret_cast<const double2*>(p.cp_w + 6 * (size_t)cp);
-            pre_w[q][0] = w2[0];
-            pre_w[q][1] = w2[1];
-            pre_w[q][2] = w2[2];
-        }
+    if (EARLY && solves) mcw = p.modes[lw];
+    // ... and the thread's entry of the split list (the end of phase 1)
+    int sp_at = 0, sp_e0 = 0, sp_ne = 0;
+    if (tid < p.n_split * H) {
+        const int* e = p.split + 3 * (tid / H);
+        sp_at = e[0];
+        sp_e0 = e[1];
+        sp_ne = e[2];
     }
-    if (sinq)
-        for (int k = tid; k <= N / 2; k += NT) L.sq[k] = sinq[k];
-    for (int k = tid; k < R * XS; k += NT) L.xs[k] = 0.0;
+    modes_load_table<C>(L.sq, p.sinq, l0, tid);
+    double2* xs2 = reinterpret_cast<double2*>(L.xs);
+    for (int k = tid; k < H * PS / 2; k += NT) xs2[k] = make_double2(0.0, 0.0);
     if (skipped) return;                                // the same for the whole workgroup
     __syncthreads();
     {
-        double acc[R];
+        double acc[H];
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[r] = 0.0;
-        for (int t0 = t_beg; t0 < t_end; t0 += kSlots) {
-            const bool more = t0 + kSlots < t_end;      // next group's loads overlap this group's sums
-            if (more) {
-#pragma unroll
-                for (int q = 0; q < kSlots; ++q) {
-                    pkn[q] = p.il_ij[(size_t)(t0 + kSlots + q) * 64 + lane];
-                    cvn[q] = corr[(size_t)(t0 + kSlots + q) * 64 + lane];
-                }
-            }
-            // sin((l0 + r) t), t = pi j / N, for r = 0 .. R-1: two table values,
-            // then s_{r+1} = 2 cos t s_r - s_{r-1}.  The group's table values are
-            // read before any of its sums is stored, so their latencies overlap
-            double s0[kSlots], s1[kSlots], c2[kSlots];
+        for (int r = 0; r < H; ++r) acc[r] = 0.0;
+        // a row beyond N/2 is looked up at its mirror N - j: sin(l t) changes sign there for even l
+        const unsigned flip0 = (l0 & 1) ? 0u : 0x80000000u, flip1 = flip0 ^ 0x80000000u;
+        auto sum_rows = [&](const Rows& n) {
+            // the group's row sines are read before any of its sums is stored, so
+            // their latencies overlap
+            double2 s01[kSlots];
+            double c2[kSlots];
 #pragma unroll
             for (int q = 0; q < kSlots; ++q) {
-                const int j = pk[q] & 0xfff;
-                const int m0 = (int)(__umul24((unsigned)j, (unsigned)l0) & mask2);
-                s0[q] = sinpi_n(sq, m0, N);
-                s1[q] = R > 1 ? sinpi_n(sq, (m0 + j) & mask2, N) : 0.0;
-                c2[q] = R > 2 ? 2.0 * sinpi_n(sq, (j + half) & mask2, N) : 0.0;
+                s01[q] = row_sines<C>(sq, n.pk[q] & kIlRow, l0);
+                c2[q] = H > 2 ? row_c2<C>(sq, n.pk[q] & kIlRow) : 0.0;
             }
 #pragma unroll
             for (int q = 0; q < kSlots; ++q) {
-                double sp = s0[q], sc = s1[q];
-                acc[0] = fma(cv[q], sp, acc[0]);
-                if (R > 1) acc[1] = fma(cv[q], sc, acc[1]);
+                double sp = flip_sign(s01[q].x, (unsigned)n.pk[q] & flip0), sc = flip_sign(s01[q].y, (unsigned)n.pk[q] & flip1);
+                const double c = flip_sign(c2[q], (unsigned)n.pk[q] & 0x80000000u);
+                acc[0] = fma(n.cv[q], sp, acc[0]);
+                if (H > 1) acc[1] = fma(n.cv[q], sc, acc[1]);
 #pragma unroll
-                for (int r = 2; r < R; ++r) {
-                    const double sn = fma(c2[q], sc, -sp);
-                    acc[r] = fma(cv[q], sn, acc[r]);
+                for (int r = 2; r < H; ++r) {
+                    const double sn = fma(c, sc, -sp);
+                    acc[r] = fma(n.cv[q], sn, acc[r]);
                     sp = sc;
                     sc = sn;
                 }
-                if (pk[q] < 0) {                        // last node of its piece
-                    const int dest = (pk[q] >> 16) & 0x7fff;
-                    double* to = dest < kExtraFlag ? L.xs + dest : L.ex + (dest - kExtraFlag);
-                    const int stride = dest < kExtraFlag ? XS : kMaxExtra;
-                    if (nact == R) {
+                if (__builtin_amdgcn_readfirstlane(n.pk[q]) & kIlLast) {   // the step's last row, for every lane
+                    double* to = L.xs + (((unsigned)n.pk[q] >> 16) & 0x7fff);
 #pragma unroll
-                        for (int r = 0; r < R; ++r) to[r * stride] = acc[r];
-                    } else {
+                    for (int r = 0; r < H; ++r) to[r * PS] = acc[r];
 #pragma unroll
-                        for (int r = 0; r < R; ++r)
-                            if (r < nact) to[r * stride] = acc[r];
-                    }
-#pragma unroll
-                    for (int r = 0; r < R; ++r) acc[r] = 0.0;
+                    for (int r = 0; r < H; ++r) acc[r] = 0.0;
                 }
             }
-            if (more) {
+        };
+        // two groups in turn: each one's next rows are requested when its sums are done
+        for (int t0 = t_beg; t0 < t_end; t0 += 2 * kSlots) {
+            if (!EARLY && t0 + kSlots < t_end) load_rows(rb, t0 + kSlots);
+            sum_rows(ra);
+            if (t0 + kSlots >= t_end) break;
+            if (t0 + 2 * kSlots < t_end) load_rows(ra, t0 + 2 * kSlots);
+            sum_rows(rb);
+            if (EARLY && t0 + 3 * kSlots < t_end) load_rows(rb, t0 + 3 * kSlots);
+        }
+    }
+    // the stencil data of the thread's first sample (phase 3), requested once the
+    // nodes' loads are through: a compute unit takes in 64 bytes a clock, and at
+    // the start these would hold up the nodes
+    int pre_pk = 0;
+    double pre_w[6] = {};
+    if (EARLY && tid < M) {
+        pre_pk = p.cp_pack[tid];
+        for (int k = 0; k < 6; ++k) pre_w[k] = p.cp_w[(size_t)k * M + tid];
+    }
+    __syncthreads();
+    // long column halves: add their extra pieces in a fixed order (at most
+    // kMaxExtra of them, and H <= 4: one a thread)
+    static_assert(kMaxExtra * H <= NT, "a thread for each split column half and pair");
+    if (tid < p.n_split * H) {
+        double* x = L.xs + (tid % H) * PS;
+        double v = x[sp_at];
+        for (int e = 0; e < sp_ne; ++e) v += x[2 * XS + sp_e0 + e];
+        x[sp_at] = v;
+    }
+    __syncthreads();
+    {
+        // the mode's right-hand side from the pair's sums over even and odd rows
+        // (N/2 is its own mirror: solved once, its mirror is zero)
+        const int gl = sub * 64 + lane, at = gl * (CH + 1) + 1;   // lane of the mode, place of its first node
+        double e[CH];
+        if (!EARLY && solves) mcw = p.modes[lw];
+        if (solves) {
+            const double* xe = L.xs + (mirror ? mode - H : mode) * PS + at;
+            const double* xo = xe + XS;
+            const double so = mirror && lw == N / 2 ? 0.0 : p.h2, se = mirror ? -so : so;
 #pragma unroll
-                for (int q = 0; q < kSlots; ++q) {
-                    pk[q] = pkn[q];
-                    cv[q] = cvn[q];
+            for (int c = 0; c < CH; ++c) {
+                e[c] = fma(so, xo[c], se * xe[c]);
+                if (CH > 16 && c % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // not all 2 CH reads in registers at once
+            }
+        }
+        __syncthreads();                                // both of a pair have read its sums
+        // The steps of mode_solve, with the rank-one fix taken into the forward
+        // recurrence: y[1] zeta is what an initial value
+        //   w[0] = r / (1 - r^(2N)) sum_k e[k] (r^k - r^(2N-k))
+        // adds (the forward recurrence turns w[0] into r^i w[0], the backward one
+        // that into w[0] (r^i - r^(2N-i)) / (1 - r^2)), and both sums come with
+        // the carries: the first by a Horner sum per lane, the second is
+        // -r^(N-1) w[N].  Each recurrence then runs twice per lane, once for the
+        // carry it passes on and once from the carry it gets: six operations a
+        // node where adding the carries' powers and the fix took eleven.
+        const double r = mcw.r, rH = mcw.rH;
+        const double rl = pow_u<4>(rH, lane & 15), r16 = pow_u<5>(rH, 16);
+        const double rlane = rl * pow_u<2>(r16, lane >> 4);      // rH^lane
+        const double r64 = (r16 * r16) * (r16 * r16);            // from one wavefront of a mode to the next
+        double w = 0.0, g1 = 0.0, up = 0.0;
+        if (solves) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                e[c] *= r;
+                w = fma(r, w, -e[c]);
+            }
+#pragma unroll
+            for (int c = CH - 1; c >= 0; --c) g1 = fma(r, g1, e[c]);
+            up = wave_scan_up(w, rH, rl * rH, lane);
+            g1 = wave_allsum(g1 * rlane);
+            if (S > 1 && lane == 63) {
+                carry_up[wave] = up;
+                carry_g[wave] = g1;
+            }
+        }
+        double in = 0.0, wN = readlane_f64(up, 63);
+        if constexpr (S > 1) {
+            __syncthreads();
+            if (solves) {
+                wN = g1 = 0.0;
+#pragma unroll
+                for (int q = S - 1; q >= 0; --q) g1 = fma(r64, g1, carry_g[wave - sub + q]);
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    if (q == sub) in = wN;
+                    wN = fma(r64, wN, carry_up[wave - sub + q]);
                 }
+            }
+        }
+        double y = 0.0, dn = 0.0;
+        if (solves) {
+            const double w0 = -mcw.smc * fma(mcw.rN1, wN, g1);
+            // the value at the node before the lane's first: the lanes below and w[0]
+            double rg = 1.0;
+#pragma unroll
+            for (int q = 1; q < S; ++q) rg *= sub >= q ? r64 : 1.0;
+            w = dpp_f64<kDppWaveShr1>(up) + rlane * fma(rg, w0, in);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                w = fma(r, w, -e[c]);
+                e[c] = w;
+            }
+            if (gl == 64 * S - 1) e[CH - 1] = 0.0;      // node N
+#pragma unroll
+            for (int c = CH - 1; c >= 0; --c) y = fma(r, y, e[c]);
+            dn = wave_scan_down(y, rH, pow_u<4>(rH, 15 - (lane & 15)) * rH, lane);
+            if (S > 1 && lane == 0) carry_dn[wave] = dn;
+        }
+        in = 0.0;
+        if constexpr (S > 1) {
+            __syncthreads();
+            if (solves) {
+#pragma unroll
+                for (int q = S - 1; q > 0; --q)
+                    if (q > sub) in = fma(r64, in, carry_dn[wave - sub + q]);
+                in *= pow_u<6>(rH, 63 - lane);
+            }
+        }
+        if (solves) {
+            y = dpp_f64<kDppWaveShl1>(dn) + in;
+            double* x = L.xs + (mirror ? (mode - H) * PS + XS : mode * PS) + at;
+#pragma unroll
+            for (int c = CH - 1; c >= 0; --c) {
+                y = fma(r, y, e[c]);
+                if (c < CH - 1 || gl < 64 * S - 1) x[c] = y;
             }
         }
     }
     __syncthreads();
-    // long columns: add their extra pieces in a fixed order
-    for (int k = tid; k < p.n_split * R; k += NT) {
-        const int c = k / R, r = k % R;
-        if (r < nact) {
-            const int pos = p.split[3 * c], e0 = p.split[3 * c + 1], ne = p.split[3 * c + 2];
-            double v = L.xs[r * XS + pos];
-            for (int e = 0; e < ne; ++e) v += L.ex[r * kMaxExtra + e0 + e];
-            L.xs[r * XS + pos] = v;
-        }
-    }
-    __syncthreads();
-    static_assert(R <= kModeWaves, "one mode per wavefront at most");
-    if (wave < nact) {
-        double* x = L.xs + wave * XS;
-        if constexpr (C > 32) {
-            mode_solve_lds<C>(x, mcw, lane, N, p.h2);
-        } else {
-            double e[C];
-#pragma unroll
-            for (int c = 0; c < C; ++c) e[c] = x[lane * (C + 1) + 1 + c] * p.h2;
-            mode_solve<C>(e, mcw, lane, N);
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (lane < 63 || c < C - 1) x[lane * (C + 1) + 1 + c] = e[c];
-        }
-    }
-    __syncthreads();
-    auto gather = [&](int cp, const int4 pk4, const double2 wa, const double2 wb, const double2 wc) {
-        const int i0 = pk4.x, j0 = pk4.y, sxy = pk4.z;
-        const int sx = (sxy & 1) ? 1 : -1;
-        const bool syp = (sxy & 2) != 0;
-        const double w0 = wa.x, wE = wa.y, wW = wb.x, wN = wb.y, wS = wc.x, wD = wc.y;
+    auto gather = [&](int cp, int pk1, const double (&w6)[6]) {
+        const int i0 = pk1 & 0x1fff, j0 = (pk1 >> 13) & 0x1fff;
+        const bool sxp = (pk1 & (1 << 26)) != 0, syp = (pk1 & (1 << 27)) != 0;
+        const double w0 = w6[0], wE = w6[1], wW = w6[2], wN = w6[3], wS = w6[4];
+        const double wDp = syp ? w6[5] : 0.0, wDm = syp ? 0.0 : w6[5];   // the diagonal node's row
         // places of the stencil columns in the padded layout (node 0 lies on
         // the box: zero); the sine arguments advance by j per mode
-        const int pc = i0 + (i0 - 1) / C, pe = i0 + i0 / C + 1, pw = i0 > 1 ? i0 - 1 + (i0 - 2) / C : -1;
-        // sines of the rows j0, j0 + 1, j0 - 1 for the modes l0 + q: two table
-        // values each, then the three-term recurrence in q
-        const int a0 = (int)(__umul24((unsigned)j0, (unsigned)l0) & mask2);
-        const int ap = (int)(__umul24((unsigned)(j0 + 1), (unsigned)l0) & mask2);
-        const int am = (int)(__umul24((unsigned)(j0 - 1), (unsigned)l0) & mask2);
-        double s0p = sinpi_n(sq, a0, N), spp = sinpi_n(sq, ap, N), smp = sinpi_n(sq, am, N);
-        double s0c = 0.0, spc = 0.0, smc = 0.0, c0 = 0.0, cpl = 0.0, cmi = 0.0;
-        if (R > 1) {
-            s0c = sinpi_n(sq, (a0 + j0) & mask2, N);
-            spc = sinpi_n(sq, (ap + j0 + 1) & mask2, N);
-            smc = sinpi_n(sq, (am + j0 - 1) & mask2, N);
-        }
-        if (R > 2) {
-            c0 = 2.0 * sinpi_n(sq, (j0 + half) & mask2, N);
-            cpl = 2.0 * sinpi_n(sq, (j0 + 1 + half) & mask2, N);
-            cmi = 2.0 * sinpi_n(sq, (j0 - 1 + half) & mask2, N);
-        }
+        const int pc = i0 + (i0 - 1) / CH, pe = i0 + i0 / CH + 1, pw = i0 > 1 ? i0 - 1 + (i0 - 2) / CH : -1;
+        const double odd = (j0 & 1) ? 1.0 : -1.0;           // sign of the mirrored mode's sine at row j0
+        // sines of the rows j0, j0 + 1, j0 - 1 for the modes l0 + q: two values
+        // each, then the three-term recurrence in q
+        const unsigned flip0 = (l0 & 1) ? 0u : 0x80000000u, flip1 = flip0 ^ 0x80000000u;
+        struct Row {
+            double s0, s1, c2;
+        };
+        auto at_row = [&](int j) {
+            const bool mir = j > N / 2;
+            const int at16 = 16 * modes_row_place(mir ? N - j : j, N);
+            const double2 v = row_sines<C>(sq, at16, l0);
+            return Row{flip_sign(v.x, mir ? flip0 : 0u), flip_sign(v.y, mir ? flip1 : 0u),
+                       H > 2 ? flip_sign(row_c2<C>(sq, at16), mir ? 0x80000000u : 0u) : 0.0};
+        };
+        const Row r0 = at_row(j0), rp = at_row(j0 + 1), rm = at_row(j0 - 1);
+        double s0p = r0.s0, spp = rp.s0, smp = rm.s0, s0c = r0.s1, spc = rp.s1, smc = rm.s1;
+        const double c0 = r0.c2, cpl = rp.c2, cmi = rm.c2;
         double s = 0.0;
-        // modes beyond n were never written: their solutions are zero
 #pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const double* xq = L.xs + q * XS;
+        for (int q = 0; q < H; ++q) {
+            const double* xq = L.xs + q * PS;
             double s0, sp, sm;
             if (q == 0) {
                 s0 = s0p;
@@ -679,22 +819,28 @@ __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __re
                 spc = sp;
                 smc = sm;
             }
-            const double xc = xq[pc];
-            const double xe = xq[pe];
-            const double xw = pw >= 0 ? xq[pw] : 0.0;
-            const double xd = sx > 0 ? xe : xw;
-            s += s0 * (w0 * xc + wE * xe + wW * xw) + sp * wN * xc + sm * wS * xc + (syp ? sp : sm) * wD * xd;
+            // the pair's values with the mirrored mode's signs: sums at row j0,
+            // differences at the rows next to it
+            double xc = xq[pc], xe = xq[pe], xw = pw >= 0 ? xq[pw] : 0.0;
+            double xcd = xc, xdd = sxp ? xe : xw;
+            if constexpr (R >= 2) {
+                const double* xm = xq + XS;
+                const double yc = xm[pc], ye = xm[pe], yw = pw >= 0 ? xm[pw] : 0.0;
+                xcd = fma(-odd, yc, xcd);
+                xdd = fma(-odd, sxp ? ye : yw, xdd);
+                xc = fma(odd, yc, xc);
+                xe = fma(odd, ye, xe);
+                xw = fma(odd, yw, xw);
+            }
+            s += s0 * (w0 * xc + wE * xe + wW * xw) + sp * (wN * xcd + wDp * xdd) + sm * (wS * xcd + wDm * xdd);
         }
         emit(cp, s);
     };
-#pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const int cp = tid + q * NT;
-        if (cp < M) gather(cp, pre_pk[q], pre_w[q][0], pre_w[q][1], pre_w[q][2]);
-    }
-    for (int cp = tid + kPre * NT; cp < M; cp += NT) {
-        const double2* w2 = reinterpret_cast<const double2*>(p.cp_w + 6 * (size_t)cp);
-        gather(cp, p.cp_pack[cp], w2[0], w2[1], w2[2]);
+    if (EARLY && tid < M) gather(tid, pre_pk, pre_w);
+    for (int cp = EARLY ? tid + NT : tid; cp < M; cp += NT) {
+        double w6[6];
+        for (int k = 0; k < 6; ++k) w6[k] = p.cp_w[(size_t)k * M + cp];
+        gather(cp, p.cp_pack[cp], w6);
     }
     __syncthreads();
 }

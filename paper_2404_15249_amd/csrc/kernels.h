@@ -16,10 +16,24 @@ struct ModeConst {
     double logr;   // log r
     double rC;     // r^C (C = N / 64, the chunk one lane owns)
     double smc;    // -r / (1 - r^(2N)): scale of the rank-one boundary fix
-    double pad[3];
+    double rH;     // r^modes_chunk(N): the chunk of a lane of the sparse fast solve
+    double rN1;    // r^(N-1)
+    double pad;
 };
 
-constexpr int kModeWaves = 8;      // wavefronts of a sparse-fast-solve workgroup (= node sub-tables)
+// nodes of a row one lane of the sparse fast solve owns: N / 64 up to 32 (a row of
+// 4096 takes two wavefronts)
+__host__ __device__ constexpr int modes_chunk(int N) { return N / 64 < 32 ? N / 64 : 32; }
+
+// doubles of one padded solution of the sparse fast solve
+__host__ __device__ constexpr int modes_stride_of(int N) { return N + N / modes_chunk(N); }
+
+// place of row j (0 <= j <= N/2) among a block's row sines: even rows, then odd
+// ones, so that neighbouring columns' nodes of one parity read neighbouring
+// places (at N = 4096 j itself: the sines are looked up)
+__host__ __device__ constexpr int modes_row_place(int j, int N) { return N <= 2048 ? (j >> 1) + (j & 1) * (N / 4 + 1) : j; }
+
+constexpr int kModeWaves = 16;     // wavefronts of a sparse-fast-solve workgroup (= node sub-tables)
 
 // Everything a kernel needs to read one problem's plan on the device.
 struct DevPlan {
@@ -42,22 +56,25 @@ struct DevPlan {
                               // table are sub-table w (multiples of kSlots)
     int sub_offv[kModeWaves + 1];   // the same offsets by value, so that a kernel given the plan by
                                     // value reads them with its arguments
-    const int* split;         // 3 n_split: (place, first extra piece, extra pieces) of each column
-                              // whose nodes are cut into several pieces (see il_ij)
+    const int* split;         // 3 n_split: (dest, first extra piece, extra pieces) of each
+                              // column half whose nodes are cut into several pieces (see il_ij)
     int n_split;
-    const int* il_ij;         // T x 64, slot t*64 + L: node (i, j) of lane L of the sub-table owning row t, packed as
-                              // (last-of-piece << 31) | (dest << 16) | j  (0: pad).  A column's nodes
-                              // form one piece, or several when the column is long; dest of the
-                              // first piece is xpos = i + (i - 1) / (N / 64), column i's place in
-                              // the padded per-wavefront mode solution; dest of an extra piece is
-                              // kExtraFlag | its index in the extra-sums buffer
+    const int* il_ij;         // T x 64, slot t*64 + L of lane L of the sub-table owning row t: kIl* below.
+                              // A column's nodes with even j and those with odd j form
+                              // one piece each, or several when there are many; a step is 64 pieces of
+                              // about equal length, one a lane, padded to the longest (pads: zero
+                              // corrections).  In the step's last row dest is the place of the lane's
+                              // sums in a pair's block: for a first piece xpos = i + (i - 1) /
+                              // modes_chunk(N), column i's place in the padded solution, plus
+                              // modes_stride_of(N) for odd j; for an extra piece 2 modes_stride_of(N) +
+                              // its index; 0 (a place nothing reads) for a lane with no piece
     const int* il_pos;        // I: slot of irregular node r in the interleaved layout
     int T;                    // slots per lane, a multiple of kSlots
-    const int4* cp_pack;      // M: (i0, j0, sxy, 0)
+    const int* cp_pack;       // M: i0 | j0 << 13 | (sx > 0) << 26 | (sy > 0) << 27
     const int* cp_i0;         // M
     const int* cp_j0;         // M
     const int* cp_sxy;        // M: bit 0 sx>0, bit 1 sy>0
-    const double* cp_w;       // 6 M: weights of the six stencil values in the extracted quantity (v+, or
+    const double* cp_w;       // 6 x M (row k: node k of every sample): weights of the six stencil values in the extracted quantity (v+, or
                               // d_n v+ for a plan that extracts the normal derivative)
     const unsigned char* cp_out;   // 6 M
     const unsigned char* inside;   // (n+1)^2
@@ -85,8 +102,9 @@ constexpr int kCorrChunk = 256;    // irregular nodes per correction chunk (one 
 constexpr int kCorrWindow = 256;   // knots of a chunk's density window
 constexpr int kSlots = 4;          // table rows loaded together by the sparse sine sums
 constexpr int kMaxModesPerGroup = 8;
-constexpr int kMaxExtra = 128;      // extra pieces of long columns (per mode, in LDS)
-constexpr int kExtraFlag = 0x4000;  // dest field of an extra piece
+constexpr int kMaxExtra = 126;      // extra pieces of long column halves (per pair of modes): what the LDS has room for at 2048
+// a node table entry: bit 31 j > N/2; 16-30 dest; 4-15 modes_row_place(min(j, N - j)); 1 last row of a step
+constexpr int kIlRow = 0xfff0, kIlLast = 2;
 constexpr int kMaxRestart = 64;
 constexpr int kMaxSamples = 12288; // boundary samples per problem (the GMRES step keeps one M-vector in LDS)   // GMRES restart length cap (LDS-resident Hessenberg)
 

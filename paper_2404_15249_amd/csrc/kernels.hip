@@ -56,9 +56,9 @@ template <int C, int R>
 __global__ __launch_bounds__(kModeWaves * 64) void k_modes(DevPlan p, const double* __restrict__ corr,
                                                           double* __restrict__ partial, const int* __restrict__ skip) {
     extern __shared__ double smem[];
-    const ModesLds L = modes_lds<R>(smem, p.N);
+    const ModesLds L = modes_lds<C>(smem);
     double* row = partial + (size_t)blockIdx.x * p.M;
-    modes_round<C, R>(p, corr, blockIdx.x * R, L, [&](int cp, double v) { row[cp] = v; }, p.sinq, skip);
+    modes_round<C, R, true>(p, corr, blockIdx.x, L, [&](int cp, double v) { row[cp] = v; }, skip);
 }
 
 // ---------------------------------------------------------------- spline of a density
@@ -86,10 +86,10 @@ __global__ __launch_bounds__(256) void k_interp_grid(DevPlan p, JumpSrc js, cons
     if (cp >= p.M) return;
     int ni[6], nj[6];
     stencil_nodes(p, cp, ni, nj);
-    const double* w = p.cp_w + 6 * (size_t)cp;
+    const double* w = p.cp_w + cp;
     double s = 0.0;
-    for (int k = 0; k < 6; ++k) s += w[k] * R[(size_t)(nj[k] - 1) * p.N + (ni[k] - 1)];
-    out[cp] = s + outside_terms(p, js, cp, ni, nj, w);
+    for (int k = 0; k < 6; ++k) s += w[(size_t)k * p.M] * R[(size_t)(nj[k] - 1) * p.N + (ni[k] - 1)];
+    out[cp] = s + outside_terms(p, js, cp, ni, nj, w, p.M);
 }
 
 // ---------------------------------------------------------------- dense path
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kGmChunk) void k_gm_emit_corr(DevPlan p, GmresBufs 
 
 template <int C, int R>
 hipError_t modes_launch(const DevPlan& p, const double* corr, double* partial, const int* skip, hipStream_t s) {
-    constexpr size_t lds = sizeof(double) * ((size_t)(32 * C + 2) + (size_t)R * (64 * (C + 1) + kMaxExtra));
+    constexpr size_t lds = sizeof(double) * modes_lds_len<C, R>();
     if constexpr (lds > 160 * 1024) {
         return hipErrorInvalidValue;                  // never fits the local data share
     } else {
@@ -283,10 +283,24 @@ hipError_t rows_solve_any(const DevPlan& p, T* A, hipStream_t s) {
     }
 }
 
+template <int C>
+size_t modes_lds_bytes_r(int R) {
+    return sizeof(double) * (R <= 1 ? modes_lds_len<C, 1>() : R == 2 ? modes_lds_len<C, 2>() : R == 4 ? modes_lds_len<C, 4>()
+                                                                                            : modes_lds_len<C, 8>());
+}
+
 }  // namespace
 
 size_t modes_lds_bytes(int N, int R) {
-    return sizeof(double) * ((size_t)(N / 2 + 2) + (size_t)R * (N + 64 + kMaxExtra));
+    switch (N) {
+        case 64: return modes_lds_bytes_r<1>(R);
+        case 128: return modes_lds_bytes_r<2>(R);
+        case 256: return modes_lds_bytes_r<4>(R);
+        case 512: return modes_lds_bytes_r<8>(R);
+        case 1024: return modes_lds_bytes_r<16>(R);
+        case 2048: return modes_lds_bytes_r<32>(R);
+        default: return modes_lds_bytes_r<64>(R);
+    }
 }
 
 hipError_t launch_correct(const DevPlan& p, JumpSrc js, double* corr, double* corr_il, double* dense,
