@@ -103,7 +103,7 @@ struct kfbi_prob {
     int h_flag = 0;              // its host copy
     GmresBufs gm{};
     GmresState st_host{};        // host copy of the GMRES state (stable address for async copies)
-    GmresState* st_pub = nullptr;   // pinned host mirror the device publishes the state to (gm.pub)
+    GmresHost host;              // what the device tells of a run (gm.pub)
     // timing: a start and an end event for each of an apply's three launches,
     // read back by kfbi_apply_timing
     static constexpr int kMaxTimed = 4096;
@@ -155,8 +155,7 @@ kfbi_status upload(kfbi_prob* p, const T** out, const std::vector<T>& v) {
 void free_prob(kfbi_prob* p) {
     for (void* a : p->allocs) hipFree(a);
     p->allocs.clear();
-    if (p->st_pub) hipHostFree(p->st_pub);
-    p->st_pub = nullptr;
+    p->host.free();
     p->gm.pub = nullptr;
     for (auto& e : p->ev)
         if (e) hipEventDestroy(e);
@@ -309,10 +308,10 @@ kfbi_status checked_apply(kfbi_prob* p, int op, const double* phi, double* out) 
 // Restarted GMRES on K_D phi = ghat (ghat already in p->gm.ghat).  Steps are
 // enqueued in batches; with tol > 0 the host polls the device state after each
 // batch, with tol <= 0 the work is fixed and the host waits once at the end.
-// One GMRES step is the apply and the orthogonalisation.  Outside timing mode
-// each step's emit launch also makes the next apply's corrections, so the
-// apply starts from them; run_gmres makes the first step's.  With timing on the
-// corrections get their own launch, timed as a stage of the apply.
+// One GMRES step slot is the apply and the step launch (gmres.h).  Outside timing
+// mode the step launch also makes the next apply's corrections, so the apply starts
+// from them; run_gmres makes the first slot's.  With timing on the corrections get
+// their own launch, timed as a stage of the apply.
 kfbi_status enqueue_steps(kfbi_prob* p, int op, int nsteps, hipStream_t s) {
     GmresBufs b = p->gm;
     const int* skip = &b.st->converged;
@@ -347,123 +346,100 @@ void ensure_graph(kfbi_prob* p, int op, int k) {
 struct GmresRun {
     kfbi_prob* p = nullptr;
     int op = kOpD;
-    int max_steps = 0, steps = 0, batches = 0;
-    bool use_graph = false, poll_each = true, extended = false, finished = false;
+    int max_steps = 0;           // slots of a run without second passes
+    GmresDriver drv;
+    bool finished = false;
 };
 
 // Set up GMRES on K phi = ghat (K_D or K_N by op) from phi_in: ghat <- rhs
 // (null: already in p->gm.ghat), the state, and the first K input with its
-// spline and corrections, in two launches (gm_start); xout (may be null)
-// receives the final iterate from the device.  The run takes at most max_iter
-// Arnoldi steps and one residual step per cycle end: those step slots are
-// launched.  A nonzero guess takes one residual step more, at the start; the
-// run finds that in its last poll and launches one more slot (gmres_more).
+// spline and corrections, in one launch (gm_begin); xout (may be null)
+// receives the final iterate from the device.  The run takes a slot for each of at
+// most max_iter Arnoldi steps and two per cycle: the one in which the cycle's end is
+// found and the residual's.  A nonzero guess takes one residual slot more, at the
+// start, and every second Gram-Schmidt pass takes one.
 kfbi_status gmres_start(kfbi_prob* p, int op, const double* rhs, const double* phi_in, double tol, int max_iter,
                         double* xout, GmresRun* r) {
     hipStream_t s = p->ctx->stream;
     const DevPlan d = op_view(p, op);
     HIP_TRY(launch_gmres_start(&d, p->dp.taps, p->M, p->gm, rhs, phi_in, tol, max_iter, p->reorth, xout,
-                               p->timing ? nullptr : p->corr_il, s));
+                               p->timing ? nullptr : p->corr_il, p->host.next_epoch(), s));
     const int m = std::max(1, p->restart);
     *r = GmresRun{};
     r->p = p;
     r->op = op;
-    r->max_steps = max_iter + (max_iter + m - 1) / m;
-    r->use_graph = !p->timing;
-    r->poll_each = tol > 0;
-    if (r->use_graph)                                   // recorded at the first run, not inside a later one
-        for (int k = 0; k < kfbi_prob::kGraphSizes; ++k) ensure_graph(p, op, k);
+    r->max_steps = max_iter + 2 * ((max_iter + m - 1) / m);
+    r->drv.host = &p->host;
+    r->drv.stream = s;
+    r->drv.most = 2 * r->max_steps + 2;
     return KFBI_OK;
 }
 
-// After the poll of the last slot: whether the run still needs its one extra
-// residual step (a nonzero initial guess); if so the slot is added.
-bool gmres_more(GmresRun& r) {
-    if (r.p->st_host.converged || r.extended) return false;
-    r.extended = true;
-    r.max_steps += 1;
-    return true;
+// One turn of a run that may stop early (GmresDriver).
+kfbi_status gmres_drive(GmresRun& r) {
+    return r.drv.drive([&](hipStream_t s) { return enqueue_steps(r.p, r.op, 1, s); }, &r.finished);
 }
 
-// Enqueue the next batch of steps: kGraphSteps, or the largest power of two
-// not above what is left (a replayed graph unless per-launch timing is on);
-// returns through *poll whether the state should be read after it (every
-// batch when the run can stop early, else only after the last).  A run that
-// can stop early takes batches of 8, 16, then 32 steps: the steps launched
-// after the device has converged return at once but still cost their
-// launches (about 7 us a step), a poll costs about three of them.
-kfbi_status gmres_batch(GmresRun& r, bool* poll) {
+// The slots of a run of fixed length, from replayed graphs of up to 32 (launched
+// directly while per-launch timing is on).
+kfbi_status gmres_fixed(GmresRun& r, int slots) {
     kfbi_prob* p = r.p;
     hipStream_t s = p->ctx->stream;
-    const int cap = r.poll_each ? std::min(kfbi_prob::kGraphSteps, 8 << std::min(r.batches, 4)) : kfbi_prob::kGraphSteps;
-    const int want = std::min(r.max_steps - r.steps, cap);
-    int k = 0;
-    while ((kfbi_prob::kGraphSteps >> k) > want && k + 1 < kfbi_prob::kGraphSizes) ++k;
-    const int n = kfbi_prob::kGraphSteps >> k;
-    if (r.use_graph) ensure_graph(p, r.op, k);
-    if (r.use_graph && p->gexec[r.op][k]) {
-        HIP_TRY(hipGraphLaunch(p->gexec[r.op][k], s));
-    } else if (kfbi_status e = enqueue_steps(p, r.op, n, s)) {
-        return e;
+    while (slots > 0) {
+        int k = 0;
+        while ((kfbi_prob::kGraphSteps >> k) > slots && k + 1 < kfbi_prob::kGraphSizes) ++k;
+        const int n = kfbi_prob::kGraphSteps >> k;
+        if (!p->timing) ensure_graph(p, r.op, k);
+        if (!p->timing && p->gexec[r.op][k]) {
+            HIP_TRY(hipGraphLaunch(p->gexec[r.op][k], s));
+        } else if (kfbi_status e = enqueue_steps(p, r.op, n, s)) {
+            return e;
+        }
+        slots -= n;
     }
-    r.steps += n;
-    r.batches += 1;
-    *poll = r.poll_each || r.steps >= r.max_steps;
-    return KFBI_OK;
-}
-
-// Wait for the stream and take the state the device last published (every
-// residual step, a run's end and its start publish it) into p->st_host.
-kfbi_status gmres_read_state(kfbi_prob* p) {
-    HIP_TRY(hipStreamSynchronize(p->ctx->stream));
-    p->st_host = *p->st_pub;
     return KFBI_OK;
 }
 
 // Restarted GMRES on K phi = ghat (K_D or K_N by op; ghat <- rhs, or already
-// in p->gm.ghat when rhs is null).  Steps go in batches (a replayed graph
-// unless per-launch timing is on); with tol > 0 the host polls the device
-// state after each batch, with tol <= 0 the work is fixed and the host waits
-// once at the end.
+// in p->gm.ghat when rhs is null).  With tol > 0 the slots are launched as the run
+// goes (GmresDriver); with tol <= 0 the work is fixed: its slots are launched at once
+// and the host waits at the end (then for the slots a nonzero guess or second passes
+// have taken besides, one, two, four at a time).
 kfbi_status run_gmres(kfbi_prob* p, int op, const double* rhs, const double* phi_in, double tol, int max_iter,
                       GmresState* out, double* x_out = nullptr) {
     GmresRun r;
     if (kfbi_status e = gmres_start(p, op, rhs, phi_in, tol, max_iter, x_out, &r)) return e;
-    for (;;) {
-        if (r.steps >= r.max_steps && !gmres_more(r)) break;
-        bool poll = false;
-        if (kfbi_status e = gmres_batch(r, &poll)) return e;
-        if (poll) {
-            if (kfbi_status e = gmres_read_state(p)) return e;
-            if (p->st_host.converged) break;
+    if (tol > 0) {
+        while (!r.finished)
+            if (kfbi_status e = gmres_drive(r)) return e;
+    } else {
+        if (!p->timing)                                     // recorded at the first run, not inside a later one
+            for (int k = 0; k < kfbi_prob::kGraphSizes; ++k) ensure_graph(p, op, k);
+        for (int slots = r.max_steps, launched = 0, more = 1;; slots = more, more *= 2) {
+            if (launched >= r.drv.most) return set_err(KFBI_ERR_DEVICE, "a GMRES run did not end");
+            if (kfbi_status e = gmres_fixed(r, slots)) return e;
+            launched += slots;
+            HIP_TRY(hipStreamSynchronize(p->ctx->stream));
+            if (p->host.over()) break;
         }
     }
-    *out = p->st_host;
+    *out = p->host.pub->st;
     return KFBI_OK;
 }
 
-// GMRES on two problems at once, each on its own stream: every round enqueues a
-// batch on each problem that is still running, then reads both states, so the
-// two runs overlap on the device.
+// GMRES on two problems at once, each on its own stream, their slots launched in
+// turn, so the two runs overlap on the device.
 kfbi_status run_gmres_pair(kfbi_prob* pa, int opa, const double* xa, kfbi_prob* pb, int opb, const double* xb,
                            GmresState* outa, GmresState* outb) {
     GmresRun r[2];
     if (kfbi_status e = gmres_start(pa, opa, nullptr, xa, pa->tol, pa->max_iter, nullptr, &r[0])) return e;
     if (kfbi_status e = gmres_start(pb, opb, nullptr, xb, pb->tol, pb->max_iter, nullptr, &r[1])) return e;
-    while (!(r[0].finished && r[1].finished)) {
-        for (auto& q : r) {
-            if (q.finished) continue;
-            bool poll = false;
-            if (kfbi_status e = gmres_batch(q, &poll)) return e;
-        }
-        for (auto& q : r) {
-            if (q.finished) continue;
-            if (kfbi_status e = gmres_read_state(q.p)) return e;
-            if (q.p->st_host.converged || (q.steps >= q.max_steps && !gmres_more(q))) q.finished = true;
-        }
-    }
-    *outa = pa->st_host;
-    *outb = pb->st_host;
+    while (!(r[0].finished && r[1].finished))
+        for (auto& q : r)
+            if (!q.finished)
+                if (kfbi_status e = gmres_drive(q)) return e;
+    *outa = pa->host.pub->st;
+    *outb = pb->host.pub->st;
     return KFBI_OK;
 }
 
@@ -477,6 +453,7 @@ kfbi_status gmres_call(kfbi_prob* p, int op, const double* rhs, double* x, doubl
     HIP_TRY(hipSetDevice(p->ctx->device));
     GmresState st{};
     if (kfbi_status e = run_gmres(p, op, rhs, x, tol, max_iter, &st, x)) return e;
+    HIP_TRY(hipStreamSynchronize(p->ctx->stream));          // the iterate's copy
     if (st.converged == kGmNonfinite) return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in rhs or the initial guess");
     if (iters) *iters = st.it;
     if (applies) *applies = st.it + st.res_applies;
@@ -800,13 +777,19 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     {
         constexpr int NW = kModeWaves * 64;
         auto xpos_of = [&](int i) { return i + (i - 1) / modes_chunk(n); };
-        std::vector<std::vector<int>> half(2 * (n + 1));      // parity q, column i: nodes at q (n + 1) + i
-        for (int i = 0; i <= n; ++i)
-            for (int r = colptr[i]; r < colptr[i + 1]; ++r) half[(P.irr_j[r] & 1) * (n + 1) + i].push_back(r);
+        // the nodes by (parity, column): half h's are by_half[off[h] .. off[h + 1])
+        const int n_half = 2 * (n + 1);
+        std::vector<int> off(n_half + 1, 0), by_half(p->I);
+        for (int r = 0; r < p->I; ++r) off[(P.irr_j[r] & 1) * (n + 1) + P.irr_i[r] + 1] += 1;
+        for (int h = 0; h < n_half; ++h) off[h + 1] += off[h];
+        {
+            std::vector<int> at(off.begin(), off.end() - 1);
+            for (int r = 0; r < p->I; ++r) by_half[at[(P.irr_j[r] & 1) * (n + 1) + P.irr_i[r]]++] = r;
+        }
         int cap = std::max(1, (p->I + NW - 1) / NW);
         for (;;) {
             long extra = 0;
-            for (const auto& v : half) extra += std::max(0, ((int)v.size() + cap - 1) / cap - 1);
+            for (int h = 0; h < n_half; ++h) extra += std::max(0, (off[h + 1] - off[h] + cap - 1) / cap - 1);
             if (extra <= kMaxExtra) break;
             cap *= 2;
         }
@@ -816,8 +799,8 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         };
         std::vector<Piece> pieces;
         int n_extra = 0;
-        for (int c = 0; c < (int)half.size(); ++c) {
-            const int cnt = (int)half[c].size(), pos = xpos_of(c % (n + 1)) + c / (n + 1) * modes_stride_of(n);
+        for (int c = 0; c < n_half; ++c) {
+            const int cnt = off[c + 1] - off[c], pos = xpos_of(c % (n + 1)) + c / (n + 1) * modes_stride_of(n);
             if (cnt == 0) continue;
             const int np = (cnt + cap - 1) / cap;
             if (np > 1) {
@@ -826,7 +809,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
                 split.push_back(np - 1);
             }
             for (int k = 0; k < np; ++k)
-                pieces.push_back({half[c].data() + k * cap, std::min(cnt - k * cap, cap),
+                pieces.push_back({by_half.data() + off[c] + k * cap, std::min(cnt - k * cap, cap),
                                   k == 0 ? pos : 2 * modes_stride_of(n) + n_extra++});
         }
         std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& b) { return a.count > b.count; });
@@ -959,9 +942,9 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         (st = dev_alloc(p, &p->gm.sn, m)) || (st = dev_alloc(p, &p->gm.g, m + 1)) ||
         (st = dev_alloc(p, &p->gm.ghat, M)) || (st = dev_alloc(p, &p->gm.phi, M)) ||
         (st = dev_alloc(p, &p->gm.xcur, M)) || (st = dev_alloc(p, &p->gm.w, M)) ||
-        (st = dev_alloc(p, &p->gm.z, M)) || (st = dev_alloc(p, &p->gm.part, gm_part_size(m, gm_chunks(M), gm_chunks64(M)))) ||
-        (st = dev_alloc(p, &p->gm.y, m + 1)) || (st = dev_alloc(p, &p->gm.st, 1)) ||
-        (st = dev_alloc(p, &p->gm.cnt, 1)))
+        (st = dev_alloc(p, &p->gm.z, M)) || (st = dev_alloc(p, &p->gm.part, gm_part_size(m, gm_chunks(M, true), gm_chunks64(M)))) ||
+        (st = dev_alloc(p, &p->gm.y, m + 1)) || (st = dev_alloc(p, &p->gm.h, m + 1)) ||
+        (st = dev_alloc(p, &p->gm.st, 1)))
         return fail(st);
     {
         IterBufs& ib = p->ib;
@@ -971,22 +954,14 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         if ((st = dev_alloc(p, &ib.st, 1))) return fail(st);
         ib.M = M;
     }
-    HIP_TRY(hipMemset(p->gm.cnt, 0, sizeof(unsigned)));
-    // the state's host mirror: pinned, coherent host memory the device writes to
-    if (hipHostMalloc((void**)&p->st_pub, sizeof(GmresState), hipHostMallocMapped | hipHostMallocCoherent) !=
-        hipSuccess) {
-        hipGetLastError();
-        p->st_pub = nullptr;
-        return fail(set_err(KFBI_ERR_OOM, "pinned host allocation of the GMRES state mirror failed"));
-    }
-    *p->st_pub = GmresState{};
-    p->gm.pub = p->st_pub;
+    if ((st = p->host.alloc())) return fail(st);
+    p->gm.pub = p->host.pub;
     if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
     if (p->refine >= 2 && (st = dev_alloc(p, &p->D, (size_t)n * n))) return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
     p->gm.m = m;
-    p->gm.gc = gm_chunks(M);
+    p->gm.gc = gm_chunks(M, true);
     p->gm.gc64 = gm_chunks64(M);
     *out = p;
     return KFBI_OK;
@@ -1449,15 +1424,13 @@ struct kfbi_batch {
     std::vector<SlotDev> h_slots;
     SlotDev* d_slots = nullptr;
     int* d_counts = nullptr;
-    int2* d_corr = nullptr;
     int2* d_mode = nullptr;
     int2* d_cp = nullptr;
     int2* d_gm = nullptr;
-    int* d_live = nullptr;
-    int cap_corr = 0, cap_mode = 0, cap_cp = 0, cap_gm = 0;
-    std::vector<int2> h_corr, h_mode, h_cp, h_gm;
-    std::vector<int> h_live;
-    int h_counts[kBatchCounts] = {0, 0, 0, 0, 0};
+    int cap_mode = 0, cap_cp = 0, cap_gm = 0;
+    std::vector<int2> h_mode, h_cp, h_gm;
+    int live = 0;
+    int h_counts[kBatchCounts] = {0, 0, 0};
     // pinned staging of the uploads, reused once the event says the stream has
     // consumed the previous upload
     char* stage = nullptr;
@@ -1471,13 +1444,12 @@ struct kfbi_batch {
 namespace {
 
 void batch_free_lists(kfbi_batch* B) {
-    for (void* q : {(void*)B->d_corr, (void*)B->d_mode, (void*)B->d_cp, (void*)B->d_gm})
+    for (void* q : {(void*)B->d_mode, (void*)B->d_cp, (void*)B->d_gm})
         if (q) hipFree(q);
-    B->d_corr = nullptr;
     B->d_mode = nullptr;
     B->d_cp = nullptr;
     B->d_gm = nullptr;
-    B->cap_corr = B->cap_mode = B->cap_cp = B->cap_gm = 0;
+    B->cap_mode = B->cap_cp = B->cap_gm = 0;
 }
 
 kfbi_status batch_grow(hipStream_t s, int2** d, int* cap, size_t need) {
@@ -1499,39 +1471,35 @@ kfbi_status batch_grow(hipStream_t s, int2** d, int* cap, size_t need) {
 
 // Rebuild the work lists of the live slots and upload them (stream ordered).
 kfbi_status batch_rebuild(kfbi_batch* B) {
-    B->h_corr.clear();
     B->h_mode.clear();
     B->h_cp.clear();
     B->h_gm.clear();
-    B->h_live.clear();
+    B->live = 0;
     for (int s = 0; s < B->max_slots; ++s) {
         kfbi_prob* p = B->slot[s];
         if (!p) continue;
-        B->h_live.push_back(s);
-        for (int r = 0; r < p->I; r += 256) B->h_corr.push_back(make_int2(s, r));
+        B->live += 1;
         for (int b = 0; b < p->Gs; ++b) B->h_mode.push_back(make_int2(s, b));
+        B->h_cp.push_back(make_int2(s, -1));             // the commit, the longest of the slot's items, first
         for (int c = 0; c < p->M; c += 64) B->h_cp.push_back(make_int2(s, c));
-        for (int c = 0; c < p->gm.gc; ++c) B->h_gm.push_back(make_int2(s, c));
+        for (int c = 0; c < p->gm.gc + p->dp.n_cc; ++c) B->h_gm.push_back(make_int2(s, c));
     }
-    const int2* old[4] = {B->d_corr, B->d_mode, B->d_cp, B->d_gm};
+    const int2* old[3] = {B->d_mode, B->d_cp, B->d_gm};
     hipStream_t gs = B->ctx->stream;
-    if (kfbi_status e = batch_grow(gs, &B->d_corr, &B->cap_corr, std::max<size_t>(B->h_corr.size(), 1))) return e;
     if (kfbi_status e = batch_grow(gs, &B->d_mode, &B->cap_mode, std::max<size_t>(B->h_mode.size(), 1))) return e;
     if (kfbi_status e = batch_grow(gs, &B->d_cp, &B->cap_cp, std::max<size_t>(B->h_cp.size(), 1))) return e;
     if (kfbi_status e = batch_grow(gs, &B->d_gm, &B->cap_gm, std::max<size_t>(B->h_gm.size(), 1))) return e;
-    if (old[0] != B->d_corr || old[1] != B->d_mode || old[2] != B->d_cp || old[3] != B->d_gm) {
+    if (old[0] != B->d_mode || old[1] != B->d_cp || old[2] != B->d_gm) {
         // the captured graph holds the old list addresses
         if (B->gexec) hipGraphExecDestroy(B->gexec);
         B->gexec = nullptr;
     }
     hipStream_t s = B->ctx->stream;
-    B->h_counts[0] = (int)B->h_corr.size();
-    B->h_counts[1] = (int)B->h_mode.size();
-    B->h_counts[2] = (int)B->h_cp.size();
-    B->h_counts[3] = (int)B->h_live.size();
-    B->h_counts[4] = (int)B->h_gm.size();
-    const size_t nb = sizeof(int2) * (B->h_corr.size() + B->h_mode.size() + B->h_cp.size() + B->h_gm.size()) +
-                      sizeof(int) * (B->h_live.size() + kBatchCounts) + sizeof(SlotDev) * B->max_slots;
+    B->h_counts[0] = (int)B->h_mode.size();
+    B->h_counts[1] = (int)B->h_cp.size();
+    B->h_counts[2] = (int)B->h_gm.size();
+    const size_t nb = sizeof(int2) * (B->h_mode.size() + B->h_cp.size() + B->h_gm.size()) +
+                      sizeof(int) * kBatchCounts + sizeof(SlotDev) * B->max_slots;
     HIP_TRY(hipEventSynchronize(B->up_ev));
     if (nb > B->stage_cap) {
         if (B->stage) hipHostFree(B->stage);
@@ -1550,11 +1518,9 @@ kfbi_status batch_rebuild(kfbi_batch* B) {
         return KFBI_OK;
     };
     kfbi_status e = KFBI_OK;
-    if ((e = put(B->d_corr, B->h_corr.data(), B->h_corr.size() * sizeof(int2))) ||
-        (e = put(B->d_mode, B->h_mode.data(), B->h_mode.size() * sizeof(int2))) ||
+    if ((e = put(B->d_mode, B->h_mode.data(), B->h_mode.size() * sizeof(int2))) ||
         (e = put(B->d_cp, B->h_cp.data(), B->h_cp.size() * sizeof(int2))) ||
         (e = put(B->d_gm, B->h_gm.data(), B->h_gm.size() * sizeof(int2))) ||
-        (e = put(B->d_live, B->h_live.data(), B->h_live.size() * sizeof(int))) ||
         (e = put(B->d_counts, B->h_counts, sizeof B->h_counts)) ||
         (e = put(B->d_slots, B->h_slots.data(), sizeof(SlotDev) * B->max_slots)))
         return e;
@@ -1565,12 +1531,9 @@ kfbi_status batch_rebuild(kfbi_batch* B) {
 BatchWork batch_work(const kfbi_batch* B) {
     BatchWork w;
     w.counts = B->d_counts;
-    w.corr_items = B->d_corr;
     w.mode_items = B->d_mode;
     w.cp_items = B->d_cp;
-    w.live = B->d_live;
     w.gm_items = B->d_gm;
-    w.max_live = B->max_slots;
     return w;
 }
 
@@ -1608,7 +1571,7 @@ kfbi_status kfbi_batch_estimate_bytes(int n, int m, int restart, size_t* bytes) 
                (size_t)(n + 1) * (n + 1) + (size_t)n * (sizeof(ModeConst) + 16) + 4096;
     b += 2 * sizeof(double) * (size_t)n * n;                                  // dense-path grids
     b += sizeof(double) * ((size_t)(restart + 1) * (m + restart) + 16 * (size_t)m +
-                           gm_part_size(restart, gm_chunks(m), gm_chunks64(m)) + restart + 2);   // GMRES
+                           gm_part_size(restart, gm_chunks(m, true), gm_chunks64(m)) + 2 * (restart + 2));   // GMRES
     b += sizeof(double) * (size_t)m * 512;                                    // single-path partials
     b += batch_extra_bytes(n, m);
     *bytes = b;
@@ -1632,8 +1595,7 @@ kfbi_status kfbi_batch_create(kfbi_ctx* ctx, int max_slots, int m_max, size_t bu
     B->h_slots.resize(max_slots);
     bool ok = hipEventCreateWithFlags(&B->up_ev, hipEventDisableTiming) == hipSuccess &&
               hipMalloc((void**)&B->d_slots, sizeof(SlotDev) * max_slots) == hipSuccess &&
-              hipMalloc((void**)&B->d_counts, sizeof(int) * kBatchCounts) == hipSuccess &&
-              hipMalloc((void**)&B->d_live, sizeof(int) * max_slots) == hipSuccess;
+              hipMalloc((void**)&B->d_counts, sizeof(int) * kBatchCounts) == hipSuccess;
     if (!ok) {
         hipGetLastError();
         kfbi_batch_destroy(B);
@@ -1653,7 +1615,7 @@ kfbi_status kfbi_batch_destroy(kfbi_batch* B) {
     hipStreamSynchronize(B->ctx->stream);
     if (B->gexec) hipGraphExecDestroy(B->gexec);
     batch_free_lists(B);
-    for (void* q : {(void*)B->d_slots, (void*)B->d_counts, (void*)B->d_live})
+    for (void* q : {(void*)B->d_slots, (void*)B->d_counts})
         if (q) hipFree(q);
     if (B->stage) hipHostFree(B->stage);
     if (B->up_ev) hipEventDestroy(B->up_ev);
@@ -1690,10 +1652,9 @@ kfbi_status kfbi_batch_admit(kfbi_batch* B, kfbi_prob* p, const double* f_grid, 
     if (kfbi_status e = dense_interface_solve(p, false, jy, f_grid, true, nullptr, false, p->tmpM)) return e;
     GmresBufs b = p->gm;
     HIP_TRY(launch_axpby(p->M, 1.0, g, -1.0, p->tmpM, b.ghat, s));
-    // the state and the first Arnoldi input (phi_0 = 0: the residual is g^);
-    // the batch's own correction stage makes its corrections
-    HIP_TRY(launch_gmres_start(nullptr, p->dp.taps, p->M, b, nullptr, nullptr, p->tol, p->max_iter, p->reorth,
-                               nullptr, nullptr, s));
+    // the state and the first Arnoldi input (phi_0 = 0: the residual is g^) with its corrections
+    HIP_TRY(launch_gmres_start(&p->dp, p->dp.taps, p->M, b, nullptr, nullptr, p->tol, p->max_iter, p->reorth, nullptr,
+                               p->corr_il, p->host.next_epoch(), s));
     p->st_host = GmresState{};
     SlotDev& S = B->h_slots[free_slot];
     S.p = p->dp;
@@ -1714,7 +1675,7 @@ kfbi_status kfbi_batch_admit(kfbi_batch* B, kfbi_prob* p, const double* f_grid, 
 
 kfbi_status kfbi_batch_step(kfbi_batch* B, int nsteps) {
     if (!B || nsteps < 0) return set_err(KFBI_ERR_ARG, "bad arguments");
-    if (B->h_live.empty() || nsteps == 0) return KFBI_OK;
+    if (B->live == 0 || nsteps == 0) return KFBI_OK;
     HIP_TRY(hipSetDevice(B->ctx->device));
     batch_ensure_graph(B);
     const int K = kfbi_batch::kGraphSteps;
@@ -1770,7 +1731,7 @@ kfbi_status kfbi_batch_finish(kfbi_batch* B, int slot, double* u_grid, double* u
 
 kfbi_status kfbi_batch_info(const kfbi_batch* B, int* live, size_t* bytes) {
     if (!B) return set_err(KFBI_ERR_ARG, "batch is NULL");
-    if (live) *live = (int)B->h_live.size();
+    if (live) *live = B->live;
     if (bytes) *bytes = B->used;
     return KFBI_OK;
 }

@@ -33,7 +33,7 @@ struct kfbi_prob3 {
     int h_flag = 0;
     int dstB = 16;
     GmresBufs gm{};
-    GmresState st_host{};
+    GmresHost host;              // what the device tells of a run (gm.pub)
     static constexpr int kGraphSteps = 8;
     hipGraphExec_t gexec = nullptr;
     bool graph_failed = false;
@@ -68,6 +68,7 @@ kfbi_status upload3(kfbi_prob3* p, const T** out, const std::vector<T>& v) {
 void free3(kfbi_prob3* p) {
     if (p->gexec) hipGraphExecDestroy(p->gexec);
     for (void* a : p->allocs) hipFree(a);
+    p->host.free();
     delete p;
 }
 
@@ -101,44 +102,43 @@ kfbi_status enqueue_steps3(kfbi_prob3* p, int nsteps, hipStream_t s) {
 }
 
 // Restarted GMRES on K_D phi = ghat (ghat already in gm.ghat), as for the
-// curve problem: batches of steps replayed from one recorded graph, the
-// host polling the device state between batches when tol > 0.
+// curve problem: slots launched as the run goes when it may stop early, else
+// replayed from one recorded graph of several.
 kfbi_status run_gmres3(kfbi_prob3* p, const double* phi_in, double tol, int max_iter, GmresState* out) {
     hipStream_t s = p->ctx->stream;
     GmresBufs b = p->gm;
-    // the state and the first K_D input on the device (gm_start)
+    // the state and the first K_D input on the device (gm_begin)
     HIP_TRY(launch_gmres_start(nullptr, nullptr, p->M, b, nullptr, phi_in, tol, max_iter, kGmReorthDefault, nullptr,
-                               nullptr, s));
-    if (!p->gexec && !p->graph_failed)
-        p->graph_failed = !record_graph(s, &p->gexec,
-                                        [&](hipStream_t st) { return enqueue_steps3(p, kfbi_prob3::kGraphSteps, st); });
-    // Arnoldi steps and one residual step per cycle end; a nonzero guess takes
-    // one residual step more, found in the last poll
-    const int m = std::max(1, p->restart);
-    int max_steps = max_iter + (max_iter + m - 1) / m;
-    bool extended = false;
-    const int B = kfbi_prob3::kGraphSteps;
-    GmresState& st = p->st_host;
-    for (int done = 0;;) {
-        if (done >= max_steps) {
-            if (st.converged || extended) break;
-            extended = true;
-            max_steps += 1;
-        }
-        const int n = std::min(B, max_steps - done);
-        if (p->gexec && n == B) {
-            HIP_TRY(hipGraphLaunch(p->gexec, s));
-        } else if (kfbi_status e = enqueue_steps3(p, n, s)) {
-            return e;
-        }
-        done += n;
-        if (tol > 0 || done >= max_steps) {
-            HIP_TRY(hipMemcpyAsync(&st, b.st, sizeof st, hipMemcpyDeviceToHost, s));
+                               nullptr, p->host.next_epoch(), s));
+    // a slot per Arnoldi step and two per cycle (its end is found in one, the
+    // residual takes the other); a nonzero guess and second Gram-Schmidt passes take more
+    const int m = std::max(1, p->restart), max_steps = max_iter + 2 * ((max_iter + m - 1) / m), most = 2 * max_steps + 2;
+    if (tol > 0) {
+        GmresDriver drv;
+        drv.host = &p->host;
+        drv.stream = s;
+        drv.most = most;
+        for (bool over = false; !over;)
+            if (kfbi_status e = drv.drive([&](hipStream_t st) { return enqueue_steps3(p, 1, st); }, &over)) return e;
+    } else {
+        const int B = kfbi_prob3::kGraphSteps;
+        if (!p->gexec && !p->graph_failed)
+            p->graph_failed = !record_graph(s, &p->gexec, [&](hipStream_t st) { return enqueue_steps3(p, B, st); });
+        for (int slots = max_steps, launched = 0, more = 1;; slots = more, more *= 2) {
+            if (launched >= most) return set_err(KFBI_ERR_DEVICE, "a GMRES run did not end");
+            launched += slots;
+            for (; slots > 0; slots -= B) {
+                if (p->gexec && slots >= B) {
+                    HIP_TRY(hipGraphLaunch(p->gexec, s));
+                } else if (kfbi_status e = enqueue_steps3(p, std::min(B, slots), s)) {
+                    return e;
+                }
+            }
             HIP_TRY(hipStreamSynchronize(s));
-            if (st.converged) break;
+            if (p->host.over()) break;
         }
     }
-    *out = st;
+    *out = p->host.pub->st;
     return KFBI_OK;
 }
 
@@ -218,14 +218,16 @@ kfbi_status kfbi3_prob_create(kfbi_ctx* ctx, const kfbi_desc3* d, kfbi_prob3** o
         (st = alloc3(p, &b.cs, m)) || (st = alloc3(p, &b.sn, m)) || (st = alloc3(p, &b.g, m + 1)) ||
         (st = alloc3(p, &b.ghat, M)) || (st = alloc3(p, &b.phi, M)) || (st = alloc3(p, &b.xcur, M)) ||
         (st = alloc3(p, &b.w, M)) || (st = alloc3(p, &b.z, M)) ||
-        (st = alloc3(p, &b.part, gm_part_size(m, gm_chunks(M), gm_chunks64(M)))) || (st = alloc3(p, &b.y, m + 1)) ||
-        (st = alloc3(p, &b.st, 1)) || (st = alloc3(p, &b.cnt, 1)))
+        (st = alloc3(p, &b.part, gm_part_size(m, gm_chunks(M, false), gm_chunks64(M)))) ||
+        (st = alloc3(p, &b.y, m + 1)) || (st = alloc3(p, &b.h, m + 1)) || (st = alloc3(p, &b.st, 1)))
         return fail(st);
+    if ((st = p->host.alloc())) return fail(st);
+    b.pub = p->host.pub;
     b.s2cur = nullptr;
     b.m = m;
-    b.gc = gm_chunks(M);
+    b.gc = gm_chunks(M, false);
     b.gc64 = gm_chunks64(M);
-    if (hipMemset(b.cnt, 0, sizeof(unsigned)) != hipSuccess || hipMemset(p->zeroM, 0, M * sizeof(double)) != hipSuccess)
+    if (hipMemset(p->zeroM, 0, M * sizeof(double)) != hipSuccess)
         return fail(set_err(KFBI_ERR_DEVICE, "hipMemset failed"));
     p->dstB = dst_default_tile(N, 2 * sizeof(double), ctx->lds_max, (long)N * N, ctx->num_cu);
     if (p->dstB == 0) return fail(set_err(KFBI_ERR_UNSUPPORTED, "no column-transform tile fits this grid"));

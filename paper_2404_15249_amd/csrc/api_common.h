@@ -7,6 +7,7 @@
 #include <string>
 
 #include <cmath>
+#include <thread>
 
 #include "graph.h"
 #include "kernels.h"
@@ -46,6 +47,100 @@ inline ModeConst row_solve_constants(double d, int N) {
     c.smc = -r / (1.0 - r2N);
     return c;
 }
+
+// The host's end of a GMRES run's GmresPub: pinned, coherent host memory.
+struct GmresHost {
+    GmresPub* pub = nullptr;
+    unsigned epoch = 0;                                      // of the run in flight
+
+    kfbi_status alloc() {
+        if (hipHostMalloc((void**)&pub, sizeof(GmresPub), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            hipGetLastError();
+            pub = nullptr;
+            return set_err(KFBI_ERR_OOM, "pinned host allocation of the GMRES state mirror failed");
+        }
+        *pub = GmresPub{};
+        return KFBI_OK;
+    }
+    void free() {
+        if (pub) hipHostFree(pub);
+        pub = nullptr;
+    }
+    unsigned next_epoch() { return epoch = epoch + 1 ? epoch + 1 : 1; }
+    bool over() const { return __atomic_load_n(&pub->done, __ATOMIC_ACQUIRE) == epoch; }
+    unsigned again() const { return __atomic_load_n(&pub->again, __ATOMIC_RELAXED); }
+    // slots of this run whose commit has run; *last: the next one is expected to end it
+    int committed(bool* last) const {
+        const unsigned long long v = __atomic_load_n(&pub->prog, __ATOMIC_RELAXED);
+        if ((unsigned)(v >> 32) != epoch) {
+            *last = false;
+            return 0;
+        }
+        *last = ((unsigned)v & kGmLastSlot) != 0;
+        return (int)((unsigned)v & (kGmLastSlot - 1));
+    }
+};
+
+// Runs the slots of a run that may stop early: `enqueue` launches one slot on the
+// stream.  A slot is launched while the one before it runs, as soon as the commit
+// before that is known, and none beyond the one expected to end the run; so the
+// device does not wait for the host between slots and no launched slot finds the run
+// over.  (Replayed graphs of several slots, polled in between, launched up to half of
+// their slots for nothing, 5 us each, and a poll left the device idle for 25 us; a
+// slot launched by itself takes 1 us more than in a graph.)  `drive` does what can be
+// done now; several runs may be driven in turn.
+struct GmresDriver {
+    GmresHost* host = nullptr;
+    hipStream_t stream = nullptr;
+    int launched = 0, most = 0;                              // most: a bound no run reaches
+    int held = 0;                                            // the commit that announced the end (0: none)
+    unsigned again = 0;                                      // residuals seen before that
+    unsigned spins = 0;
+    bool idle = false;                                       // the stream was seen empty after the last launch
+
+    template <class F>
+    kfbi_status drive(F enqueue, bool* over) {
+        *over = host->over();
+        if (*over) return KFBI_OK;
+        bool last = false;
+        const unsigned seen = host->again();                 // before the commit: a residual in between counts as new
+        int done = host->committed(&last);
+        if (idle) {                                          // everything launched has run
+            done = launched;
+            held = 0;
+        } else if (last && held != done) {
+            held = done;
+            again = seen;
+        }
+        const bool hold = held && launched > held && host->again() == again;
+        if (launched - done <= 1 && !hold) {
+            if (launched >= most) {                          // never: the device ends every run before
+                const hipError_t e = hipStreamSynchronize(stream);
+                if (e != hipSuccess) return set_err(KFBI_ERR_DEVICE, hipGetErrorString(e));
+                if ((*over = host->over())) return KFBI_OK;
+                return set_err(KFBI_ERR_DEVICE, "a GMRES run did not end");
+            }
+            spins = 0;
+            idle = false;
+            launched += 1;
+            return enqueue(stream);
+        }
+        // waiting: now and then ask the runtime, so that a failed stream is found
+        // and none is waited for in vain
+        if ((++spins & 0x3ff) == 0) {
+            const hipError_t e = hipStreamQuery(stream);
+            if (e == hipErrorNotReady) {
+                hipGetLastError();
+            } else if (e != hipSuccess) {
+                return set_err(KFBI_ERR_DEVICE, hipGetErrorString(e));
+            } else {
+                idle = true;
+            }
+        }
+        std::this_thread::yield();
+        return KFBI_OK;
+    }
+};
 
 // Record what `enqueue(stream)` launches as the nodes of a new graph (see
 // graph.h: no stream capture) and instantiate it.  Returns false (and leaves

@@ -32,18 +32,15 @@ struct SlotDev {
 };
 
 // Work lists of the batched launches, rebuilt on the host when a slot is
-// admitted or released.  counts = {correction items, mode items, sample items,
-// live slots, GMRES chunk items}; items are (slot, first index) pairs.
+// admitted or released.  counts = {mode items, reduce items, step items}; items
+// are (slot, first index) pairs.
 struct BatchWork {
     const int* counts;
-    const int2* corr_items;   // blocks of 256 irregular nodes
     const int2* mode_items;   // mode blocks of batch_modes_per_group(N) modes
-    const int2* cp_items;     // blocks of 64 samples
-    const int* live;          // live slot ids
-    const int2* gm_items;     // (slot, chunk) of the GMRES vector launches
-    int max_live;
+    const int2* cp_items;     // blocks of 64 samples, and (slot, -1) the commit
+    const int2* gm_items;     // (slot, chunk): vector chunks, then correction chunks
 };
-constexpr int kBatchCounts = 5;
+constexpr int kBatchCounts = 3;
 
 size_t modes_b_lds_bytes();
 hipError_t launch_batch_step(const SlotDev* slots, BatchWork w, int n_cu, hipStream_t s);

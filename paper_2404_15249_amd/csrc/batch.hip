@@ -18,19 +18,6 @@ namespace {
 
 __device__ __forceinline__ bool slot_done(const SlotDev& S) { return S.b.st->converged != 0; }
 
-__global__ __launch_bounds__(256) void k_correct_b(const SlotDev* __restrict__ slots, BatchWork w) {
-    const int n_items = w.counts[0];
-    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const int2 item = w.corr_items[it];
-        const SlotDev& S = slots[item.x];
-        if (slot_done(S)) continue;
-        const int r = item.y + threadIdx.x;
-        if (r >= S.p.I) continue;
-        const JumpSrc js{S.b.xcur, S.b.s2cur, nullptr, nullptr, nullptr, nullptr};
-        S.corr_il[S.p.il_pos[r]] = correction_at(S.p, js, r);
-    }
-}
-
 template <int C>
 __device__ __forceinline__ void modes_item(const DevPlan& p, const double* corr, int row, const ModesLds& L,
                                            double* part) {
@@ -43,7 +30,7 @@ __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __re
     ModesLds L;
     L.sq = smem;
     L.xs = smem + kBatchTable;
-    const int n_items = w.counts[1];
+    const int n_items = w.counts[0];
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 item = w.mode_items[it];
         const SlotDev& S = slots[item.x];
@@ -61,30 +48,38 @@ __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __re
     }
 }
 
+// A slot's reduce items: 64 samples from item.y on, or (item.y < 0) its commit.
 __global__ __launch_bounds__(1024) void k_reduce_b(const SlotDev* __restrict__ slots, BatchWork w) {
     __shared__ double red[16 * 64];
-    const int n_items = w.counts[2];
+    const int n_items = w.counts[1];
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 item = w.cp_items[it];
         const SlotDev& S = slots[item.x];
-        if (slot_done(S)) continue;
-        const JumpSrc js{S.b.xcur, S.b.s2cur, nullptr, nullptr, nullptr, nullptr};
-        reduce_samples64(S.p, js, S.partial, S.Gs, item.y, S.b.w, red);
-        gm_dots1_64(S.b, S.p.M, item.y / 64, red);
-        __syncthreads();                                 // red is reused by the next item
+        if (item.y < 0) {
+            gm_commit(S.b, S.p.M);
+        } else if (!slot_done(S)) {
+            const GmPre pre = gm_reduce_prefetch(S.b, S.p.M, item.y / 64);
+            const GmPh ph{S.b.st->ph, S.b.st->j, S.b.st->second, S.b.st->reorth};
+            const JumpSrc js{S.b.xcur, S.b.s2cur, nullptr, nullptr, nullptr, nullptr};
+            reduce_samples64(S.p, js, S.partial, S.Gs, item.y, nullptr, red);
+            gm_reduce64(S.b, S.p.M, item.y / 64, red, pre, ph);
+        }
+        __syncthreads();                                 // the item's LDS is reused by the next item
     }
 }
 
-// GMRES (gmres.h): the update and emit launches walk (slot, chunk) items; the
-// first pass's dots ride on k_reduce_b and the commit on the update.
-template <int Kind>
-__global__ __launch_bounds__(kGmChunk) void k_gm_vec_b(const SlotDev* __restrict__ slots, BatchWork w) {
-    const int n_items = w.counts[4];
+// GMRES (gmres.h): the step launch walks (slot, chunk) items, the vector's chunks
+// and then the correction chunks of each slot.
+__global__ __launch_bounds__(kGmChunk) void k_gm_step_b(const SlotDev* __restrict__ slots, BatchWork w) {
+    const int n_items = w.counts[2];
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 item = w.gm_items[it];
         const SlotDev& S = slots[item.x];
-        if (Kind == 1) gm_update1_commit(S.b, S.p.M, item.y);
-        if (Kind == 3) gm_emit(S.p.taps, S.b, S.p.M, item.y);
+        if (item.y < S.b.gc) {
+            gm_step(S.p.taps, S.b, S.p.M, item.y);
+        } else {
+            gm_step_corrections(S.p, S.b, item.y - S.b.gc, S.corr_il);
+        }
         __syncthreads();                                 // the item's LDS is reused by the next item
     }
 }
@@ -100,12 +95,9 @@ hipError_t launch_batch_step(const SlotDev* slots, BatchWork w, int n_cu, hipStr
     const size_t lds = modes_b_lds_bytes();
     if (hipError_t e = hipFuncSetAttribute((const void*)k_modes_b, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))
         return e;
-    const dim3 t(kGmChunk), gv(n_cu);
-    if (hipError_t e = klaunch(&k_correct_b, dim3(n_cu * 2), dim3(256), 0, s, slots, w)) return e;
     if (hipError_t e = klaunch(&k_modes_b, dim3(n_cu), dim3(kModeWaves * 64), lds, s, slots, w)) return e;
     if (hipError_t e = klaunch(&k_reduce_b, dim3(n_cu), dim3(1024), 0, s, slots, w)) return e;
-    if (hipError_t e = klaunch(&k_gm_vec_b<1>, gv, t, 0, s, slots, w)) return e;
-    return klaunch(&k_gm_vec_b<3>, gv, t, 0, s, slots, w);
+    return klaunch(&k_gm_step_b, dim3(n_cu), dim3(kGmChunk), 0, s, slots, w);
 }
 
 }  // namespace kfbi

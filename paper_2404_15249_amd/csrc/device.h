@@ -24,6 +24,12 @@ __device__ __forceinline__ int load_flag_late(const int* f) {
     asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
     return load_flag(f + zero);
 }
+__device__ __forceinline__ double load_real_late(const double* f) {
+    using global_real = __attribute__((address_space(1))) double;
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    return __hip_atomic_load((global_real*)(f + zero), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // A flag that is never set, read in place of a null one (a load from one of two
 // addresses, with no branch that would wait for it).
 static __device__ const int kFlagZero = 0;
@@ -356,8 +362,8 @@ __device__ inline double correction_at(const DevPlan& p, const JumpSrc& js, int 
 // workgroup partials of the weighted sine sums (row g of `partial` holds
 // workgroup g's sums for all M samples) are split over wavefronts 0..14, added
 // in a fixed order; wavefront 15 makes the jump terms of the stencil nodes
-// outside Omega, and wavefront 0 adds them and writes out[cp] (also to
-// red[lane], for the caller).
+// outside Omega, and wavefront 0 adds them and writes out[cp] (unless out is null;
+// also to red[lane], for the caller).
 // red: 16 x 64 doubles of LDS.  Returns false, having written nothing, while
 // *skip is nonzero (skip may be null); the flag's latency overlaps the loads.
 __device__ inline bool reduce_samples64(const DevPlan& p, const JumpSrc& js, const double* __restrict__ partial,
@@ -398,7 +404,7 @@ __device__ inline bool reduce_samples64(const DevPlan& p, const JumpSrc& js, con
 #pragma unroll
         for (int w = 0; w < 16; ++w) t += red[w * 64 + lane];
         const double v = t * (2.0 / p.N) + outside[lane];
-        out[cp] = v;
+        if (out) out[cp] = v;
         red[lane] = v;                                  // left in LDS for the caller
     }
     __syncthreads();

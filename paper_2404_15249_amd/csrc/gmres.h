@@ -1,108 +1,87 @@
 // Restarted GMRES (Alg. 5) on the boundary density, resident on the device.
 //
-// One step of the iteration follows one K_D apply and takes, besides it, two
-// launches, so the vector work is spread over many workgroups:
-//   dots1   fused into the apply's last launch (reduce_samples64), per 64
-//           samples: mode 0: phi <- xcur (the iterate the apply was given),
-//           z = ghat - w and partial |z|^2; mode 1: partial dots V_i . w, i <= j
-//   upd1    per chunk of kGmChunk: h_i = sum of the partials; z = w - sum h_i
-//           V_i; partial |z|^2 and |w|^2.  The workgroup that finishes last (an
-//           atomic count, no waiting) commits.  Classical Gram-Schmidt keeps
-//           the new vector orthogonal to the basis to about eps |w| / |z|; only
-//           when |z| < reorth |w| (1e-3 by default) does that workgroup first
-//           make a second pass over the whole vector itself.  For these
-//           second-kind operators the cancellation stays far above that bound.
-//   commit  the new Hessenberg column, the Givens rotations and the residual
-//           estimate (mode 1) or the true residual (mode 0), the state
-//           transition, and at the end of a cycle the triangular solve
-//   emit    per chunk: the next K_D input (new basis vector, or the updated
-//           iterate at the end of a cycle) and its spline second derivatives.
+// One step slot is a K apply and, with its last launch, two roles of GMRES work:
+//   reduce  (the apply's last launch, per 64 samples) finishes what the step launch
+//           before it left: with |z| from that launch's norm partials it scales the
+//           apply's output, w = K z / |z|, stores the basis vector V_j = z / |z| and
+//           makes the partial dots V_i . w, i <= j.  One more workgroup of the same
+//           launch commits column j - 1 meanwhile (gm_commit): the Hessenberg
+//           column, the Givens rotations, the residual estimate, and whether the
+//           cycle ends (then the triangular solve).
+//   step    (gm_step, per chunk of the vector) acts on that: the next K input
+//           z = w - sum h_i V_i with its norm partials (not yet scaled: the operator
+//           is linear, so |z| is only needed after the apply), or the updated
+//           iterate x = phi + sum y_i V_i at the end of a cycle, or the residual
+//           as the first vector of a new cycle, or the end of the run; in extra
+//           workgroups the next apply's corrections, from the same values.
+// So a step needs no launch that waits for the norm, and no count of finished
+// workgroups; what it pays is one apply per cycle whose vector is not used (the
+// cycle's end is found while it runs).
+// Classical Gram-Schmidt keeps the new vector orthogonal to the basis to about
+// eps |w| / |z|; only when |z| < reorth |w| (1e-3 by default) does the reduce launch
+// put the dots V_i . z in place of the apply's, and the step launch makes a second
+// pass; the apply is repeated on its result.  For these second-kind operators the
+// cancellation stays far above that bound.
 // Partial sums are added in a fixed order, so results do not depend on timing.
-// Only commit writes the state, and it runs after every other workgroup of its
-// launch has read it.
+// The state's two halves alternate: the step launch writes what the apply's
+// launches read (ph, converged, r0), the reduce launch what the step launch reads
+// (act); no launch reads what it writes, but for the commit's own counters.
 #pragma once
 
 #include "device.h"
 
 namespace kfbi {
 
-constexpr int kGmChunk = 256;            // vector elements per workgroup (one per thread)
+constexpr int kGmChunk = 256;            // threads of a step workgroup: one vector place each
 constexpr int kGmHalo = kSplineK + 1;    // reach of the spline filter on each side
+constexpr int kGmOwnSpline = kGmChunk - 2 * kGmHalo;   // places a step workgroup owns beside its halos
 
-enum GmKind { kGmNewCycle = 0, kGmNextVector = 1, kGmCycleEnd = 2, kGmDone = 3 };
+enum GmPhase { kGmResidualPh = 0, kGmArnoldi = 1, kGmOver = 2 };
+enum GmAct { kGmNextVector = 0, kGmSecondPass = 1, kGmCycleEnd = 2, kGmResidual = 3, kGmDone = 4 };
 
 // GmresState::converged when a norm of the iteration came out NaN or Inf
 constexpr int kGmNonfinite = -2;
 
-__host__ __device__ inline int gm_chunks(int M) { return (M + kGmChunk - 1) / kGmChunk; }
+// places a step workgroup owns: fewer with a spline, whose filter reads neighbours
+__host__ __device__ constexpr int gm_own(bool spline) { return spline ? kGmOwnSpline : kGmChunk; }
+__host__ __device__ inline int gm_chunks(int M, bool spline) { return (M + gm_own(spline) - 1) / gm_own(spline); }
 __host__ __device__ inline int gm_chunks64(int M) { return (M + 63) / 64; }
-// doubles of partial sums a problem needs: first-pass dots (m+1) x gc64, norms
-// of the update (gc), of the residual (gc64) and of the apply's output (gc)
+// doubles of partial sums a problem needs: dots (m+1) x gc64, norms of the new
+// vector and of the apply's output (gc each) and of the residual (gc64)
 __host__ __device__ inline size_t gm_part_size(int m, int gc, int gc64) {
     return (size_t)(m + 1) * gc64 + 2 * gc + gc64;
 }
 
 struct GmPart {
     double* d1;     // [i * gc64 + c64]
-    double* nrm;    // [c]
+    double* nrm;    // [c]: |z|^2 of the chunk
+    double* nrmw;   // [c]: |w|^2 of the chunk
     double* nrm0;   // [c64]
-    double* nrmw;   // [c]: |w|^2 of the chunk (first update)
 };
 __device__ __forceinline__ GmPart gm_part(const GmresBufs& b) {
     GmPart q;
     q.d1 = b.part;
     q.nrm = q.d1 + (size_t)(b.m + 1) * b.gc64;
-    q.nrm0 = q.nrm + b.gc;
-    q.nrmw = q.nrm0 + b.gc64;
+    q.nrmw = q.nrm + b.gc;
+    q.nrm0 = q.nrmw + b.gc;
     return q;
 }
 
-// The state an update launch works from, read once at its start: only the
-// commit writes the state, after every workgroup of the launch has read it.
-struct GmSnap {
-    int mode, j, it, first, max_iter;
-    double r0, tol, reorth;
-};
-__device__ __forceinline__ GmSnap gm_snap(const GmresState* st) {
-    GmSnap s;
-    s.mode = st->mode;
-    s.j = st->j;
-    s.it = st->it;
-    s.first = st->first;
-    s.max_iter = st->max_iter;
-    s.r0 = st->r0;
-    s.tol = st->tol;
-    s.reorth = st->reorth;
-    return s;
+// The end of the run, told to the host (GmresPub) by the thread that just wrote the
+// state: the state, then (ordered after it) the run's number.
+__device__ inline void gm_publish_end(const GmresBufs& b) {
+    if (!b.pub) return;
+    b.pub->st = *b.st;
+    __hip_atomic_store(&b.pub->done, b.st->epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-
-// The state, copied to the host-visible mirror (pinned host memory, null when
-// there is none) by the thread that just wrote it: the host reads the mirror
-// after a stream wait instead of copying the state back.
-__device__ __forceinline__ void gm_publish(const GmresBufs& b) {
-    if (b.pub) *b.pub = *b.st;
+// A slot's commit, told to the host; `last`: the next slot's residual is expected to
+// end the run.
+__device__ __forceinline__ void gm_publish_slot(const GmresBufs& b, bool last) {
+    const unsigned slot = (unsigned)(b.st->slot += 1);
+    if (!b.pub) return;
+    __hip_atomic_store(&b.pub->prog, (unsigned long long)b.st->epoch << 32 | (last ? kGmLastSlot : 0u) | slot,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-
-// What an emit launch takes from the state, given directly by the launch that
-// starts a run (which writes the state itself): the kind, the scale, the
-// source of the next input (x = xsrc * scale) and, when the run ends with
-// x = 0 right away, where that zero goes.
-struct EmitCtl {
-    int kind;
-    double scale;
-    const double* xsrc;
-    double* xzero;
-};
-
-// What the commit of an Arnoldi step reads besides the norms: the first-pass
-// coefficients, the previous rotations and g_j.  Every workgroup of the update
-// loads them beside its basis values (none changes before the commit), so the
-// one that commits has them at hand.
-struct GmCommitIn {
-    double h1[kMaxRestart + 2];
-    double cs[kMaxRestart], sn[kMaxRestart];
-    double gj;
-};
 
 __device__ __forceinline__ double wave_sum(double v) { return wave_allsum(v); }
 
@@ -115,133 +94,229 @@ __device__ inline double gm_block_sum(double v, double* red) {
     return red[0] + red[1] + red[2] + red[3];
 }
 
-// Sums over the wavefront of G values per lane at once: log2(G) halving steps
-// (each lane keeps half of its values and adds its partner's other half), then
-// plain butterfly steps.  Returns the wavefront sum of value number
-// (lane >> (6 - log2 G)) & (G - 1); 64 / G lanes hold each sum.
-template <int G>
-__device__ __forceinline__ double wave_sum_many(double (&p)[G]) {
-    static_assert(G >= 2 && G <= 64 && (G & (G - 1)) == 0, "G must be a power of two");
+// This lane's share of n partial sums (every 64th); a wave_sum of it is the same
+// in every wavefront that forms it.
+__device__ __forceinline__ double gm_lane_share(const double* part, int n) {
     const int lane = threadIdx.x & 63;
-    int off = 32;
-#pragma unroll
-    for (int half = G / 2; half >= 1; half /= 2, off >>= 1) {
-        const bool hi = (lane & off) != 0;
-#pragma unroll
-        for (int u = 0; u < half; ++u) {
-            // the empty asm makes both operands register values: otherwise the
-            // compiler turns "hi ? p[a] : p[b]" into p[hi ? a : b], a run-time
-            // index into the array that it lowers to a chain of G selects
-            double lo_v = p[u], hi_v = p[u + half];
-            asm volatile("" : "+v"(lo_v), "+v"(hi_v));
-            const double keep = hi ? hi_v : lo_v;
-            const double send = hi ? lo_v : hi_v;
-            p[u] = keep + __shfl_xor(send, off, 64);
-        }
-    }
-    for (; off >= 1; off >>= 1) p[0] += __shfl_xor(p[0], off, 64);
-    return p[0];
+    double s = lane < n ? part[lane] : 0.0;
+    for (int k = lane + 64; k < n; k += 64) s += part[k];
+    return s;
 }
 
-// Loads V_i at element e (0 outside [0, M) and for i > j) for i < 4 * 16,
-// grouped by 16.
-__device__ __forceinline__ void gm_load_basis(const double* __restrict__ V, int M, int e, int j, double (&v)[4][16]) {
-    const bool in = e < M;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int i = 16 * g + u;
-            v[g][u] = (in && i <= j) ? V[(size_t)i * M + e] : 0.0;
-        }
-    }
-}
+// Whether |z|^2 (after the first pass over w) calls for a second pass.
+__device__ __forceinline__ bool gm_cancelled(double zz, double ww, double reorth) { return zz < reorth * reorth * ww; }
 
-// The basis values the first pass needs from this wavefront (V_i at its lane's
-// sample for i = wave, wave + 16, ...; kMaxRestart <= 64), requested before the
-// apply's reduction so that their latency overlaps it.  Every row that can be
-// in use (i < m) is requested without waiting for the state; rows past the
-// current column are not used.
-// Wavefront 0 also requests what a residual step reads: the iterate the apply
-// was given and ghat at its lane's sample.
+// ---------------------------------------------------------------- reduce launch
+
+// What the reduce launch reads besides the apply's partials, requested before the
+// reduction so that the latencies overlap: V_i at the lane's sample for
+// i = wave, wave + 16, ... (kMaxRestart <= 64; every row that can be in use, none
+// waits for the state), the apply's input, ghat, and the lane's share of the norm
+// partials.
 struct GmPre {
     double v[4];
-    double xc, gh;
+    double xc, gh, zz, ww;
 };
-__device__ __forceinline__ GmPre gm_dots1_prefetch(const GmresBufs& b, int M, int c64) {
+__device__ __forceinline__ GmPre gm_reduce_prefetch(const GmresBufs& b, int M, int c64) {
     static_assert(kMaxRestart <= 64, "four basis values per lane");
     GmPre pre;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cp = c64 * 64 + lane;
+    const GmPart q = gm_part(b);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int i = wave + 16 * k;
         pre.v[k] = (i < b.m && cp < M) ? b.V[(size_t)i * M + cp] : 0.0;
     }
-    pre.xc = pre.gh = 0.0;
-    if (wave == 0 && cp < M) {
-        pre.xc = b.xcur[cp];
-        pre.gh = b.ghat[cp];
-    }
+    pre.xc = cp < M ? b.xcur[cp] : 0.0;
+    pre.gh = wave == 0 && cp < M ? b.ghat[cp] : 0.0;
+    pre.zz = gm_lane_share(q.nrm, b.gc);
+    pre.ww = gm_lane_share(q.nrmw, b.gc);
     return pre;
 }
 
-// First step of GMRES on samples c64 * 64 .. + 63, called by a workgroup of 16
-// wavefronts right after it computed w there (wv[lane] in LDS); pre: the
-// values from gm_dots1_prefetch (null: loaded here); mode, j: the state's, as
-// read by the caller at its start.
-__device__ inline void gm_dots1_64(const GmresBufs& b, int M, int c64, const double* wv, const GmPre* pre, int mode,
-                                   int j) {
-    if (mode == 2) return;
+// The state the reduce launch works from.
+struct GmPh {
+    int phase, j, second;
+    double reorth;
+};
+
+// Samples c64 * 64 .. + 63 by a workgroup of 16 wavefronts right after the apply's
+// output there (wv[lane] in LDS).
+__device__ inline void gm_reduce64(const GmresBufs& b, int M, int c64, const double* wv, const GmPre& pre, GmPh ph) {
+    if (ph.phase == kGmOver) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int cp = c64 * 64 + lane;
     const GmPart q = gm_part(b);
-    if (mode == 0) {
+    if (ph.phase == kGmResidualPh) {                       // the apply was given the iterate
         if (wave != 0) return;
         double r = 0.0;
         if (cp < M) {
-            const double xc = pre ? pre->xc : b.xcur[cp], gh = pre ? pre->gh : b.ghat[cp];
-            b.phi[cp] = xc;
-            r = gh - wv[lane];
+            b.phi[cp] = pre.xc;
+            r = pre.gh - wv[lane];
             b.z[cp] = r;
         }
         const double s = wave_sum(r * r);
         if (lane == 0) q.nrm0[c64] = s;
         return;
     }
-    const int gc64 = b.gc64;
-    const double x = cp < M ? wv[lane] : 0.0;
-    if (pre) {
+    const double zz = wave_sum(pre.zz), ww = wave_sum(pre.ww);
+    const bool second = ph.j > 0 && !ph.second && gm_cancelled(zz, ww, ph.reorth);
+    const double hn = sqrt(zz), sc = hn > 0.0 ? 1.0 / hn : 0.0;
+    const double vj = pre.xc * sc;                         // the new basis vector
+    const double x = second ? pre.xc : cp < M ? wv[lane] * sc : 0.0;
+    if (wave == 0 && cp < M) {
+        b.w[cp] = x;
+        if (!second) b.V[(size_t)ph.j * M + cp] = vj;
+    }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = wave + 16 * k;
-            if (i <= j) {
-                const double s = wave_sum(cp < M ? pre->v[k] * x : 0.0);
-                if (lane == 0) q.d1[(size_t)i * gc64 + c64] = s;
-            }
+    for (int k = 0; k < 4; ++k) {
+        const int i = wave + 16 * k;
+        if (i < ph.j) {
+            const double s = wave_sum(pre.v[k] * x);
+            if (lane == 0) q.d1[(size_t)i * b.gc64 + c64] = s;
+        }
+    }
+    if (!second && wave == (ph.j & 15)) {
+        const double s = wave_sum(vj * x);
+        if (lane == 0) q.d1[(size_t)ph.j * b.gc64 + c64] = s;
+    }
+}
+
+// The commit, by one more workgroup of the reduce launch: the column the last step
+// launch made (its coefficients in b.h, |z| from its norm partials), and what the
+// next step launch has to do (st->act).
+__device__ inline void gm_commit(const GmresBufs& b, int M) {
+    __shared__ double col[kMaxRestart + 2];
+    __shared__ double rot[kMaxRestart];
+    __shared__ double cs[kMaxRestart], sn[kMaxRestart];
+    __shared__ double Hs[kMaxRestart * (kMaxRestart + 1)];
+    __shared__ int s_end;
+    GmresState* st = b.st;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = b.m;
+    const GmPart q = gm_part(b);
+    // requested together: the norms and what the column needs whatever j is
+    const double zzl = gm_lane_share(q.nrm, b.gc), wwl = gm_lane_share(q.nrmw, b.gc);
+    double hv = 0.0, cv = 0.0, sv = 0.0;
+    if (tid < m) {
+        hv = b.h[tid];
+        cv = b.cs[tid];
+        sv = b.sn[tid];
+    }
+    const GmPh ph{st->ph, st->j, st->second, st->reorth};
+    if (st->converged || ph.phase == kGmOver) {
+        if (tid == 0) st->act = kGmDone;
+        return;
+    }
+    if (ph.phase == kGmResidualPh) {
+        if (tid == 0) {
+            st->act = kGmResidual;
+            gm_publish_slot(b, false);
         }
         return;
     }
-    for (int i = wave; i <= j; i += 16) {
-        const double s = wave_sum(cp < M ? b.V[(size_t)i * M + cp] * x : 0.0);
-        if (lane == 0) q.d1[(size_t)i * gc64 + c64] = s;
+    const double zz = wave_sum(zzl), ww = wave_sum(wwl), hn = sqrt(zz);
+    if (ph.j == 0) {                                       // a new cycle's first vector
+        if (tid <= m) b.g[tid] = tid == 0 ? hn : 0.0;
+        if (tid == 0) {
+            st->first = 0;                                 // read by the residual's step launch only
+            st->act = kGmNextVector;
+            st->act_j = 0;
+            gm_publish_slot(b, false);
+        }
+        return;
+    }
+    const int j = ph.j - 1, jn = ph.j;                     // the column committed; columns made
+    if (!ph.second && gm_cancelled(zz, ww, ph.reorth)) {
+        if (tid == 0) {
+            st->act = kGmSecondPass;
+            st->act_j = j;
+            gm_publish_slot(b, false);
+        }
+        return;
+    }
+    if (tid <= j) col[tid] = hv;
+    if (tid < j) {
+        cs[tid] = cv;
+        sn[tid] = sv;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        // previous rotations down the column, eight at a time: their operands
+        // are read together; the rotated entries go to rot[]
+        double a = col[0];
+        for (int i0 = 0; i0 < j; i0 += 8) {
+            double cn[8], c8[8], s8[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool in = i0 + u < j;
+                cn[u] = in ? col[i0 + u + 1] : 0.0;
+                c8[u] = in ? cs[i0 + u] : 1.0;
+                s8[u] = in ? sn[i0 + u] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (i0 + u < j) {
+                    rot[i0 + u] = c8[u] * a + s8[u] * cn[u];
+                    a = -s8[u] * a + c8[u] * cn[u];
+                }
+            }
+        }
+        for (int i = 0; i < j; ++i) col[i] = rot[i];
+        const double den = hypot(a, hn), gj = b.g[j];
+        if (!isfinite(den) || !isfinite(gj)) {             // NaN or Inf in the data: stop here
+            st->converged = kGmNonfinite;
+            st->act = kGmDone;
+            gm_publish_end(b);
+            s_end = -1;
+        } else {
+            const double c = den > 0.0 ? a / den : 1.0;
+            const double s = den > 0.0 ? hn / den : 0.0;
+            col[j] = den;
+            col[j + 1] = 0.0;
+            b.cs[j] = c;
+            b.sn[j] = s;
+            b.g[j + 1] = -s * gj;
+            b.g[j] = c * gj;
+            const int itn = st->it + 1;
+            const double est = fabs(s * gj) / st->r0;
+            st->relres = est;
+            st->it = itn;
+            const bool end = est < st->tol || jn == m || itn >= st->max_iter || hn == 0.0;
+            s_end = end ? 1 : 0;
+            st->jn = jn;
+            st->act = end ? kGmCycleEnd : kGmNextVector;
+            st->act_j = jn;
+            gm_publish_slot(b, est < st->tol || itn >= st->max_iter || hn == 0.0);
+        }
+    }
+    __syncthreads();
+    if (s_end < 0) return;
+    double* Hj = b.H + (size_t)j * (m + 1);
+    if (tid <= j + 1) Hj[tid] = col[tid];
+    if (!s_end) return;
+    // end of the cycle: H[0:jn, 0:jn] y = g[0:jn], one wavefront, column by column
+    for (int t = tid; t < jn * (m + 1); t += blockDim.x) {
+        const int kc = t / (m + 1), i = t % (m + 1);
+        Hs[t] = kc == j ? (i <= jn ? col[i] : 0.0) : b.H[t];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        double gk = lane < jn ? b.g[lane] : 0.0;
+        double yk = 0.0;
+        for (int i = jn - 1; i >= 0; --i) {
+            const double yi = readlane_f64(gk, i) / Hs[i * (m + 1) + i];   // i is the same in every lane
+            if (lane == i) yk = yi;
+            if (lane < i) gk -= Hs[i * (m + 1) + lane] * yi;
+        }
+        if (lane < jn) b.y[lane] = yk;
     }
 }
-__device__ inline void gm_dots1_64(const GmresBufs& b, int M, int c64, const double* wv) {
-    gm_dots1_64(b, M, c64, wv, nullptr, b.st->mode, b.st->j);
-}
 
-// What one update workgroup loads, requested before the state is known: the
-// basis values at its element for every row that can be in use (i < m; rows
-// past the current column are loaded and not used), w, and per thread i < m
-// row i's first-pass dot partials summed, the rotation (c_i, s_i) and g_i.
-struct GmUpdIn {
-    double v[4][16];
-    double w;
-    double h, cs, sn, g;
-};
-// Chunk counts up to which one thread adds a row of partials (or the chunk
-// norms) itself; above them (the surface problem's long vectors) the
-// workgroup's threads split the work, so the chain of dependent loads stays short.
+// ---------------------------------------------------------------- step launch
+
+// Chunk counts up to which one thread adds a row of dot partials itself; above
+// them (the surface problem's long vectors) the workgroup's threads split the work,
+// so the chain of dependent loads stays short.
 constexpr int kGmSerialSums = 32;
 
 // h_i = the sum of row i of the nco chunk partials, i < m, for many chunks:
@@ -271,19 +346,34 @@ __device__ inline double gm_dots_spread(const double* d1, int m, int nco) {
     return h;
 }
 
-__device__ __forceinline__ GmUpdIn gm_update_loads(const GmresBufs& b, int M, int c) {
+// What a step workgroup reads, requested before the state is known: at the
+// thread's vector element every basis row that can be in use (rows past the current
+// column are not used), the apply's output, the iterate and the residual; per
+// thread i < m the sum of row i's dot partials and y_i; the lane's share of the
+// residual's norm.
+struct GmStepIn {
+    double v[4][16];
+    double w, phi, z;
+    double h, y, rr;
+};
+__device__ __forceinline__ GmStepIn gm_step_loads(const GmresBufs& b, int M, int e, bool in) {
     const int tid = threadIdx.x, m = b.m, nco = b.gc64;
     const GmPart q = gm_part(b);
-    const int e = c * kGmChunk + tid;
-    GmUpdIn u;
-    gm_load_basis(b.V, M, e, m - 1, u.v);
-    u.w = e < M ? b.w[e] : 0.0;
-    u.h = u.cs = u.sn = u.g = 0.0;
-    if (tid < m) {
-        u.cs = b.cs[tid];
-        u.sn = b.sn[tid];
-        u.g = b.g[tid];
+    GmStepIn u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int i = 16 * g + k;
+            u.v[g][k] = (in && i < m) ? b.V[(size_t)i * M + e] : 0.0;
+        }
     }
+    u.w = in ? b.w[e] : 0.0;
+    u.phi = in ? b.phi[e] : 0.0;
+    u.z = in ? b.z[e] : 0.0;
+    u.h = u.y = 0.0;
+    if (tid < m) u.y = b.y[tid];
+    u.rr = gm_lane_share(q.nrm0, nco);
     if (nco <= kGmSerialSums) {
         if (tid < m) {
             double sum = 0.0;
@@ -297,312 +387,63 @@ __device__ __forceinline__ GmUpdIn gm_update_loads(const GmresBufs& b, int M, in
     return u;
 }
 
-// The first Gram-Schmidt pass on chunk c from the loads above: h_i (into
-// ci.h1, with the commit's other operands), z = w - sum h_i V_i, and the
-// chunk's |z|^2 and |w|^2.
-__device__ __forceinline__ void gm_update(const GmresBufs& b, int M, int c, int j, const GmUpdIn& u, GmCommitIn& ci,
-                                          double* red) {
-    const int tid = threadIdx.x;
-    const GmPart q = gm_part(b);
-    const int e = c * kGmChunk + tid;
-    if (tid <= j) ci.h1[tid] = u.h;
-    if (tid < j) {
-        ci.cs[tid] = u.cs;
-        ci.sn[tid] = u.sn;
+// What a step does, the same in every workgroup of the launch.
+struct GmTodo {
+    int act, j;              // act_j
+    bool done;               // the run has ended (with kGmResidual, or kGmDone)
+    int converged;           // then
+    double rel, r0;
+};
+__device__ __forceinline__ GmTodo gm_todo(const GmresBufs& b, const GmStepIn& u) {
+    const GmresState* st = b.st;
+    GmTodo t{st->act, st->act_j, false, 0, 0.0, 0.0};
+    if (t.act == kGmDone) t.done = true;
+    if (t.act != kGmResidual) return t;
+    const double beta = sqrt(wave_sum(u.rr));
+    if (!isfinite(beta)) {                                 // NaN or Inf in the data: stop here
+        t.done = true;
+        t.converged = kGmNonfinite;
+        return t;
     }
-    if (tid == j) ci.gj = u.g;
+    t.r0 = st->first ? beta : st->r0;
+    t.rel = t.r0 > 0.0 ? beta / t.r0 : 0.0;
+    const bool small = t.r0 == 0.0 || beta == 0.0 || t.rel < st->tol;
+    if (small || st->it >= st->max_iter) {
+        t.done = true;
+        t.converged = small ? 1 : -1;
+    }
+    return t;
+}
+
+// The coefficients of the basis vectors (into coef, kMaxRestart doubles of LDS) and
+// the next input at the thread's element: the new vector w - sum h_i V_i (the
+// second pass the same with its own dots), the updated iterate phi + sum y_i V_i,
+// or the residual.
+__device__ __forceinline__ double gm_next_value(const GmTodo& t, const GmStepIn& u, double* coef) {
+    const int tid = threadIdx.x;
+    const bool cycle_end = t.act == kGmCycleEnd;
+    const int n = t.act == kGmResidual ? 0 : cycle_end ? t.j : t.j + 1;   // basis vectors used
+    double cy = u.y, ch = -u.h;
+    asm volatile("" : "+v"(cy), "+v"(ch));
+    if (tid < kMaxRestart) coef[tid] = tid < n ? (cycle_end ? cy : ch) : 0.0;
     __syncthreads();
-    double a = u.w;
+    // values, not addresses, to choose from (the struct has to stay in registers)
+    double aw = u.w, ap = u.phi, az = u.z;
+    asm volatile("" : "+v"(aw), "+v"(ap), "+v"(az));
+    double a = t.act == kGmResidual ? az : cycle_end ? ap : aw;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        if (16 * g <= j) {
+        if (16 * g < n) {
 #pragma unroll
             for (int k = 0; k < 16; ++k)
-                if (16 * g + k <= j) a -= ci.h1[16 * g + k] * u.v[g][k];
+                if (16 * g + k < n) a = fma(coef[16 * g + k], u.v[g][k], a);
         }
     }
-    if (e < M) b.z[e] = a;
-    const double sz = gm_block_sum(a * a, red);
-    const double sw = gm_block_sum(u.w * u.w, red);
-    if (tid == 0) {
-        q.nrm[c] = sz;
-        q.nrmw[c] = sw;
-    }
-}
-
-// Commit of a residual step (mode 0), by one workgroup of kGmChunk threads:
-// beta = |ghat - K phi| from the partials the apply's reduction left, then the
-// end of the solve or a new cycle.
-__device__ inline void gm_commit_residual(const GmresBufs& b, const GmSnap& s, double* red) {
-    const int tid = threadIdx.x, m = b.m;
-    const GmPart q = gm_part(b);
-    double v = 0.0;
-    for (int cc = tid; cc < b.gc64; cc += kGmChunk) v += q.nrm0[cc];
-    const double beta = sqrt(gm_block_sum(v, red));
-    if (tid != 0) return;
-    GmresState* st = b.st;
-    if (!isfinite(beta)) {                                 // NaN or Inf in the data: stop here
-        st->converged = kGmNonfinite;
-        st->mode = 2;
-        st->kind = kGmDone;
-        gm_publish(b);
-        return;
-    }
-    st->res_applies += 1;
-    const double r0 = s.first ? beta : s.r0;
-    const double rel = r0 > 0.0 ? beta / r0 : 0.0;
-    const bool done = r0 == 0.0 || beta == 0.0 || rel < s.tol || s.it >= s.max_iter;
-    st->r0 = r0;
-    st->first = 0;
-    st->relres = rel;
-    if (done) {
-        st->converged = (r0 == 0.0 || beta == 0.0 || rel < s.tol) ? 1 : -1;
-        st->mode = 2;
-        st->kind = kGmDone;
-    } else {
-        b.g[0] = beta;
-        for (int k = 1; k <= m; ++k) b.g[k] = 0.0;
-        st->j = 0;
-        st->mode = 1;
-        st->cycles += 1;
-        st->kind = kGmNewCycle;
-        st->scale = 1.0 / beta;
-    }
-    gm_publish(b);
-}
-
-// Commit of an Arnoldi step (mode 1), by one workgroup of kGmChunk threads:
-// column j of the Hessenberg matrix (h1 + h2 from the two Gram-Schmidt
-// passes, h_{j+1,j} = hn), the previous rotations down it and a new one, the
-// residual estimate, the state transition, and at the end of a cycle the
-// triangular solve.
-__device__ inline void gm_commit_arnoldi(const GmresBufs& b, const GmSnap& s, const GmCommitIn& ci,
-                                         const double* h2, double hn) {
-    __shared__ double col[kMaxRestart + 2];
-    __shared__ double rot[kMaxRestart];
-    __shared__ double Hs[kMaxRestart * (kMaxRestart + 1)];
-    __shared__ int s_end;
-    GmresState* st = b.st;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = b.m, j = s.j;
-    if (tid <= j) col[tid] = ci.h1[tid] + h2[tid];
-    __syncthreads();
-    if (tid == 0) {
-        // previous rotations down the column, eight at a time: their operands
-        // are read together; the rotated entries go to rot[]
-        double a = col[0];
-        for (int i0 = 0; i0 < j; i0 += 8) {
-            double cn[8], c8[8], s8[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool in = i0 + u < j;
-                cn[u] = in ? col[i0 + u + 1] : 0.0;
-                c8[u] = in ? ci.cs[i0 + u] : 1.0;
-                s8[u] = in ? ci.sn[i0 + u] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (i0 + u < j) {
-                    rot[i0 + u] = c8[u] * a + s8[u] * cn[u];
-                    a = -s8[u] * a + c8[u] * cn[u];
-                }
-            }
-        }
-        for (int i = 0; i < j; ++i) col[i] = rot[i];
-        const double den = hypot(a, hn);
-        if (!isfinite(den) || !isfinite(ci.gj)) {         // NaN or Inf in the data: stop here
-            st->converged = kGmNonfinite;
-            st->mode = 2;
-            st->kind = kGmDone;
-            gm_publish(b);
-            s_end = -1;
-        } else {
-            const double cs = den > 0.0 ? a / den : 1.0;
-            const double sn = den > 0.0 ? hn / den : 0.0;
-            col[j] = den;
-            col[j + 1] = 0.0;
-            b.cs[j] = cs;
-            b.sn[j] = sn;
-            const double gj = ci.gj;
-            b.g[j + 1] = -sn * gj;
-            b.g[j] = cs * gj;
-            const int jn = j + 1, itn = s.it + 1;
-            const double est = fabs(sn * gj) / s.r0;
-            st->relres = est;
-            st->it = itn;
-            const bool end = est < s.tol || jn == m || itn >= s.max_iter || hn == 0.0;
-            s_end = end ? 1 : 0;
-            st->jn = jn;
-            if (end) {
-                st->mode = 0;
-                st->kind = kGmCycleEnd;
-            } else {
-                st->j = jn;
-                st->kind = kGmNextVector;
-                st->scale = hn > 0.0 ? 1.0 / hn : 0.0;
-            }
-        }
-    }
-    __syncthreads();
-    if (s_end < 0) return;
-    double* Hj = b.H + (size_t)j * (m + 1);
-    if (tid <= j + 1) Hj[tid] = col[tid];
-    if (!s_end) return;
-    // end of the cycle: H[0:jn, 0:jn] y = g[0:jn], one wavefront, column by column
-    const int jn = j + 1;
-    for (int t = tid; t < jn * (m + 1); t += kGmChunk) {
-        const int kc = t / (m + 1), i = t % (m + 1);
-        Hs[t] = kc == j ? col[i] : b.H[t];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        double gk = lane < jn ? b.g[lane] : 0.0;
-        double yk = 0.0;
-        for (int i = jn - 1; i >= 0; --i) {
-            const double yi = readlane_f64(gk, i) / Hs[i * (m + 1) + i];   // i is the same in every lane
-            if (lane == i) yk = yi;
-            if (lane < i) gk -= Hs[i * (m + 1) + lane] * yi;
-        }
-        if (lane < jn) b.y[lane] = yk;
-    }
-}
-
-// Whether this workgroup finished the problem's last chunk of the launch (an
-// atomic count of finished chunks; nobody waits); the last one resets the
-// count for the next launch.  Called by the whole workgroup after its writes.
-__device__ inline bool gm_last_chunk(const GmresBufs& b, int* s_last) {
-    // every wavefront's stores (z, which a second pass of the committing
-    // workgroup reads) complete before thread 0's fence publishes them: the
-    // workgroup barrier alone does not wait for them
-    __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0) (expcnt, lgkmcnt not waited)
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();                                   // this chunk's partials before the count
-        const unsigned done = atomicAdd(b.cnt, 1u) + 1;
-        *s_last = done == (unsigned)b.gc;
-        if (*s_last) {
-            __hip_atomic_store(b.cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __threadfence();                               // the other chunks' partials after it
-        }
-    }
-    __syncthreads();
-    return *s_last != 0;
-}
-
-// The second Gram-Schmidt pass over the whole vector by the one workgroup that
-// commits (only when the first pass cancelled below the threshold): h2 = V^T z
-// in groups of sixteen basis vectors, z -= V h2; returns the new |z|^2.  h2
-// goes to h2s (LDS).
-__device__ inline double gm_second_pass(const GmresBufs& b, int M, int j, double* h2s, double* red) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        if (16 * g <= j) {
-            double p[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) p[u] = 0.0;
-            for (int e = tid; e < M; e += kGmChunk) {
-                const double ze = b.z[e];
-#pragma unroll
-                for (int u = 0; u < 16; ++u)
-                    if (16 * g + u <= j) p[u] = fma(b.V[(size_t)(16 * g + u) * M + e], ze, p[u]);
-            }
-            const double s = wave_sum_many<16>(p);
-            if ((lane & 3) == 0) red[wave * 16 + (lane >> 2)] = s;
-            __syncthreads();
-            if (tid < 16) h2s[16 * g + tid] = 16 * g + tid <= j ? red[tid] + red[16 + tid] + red[32 + tid] + red[48 + tid] : 0.0;
-            __syncthreads();
-        }
-    }
-    double zz = 0.0;
-    for (int e = tid; e < M; e += kGmChunk) {
-        double a = b.z[e];
-        for (int i = 0; i <= j; ++i) a -= h2s[i] * b.V[(size_t)i * M + e];
-        b.z[e] = a;
-        zz = fma(a, a, zz);
-    }
-    return gm_block_sum(zz, red);
-}
-
-// upd1 on chunk c; the workgroup that finishes the problem's last chunk then
-// commits: a residual step (mode 0) from the residual's norm partials, an
-// Arnoldi step (mode 1) from the first pass, after a second pass of its own
-// when |z| < reorth |w|.
-__device__ inline void gm_update1_commit(const GmresBufs& b, int M, int c) {
-    __shared__ int s_last;
-    __shared__ int s_second;
-    __shared__ double s_zz;
-    __shared__ double h2s[kMaxRestart + 2];
-    __shared__ double red[64];
-    __shared__ GmCommitIn ci;
-    const GmUpdIn u = gm_update_loads(b, M, c);
-    const GmSnap s = gm_snap(b.st);
-    if (s.mode == 2) return;
-    if (s.mode == 1) gm_update(b, M, c, s.j, u, ci, red);
-    if (!gm_last_chunk(b, &s_last)) return;
-    if (s.mode == 0) {
-        gm_commit_residual(b, s, red);
-        return;
-    }
-    for (int i = threadIdx.x; i < kMaxRestart + 2; i += kGmChunk) h2s[i] = 0.0;
-    if (b.gc <= kGmSerialSums) {
-        if (threadIdx.x == 0) {
-            const GmPart q = gm_part(b);
-            double zz = 0.0, ww = 0.0;
-#pragma unroll 8
-            for (int cc = 0; cc < b.gc; ++cc) {            // fixed order
-                zz += q.nrm[cc];
-                ww += q.nrmw[cc];
-            }
-            s_second = zz < s.reorth * s.reorth * ww;
-            s_zz = zz;
-        }
-    } else {                                               // many chunks: every thread, then a block sum
-        const GmPart q = gm_part(b);
-        double a = 0.0, w = 0.0;
-        for (int cc = threadIdx.x; cc < b.gc; cc += kGmChunk) {
-            a += q.nrm[cc];
-            w += q.nrmw[cc];
-        }
-        const double zz = gm_block_sum(a, red), ww = gm_block_sum(w, red);
-        if (threadIdx.x == 0) {
-            s_second = zz < s.reorth * s.reorth * ww;
-            s_zz = zz;
-        }
-    }
-    __syncthreads();
-    const double zz = s_second ? gm_second_pass(b, M, s.j, h2s, red) : s_zz;
-    gm_commit_arnoldi(b, s, ci, h2s, sqrt(zz));
-}
-
-// The next K_D input for elements of chunk c, and with taps (the spline filter
-// of a curve's density) its spline second derivatives (the filter reads
-// kGmHalo neighbours on each side, wrapping around Gamma); taps is null where
-// the density has no spline (the surface problem).
-// Element e of the next K_D input the last commit left (kind != kGmDone): the
-// updated iterate at the end of a cycle, else the normalised vector.
-__device__ __forceinline__ double gm_next_x(const GmresBufs& b, int M, int kind, double scale, int jn, int e) {
-    if (kind == kGmCycleEnd) {
-        double x = b.phi[e];
-        for (int i0 = 0; i0 < jn; i0 += 8) {
-            double vv[8], yy[8];                         // the coefficients with the basis values
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool in = i0 + u < jn;
-                vv[u] = in ? b.V[(size_t)(i0 + u) * M + e] : 0.0;
-                yy[u] = in ? b.y[i0 + u] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (i0 + u < jn) x = fma(yy[u], vv[u], x);
-        }
-        return x;
-    }
-    return b.z[e] * scale;
+    return a;
 }
 
 // Spline second derivative at window place w (the filter reads kGmHalo places
-// on each side): the same periodic filter gm_emit applies.
+// on each side).
 __device__ __forceinline__ double gm_spline_s2(const double* __restrict__ taps, const double* win, int w) {
     constexpr int K = kSplineK;
     double s = 0.0;
@@ -611,117 +452,155 @@ __device__ __forceinline__ double gm_spline_s2(const double* __restrict__ taps, 
     return s;
 }
 
-// ctl: null in a GMRES step (everything from the state), else given by the
-// launch that starts the run.
-__device__ inline void gm_emit(const double* __restrict__ taps, const GmresBufs& b, int M, int c,
-                               const EmitCtl* ctl = nullptr) {
-    constexpr int W = kGmChunk + 2 * kGmHalo;
-    __shared__ double win[W];
-    const int tid = threadIdx.x, c0 = c * kGmChunk;
-    // z at this thread's window places is requested before the state is read:
-    // it is the next input (scaled) unless the cycle has just ended
-    const double* zsrc = ctl ? ctl->xsrc : b.z;
-    int ek[2];
-    double zk[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int k = tid + r * kGmChunk;
-        int e = (c0 - kGmHalo + k) % M;
-        if (e < 0) e += M;
-        ek[r] = e;
-        zk[r] = k < W ? zsrc[e] : 0.0;
-    }
-    const GmresState* st = b.st;
-    const int kind = ctl ? ctl->kind : st->kind;
-    if (kind == kGmDone) {                               // the run has ended: the iterate goes out
-        const int e = c0 + tid;
-        if (ctl) {
-            if (ctl->xzero && e < M) ctl->xzero[e] = 0.0;
-            return;
+// The state for the next slot, by thread 0 of the step launch's first workgroup.
+__device__ __forceinline__ void gm_advance(const GmresBufs& b, const GmTodo& t) {
+    GmresState* st = b.st;
+    if (t.act == kGmNextVector || t.act == kGmSecondPass) {
+        st->ph = kGmArnoldi;
+        st->j = t.j + 1;
+        st->second = t.act == kGmSecondPass;
+    } else if (t.act == kGmCycleEnd) {
+        st->ph = kGmResidualPh;
+    } else if (t.act == kGmResidual) {
+        if (t.converged != kGmNonfinite) {
+            st->res_applies += 1;
+            st->r0 = t.r0;
+            st->relres = t.rel;
         }
-        double* xo = st->xout;
-        if (xo && st->converged != kGmNonfinite && e < M) xo[e] = b.phi[e];
-        return;
+        if (t.done) {
+            st->converged = t.converged;
+            st->ph = kGmOver;
+            gm_publish_end(b);
+        } else {
+            st->cycles += 1;
+            st->ph = kGmArnoldi;
+            st->j = 0;
+            st->second = 0;
+            if (b.pub) b.pub->again += 1;
+        }
     }
-    const double scale = ctl ? ctl->scale : st->scale;
-    const int jn = ctl ? 0 : st->jn;
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int k = tid + r * kGmChunk;
-        if (k < W) win[k] = kind == kGmCycleEnd && !ctl ? gm_next_x(b, M, kind, scale, jn, ek[r]) : zk[r] * scale;
-    }
-    __syncthreads();
-    const int e = c0 + tid;
-    if (e >= M) return;
-    const double x = win[kGmHalo + tid];
-    if (kind == kGmNewCycle) b.V[e] = x;
-    if (kind == kGmNextVector) b.V[(size_t)st->j * M + e] = x;
-    b.xcur[e] = x;
-    if (!taps) return;
-    b.s2cur[e] = gm_spline_s2(taps, win, kGmHalo + tid);
 }
 
-// The corrections (Alg. 2) of the next K_D apply for correction chunk cc, made
-// in the same launch as gm_emit: the chunk's window of the next input is
-// formed here from the same values gm_emit writes (gm_next_x), its spline
-// second derivatives by the same filter, and the corrections by the same
-// arithmetic as a separate correction launch after gm_emit.  One workgroup of
-// kGmChunk threads; corr_il in the sparse-sum layout.
-__device__ inline void gm_emit_corrections(const DevPlan& p, const GmresBufs& b, int cc, double* __restrict__ corr_il,
-                                           const EmitCtl* ctl = nullptr) {
-    __shared__ double xw[kCorrWindow];
-    __shared__ double sw[kCorrWindow];
-    const int M = p.M, tid = threadIdx.x;
-    static_assert(kCorrWindow <= kGmChunk && kCorrChunk <= kGmChunk, "one window place and one node place per thread");
-    // the node's plan data (place tid of the chunk's kCorrChunk) is requested
-    // with the chunk itself: neither waits for the other
-    int4 arm = make_int4(-1, -1, -1, -1);
-    double4 dd = make_double4(0.0, 0.0, 0.0, 0.0);
-    double sg = 0.0;
-    int slot = 0;
-    if (tid < kCorrChunk) {
-        const size_t at = (size_t)cc * kCorrChunk + tid;
-        arm = p.cc_arm[at];
-        dd = p.cc_d[at];
-        sg = p.cc_s[at];
-        slot = p.cc_pos[at];
+// The place of window index tid of chunk c: the element, whether it exists and
+// whether the chunk owns it (with a spline the window wraps around Gamma and has
+// kGmHalo places on each side).
+struct GmPlaceOf {
+    int e;
+    bool in, own;
+};
+__device__ __forceinline__ GmPlaceOf gm_place(const GmresBufs& b, int M, int c, bool spline) {
+    const int tid = threadIdx.x;
+    if (!spline) {
+        const int e = c * kGmChunk + tid;
+        return {e, e < M, e < M};
     }
-    const int4 ch = p.cc_chunk[cc];                      // first, end, first knot, width
-    const bool act = tid < ch.y - ch.x;
-    // z at the thread's window place: the next input (scaled) unless the cycle
-    // has just ended
-    const int ew = (ch.z + tid) % M;
-    const double zw = tid < ch.w ? (ctl ? ctl->xsrc : b.z)[ew] : 0.0;
-    const int ks[4] = {arm.x, arm.y, arm.z, arm.w};
-    const double ds[4] = {dd.x, dd.y, dd.z, dd.w};
+    const int at = c * kGmOwnSpline - kGmHalo + tid;
+    int e = at % M;
+    if (e < 0) e += M;
+    return {e, true, tid >= kGmHalo && tid < kGmHalo + kGmOwnSpline && at < M};
+}
+
+// Chunk c of the step launch (see the head of this file); taps: the spline filter
+// of a curve's density, null where the density has no spline (the surface problem).
+__device__ inline void gm_step(const double* __restrict__ taps, const GmresBufs& b, int M, int c) {
+    __shared__ double win[kGmChunk];
+    __shared__ double coef[kMaxRestart];
+    __shared__ double red[kGmChunk / 64];
+    const int tid = threadIdx.x;
+    const GmPlaceOf pl = gm_place(b, M, c, taps != nullptr);
+    const GmStepIn u = gm_step_loads(b, M, pl.e, pl.in);
+    const GmTodo t = gm_todo(b, u);
+    if (t.act == kGmDone) return;
+    if (t.done) {                                          // the run has ended: the iterate goes out
+        double* xo = b.st->xout;
+        if (xo && t.converged != kGmNonfinite && pl.own) xo[pl.e] = u.phi;
+        if (c == 0 && tid == 0) gm_advance(b, t);
+        return;
+    }
+    const double x = gm_next_value(t, u, coef);
+    if (pl.own) b.xcur[pl.e] = x;
+    if (taps) {
+        win[tid] = x;
+        __syncthreads();
+        if (pl.own) b.s2cur[pl.e] = gm_spline_s2(taps, win, tid);
+    }
+    if (t.act != kGmCycleEnd) {
+        const GmPart q = gm_part(b);
+        const double sz = gm_block_sum(pl.own ? x * x : 0.0, red);
+        const double sw = gm_block_sum(pl.own ? u.w * u.w : 0.0, red);
+        if (tid == 0) {
+            q.nrm[c] = sz;
+            q.nrmw[c] = sw;
+        }
+    }
+    if (c == 0) {
+        if (tid <= t.j && t.act == kGmNextVector) b.h[tid] = u.h;
+        if (tid <= t.j && t.act == kGmSecondPass) b.h[tid] += u.h;
+        if (tid == 0) gm_advance(b, t);
+    }
+}
+
+// The corrections (Alg. 2) of correction chunk cc from the density's values and
+// second derivatives over the chunk's window (xw, sw), requested plan data in hand.
+struct GmCorr {
+    int4 arm, ch;
+    double4 dd;
+    double sg;
+    int slot;
     PointGeom gs[4];
     int axs[4];
+};
+__device__ __forceinline__ GmCorr gm_corr_loads(const DevPlan& p, int cc) {
+    static_assert(kCorrWindow <= kGmChunk && kCorrChunk <= kGmChunk, "one window place and one node place per thread");
+    const int tid = threadIdx.x;
+    // the node's plan data (place tid of the chunk's kCorrChunk) is requested
+    // with the chunk itself: neither waits for the other
+    GmCorr k;
+    k.arm = make_int4(-1, -1, -1, -1);
+    k.dd = make_double4(0.0, 0.0, 0.0, 0.0);
+    k.sg = 0.0;
+    k.slot = 0;
+    if (tid < kCorrChunk) {
+        const size_t at = (size_t)cc * kCorrChunk + tid;
+        k.arm = p.cc_arm[at];
+        k.dd = p.cc_d[at];
+        k.sg = p.cc_s[at];
+        k.slot = p.cc_pos[at];
+    }
+    k.ch = p.cc_chunk[cc];                                 // first, end, first knot, width
+    return k;
+}
+__device__ __forceinline__ void gm_corr_geometry(const DevPlan& p, GmCorr& k) {
+    const int ks[4] = {k.arm.x, k.arm.y, k.arm.z, k.arm.w};
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         if (ks[a] >= 0) {
-            gs[a] = p.q_geo[ks[a]];
-            axs[a] = p.q_axis[ks[a]];
+            k.gs[a] = p.q_geo[ks[a]];
+            k.axs[a] = p.q_axis[ks[a]];
         } else {
-            gs[a] = PointGeom{};
-            axs[a] = 0;
+            k.gs[a] = PointGeom{};
+            k.axs[a] = 0;
         }
     }
-    const GmresState* st = b.st;
-    const int kind = ctl ? ctl->kind : st->kind;
-    if (kind == kGmDone) return;
-    const double scale = ctl ? ctl->scale : st->scale;
-    const int jn = ctl ? 0 : st->jn;
-    if (tid < ch.w) xw[tid] = kind == kGmCycleEnd && !ctl ? gm_next_x(b, M, kind, scale, jn, ew) : zw * scale;
+}
+// xw: the window's values (place tid written by thread tid before a barrier here)
+__device__ inline void gm_corr_finish(const DevPlan& p, const GmCorr& k, const double* xw, double* sw,
+                                      double* __restrict__ corr_il) {
+    const int M = p.M, tid = threadIdx.x;
+    const int4 ch = k.ch;
     __syncthreads();
-    for (int w = kGmHalo + tid; w < ch.w - kGmHalo; w += kGmChunk) sw[w] = gm_spline_s2(p.taps, xw, w);
+    if (tid >= kGmHalo && tid < ch.w - kGmHalo) sw[tid] = gm_spline_s2(p.taps, xw, tid);
     __syncthreads();
-    if (!act) return;
+    if (tid >= ch.y - ch.x) return;
+    const int ks[4] = {k.arm.x, k.arm.y, k.arm.z, k.arm.w};
+    const double ds[4] = {k.dd.x, k.dd.y, k.dd.z, k.dd.w};
+    const double sg = k.sg;
     double acc = 0.0;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         if (ks[a] < 0) continue;
         const double d = ds[a];
-        const PointGeom& g = gs[a];
+        const PointGeom& g = k.gs[a];
         // the segment's first knot in the window; a window longer than M holds
         // some knots twice, and the copy inside the filter's reach of the
         // window's ends has no second derivative: take the other
@@ -740,7 +619,7 @@ __device__ inline void gm_emit_corrections(const DevPlan& p, const GmresBufs& b,
         if (p.normal_jump) {
             const double vtt = g.curv * P, vtn = Ps, vnn = 0.0 - vtt;
             jv = 0.0;
-            if (axs[a]) {
+            if (k.axs[a]) {
                 gv = P * g.ny;
                 hh = vtt * g.ty * g.ty + 2.0 * vtn * g.ty * g.ny + vnn * g.ny * g.ny;
             } else {
@@ -751,7 +630,7 @@ __device__ inline void gm_emit_corrections(const DevPlan& p, const GmresBufs& b,
             const double Pss = P2 * g.a2 - P1 * g.a3;
             const double vtt = Pss, vtn = -g.curv * Ps, vnn = 0.0 + p.kappa * P - vtt;
             jv = P;
-            if (axs[a]) {
+            if (k.axs[a]) {
                 gv = Ps * g.ty;
                 hh = vtt * g.ty * g.ty + 2.0 * vtn * g.ty * g.ny + vnn * g.ny * g.ny;
             } else {
@@ -761,35 +640,58 @@ __device__ inline void gm_emit_corrections(const DevPlan& p, const GmresBufs& b,
         }
         acc -= sg * (jv + d * gv + 0.5 * d * d * hh);
     }
-    corr_il[slot] = acc * p.inv_h2;
+    corr_il[k.slot] = acc * p.inv_h2;
 }
 
+// Correction chunk cc in the step launch: the chunk's window of the next input is
+// formed here from the same values, in the same order, as gm_step forms it, so the
+// next apply starts at its sparse sums.  corr_il in the sparse-sum layout.
+__device__ inline void gm_step_corrections(const DevPlan& p, const GmresBufs& b, int cc, double* __restrict__ corr_il) {
+    __shared__ double xw[kCorrWindow];
+    __shared__ double sw[kCorrWindow];
+    __shared__ double coef[kMaxRestart];
+    const int tid = threadIdx.x;
+    GmCorr k = gm_corr_loads(p, cc);
+    const GmStepIn u = gm_step_loads(b, p.M, (k.ch.z + tid) % p.M, tid < k.ch.w);
+    gm_corr_geometry(p, k);
+    const GmTodo t = gm_todo(b, u);
+    if (t.done) return;
+    const double x = gm_next_value(t, u, coef);
+    if (tid < k.ch.w) xw[tid] = x;
+    gm_corr_finish(p, k, xw, sw, corr_il);
+}
+
+// ---------------------------------------------------------------- start of a run
+
 // The start of a GMRES run, one launch of kGmChunk-thread workgroups: the gc
-// emit workgroups, then (with p) one per correction chunk.  Every workgroup
-// first tests the initial guess phi_in (null: zero) for nonzero values and
-// sums |ghat|^2 (ghat <- rhs when rhs is given, else already in place) in one
-// fixed order, so all of them hold the same beta and know what the run does:
+// step chunks, then (with p) one per correction chunk.  Every workgroup first
+// tests the initial guess phi_in (null: zero) for nonzero values and sums |ghat|^2
+// (ghat <- rhs when rhs is given, else already in place) in one fixed order, so all
+// of them hold the same beta and know what the run does:
 //  - a zero guess has the residual ghat itself (K 0 = 0; Alg. 5 with x_0 = 0),
-//    so its first cycle starts here: V_0 = ghat / beta is the first K input;
-//  - any other guess makes phi_in the first K input, and the first step is a
-//    residual step;
+//    so its first cycle starts here: ghat is the first K input;
+//  - any other guess makes phi_in the first K input, and the first slot is a
+//    residual slot;
 //  - beta = 0 (x = 0 solves it) or a NaN or Inf ends the run at once.
-// Workgroup 0 writes the whole state (nothing is uploaded from the host) and
-// publishes it; the emit workgroups copy phi_in and rhs into phi and ghat for
-// their chunk and write the first input with its spline second derivatives;
-// the correction workgroups make its corrections.  xout (may be null) is where
-// the emit launch of the step that ends the run copies the iterate.
+// Workgroup 0 writes the whole state (nothing is uploaded from the host); the step
+// chunks copy phi_in and rhs into phi and ghat and write the
+// first input with its spline second derivatives; the correction workgroups make
+// its corrections.  xout (may be null) is where the step launch that ends the run
+// copies the iterate.
 __device__ inline void gm_begin(const DevPlan* p, const double* __restrict__ taps, const GmresBufs& b, int M,
                                 const double* __restrict__ rhs, const double* __restrict__ phi_in, double tol,
-                                int max_iter, double reorth, double* xout, double* __restrict__ corr_il) {
+                                int max_iter, double reorth, double* xout, double* __restrict__ corr_il,
+                                unsigned epoch) {
     __shared__ double red[kGmChunk / 64];
+    __shared__ double win[kGmChunk];
+    __shared__ double sw[kGmChunk];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = blockIdx.x;
     const double* gsrc = rhs ? rhs : b.ghat;
     double ss = 0.0;
     int nz = 0;
     for (int e = tid; e < M; e += kGmChunk) {
         const double gh = gsrc[e];
-        if (phi_in) nz |= phi_in[e] != 0.0;               // a NaN counts as nonzero
+        if (phi_in) nz |= phi_in[e] != 0.0;                // a NaN counts as nonzero
         ss = fma(gh, gh, ss);
     }
     ss = wave_sum(ss);
@@ -797,29 +699,20 @@ __device__ inline void gm_begin(const DevPlan* p, const double* __restrict__ tap
     const bool nonzero = __syncthreads_or(nz) != 0;
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < kGmChunk / 64; ++w) t += red[w];  // fixed order
+    for (int w = 0; w < kGmChunk / 64; ++w) t += red[w];   // fixed order
     const double beta = sqrt(t);
-    EmitCtl ctl{kGmNewCycle, 1.0, gsrc, nullptr};
-    int converged = 0;
-    if (nonzero) {
-        ctl.kind = kGmCycleEnd;
-        ctl.xsrc = phi_in;
-    } else if (!isfinite(beta)) {
-        ctl.kind = kGmDone;
-        converged = kGmNonfinite;
-    } else if (beta == 0.0) {
-        ctl.kind = kGmDone;
-        ctl.xzero = xout;
-        converged = 1;
-    } else {
-        ctl.scale = 1.0 / beta;
-    }
+    const bool bad = !nonzero && !isfinite(beta), zero = !nonzero && beta == 0.0, over = bad || zero;
+    const double* xsrc = nonzero ? phi_in : gsrc;
     if (c == 0) {
-        for (int k = 1 + tid; k <= b.m; k += kGmChunk) b.g[k] = 0.0;
+        const GmPart q = gm_part(b);
+        for (int k = tid; k < b.gc; k += kGmChunk) {       // the first vector's norm, for the reduce launch
+            q.nrm[k] = k == 0 ? t : 0.0;
+            q.nrmw[k] = 0.0;
+        }
         if (tid == 0) {
             GmresState* st = b.st;
-            b.g[0] = nonzero ? 0.0 : beta;
             st->j = 0;
+            st->second = 0;
             st->it = 0;
             st->res_applies = 0;
             st->tol = tol;
@@ -827,26 +720,39 @@ __device__ inline void gm_begin(const DevPlan* p, const double* __restrict__ tap
             st->reorth = reorth;
             st->jn = 0;
             st->xout = xout;
-            st->converged = converged;
-            st->kind = ctl.kind;
+            st->converged = bad ? kGmNonfinite : zero ? 1 : 0;
             st->first = nonzero ? 1 : 0;
             st->r0 = nonzero ? 0.0 : beta;
-            st->relres = converged == 1 ? 0.0 : 1.0;
-            st->scale = ctl.scale;
-            st->cycles = ctl.kind == kGmNewCycle ? 1 : 0;
-            st->mode = ctl.kind == kGmNewCycle ? 1 : ctl.kind == kGmCycleEnd ? 0 : 2;
-            gm_publish(b);
+            st->relres = zero ? 0.0 : 1.0;
+            st->cycles = nonzero || over ? 0 : 1;
+            st->ph = over ? kGmOver : nonzero ? kGmResidualPh : kGmArnoldi;
+            st->act = kGmDone;
+            st->act_j = 0;
+            st->epoch = epoch;
+            st->slot = 0;
+            if (over) gm_publish_end(b);
         }
     }
     if (c < b.gc) {
-        const int e = c * kGmChunk + tid;
-        if (e < M) {
-            b.phi[e] = phi_in ? phi_in[e] : 0.0;
-            if (rhs) b.ghat[e] = rhs[e];
+        const GmPlaceOf pl = gm_place(b, M, c, taps != nullptr);
+        if (pl.own) {
+            b.phi[pl.e] = phi_in ? phi_in[pl.e] : 0.0;
+            if (rhs) b.ghat[pl.e] = rhs[pl.e];
+            if (zero && xout) xout[pl.e] = 0.0;
         }
-        gm_emit(taps, b, M, c, &ctl);
+        if (over) return;
+        const double x = pl.in ? xsrc[pl.e] : 0.0;
+        if (pl.own) b.xcur[pl.e] = x;
+        if (!taps) return;
+        win[tid] = x;
+        __syncthreads();
+        if (pl.own) b.s2cur[pl.e] = gm_spline_s2(taps, win, tid);
     } else {
-        gm_emit_corrections(*p, b, c - b.gc, corr_il, &ctl);
+        if (over) return;
+        GmCorr k = gm_corr_loads(*p, c - b.gc);
+        if (tid < k.ch.w) win[tid] = xsrc[(k.ch.z + tid) % M];
+        gm_corr_geometry(*p, k);
+        gm_corr_finish(*p, k, win, sw, corr_il);
     }
 }
 

@@ -155,20 +155,23 @@ __global__ __launch_bounds__(256) void k_interp3(DevPlan3 p, const double* __res
     if (m < p.M) out[m] = interp3_at(p, G, J, m);
 }
 
-// inside GMRES: v+ at 64 control points, then the first Gram-Schmidt pass
+// inside GMRES: v+ at 64 control points, then the reduce part of the step; the last
+// workgroup commits the previous column
 __global__ __launch_bounds__(1024) void k_interp3_gm(DevPlan3 p, const double* __restrict__ G,
                                                      const double* __restrict__ J, GmresBufs b) {
     __shared__ double red[64];
+    if ((int)blockIdx.x == b.gc64) {
+        gm_commit(b, p.M);
+        return;
+    }
     if (b.st->converged) return;
+    const GmPre pre = gm_reduce_prefetch(b, p.M, blockIdx.x);
+    const GmPh ph{b.st->ph, b.st->j, b.st->second, b.st->reorth};
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = blockIdx.x * 64 + lane;
-    if (wave == 0) {
-        const double v = m < p.M ? interp3_at(p, G, J, m) : 0.0;
-        if (m < p.M) b.w[m] = v;
-        red[lane] = v;
-    }
+    if (wave == 0) red[lane] = m < p.M ? interp3_at(p, G, J, m) : 0.0;
     __syncthreads();
-    gm_dots1_64(b, p.M, blockIdx.x, red);
+    gm_reduce64(b, p.M, blockIdx.x, red, pre, ph);
 }
 
 __global__ __launch_bounds__(256) void k_grid_out3(DevPlan3 p, const double* __restrict__ G, int mask,
@@ -231,7 +234,7 @@ hipError_t launch_solve3(const DevPlan3& p, double* G, int B, const int* skip, h
 
 hipError_t launch_interp3(const DevPlan3& p, const double* G, const double* J, double* out, const GmresBufs* gm,
                           hipStream_t s) {
-    if (gm) return klaunch(&k_interp3_gm, dim3((p.M + 63) / 64), dim3(1024), 0, s, p, G, J, *gm);
+    if (gm) return klaunch(&k_interp3_gm, dim3(gm->gc64 + 1), dim3(1024), 0, s, p, G, J, *gm);
     if (hipError_t e = klaunch(&k_interp3, dim3((p.M + 255) / 256), dim3(256), 0, s, p, G, J, out)) return e;
     return hipGetLastError();
 }

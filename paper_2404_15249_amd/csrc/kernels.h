@@ -120,8 +120,11 @@ struct JumpSrc {
 };
 
 struct GmresState {
-    int mode;        // 0: residual step pending, 1: Arnoldi, 2: done
-    int j;           // Arnoldi column inside the cycle
+    int ph;          // what the next apply is of (GmPhase in gmres.h): the iterate, or basis vector j
+    int j;           // the basis vector the apply makes (its input is that vector, not yet scaled)
+    int second;      // 1: the input has had its second Gram-Schmidt pass
+    int act;         // what the next step launch does (GmAct in gmres.h), and the column it is about
+    int act_j;
     int it;          // K_D applications made by the Arnoldi process
     int first;       // 1 until r0 is known
     int converged;   // 1 converged, -1 iteration cap, -2 a NaN or Inf met (kGmNonfinite), 0 running
@@ -130,17 +133,30 @@ struct GmresState {
     double relres;
     double tol;      // stop when the relative residual drops below tol (<= 0: never)
     int max_iter;    // cap on Arnoldi steps
-    int kind;        // what the last commit left for the emit launch (GmKind in gmres.h)
-    int jn;          // columns of the cycle just finished (kGmCycleEnd)
+    int jn;          // columns of the cycle just finished
     int res_applies; // K applications made for residuals (cycle starts and the final check)
-    double scale;    // 1/beta (new cycle) or 1/h_{j+1,j} (next vector)
     double reorth;   // second Gram-Schmidt pass when |z| < reorth |w| (0: never, 1: always)
-    double* xout;    // where the emit launch of the finishing step copies the iterate (null: nowhere)
+    double* xout;    // where the step launch that ends the run copies the iterate (null: nowhere)
+    unsigned epoch;  // the run's number, for the host (GmresPub)
+    int slot;        // slots whose commit has run
 };
+
+// What a run tells the host while it goes on (pinned, coherent host memory the
+// device writes; the host reads it without waiting for the stream).  prog: epoch in
+// the upper half; then kGmLastSlot when the commit found that the run ends at the
+// next slot's residual if that confirms it; slots committed in the low bits.
+struct GmresPub {
+    GmresState st;             // the final state, written before `done`
+    unsigned long long prog;
+    unsigned done;             // the run's epoch once it is over
+    unsigned again;            // residuals that did not end a run (any run's)
+};
+constexpr unsigned kGmLastSlot = 0x80000000u;
 
 struct GmresBufs {
     double* V;       // (m+1) M
     double* H;       // (m+1) m, column j at H + j (m+1)
+    double* h;       // m: the column's coefficients, as the step launch made them
     double* cs;      // m
     double* sn;      // m
     double* g;       // m + 1
@@ -148,16 +164,15 @@ struct GmresBufs {
     double* phi;     // M
     double* xcur;    // M: input of the next K_D apply
     double* s2cur;   // M: spline second derivatives of xcur
-    double* w;       // M: output of the last K_D apply
-    double* z;       // M: the vector being orthogonalised (or the residual)
+    double* w;       // M: K of the last basis vector
+    double* z;       // M: the residual
     double* part;    // gm_part_size(m, gc, gc64): per-chunk partial dots and norms
     double* y;       // m + 1: solution of the cycle's triangular system
     GmresState* st;  // state machine; also holds tol and max_iter so launches are call independent
-    GmresState* pub; // host-visible mirror of the state (pinned host memory; may be null)
-    unsigned* cnt;   // chunks of the current update launch that have finished (0 between launches)
+    GmresPub* pub;   // what the host sees of the run (may be null)
     int m;
-    int gc;          // chunks of kGmChunk elements covering the M samples
-    int gc64;        // chunks of 64 samples (the first Gram-Schmidt pass)
+    int gc;          // chunks of the step launch (gm_chunks)
+    int gc64;        // chunks of 64 samples (the reduce launch)
 };
 
 constexpr int kIterNonfinite = -2;
@@ -198,7 +213,7 @@ hipError_t launch_modes(const DevPlan& p, const double* corr, double* partial, i
                         const int* skip, hipStream_t s);
 hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const int* skip, hipStream_t s);
 // with gm non-null (a GMRES step) the output goes to gm->w, the launch is skipped
-// once GMRES is done, and it also makes the first Gram-Schmidt pass (gmres.h)
+// once GMRES is done, and it also makes its part of the GMRES step (gmres.h)
 hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* partial, int G, double* out,
                                 const int* skip, const GmresBufs* gm, hipStream_t s);
 hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* R, double* out, hipStream_t s);
@@ -241,15 +256,17 @@ hipError_t launch_nonfinite(int n, const double* x, int* flag, hipStream_t s);
 // the first K input (its spline second derivatives with taps; with p and
 // corr_il also its corrections, in the sparse-sum layout).  rhs may be null
 // (ghat already in place); phi_in may be null (a zero guess); xout (may be
-// null) receives the iterate from the emit launch of the step that ends the run.
+// null) receives the iterate from the step launch that ends the run; epoch: the run's
+// number (not 0, another for each run).
 hipError_t launch_gmres_start(const DevPlan* p, const double* taps, int M, GmresBufs b, const double* rhs,
                               const double* phi_in, double tol, int max_iter, double reorth, double* xout,
-                              double* corr_il, hipStream_t s);
-// taps: the spline filter of the density (null: no spline, the surface problem)
+                              double* corr_il, unsigned epoch, hipStream_t s);
+// The step launch (gmres.h).  taps: the spline filter of the density (null: no
+// spline, the surface problem)
 hipError_t launch_gmres_step(const double* taps, int M, GmresBufs b, hipStream_t s);
 // default of GmresState::reorth (see gmres.h)
 constexpr double kGmReorthDefault = 1e-3;
-// the same step with the next apply's corrections made in the emit launch
+// the same with the next apply's corrections made in the launch
 // (into corr_il, the sparse-sum layout)
 hipError_t launch_gmres_step_corr(const DevPlan& p, GmresBufs b, double* corr_il, hipStream_t s);
 

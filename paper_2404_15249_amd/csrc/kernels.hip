@@ -20,7 +20,7 @@
 //              order plus the jump terms of the stencil nodes outside Omega
 //              (Alg. 3).
 // k_spline precomputes the spline second derivatives of the density (inside
-// GMRES the emit launch of gmres.h does it for the next input).
+// GMRES the step launch of gmres.h does it for the next input).
 // The dense solve (volume potential, final solution) uses the same tridiagonal
 // solver on full rows (k_rows_solve), between two column sine transforms
 // (dst.hip); in the FP32 mode the transforms and the stored rows are FP32 and
@@ -206,31 +206,37 @@ __global__ __launch_bounds__(256) void k_nonfinite(int n, const double* __restri
 
 // ---------------------------------------------------------------- GMRES step (Alg. 5)
 
-// the apply's last launch inside GMRES: w at 64 samples, then the first pass
+// the apply's last launch inside GMRES: its output at 64 samples, then the reduce
+// part of the step; the last workgroup commits the previous column
 __global__ __launch_bounds__(1024) void k_reduce_gm(DevPlan p, JumpSrc js, const double* __restrict__ partial, int G,
                                                     GmresBufs b) {
     __shared__ double red[16 * 64];
-    const GmPre pre = gm_dots1_prefetch(b, p.M, blockIdx.x);
-    const int mode = load_flag_late(&b.st->mode), j = load_flag_late(&b.st->j);   // waited for where used
-    if (!reduce_samples64(p, js, partial, G, blockIdx.x * 64, b.w, red, &b.st->converged)) return;
-    gm_dots1_64(b, p.M, blockIdx.x, red, &pre, mode, j);
+    if ((int)blockIdx.x == b.gc64) {
+        gm_commit(b, p.M);
+        return;
+    }
+    const GmPre pre = gm_reduce_prefetch(b, p.M, blockIdx.x);
+    const GmPh ph{load_flag_late(&b.st->ph), load_flag_late(&b.st->j), load_flag_late(&b.st->second),
+                  load_real_late(&b.st->reorth)};       // waited for where used
+    if (!reduce_samples64(p, js, partial, G, blockIdx.x * 64, nullptr, red, &b.st->converged)) return;
+    gm_reduce64(b, p.M, blockIdx.x, red, pre, ph);
 }
-__global__ __launch_bounds__(kGmChunk) void k_gm_upd1(GmresBufs b, int M) { gm_update1_commit(b, M, blockIdx.x); }
 __global__ __launch_bounds__(kGmChunk) void k_gm_begin(DevPlan p, int has_p, const double* taps, GmresBufs b, int M,
                                                        const double* rhs, const double* phi_in, double tol,
-                                                       int max_iter, double reorth, double* xout, double* corr_il) {
-    gm_begin(has_p ? &p : nullptr, taps, b, M, rhs, phi_in, tol, max_iter, reorth, xout, corr_il);
+                                                       int max_iter, double reorth, double* xout, double* corr_il,
+                                                       unsigned epoch) {
+    gm_begin(has_p ? &p : nullptr, taps, b, M, rhs, phi_in, tol, max_iter, reorth, xout, corr_il, epoch);
 }
-__global__ __launch_bounds__(kGmChunk) void k_gm_emit(const double* taps, GmresBufs b, int M) {
-    gm_emit(taps, b, M, blockIdx.x);
+__global__ __launch_bounds__(kGmChunk) void k_gm_step(const double* taps, GmresBufs b, int M) {
+    gm_step(taps, b, M, blockIdx.x);
 }
-// the emit launch with the next apply's corrections: workgroups 0 .. gc-1
-// emit, the rest make one correction chunk each
-__global__ __launch_bounds__(kGmChunk) void k_gm_emit_corr(DevPlan p, GmresBufs b, double* __restrict__ corr_il) {
+// the step launch with the next apply's corrections: workgroups 0 .. gc-1 make the
+// vector's chunks, the rest one correction chunk each
+__global__ __launch_bounds__(kGmChunk) void k_gm_step_corr(DevPlan p, GmresBufs b, double* __restrict__ corr_il) {
     if ((int)blockIdx.x < b.gc) {
-        gm_emit(p.taps, b, p.M, blockIdx.x);
+        gm_step(p.taps, b, p.M, blockIdx.x);
     } else {
-        gm_emit_corrections(p, b, (int)blockIdx.x - b.gc, corr_il);
+        gm_step_corrections(p, b, (int)blockIdx.x - b.gc, corr_il);
     }
 }
 
@@ -331,7 +337,7 @@ hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const in
 
 hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* partial, int G, double* out,
                                 const int* skip, const GmresBufs* gm, hipStream_t s) {
-    if (gm) return klaunch(&k_reduce_gm, dim3((p.M + 63) / 64), dim3(1024), 0, s, p, js, partial, G, *gm);
+    if (gm) return klaunch(&k_reduce_gm, dim3(gm->gc64 + 1), dim3(1024), 0, s, p, js, partial, G, *gm);
     if (hipError_t e_ = klaunch(&k_reduce_interp, dim3((p.M + 63) / 64), dim3(1024), 0, s, p, js, partial, G, out, skip)) return e_;
     return hipGetLastError();
 }
@@ -381,25 +387,21 @@ hipError_t launch_nonfinite(int n, const double* x, int* flag, hipStream_t s) {
 }
 
 hipError_t launch_gmres_step_corr(const DevPlan& p, GmresBufs b, double* corr_il, hipStream_t s) {
-    const dim3 g(b.gc), t(kGmChunk);
-    if (hipError_t e = klaunch(&k_gm_upd1, g, t, 0, s, b, p.M)) return e;
-    return klaunch(&k_gm_emit_corr, dim3(b.gc + p.n_cc), t, 0, s, p, b, corr_il);
+    return klaunch(&k_gm_step_corr, dim3(b.gc + p.n_cc), dim3(kGmChunk), 0, s, p, b, corr_il);
 }
 
 hipError_t launch_gmres_start(const DevPlan* p, const double* taps, int M, GmresBufs b, const double* rhs,
                               const double* phi_in, double tol, int max_iter, double reorth, double* xout,
-                              double* corr_il, hipStream_t s) {
+                              double* corr_il, unsigned epoch, hipStream_t s) {
     const bool corr = p && corr_il;
     const DevPlan pv = corr ? *p : DevPlan{};
     const int groups = b.gc + (corr ? p->n_cc : 0);
     return klaunch(&k_gm_begin, dim3(groups), dim3(kGmChunk), 0, s, pv, corr ? 1 : 0, taps, b, M, rhs, phi_in, tol,
-                   max_iter, reorth, xout, corr ? corr_il : nullptr);
+                   max_iter, reorth, xout, corr ? corr_il : nullptr, epoch);
 }
 
 hipError_t launch_gmres_step(const double* taps, int M, GmresBufs b, hipStream_t s) {
-    const dim3 g(b.gc), t(kGmChunk);
-    if (hipError_t e = klaunch(&k_gm_upd1, g, t, 0, s, b, M)) return e;
-    return klaunch(&k_gm_emit, g, t, 0, s, taps, b, M);
+    return klaunch(&k_gm_step, dim3(b.gc), dim3(kGmChunk), 0, s, taps, b, M);
 }
 
 }  // namespace kfbi
