@@ -99,8 +99,8 @@ struct kfbi_prob {
     const double* b_fgam = nullptr;
     double* s2a = nullptr;       // M: spline second derivatives (density)
     double* s2b = nullptr;       // M: spline second derivatives (f on Gamma)
-    int* d_flag = nullptr;       // 1: the density checked by a kfbi_apply call holds a NaN or Inf
-    int h_flag = 0;              // its host copy
+    int* d_flag = nullptr;       // 2: 1 when the density checked by a kfbi_apply call holds a NaN or Inf (calls in turn)
+    unsigned n_apply = 0;        // kfbi_apply and kfbi_apply_neumann calls so far
     GmresBufs gm{};
     GmresState st_host{};        // host copy of the GMRES state (stable address for async copies)
     GmresHost host;              // what the device tells of a run (gm.pub)
@@ -293,15 +293,17 @@ kfbi_status sparse_apply(kfbi_prob* p, int op, const double* phi, const double* 
 
 // K_D phi or K_N phi (op) of a caller's density, checked first: the apply's
 // launches skip when the check finds a NaN or Inf, so nothing is written, and
-// the call waits for the check's flag.
+// the call waits for them.
 kfbi_status checked_apply(kfbi_prob* p, int op, const double* phi, double* out) {
     hipStream_t s = p->ctx->stream;
-    HIP_TRY(launch_nonfinite(p->M, phi, p->d_flag, s));
-    HIP_TRY(launch_spline(p->dp, phi, p->s2a, p->d_flag, s));
-    if (kfbi_status e = sparse_apply(p, op, phi, p->s2a, out, p->d_flag, nullptr, s)) return e;
-    HIP_TRY(hipMemcpyAsync(&p->h_flag, p->d_flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    const unsigned number = p->n_apply = p->n_apply + 1 ? p->n_apply + 1 : 2;   // never 0; parity alternates
+    const DensityCheck check{p->d_flag + (number & 1), p->d_flag + (~number & 1), &p->host.pub->bad, number};
+    const bool ready = !p->timing;                          // timed: the corrections are a launch of their own
+    HIP_TRY(launch_density(op_view(p, op), phi, p->s2a, p->corr_il, nullptr, &check, s));
+    if (kfbi_status e = sparse_apply(p, op, phi, p->s2a, out, check.flag, nullptr, s, ready)) return e;
     HIP_TRY(hipStreamSynchronize(s));
-    if (p->h_flag) return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in the density");
+    if (__atomic_load_n(check.bad, __ATOMIC_ACQUIRE) == number)
+        return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in the density");
     return KFBI_OK;
 }
 
@@ -467,11 +469,11 @@ kfbi_status gmres_call(kfbi_prob* p, int op, const double* rhs, double* x, doubl
 enum IterMethod { kRich = 0, kBicg = 1 };
 constexpr int kIterBatch[2] = {8, 4};   // iterations per replayed batch (8 applies each)
 
-// One K_D apply of `in` into ib.w (spline, correction, sparse solve, reduction),
+// One K_D apply of `in` into ib.w (spline and corrections, sparse solve, reduction),
 // skipped once the run is done.
 kfbi_status iter_apply(kfbi_prob* p, const double* in, const int* skip, hipStream_t s) {
-    HIP_TRY(launch_spline(p->dp, in, p->ib.s2, skip, s));
-    return sparse_apply(p, kOpD, in, p->ib.s2, p->ib.w, skip, nullptr, s);
+    HIP_TRY(launch_density(p->dp, in, p->ib.s2, p->corr_il, skip, nullptr, s));
+    return sparse_apply(p, kOpD, in, p->ib.s2, p->ib.w, skip, nullptr, s, true);
 }
 
 kfbi_status enqueue_iters(kfbi_prob* p, int method, int n, hipStream_t s) {
@@ -936,7 +938,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     if ((st = dev_alloc(p, &p->corr, p->I)) || (st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
         (st = dev_alloc(p, &p->R, (size_t)n * n)) || (st = dev_alloc(p, &p->A, (size_t)n * n)) ||
         (st = dev_alloc(p, &p->tmpM, M)) || (st = dev_alloc(p, &p->s2a, M)) || (st = dev_alloc(p, &p->s2b, M)) ||
-        (st = dev_alloc(p, &p->d_flag, 1)) ||
+        (st = dev_alloc(p, &p->d_flag, 2)) ||
         (st = dev_alloc(p, &p->gm.s2cur, M)) || (st = dev_alloc(p, &p->gm.V, (size_t)(m + 1) * M)) ||
         (st = dev_alloc(p, &p->gm.H, (size_t)(m + 1) * m)) || (st = dev_alloc(p, &p->gm.cs, m)) ||
         (st = dev_alloc(p, &p->gm.sn, m)) || (st = dev_alloc(p, &p->gm.g, m + 1)) ||
@@ -954,6 +956,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         if ((st = dev_alloc(p, &ib.st, 1))) return fail(st);
         ib.M = M;
     }
+    HIP_TRY(hipMemset(p->d_flag, 0, 2 * sizeof(int)));
     if ((st = p->host.alloc())) return fail(st);
     p->gm.pub = p->host.pub;
     if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
@@ -1065,9 +1068,8 @@ kfbi_status kfbi_apply_noalloc(kfbi_prob* p, const double* phi, double* out) {
     // be zero; the flag is written by its check whatever it finds
     HIP_TRY(launch_fill((size_t)d.T * 64, 0.0, corr_il, s));
     HIP_TRY(launch_nonfinite(M, phi, flag, s));
-    HIP_TRY(launch_spline(p->dp, phi, s2, flag, s));
+    HIP_TRY(launch_density(d, phi, s2, corr_il, flag, nullptr, s));
     const JumpSrc js{phi, s2, nullptr, nullptr, nullptr, nullptr};
-    HIP_TRY(launch_correct(d, js, nullptr, corr_il, nullptr, flag, s));
     HIP_TRY(launch_modes(d, corr_il, part, p->Rm, flag, s));
     HIP_TRY(launch_reduce_interp(d, js, part, p->G, out, flag, nullptr, s));
     return KFBI_OK;

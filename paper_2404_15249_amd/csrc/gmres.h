@@ -661,6 +661,44 @@ __device__ inline void gm_step_corrections(const DevPlan& p, const GmresBufs& b,
     gm_corr_finish(p, k, xw, sw, corr_il);
 }
 
+// ---------------------------------------------------------------- a caller's density
+
+// What an apply needs of a caller's density y before its sparse solve, in one launch
+// of kGmChunk-thread workgroups: gc chunks make the spline second derivatives
+// (s2), the rest one correction chunk each from their own windows of y, as the step
+// launch does (three launches before: the check, the spline, the corrections, 13 us
+// together against 5).  With flag, the chunks also look for a NaN or Inf: flag is
+// set (it is 0 before: the launch of the call before cleared it, as this one clears
+// flag_next), and the call's number goes to *bad for the host.
+__device__ inline void gm_density(const DevPlan& p, const double* __restrict__ y, double* __restrict__ s2,
+                                  double* __restrict__ corr_il, int gc, int* flag, int* flag_next, unsigned* bad,
+                                  unsigned number) {
+    __shared__ double win[kGmChunk];
+    __shared__ double sw[kGmChunk];
+    const int tid = threadIdx.x, c = blockIdx.x, M = p.M;
+    if (c >= gc) {
+        GmCorr k = gm_corr_loads(p, c - gc);
+        if (tid < k.ch.w) win[tid] = y[(k.ch.z + tid) % M];
+        gm_corr_geometry(p, k);
+        gm_corr_finish(p, k, win, sw, corr_il);
+        return;
+    }
+    const int at = c * kGmOwnSpline - kGmHalo + tid;
+    int e = at % M;
+    if (e < 0) e += M;
+    const double x = y[e];
+    win[tid] = x;
+    if (flag) {
+        if (!isfinite(x)) {                                // benign races: every writer stores the same
+            *flag = 1;
+            __hip_atomic_store(bad, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        if (c == 0 && tid == 0) *flag_next = 0;
+    }
+    __syncthreads();
+    if (tid >= kGmHalo && tid < kGmHalo + kGmOwnSpline && at < M) s2[e] = gm_spline_s2(p.taps, win, tid);
+}
+
 // ---------------------------------------------------------------- start of a run
 
 // The start of a GMRES run, one launch of kGmChunk-thread workgroups: the gc

@@ -150,6 +150,7 @@ struct GmresPub {
     unsigned long long prog;
     unsigned done;             // the run's epoch once it is over
     unsigned again;            // residuals that did not end a run (any run's)
+    unsigned bad;              // number of the last apply whose density held a NaN or Inf
 };
 constexpr unsigned kGmLastSlot = 0x80000000u;
 
@@ -211,6 +212,20 @@ hipError_t launch_correct(const DevPlan& p, JumpSrc js, double* corr, double* co
 // ceil((N-1) / R) workgroups, each writing one row of M partial sums
 hipError_t launch_modes(const DevPlan& p, const double* corr, double* partial, int R,
                         const int* skip, hipStream_t s);
+// A check of a density for NaN or Inf: flag (0 before the launch) is set and number
+// stored to *bad (host memory the device can write) when there is one; flag_next, the
+// flag of the next call, is cleared.
+struct DensityCheck {
+    int* flag;
+    int* flag_next;
+    unsigned* bad;
+    unsigned number;
+};
+// What an apply needs of a density y before the sparse solve (gm_density in
+// gmres.h): its spline second derivatives and its corrections in the sparse-sum
+// layout; with check (may be null) also the check.
+hipError_t launch_density(const DevPlan& p, const double* y, double* s2, double* corr_il, const int* skip,
+                          const DensityCheck* check, hipStream_t s);
 hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const int* skip, hipStream_t s);
 // with gm non-null (a GMRES step) the output goes to gm->w, the launch is skipped
 // once GMRES is done, and it also makes its part of the GMRES step (gmres.h)

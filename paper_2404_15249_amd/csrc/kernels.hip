@@ -240,6 +240,12 @@ __global__ __launch_bounds__(kGmChunk) void k_gm_step_corr(DevPlan p, GmresBufs 
     }
 }
 
+__global__ __launch_bounds__(kGmChunk) void k_density(DevPlan p, const double* __restrict__ y, double* __restrict__ s2,
+                                                      double* __restrict__ corr_il, int gc, const int* __restrict__ skip,
+                                                      int* flag, int* flag_next, unsigned* bad, unsigned number) {
+    if (skip && *skip) return;
+    gm_density(p, y, s2, corr_il, gc, flag, flag_next, bad, number);
+}
 
 template <int C, int R>
 hipError_t modes_launch(const DevPlan& p, const double* corr, double* partial, const int* skip, hipStream_t s) {
@@ -333,6 +339,14 @@ hipError_t launch_modes(const DevPlan& p, const double* corr, double* partial, i
 hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const int* skip, hipStream_t s) {
     if (hipError_t e_ = klaunch(&k_spline, dim3((p.M + 255) / 256), dim3(256), 0, s, p, y, s2, skip)) return e_;
     return hipGetLastError();
+}
+
+hipError_t launch_density(const DevPlan& p, const double* y, double* s2, double* corr_il, const int* skip,
+                          const DensityCheck* check, hipStream_t s) {
+    const int gc = gm_chunks(p.M, true);
+    const DensityCheck k = check ? *check : DensityCheck{};
+    return klaunch(&k_density, dim3(gc + p.n_cc), dim3(kGmChunk), 0, s, p, y, s2, corr_il, gc, skip, k.flag, k.flag_next,
+                   k.bad, k.number);
 }
 
 hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* partial, int G, double* out,
