@@ -84,8 +84,11 @@ struct kfbi_prob {
     // work buffers
     double* corr = nullptr;      // I
     double* corr_il = nullptr;   // T x 64: corrections in the interleaved layout of the sparse sums
+    double* corr_d = nullptr;    // the same for an interface solve (corr_il may hold an admitted request's next ones)
     double* partial = nullptr;   // G M
-    double* R = nullptr;         // N N
+    double* R = nullptr;         // N N: right-hand side, modes or their solution (padded layout)
+    unsigned modes_of = 0;       // number of the dense solve whose right-hand side's modes R holds (0: none; FP64)
+    unsigned modes_number = 0;   // the last such number given
     double* A = nullptr;         // N N
     int precision = KFBI_FP64, refine = 0;
     float* X32 = nullptr;        // N N: FP32 transform storage (KFBI_FP32_REFINED)
@@ -95,6 +98,7 @@ struct kfbi_prob {
     double* tmpM = nullptr;      // M
     double* partial_b = nullptr; // M x Gs: partials of the batched fast solve (allocated on first admission)
     int Gs = 0;
+    unsigned b_modes = 0;              // modes_of after the admission's dense solve
     const double* b_fgrid = nullptr;   // right-hand side of the batched request (caller owned)
     const double* b_fgam = nullptr;
     double* s2a = nullptr;       // M: spline second derivatives (density)
@@ -200,21 +204,14 @@ DevPlan op_view(const kfbi_prob* p, int op) { return plan_view(p, op == kOpN, op
 size_t cpx_bytes(int precision) { return precision == KFBI_FP64 ? 2 * sizeof(double) : 2 * sizeof(float); }
 
 
-// Alg. 4 on the full grid: solve (L_h - kappa) V = R (R in the padded interior
-// layout, consumed).  FP64: in place, *V = R.  FP32 with refinement: an FP32
-// solve (FP32 column transforms around the FP64 row solves) of R into A, then
-// per refine step: R <- R - (L_h - kappa) d for the last correction d (FP64),
-// and the FP32 solve of R as the next correction; *V = A, the sum of them.
-kfbi_status grid_solve(kfbi_prob* p, const double** V) {
+// Alg. 4 on the full grid with FP32 transforms (KFBI_FP32_REFINED): solve
+// (L_h - kappa) V = R (R in the padded interior layout, consumed): an FP32 solve (FP32
+// column transforms around the FP64 row solves) of R into A, then per refine step:
+// R <- R - (L_h - kappa) d for the last correction d (FP64), and the FP32 solve of R as
+// the next correction; A is the sum of them.
+kfbi_status grid_solve_f32(kfbi_prob* p) {
     hipStream_t s = p->ctx->stream;
     const double inv = 2.0 / p->N;
-    if (p->precision == KFBI_FP64) {
-        HIP_TRY(launch_dst_cols(p->dp, p->R, p->R, 1.0, false, p->dstB, s));
-        HIP_TRY(launch_rows_solve(p->dp, p->R, s));
-        HIP_TRY(launch_dst_cols(p->dp, p->R, p->R, inv, false, p->dstB, s));
-        *V = p->R;
-        return KFBI_OK;
-    }
     // corrections: the first lands in A; middle ones in D (then added to A while
     // forming the next residual); the last is accumulated into A directly
     for (int k = 0; k <= p->refine; ++k) {
@@ -225,34 +222,108 @@ kfbi_status grid_solve(kfbi_prob* p, const double** V) {
         const bool middle = k > 0 && k < p->refine;
         HIP_TRY(launch_dst_cols_f32_to64(p->dp, p->X32, middle ? p->D : p->A, inv, k > 0 && !middle, p->dstB, s));
     }
-    *V = p->A;
     return KFBI_OK;
 }
 
-// Dense interface solve: R <- f~ (+ corrections), the grid solve, then
-// interpolation at the samples (v+ into vz, d_n v+ into dnz; either may be
-// null) and, optionally, the grid written to `vgrid`.  normal_jump: the
-// density in js is [d_n v] (else [v]).
-kfbi_status dense_interface_solve(kfbi_prob* p, bool normal_jump, JumpSrc js, const double* f, bool mask,
-                                  double* vgrid, bool mask_out, double* vz, double* dnz = nullptr) {
+// An interface solve on the full grid: right-hand side f (null: zero; with mask zero
+// outside Omega) and the jumps js; v+ at the samples into vz (with `from`: from - v+),
+// d_n v+ into dnz, the grid into vgrid (with mask_out zero outside Omega); each may be
+// null.  normal_jump: the density in js is [d_n v] (else [v]).
+struct DenseArgs {
+    bool normal_jump = false;
+    JumpSrc js{};
+    const double* f = nullptr;
+    bool mask = false;
+    double* vgrid = nullptr;
+    bool mask_out = false;
+    double* vz = nullptr;
+    double* dnz = nullptr;
+    const double* from = nullptr;    // with exactly one of vz, dnz: out = from - it
+    unsigned modes = 0;              // p->modes_of after an earlier solve of this f: reuse its modes if R still holds them
+};
+
+// With FP32 transforms: the right-hand side with its corrections in the padded
+// layout, the refined grid solve, then interpolation and output from the grid.
+kfbi_status dense_solve_f32(kfbi_prob* p, const DenseArgs& a) {
     hipStream_t s = p->ctx->stream;
-    if (js.phi) {
-        HIP_TRY(launch_spline(p->dp, js.phi, p->s2a, nullptr, s));
-        js.phi_s2 = p->s2a;
-    }
-    if (js.fgam) {
-        HIP_TRY(launch_spline(p->dp, js.fgam, p->s2b, nullptr, s));
-        js.fgam_s2 = p->s2b;
-    }
-    const DevPlan dv = plan_view(p, normal_jump, false);
-    HIP_TRY(launch_fill_rhs(dv, f, mask, p->R, s));
-    HIP_TRY(launch_correct(dv, js, nullptr, nullptr, p->R, nullptr, s));
-    const double* V = nullptr;
-    if (kfbi_status e = grid_solve(p, &V)) return e;
-    if (vz) HIP_TRY(launch_interp_grid(dv, js, V, vz, s));
-    if (dnz) HIP_TRY(launch_interp_grid(plan_view(p, normal_jump, true), js, V, dnz, s));
-    if (vgrid) HIP_TRY(launch_grid_out(dv, V, mask_out, vgrid, s));
+    const DevPlan dv = plan_view(p, a.normal_jump, false);
+    HIP_TRY(launch_fill_rhs(dv, a.f, a.mask, p->R, s));
+    HIP_TRY(launch_correct(dv, a.js, nullptr, nullptr, p->R, nullptr, s));
+    if (kfbi_status e = grid_solve_f32(p)) return e;
+    double* vz = a.from && a.vz ? p->tmpM : a.vz;
+    double* dnz = a.from && a.dnz ? p->tmpM : a.dnz;
+    if (vz) HIP_TRY(launch_interp_grid(dv, a.js, p->A, vz, s));
+    if (dnz) HIP_TRY(launch_interp_grid(plan_view(p, a.normal_jump, true), a.js, p->A, dnz, s));
+    if (a.from) HIP_TRY(launch_axpby(p->M, 1.0, a.from, -1.0, p->tmpM, a.vz ? a.vz : a.dnz, s));
+    if (a.vgrid) HIP_TRY(launch_grid_out(dv, p->A, a.mask_out, a.vgrid, s));
     return KFBI_OK;
+}
+
+// In FP64 the grid is touched only by what its values are wanted for: a transform
+// reads f and leaves its modes in R; the row solves add the corrections' sparse sums
+// to them and make the samples' partial sums as the apply does; and a transform
+// writes the solution, when it is wanted, to the caller's grid.  A solve's second
+// interface solve, with the same f, starts from the modes the first one left.
+kfbi_status dense_interface_solve(kfbi_prob* p, DenseArgs a) {
+    hipStream_t s = p->ctx->stream;
+    const bool f64 = p->precision == KFBI_FP64;
+    const DevPlan dv = plan_view(p, a.normal_jump, false);
+    if (a.js.phi) a.js.phi_s2 = p->s2a;
+    if (a.js.fgam) a.js.fgam_s2 = p->s2b;
+    if (f64 && !a.js.jq) {
+        HIP_TRY(launch_density_f(dv, a.js.phi, a.js.fgam, p->s2a, p->s2b, p->corr_d, s));
+    } else {
+        if (a.js.phi) HIP_TRY(launch_spline(p->dp, a.js.phi, p->s2a, nullptr, s));
+        if (a.js.fgam) HIP_TRY(launch_spline(p->dp, a.js.fgam, p->s2b, nullptr, s));
+        if (f64) HIP_TRY(launch_correct(dv, a.js, nullptr, p->corr_d, nullptr, nullptr, s));
+    }
+    const bool held = a.modes && a.modes == p->modes_of;
+    p->modes_of = 0;
+    if (!f64) return dense_solve_f32(p, a);
+    if (a.f && !held) HIP_TRY(launch_dst_from_grid(p->dp, a.f, a.mask, p->R, p->dstB, s));
+    // the samples' weights: v+, d_n v+, or both (then two sets of partial sums, which
+    // the default tile's share of the buffer has room for, half of that tile not)
+    const DevPlan dw = plan_view(p, a.normal_jump, !a.vz && a.dnz), dn = plan_view(p, a.normal_jump, true);
+    const bool both = a.vz && a.dnz;
+    const int Rm = both && 2 * p->G > p->Gcap ? 2 * p->Rm : p->Rm, G = (p->n + Rm - 1) / Rm;
+    double* second = both ? p->partial + (size_t)G * p->M : nullptr;
+    HIP_TRY(launch_modes_dense(dw, p->corr_d, p->R, a.f != nullptr, a.vgrid != nullptr, Rm,
+                               a.vz || a.dnz ? p->partial : nullptr, both ? dn.cp_w : nullptr, second, s));
+    if (a.vz || a.dnz)
+        HIP_TRY(launch_reduce_interp(dw, a.js, p->partial, G, a.vz ? a.vz : a.dnz, nullptr, nullptr, s, a.from));
+    if (both) HIP_TRY(launch_reduce_interp(dn, a.js, second, G, a.dnz, nullptr, nullptr, s));
+    if (a.vgrid) HIP_TRY(launch_dst_to_grid(p->dp, p->R, a.vgrid, 2.0 / p->N, a.mask_out, p->dstB, s));
+    if (a.f && !a.vgrid) {                                   // R still holds the modes of f
+        p->modes_number = p->modes_number + 1 ? p->modes_number + 1 : 1;
+        p->modes_of = p->modes_number;
+    }
+    return KFBI_OK;
+}
+
+// The Dirichlet solve in parts: ghat = g - (Y f)^+ at the samples (Sec. 2.1), then,
+// phi known, u = W phi + Y f with its trace; modes as in DenseArgs.
+kfbi_status dirichlet_prepare(kfbi_prob* p, const double* f, const double* f_gamma, const double* g, double* ghat) {
+    DenseArgs y;
+    y.js.fgam = f_gamma;
+    y.f = f;
+    y.mask = true;
+    y.vz = ghat;
+    y.from = g;
+    return dense_interface_solve(p, y);
+}
+
+kfbi_status dirichlet_finish(kfbi_prob* p, const double* phi, const double* f, const double* f_gamma, double* u_grid,
+                             double* u_gamma, unsigned modes) {
+    DenseArgs u;
+    u.js.phi = phi;
+    u.js.fgam = f_gamma;
+    u.f = f;
+    u.mask = true;
+    u.vgrid = u_grid;
+    u.mask_out = true;
+    u.vz = u_gamma;
+    u.modes = modes;
+    return dense_interface_solve(p, u);
 }
 
 // K_D phi or K_N phi (op) without the dense grid (correction, sparse fast
@@ -570,17 +641,30 @@ kfbi_status neumann_check(kfbi_prob* p, const NeumannIO& io) {
 
 // g^ = g_n - d_n (Y f)^+ into the GMRES right-hand side.
 kfbi_status neumann_prepare(kfbi_prob* p, const NeumannIO& io) {
-    JumpSrc jy{nullptr, nullptr, io.f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, true, jy, io.f_grid, true, nullptr, false, nullptr, p->tmpM)) return e;
-    HIP_TRY(launch_axpby(p->M, 1.0, io.g_n, -1.0, p->tmpM, p->gm.ghat, p->ctx->stream));
-    return KFBI_OK;
+    DenseArgs y;
+    y.normal_jump = true;
+    y.js.fgam = io.f_gamma;
+    y.f = io.f_grid;
+    y.mask = true;
+    y.dnz = p->gm.ghat;
+    y.from = io.g_n;
+    return dense_interface_solve(p, y);
 }
 
 // u = v_psi + Y f with its trace and normal derivative, and psi out.
 kfbi_status neumann_finish(kfbi_prob* p, const NeumannIO& io) {
-    JumpSrc jf{p->gm.phi, nullptr, io.f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, true, jf, io.f_grid, true, io.u_grid, true, io.u_gamma, io.dn_gamma))
-        return e;
+    DenseArgs u;
+    u.normal_jump = true;
+    u.js.phi = p->gm.phi;
+    u.js.fgam = io.f_gamma;
+    u.f = io.f_grid;
+    u.mask = true;
+    u.vgrid = io.u_grid;
+    u.mask_out = true;
+    u.vz = io.u_gamma;
+    u.dnz = io.dn_gamma;
+    u.modes = p->modes_of;
+    if (kfbi_status e = dense_interface_solve(p, u)) return e;
     HIP_TRY(hipMemcpyAsync(io.psi, p->gm.phi, p->M * sizeof(double), hipMemcpyDeviceToDevice, p->ctx->stream));
     return KFBI_OK;
 }
@@ -732,8 +816,9 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
                 break;
             }
         p->G = (p->n + p->Rm - 1) / p->Rm;
-        // the autotuner may halve Rm once: room for that many partial rows
-        p->Gcap = (p->n + std::max(1, p->Rm / 2) - 1) / std::max(1, p->Rm / 2);
+        // the autotuner may halve Rm once, and an interface solve may want two sets of
+        // partial rows: room for twice as many
+        p->Gcap = 2 * p->G;
     }
     p->dstB = dst_default_tile(n, cpx_bytes(p->precision), ctx->lds_max, n, ctx->num_cu);
     if (p->dstB == 0) {
@@ -917,6 +1002,14 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
             cc_pos[q] = il_pos[r];
         }
     }
+    std::vector<unsigned char> mask8((size_t)(n + 1) * (n / 8), 0);
+    for (int j = 1; j < n; ++j)
+        for (int b = 0; b < n / 8; ++b) {                     // eight nodes' bytes (0 or 1) to bits
+            unsigned long long w;
+            std::memcpy(&w, &P.inside[(size_t)j * (n + 1) + 8 * b + 1], 8);
+            mask8[(size_t)j * (n / 8) + b] = (unsigned char)(w * 0x0102040810204080ull >> 56);
+        }
+    if ((st = upload(p, &dp.mask8, mask8))) return fail(st);
     if ((st = upload(p, &dp.cc_arm, cc_arm)) || (st = upload(p, &dp.cc_d, cc_d)) || (st = upload(p, &dp.cc_s, cc_s)) ||
         (st = upload(p, &dp.cc_pos, cc_pos)) || (st = upload(p, &dp.cc_chunk, cc_chunk)))
         return fail(st);
@@ -935,7 +1028,8 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         return fail(st);
     for (int w = 0; w <= kModeWaves; ++w) dp.sub_offv[w] = sub_off[w];
     const int M = p->M, m = p->restart;
-    if ((st = dev_alloc(p, &p->corr, p->I)) || (st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
+    if ((st = dev_alloc(p, &p->corr, p->I)) || (st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) ||
+        (st = dev_alloc(p, &p->corr_d, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
         (st = dev_alloc(p, &p->R, (size_t)n * n)) || (st = dev_alloc(p, &p->A, (size_t)n * n)) ||
         (st = dev_alloc(p, &p->tmpM, M)) || (st = dev_alloc(p, &p->s2a, M)) || (st = dev_alloc(p, &p->s2b, M)) ||
         (st = dev_alloc(p, &p->d_flag, 2)) ||
@@ -963,6 +1057,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     if (p->refine >= 2 && (st = dev_alloc(p, &p->D, (size_t)n * n))) return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
+    HIP_TRY(hipMemset(p->corr_d, 0, sizeof(double) * (size_t)dp.T * 64));
     p->gm.m = m;
     p->gm.gc = gm_chunks(M, true);
     p->gm.gc64 = gm_chunks64(M);
@@ -1099,10 +1194,16 @@ kfbi_status kfbi_fast_solve(kfbi_prob* p, const double* rhs, double* v) {
     if (kfbi_status s = check_ptr(v, "v")) return s;
     HIP_TRY(hipSetDevice(p->ctx->device));
     hipStream_t s = p->ctx->stream;
+    p->modes_of = 0;
+    if (p->precision == KFBI_FP64) {
+        HIP_TRY(launch_dst_from_grid(p->dp, rhs, false, p->R, p->dstB, s));
+        HIP_TRY(launch_rows_solve(p->dp, p->R, s));
+        HIP_TRY(launch_dst_to_grid(p->dp, p->R, v, 2.0 / p->N, false, p->dstB, s));
+        return KFBI_OK;
+    }
     HIP_TRY(launch_fill_rhs(p->dp, rhs, false, p->R, s));
-    const double* V = nullptr;
-    if (kfbi_status e = grid_solve(p, &V)) return e;
-    HIP_TRY(launch_grid_out(p->dp, V, false, v, s));
+    if (kfbi_status e = grid_solve_f32(p)) return e;
+    HIP_TRY(launch_grid_out(p->dp, p->A, false, v, s));
     return KFBI_OK;
 }
 
@@ -1111,8 +1212,13 @@ kfbi_status kfbi_interface_solve(kfbi_prob* p, const double* phi, const double* 
     if (!p) return set_err(KFBI_ERR_ARG, "prob is NULL");
     if (!vgrid && !vz) return set_err(KFBI_ERR_ARG, "no output requested");
     HIP_TRY(hipSetDevice(p->ctx->device));
-    JumpSrc js{phi, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    return dense_interface_solve(p, false, js, ftilde, false, vgrid, false, vz);
+    DenseArgs a;
+    a.js.phi = phi;
+    a.js.fgam = f_gamma;
+    a.f = ftilde;
+    a.vgrid = vgrid;
+    a.vz = vz;
+    return dense_interface_solve(p, a);
 }
 
 kfbi_status kfbi_interface_solve_jumps(kfbi_prob* p, const double* jq, const double* jz, const double* ftilde,
@@ -1121,8 +1227,13 @@ kfbi_status kfbi_interface_solve_jumps(kfbi_prob* p, const double* jq, const dou
     if (kfbi_status s = check_ptr(jq, "jq")) return s;
     if (kfbi_status s = check_ptr(jz, "jz")) return s;
     HIP_TRY(hipSetDevice(p->ctx->device));
-    JumpSrc js{nullptr, nullptr, nullptr, nullptr, jq, jz};
-    return dense_interface_solve(p, false, js, ftilde, false, vgrid, false, vz);
+    DenseArgs a;
+    a.js.jq = jq;
+    a.js.jz = jz;
+    a.f = ftilde;
+    a.vgrid = vgrid;
+    a.vz = vz;
+    return dense_interface_solve(p, a);
 }
 
 kfbi_status kfbi_solve(kfbi_prob* p, const double* f_grid, const double* f_gamma, const double* g, double* u_grid,
@@ -1135,17 +1246,14 @@ kfbi_status kfbi_solve(kfbi_prob* p, const double* f_grid, const double* f_gamma
     hipStream_t s = p->ctx->stream;
     const int M = p->M;
     // g^ = g - (Y f)^+ (Sec. 2.1)
-    JumpSrc jy{nullptr, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, false, jy, f_grid, true, nullptr, false, p->tmpM)) return e;
     GmresBufs b = p->gm;
-    HIP_TRY(launch_axpby(M, 1.0, g, -1.0, p->tmpM, b.ghat, s));
+    if (kfbi_status e = dirichlet_prepare(p, f_grid, f_gamma, g, b.ghat)) return e;
     // GMRES (Alg. 5): every step is one K_D apply plus one orthogonalisation
     GmresState st{};
     if (kfbi_status e = run_gmres(p, kOpD, nullptr, phi, p->tol, p->max_iter, &st)) return e;
     if (st.converged == kGmNonfinite) return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in f, f_gamma, g or phi");
     // u = W phi + Y f
-    JumpSrc jf{b.phi, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, false, jf, f_grid, true, u_grid, true, u_gamma)) return e;
+    if (kfbi_status e = dirichlet_finish(p, b.phi, f_grid, f_gamma, u_grid, u_gamma, p->modes_of)) return e;
     HIP_TRY(hipMemcpyAsync(phi, b.phi, M * sizeof(double), hipMemcpyDeviceToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (iters) *iters = st.it;
@@ -1194,16 +1302,12 @@ kfbi_status kfbi_solve_method(kfbi_prob* p, int method, double relax, const doub
         if (kfbi_status s = check_ptr(ptr, name)) return s;
     HIP_TRY(hipSetDevice(p->ctx->device));
     hipStream_t s = p->ctx->stream;
-    const int M = p->M;
-    JumpSrc jy{nullptr, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, false, jy, f_grid, true, nullptr, false, p->tmpM)) return e;
-    HIP_TRY(launch_axpby(M, 1.0, g, -1.0, p->tmpM, p->tmpM, s));
+    if (kfbi_status e = dirichlet_prepare(p, f_grid, f_gamma, g, p->tmpM)) return e;
     IterState st{};
     if (kfbi_status e = run_iters(p, method == KFBI_BICGSTAB ? kBicg : kRich, p->tmpM, phi, relax, p->tol,
                                   p->max_iter, &st))
         return e;
-    JumpSrc jf{phi, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, false, jf, f_grid, true, u_grid, true, u_gamma)) return e;
+    if (kfbi_status e = dirichlet_finish(p, phi, f_grid, f_gamma, u_grid, u_gamma, p->modes_of)) return e;
     HIP_TRY(hipStreamSynchronize(s));
     if (iters) *iters = st.it;
     if (rel_res) *rel_res = st.relres;
@@ -1224,8 +1328,15 @@ kfbi_status kfbi_interface_solve_neumann(kfbi_prob* p, const double* psi, const 
     if (!p) return set_err(KFBI_ERR_ARG, "prob is NULL");
     if (!vgrid && !vz && !dnz) return set_err(KFBI_ERR_ARG, "no output requested");
     HIP_TRY(hipSetDevice(p->ctx->device));
-    JumpSrc js{psi, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    return dense_interface_solve(p, true, js, ftilde, false, vgrid, false, vz, dnz);
+    DenseArgs a;
+    a.normal_jump = true;
+    a.js.phi = psi;
+    a.js.fgam = f_gamma;
+    a.f = ftilde;
+    a.vgrid = vgrid;
+    a.vz = vz;
+    a.dnz = dnz;
+    return dense_interface_solve(p, a);
 }
 
 kfbi_status kfbi_gmres_neumann(kfbi_prob* p, const double* rhs, double* psi, double tol, int max_iter, int* iters,
@@ -1391,14 +1502,18 @@ kfbi_status kfbi_prob_autotune(kfbi_prob* p, int reps, kfbi_tiles* out) {
     p->tuned_apply_us = best;
     double bestg = 1e300;
     int bb = p->dstB;
-    const double* V = nullptr;
+    p->modes_of = 0;
     for (int B : {4, 8, 16}) {
         if (!tiles_valid(p, p->Rm, B)) continue;
         p->dstB = B;
         double us = 0;
         if (kfbi_status e = time_us(s, reps, &us, [&] {
                 HIP_TRY(launch_fill_rhs(p->dp, nullptr, false, p->R, s));
-                return grid_solve(p, &V);
+                if (p->precision != KFBI_FP64) return grid_solve_f32(p);
+                HIP_TRY(launch_dst_cols(p->dp, p->R, p->R, 1.0, false, p->dstB, s));
+                HIP_TRY(launch_rows_solve(p->dp, p->R, s));
+                HIP_TRY(launch_dst_cols(p->dp, p->R, p->R, 2.0 / p->N, false, p->dstB, s));
+                return KFBI_OK;
             })) {
             p->dstB = bb;
             return e;
@@ -1569,8 +1684,8 @@ kfbi_status kfbi_batch_estimate_bytes(int n, int m, int restart, size_t* bytes) 
     // plan: crossings and irregular nodes are O(perimeter / h); bound them by 8 n
     const size_t nq = 8 * (size_t)n, ni = 8 * (size_t)n;
     const size_t slots = ni + 64 * (size_t)(kSlots + 64);                  // interleaved table, padded
-    size_t b = nq * (sizeof(PointGeom) + 4) + (size_t)m * 256 + ni * 80 + slots * 12 +
-               (size_t)(n + 1) * (n + 1) + (size_t)n * (sizeof(ModeConst) + 16) + 4096;
+    size_t b = nq * (sizeof(PointGeom) + 4) + (size_t)m * 256 + ni * 80 + slots * 20 +
+               (size_t)(n + 1) * (n + 1) + (size_t)(n + 1) * (n / 8) + (size_t)n * (sizeof(ModeConst) + 16) + 4096;
     b += 2 * sizeof(double) * (size_t)n * n;                                  // dense-path grids
     b += sizeof(double) * ((size_t)(restart + 1) * (m + restart) + 16 * (size_t)m +
                            gm_part_size(restart, gm_chunks(m, true), gm_chunks64(m)) + 2 * (restart + 2));   // GMRES
@@ -1650,10 +1765,8 @@ kfbi_status kfbi_batch_admit(kfbi_batch* B, kfbi_prob* p, const double* f_grid, 
         if (kfbi_status e = dev_alloc(p, &p->partial_b, (size_t)p->M * p->Gs)) return e;
     }
     // g^ = g - (Y f)^+ and a fresh GMRES state (phi_0 = 0)
-    JumpSrc jy{nullptr, nullptr, f_gamma, nullptr, nullptr, nullptr};
-    if (kfbi_status e = dense_interface_solve(p, false, jy, f_grid, true, nullptr, false, p->tmpM)) return e;
     GmresBufs b = p->gm;
-    HIP_TRY(launch_axpby(p->M, 1.0, g, -1.0, p->tmpM, b.ghat, s));
+    if (kfbi_status e = dirichlet_prepare(p, f_grid, f_gamma, g, b.ghat)) return e;
     // the state and the first Arnoldi input (phi_0 = 0: the residual is g^) with its corrections
     HIP_TRY(launch_gmres_start(&p->dp, p->dp.taps, p->M, b, nullptr, nullptr, p->tol, p->max_iter, p->reorth, nullptr,
                                p->corr_il, p->host.next_epoch(), s));
@@ -1665,6 +1778,7 @@ kfbi_status kfbi_batch_admit(kfbi_batch* B, kfbi_prob* p, const double* f_grid, 
     S.partial = p->partial_b;
     S.Gs = p->Gs;
     S.pad = 0;
+    p->b_modes = p->modes_of;
     p->b_fgrid = f_grid;
     p->b_fgam = f_gamma;
     B->slot[free_slot] = p;
@@ -1719,8 +1833,7 @@ kfbi_status kfbi_batch_finish(kfbi_batch* B, int slot, double* u_grid, double* u
     // with nothing written
     const bool bad = p->st_host.converged == kGmNonfinite;
     if (!bad) {
-        JumpSrc jf{p->gm.phi, nullptr, p->b_fgam, nullptr, nullptr, nullptr};
-        if (kfbi_status e = dense_interface_solve(p, false, jf, p->b_fgrid, true, u_grid, true, u_gamma)) return e;
+        if (kfbi_status e = dirichlet_finish(p, p->gm.phi, p->b_fgrid, p->b_fgam, u_grid, u_gamma, p->b_modes)) return e;
         HIP_TRY(hipMemcpyAsync(phi, p->gm.phi, p->M * sizeof(double), hipMemcpyDeviceToDevice, s));
     }
     B->used -= B->slot_bytes[slot];

@@ -22,7 +22,7 @@ template <int C>
 __device__ __forceinline__ void modes_item(const DevPlan& p, const double* corr, int row, const ModesLds& L,
                                            double* part) {
     constexpr int R = batch_modes_per_group(64 * C);
-    modes_round<C, R, false>(p, corr, row, L, [&](int cp, double s) { part[(size_t)row * p.M + cp] = s; });
+    modes_round<C, R, false, false>(p, corr, row, L, [&](int, int cp, double s) { part[(size_t)row * p.M + cp] = s; });
 }
 
 __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __restrict__ slots, BatchWork w) {

@@ -363,12 +363,13 @@ __device__ inline double correction_at(const DevPlan& p, const JumpSrc& js, int 
 // workgroup g's sums for all M samples) are split over wavefronts 0..14, added
 // in a fixed order; wavefront 15 makes the jump terms of the stencil nodes
 // outside Omega, and wavefront 0 adds them and writes out[cp] (unless out is null;
-// also to red[lane], for the caller).
+// also to red[lane], for the caller); with `from`, out[cp] = from[cp] - that.
 // red: 16 x 64 doubles of LDS.  Returns false, having written nothing, while
 // *skip is nonzero (skip may be null); the flag's latency overlaps the loads.
 __device__ inline bool reduce_samples64(const DevPlan& p, const JumpSrc& js, const double* __restrict__ partial,
                                         int G, int cp0, double* __restrict__ out, double* red,
-                                        const int* __restrict__ skip = nullptr) {
+                                        const int* __restrict__ skip = nullptr,
+                                        const double* __restrict__ from = nullptr) {
     __shared__ double outside[64];
     constexpr int kOutsideWave = 15;                    // makes the jump terms only
     constexpr int kRowWaves = 15, kRows = 18;           // rows wave + 15 k, k < 18, requested at once
@@ -404,7 +405,7 @@ __device__ inline bool reduce_samples64(const DevPlan& p, const JumpSrc& js, con
 #pragma unroll
         for (int w = 0; w < 16; ++w) t += red[w * 64 + lane];
         const double v = t * (2.0 / p.N) + outside[lane];
-        if (out) out[cp] = v;
+        if (out) out[cp] = from ? from[cp] - v : v;
         red[lane] = v;                                  // left in LDS for the caller
     }
     __syncthreads();
@@ -520,7 +521,7 @@ __device__ __forceinline__ void modes_load_table(double* sq, const double* __res
 //     wavefront's registers beside sixteen wavefronts' worth of the rest).
 //  3. The weighted six-point gather at every sample: the row sines by the same
 //     recurrence, again one set per pair (the rows j0 and j0 +- 1 have opposite
-//     signs in the mirrored mode).  emit(cp, s) gets the sum s over the block's
+//     signs in the mirrored mode).  emit(0, cp, s) gets the sum s over the block's
 //     modes, for cp = tid, tid + 64 kModeWaves, ...
 // What bounds it: a compute unit's intake of the node and sample tables from L2
 // (64 bytes a clock, 12 bytes a node) until the sums are done, then LDS and issue;
@@ -535,9 +536,19 @@ __device__ __forceinline__ void modes_load_table(double* sq, const double* __res
 // EARLY: the wavefront's mode constants and the thread's first stencil are
 // requested ahead of their phases (off where the registers are short: the
 // batched kernel holds every grid size's code).
-template <int C, int R, bool EARLY, class Emit>
+// dense (DENSE): the rows of the modes' transformed right-hand side on the whole
+// grid, added to the sums (null: none); with `store` the solutions are written back
+// there; emit(1, cp, s) gets the sums with the weights w2 (null: not wanted), and
+// with gather = false phase 3 is left out.
+struct ModesDense {
+    double* rows;
+    bool load, store, gather;
+    const double* w2;
+};
+template <int C, int R, bool EARLY, bool DENSE, class Emit>
 __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __restrict__ corr, int g,
-                                            const ModesLds& L, Emit emit, const int* __restrict__ skip = nullptr) {
+                                            const ModesLds& L, Emit emit, const int* __restrict__ skip = nullptr,
+                                            const ModesDense& dn = ModesDense{}) {
     constexpr int N = 64 * C, XS = modes_stride<C>(), PS = modes_pair_len<C>();
     constexpr int CH = modes_chunk(N), S = C / CH;
     static_assert(R * S <= kModeWaves, "S wavefronts for each mode");
@@ -661,7 +672,7 @@ __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __re
     // the start these would hold up the nodes
     int pre_pk = 0;
     double pre_w[6] = {};
-    if (EARLY && tid < M) {
+    if (EARLY && !DENSE && tid < M) {
         pre_pk = p.cp_pack[tid];
         for (int k = 0; k < 6; ++k) pre_w[k] = p.cp_w[(size_t)k * M + tid];
     }
@@ -676,6 +687,28 @@ __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __re
         x[sp_at] = v;
     }
     __syncthreads();
+    // row l of the dense arrays: element (l - 1) N + i - 1, node i at i + (i - 1) / CH here
+    auto place = [](int i) { return i + (i - 1) / CH; };
+    auto row_of = [&](int l) { return dn.rows + (size_t)(l - 1) * N; };
+    if constexpr (DENSE) {
+        // the sums become the two modes' right-hand sides in place, with the dense rows
+#pragma unroll
+        for (int r = 0; r < H; ++r) {
+            const int l = l0 + r;
+            const bool self = R < 2 || l == N / 2;
+            const double* da = row_of(l);
+            const double* db = row_of(self ? l : N - l);
+            double* xe = L.xs + r * PS;
+            for (int i = 1 + tid; i < N; i += NT) {
+                const double ga = dn.load ? da[i - 1] : 0.0, gb = dn.load ? db[i - 1] : 0.0;
+                const int at = place(i);
+                const double e = xe[at], o = xe[XS + at];
+                xe[at] = e + o + ga;
+                xe[XS + at] = self ? 0.0 : o - e + gb;
+            }
+        }
+        __syncthreads();
+    }
     {
         // the mode's right-hand side from the pair's sums over even and odd rows
         // (N/2 is its own mirror: solved once, its mirror is zero)
@@ -685,14 +718,20 @@ __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __re
         if (solves) {
             const double* xe = L.xs + (mirror ? mode - H : mode) * PS + at;
             const double* xo = xe + XS;
-            const double so = mirror && lw == N / 2 ? 0.0 : p.h2, se = mirror ? -so : so;
+            if constexpr (DENSE) {
+                const double* x = mirror ? xo : xe;
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                e[c] = fma(so, xo[c], se * xe[c]);
-                if (CH > 16 && c % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // not all 2 CH reads in registers at once
+                for (int c = 0; c < CH; ++c) e[c] = p.h2 * x[c];
+            } else {
+                const double so = mirror && lw == N / 2 ? 0.0 : p.h2, se = mirror ? -so : so;
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    e[c] = fma(so, xo[c], se * xe[c]);
+                    if (CH > 16 && c % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // not all 2 CH reads in registers at once
+                }
             }
         }
-        __syncthreads();                                // both of a pair have read its sums
+        if (!DENSE) __syncthreads();                    // both of a pair have read its sums
         // The steps of mode_solve, with the rank-one fix taken into the forward
         // recurrence: y[1] zeta is what an initial value
         //   w[0] = r / (1 - r^(2N)) sum_k e[k] (r^k - r^(2N-k))
@@ -776,7 +815,25 @@ __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __re
         }
     }
     __syncthreads();
-    auto gather = [&](int cp, int pk1, const double (&w6)[6]) {
+    if constexpr (DENSE) {
+        if (dn.store) {
+#pragma unroll
+            for (int r = 0; r < H; ++r) {
+                const int l = l0 + r;
+                const bool self = R < 2 || l == N / 2;
+                double* da = row_of(l);
+                double* db = row_of(N - l);
+                const double* xe = L.xs + r * PS;
+                for (int i = 1 + tid; i <= N; i += NT) {   // i = N: the pad
+                    const int at = place(i);
+                    da[i - 1] = i < N ? xe[at] : 0.0;
+                    if (!self) db[i - 1] = i < N ? xe[XS + at] : 0.0;
+                }
+            }
+        }
+        if (!dn.gather) return;
+    }
+    auto gather = [&](int set, int cp, int pk1, const double (&w6)[6]) {
         const int i0 = pk1 & 0x1fff, j0 = (pk1 >> 13) & 0x1fff;
         const bool sxp = (pk1 & (1 << 26)) != 0, syp = (pk1 & (1 << 27)) != 0;
         const double w0 = w6[0], wE = w6[1], wW = w6[2], wN = w6[3], wS = w6[4];
@@ -840,13 +897,17 @@ __device__ __forceinline__ void modes_round(const DevPlan& p, const double* __re
             }
             s += s0 * (w0 * xc + wE * xe + wW * xw) + sp * (wN * xcd + wDp * xdd) + sm * (wS * xcd + wDm * xdd);
         }
-        emit(cp, s);
+        emit(set, cp, s);
     };
-    if (EARLY && tid < M) gather(tid, pre_pk, pre_w);
-    for (int cp = EARLY ? tid + NT : tid; cp < M; cp += NT) {
+    if (EARLY && !DENSE && tid < M) gather(0, tid, pre_pk, pre_w);
+    for (int cp = EARLY && !DENSE ? tid + NT : tid; cp < M; cp += NT) {
         double w6[6];
         for (int k = 0; k < 6; ++k) w6[k] = p.cp_w[(size_t)k * M + cp];
-        gather(cp, p.cp_pack[cp], w6);
+        gather(0, cp, p.cp_pack[cp], w6);
+        if (DENSE && dn.w2) {
+            for (int k = 0; k < 6; ++k) w6[k] = dn.w2[(size_t)k * M + cp];
+            gather(1, cp, p.cp_pack[cp], w6);
+        }
     }
     __syncthreads();
 }

@@ -116,6 +116,31 @@ struct pair_of<float> {
     using type = float2;
 };
 
+// Where a transform reads or writes: the padded N x N layout, or directly the user's
+// (N+1) x (N+1) grid (FP64): node (i, j), i = column + 1, j = row + 1, at j (N+1) + i,
+// a pair of columns 8-byte aligned there.  mask8 (null: every node) holds a bit per
+// node, byte j (N/8) + column / 8, zero outside Omega and on the box: masked nodes
+// are read and written as zero.  So the right-hand side needs no copy into the padded
+// layout and the solution none out of it (two passes over the grid each, 13 + 13 us
+// at 2048^2 beside transforms of 23).
+enum DstIo { kPadded = 0, kFromGrid = 1, kToGrid = 2 };
+struct alignas(8) GridPair {
+    double x, y;
+};
+__device__ __forceinline__ unsigned mask_bits(const unsigned char* mask8, int N, int j, int col) {
+    return mask8 ? mask8[(size_t)j * (N >> 3) + (col >> 3)] >> (col & 7) : col + 2 < N ? 3u : 1u;
+}
+// columns col, col + 1 of row j - 1 from the grid f (the second may be the box's, i = N: zero)
+__device__ __forceinline__ double2 grid_pair(const double* f, const unsigned char* mask8, int N, int j, int col) {
+    const GridPair v = *reinterpret_cast<const GridPair*>(f + (size_t)j * (N + 1) + col + 1);
+    const unsigned m = mask_bits(mask8, N, j, col);
+    return make_double2((m & 1) ? v.x : 0.0, (m & 2) ? v.y : 0.0);
+}
+__device__ __forceinline__ void grid_put(double* u, const unsigned char* mask8, int N, int j, int col, double x, double y) {
+    const unsigned m = j < N ? mask_bits(mask8, N, j, col) : 0u;
+    *reinterpret_cast<GridPair*>(u + (size_t)j * (N + 1) + col + 1) = GridPair{(m & 1) ? x : 0.0, (m & 2) ? y : 0.0};
+}
+
 constexpr int kDstThreads = 1024;   // 16 wavefronts per workgroup: the LDS tile limits a CU to one
 constexpr int kLoadBatch = 8;       // vector loads in flight per thread
 
@@ -215,10 +240,11 @@ __device__ __forceinline__ void radix2_step(const cpx<double>* sq, int tw, int N
 
 // Rows are ld elements apart; blockIdx.y selects a slice of `slice` elements
 // (several independent N-row arrays, as the planes of a 3D grid).
-template <class T, class Tin, class Tout, int B>
+template <class T, class Tin, class Tout, int B, int IO>
 __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, const double* __restrict__ sinq,
                                                           const Tin* in, Tout* out, double alpha, int accumulate,
-                                                          int ld, size_t slice, const int* __restrict__ skip) {
+                                                          int ld, size_t slice, const int* __restrict__ skip,
+                                                          const unsigned char* __restrict__ mask8) {
     if (skip && *skip) return;
     in += blockIdx.y * slice;
     out += blockIdx.y * slice;
@@ -273,8 +299,13 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
             int lo;
             const int i = place(idx >> LP, lo);
             const int j = bitrev(i, log2N);
-            va[u] = *reinterpret_cast<const Vin*>(in + (size_t)(j - 1) * ld + col0 + 2 * p);
-            vb[u] = *reinterpret_cast<const Vin*>(in + (size_t)(N - j - 1) * ld + col0 + 2 * p);
+            if constexpr (IO == kFromGrid) {
+                va[u] = grid_pair(in, mask8, N, j, col0 + 2 * p);
+                vb[u] = grid_pair(in, mask8, N, N - j, col0 + 2 * p);
+            } else {
+                va[u] = *reinterpret_cast<const Vin*>(in + (size_t)(j - 1) * ld + col0 + 2 * p);
+                vb[u] = *reinterpret_cast<const Vin*>(in + (size_t)(N - j - 1) * ld + col0 + 2 * p);
+            }
             sv[u] = sinq[min(j, N - j)];
         }
 #pragma unroll
@@ -540,11 +571,20 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
         for (int u = 0; u < kLoadBatch; ++u) {
             const int idx = base + u * NTH + tid;
             const int r = idx >> LP, p = idx & (P - 1);
-            Vout o;
-            o.x = (Tout)vx[u];
-            o.y = (Tout)vy[u];
-            if (idx < N * P) *reinterpret_cast<Vout*>(out + (size_t)r * ld + col0 + 2 * p) = o;
+            if constexpr (IO == kToGrid) {
+                if (idx < N * P) grid_put(out, mask8, N, r + 1, col0 + 2 * p, vx[u], vy[u]);
+            } else {
+                Vout o;
+                o.x = (Tout)vx[u];
+                o.y = (Tout)vy[u];
+                if (idx < N * P) *reinterpret_cast<Vout*>(out + (size_t)r * ld + col0 + 2 * p) = o;
+            }
         }
+    }
+    if constexpr (IO == kToGrid) {                           // the box's row 0 and column 0
+        if (tid < B) out[col0 + 1 + tid] = 0.0;
+        if (col0 == 0)
+            for (int j = tid; j <= N; j += NTH) out[(size_t)j * (N + 1)] = 0.0;
     }
 }
 
@@ -592,10 +632,11 @@ __device__ __forceinline__ double lane_xor(double v, int s, int lane) {
 // quarter-period twiddle table, no barrier after it.
 constexpr int kShortThreads = 256;   // four pairs (eight columns) per workgroup
 
-template <int NP>
+template <int NP, int IO>
 __global__ __launch_bounds__(kShortThreads) void k_dst_short(const double* __restrict__ sinq, const double* in,
                                                              double* out, double alpha, int accumulate, int ld,
-                                                             size_t slice, const int* __restrict__ skip) {
+                                                             size_t slice, const int* __restrict__ skip,
+                                                             const unsigned char* __restrict__ mask8) {
     constexpr int N = 64 * NP;
     constexpr int LOG2N = NP == 1 ? 6 : NP == 2 ? 7 : 8;
     constexpr int KT = NP >= 2 ? NP / 2 : 1;                 // values of k per lane
@@ -624,8 +665,13 @@ __global__ __launch_bounds__(kShortThreads) void k_dst_short(const double* __res
             const int j = L + 64 * r;
             xa[r] = xb[r] = make_double2(0.0, 0.0);
             if (j >= 1) {
-                xa[r] = *reinterpret_cast<const double2*>(in + (size_t)(j - 1) * ld + col);
-                xb[r] = *reinterpret_cast<const double2*>(in + (size_t)(N - j - 1) * ld + col);
+                if constexpr (IO == kFromGrid) {
+                    xa[r] = grid_pair(in, mask8, N, j, col);
+                    xb[r] = grid_pair(in, mask8, N, N - j, col);
+                } else {
+                    xa[r] = *reinterpret_cast<const double2*>(in + (size_t)(j - 1) * ld + col);
+                    xb[r] = *reinterpret_cast<const double2*>(in + (size_t)(N - j - 1) * ld + col);
+                }
             }
             sj[r] = sinq[min(j, N - j)];
         }
@@ -704,6 +750,10 @@ __global__ __launch_bounds__(kShortThreads) void k_dst_short(const double* __res
     }
     // write: X_{2k+1} to row 2k, X_{2k} = -I_k to row 2k-1, the pad row N-1 zero
     auto put = [&](int row, double a, double b) {
+        if constexpr (IO == kToGrid) {
+            grid_put(out, mask8, N, row + 1, col, alpha * a, alpha * b);
+            return;
+        }
         double2* o = reinterpret_cast<double2*>(out + (size_t)row * ld + col);
         double2 val = make_double2(alpha * a, alpha * b);
         if (accumulate) {
@@ -722,6 +772,11 @@ __global__ __launch_bounds__(kShortThreads) void k_dst_short(const double* __res
             else put(N - 1, 0.0, 0.0);
         }
     }
+    if constexpr (IO == kToGrid) {                           // the box's row 0 and column 0
+        if (L < 2) out[col + 1 + L] = 0.0;
+        if (col == 0)
+            for (int j = L; j <= N; j += 64) out[(size_t)j * (N + 1)] = 0.0;
+    }
 }
 
 // The transform geometry of one launch: N-row arrays with rows ld elements
@@ -732,52 +787,53 @@ struct Lines {
     int ld, slices;
     size_t slice;
     const int* skip;
+    const unsigned char* mask8;
 };
 
-template <class T, class Tin, class Tout, int B>
+template <class T, class Tin, class Tout, int B, int IO>
 hipError_t dst_launch(const Lines& g, const Tin* in, Tout* out, double alpha, bool acc, hipStream_t s) {
     const size_t lds = dst_lds_bytes(g.N, B, sizeof(cpx<T>));
-    if (hipError_t e = hipFuncSetAttribute((const void*)k_dst_cols<T, Tin, Tout, B>,
+    if (hipError_t e = hipFuncSetAttribute((const void*)k_dst_cols<T, Tin, Tout, B, IO>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))
         return e;
-    if (hipError_t e_ = klaunch(&k_dst_cols<T, Tin, Tout, B>, dim3(g.ld / B, g.slices), dim3(kDstThreads), lds, s,
-                                g.N, g.log2N, g.sinq, in, out, alpha, acc ? 1 : 0, g.ld, g.slice, g.skip))
+    if (hipError_t e_ = klaunch(&k_dst_cols<T, Tin, Tout, B, IO>, dim3(g.ld / B, g.slices), dim3(kDstThreads), lds, s,
+                                g.N, g.log2N, g.sinq, in, out, alpha, acc ? 1 : 0, g.ld, g.slice, g.skip, g.mask8))
         return e_;
     return hipGetLastError();
 }
 
-template <int NP>
+template <int NP, int IO>
 hipError_t short_launch(const Lines& g, const double* in, double* out, double alpha, bool acc, hipStream_t s) {
     constexpr int cols = 2 * (kShortThreads / 64);
-    if (hipError_t e_ = klaunch(&k_dst_short<NP>, dim3(g.ld / cols, g.slices), dim3(kShortThreads), 0, s, g.sinq,
-                                in, out, alpha, acc ? 1 : 0, g.ld, g.slice, g.skip))
+    if (hipError_t e_ = klaunch(&k_dst_short<NP, IO>, dim3(g.ld / cols, g.slices), dim3(kShortThreads), 0, s, g.sinq,
+                                in, out, alpha, acc ? 1 : 0, g.ld, g.slice, g.skip, g.mask8))
         return e_;
     return hipGetLastError();
 }
 
-template <class T, class Tin, class Tout>
+template <class T, class Tin, class Tout, int IO = kPadded>
 hipError_t dst_dispatch(const Lines& g, const Tin* in, Tout* out, double alpha, bool acc, int B, hipStream_t s) {
     // FP64 columns of 64 rows: one wavefront per column pair (4.6 against 7.2
     // us for the 64^3 grid's transform along z; at 128 and 256 rows the tiled
     // kernel is the faster one: 12.0 against 15.5 us, 75 against 93 us)
     if constexpr (sizeof(T) == 8 && sizeof(Tin) == 8 && sizeof(Tout) == 8) {
-        if (g.ld % 8 == 0 && g.N == 64) return short_launch<1>(g, in, out, alpha, acc, s);
+        if (g.ld % 8 == 0 && g.N == 64) return short_launch<1, IO>(g, in, out, alpha, acc, s);
     }
     if (!dst_tile_ok(g.N, B, sizeof(cpx<T>), ~(size_t)0) || g.ld % B != 0) return hipErrorInvalidValue;
     switch (B) {
-        case 4: return dst_launch<T, Tin, Tout, 4>(g, in, out, alpha, acc, s);
-        case 8: return dst_launch<T, Tin, Tout, 8>(g, in, out, alpha, acc, s);
-        case 16: return dst_launch<T, Tin, Tout, 16>(g, in, out, alpha, acc, s);
+        case 4: return dst_launch<T, Tin, Tout, 4, IO>(g, in, out, alpha, acc, s);
+        case 8: return dst_launch<T, Tin, Tout, 8, IO>(g, in, out, alpha, acc, s);
+        case 16: return dst_launch<T, Tin, Tout, 16, IO>(g, in, out, alpha, acc, s);
         default:
             if constexpr (sizeof(T) == 8) {                  // wide tiles: 16-byte pairs only
-                if (B == 32) return dst_launch<T, Tin, Tout, 32>(g, in, out, alpha, acc, s);
-                return dst_launch<T, Tin, Tout, 64>(g, in, out, alpha, acc, s);
+                if (B == 32) return dst_launch<T, Tin, Tout, 32, IO>(g, in, out, alpha, acc, s);
+                return dst_launch<T, Tin, Tout, 64, IO>(g, in, out, alpha, acc, s);
             }
             return hipErrorInvalidValue;
     }
 }
 
-Lines grid2(const DevPlan& p) { return Lines{p.N, p.log2N, p.sinq, p.N, 1, 0, nullptr}; }
+Lines grid2(const DevPlan& p) { return Lines{p.N, p.log2N, p.sinq, p.N, 1, 0, nullptr, nullptr}; }
 
 }  // namespace
 
@@ -815,6 +871,19 @@ hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, doub
     return dst_dispatch<double>(grid2(p), in, out, alpha, acc, B, s);
 }
 
+hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, double* out, int B, hipStream_t s) {
+    Lines g = grid2(p);
+    g.mask8 = mask ? p.mask8 : nullptr;
+    return dst_dispatch<double, double, double, kFromGrid>(g, f, out, 1.0, false, B, s);
+}
+
+hipError_t launch_dst_to_grid(const DevPlan& p, const double* in, double* u, double alpha, bool mask, int B,
+                              hipStream_t s) {
+    Lines g = grid2(p);
+    g.mask8 = mask ? p.mask8 : nullptr;
+    return dst_dispatch<double, double, double, kToGrid>(g, in, u, alpha, false, B, s);
+}
+
 hipError_t launch_dst_cols_f32(const DevPlan& p, const double* in, float* out, double alpha, int B, hipStream_t s) {
     return dst_dispatch<float>(grid2(p), in, out, alpha, false, B, s);
 }
@@ -826,7 +895,7 @@ hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* o
 
 hipError_t launch_dst_lines(int N, int log2N, const double* sinq, double* a, double alpha, int B, int ld, int slices,
                             size_t slice, const int* skip, hipStream_t s) {
-    return dst_dispatch<double>(Lines{N, log2N, sinq, ld, slices, slice, skip}, a, a, alpha, false, B, s);
+    return dst_dispatch<double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr}, a, a, alpha, false, B, s);
 }
 
 }  // namespace kfbi

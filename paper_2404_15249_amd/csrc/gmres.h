@@ -583,13 +583,17 @@ __device__ __forceinline__ void gm_corr_geometry(const DevPlan& p, GmCorr& k) {
         }
     }
 }
-// xw: the window's values (place tid written by thread tid before a barrier here)
+// xw: the window's values (place tid written by thread tid before a barrier here);
+// fw (null: [F] = 0), f2w: the same of f on Gamma
 __device__ inline void gm_corr_finish(const DevPlan& p, const GmCorr& k, const double* xw, double* sw,
-                                      double* __restrict__ corr_il) {
+                                      double* __restrict__ corr_il, const double* fw = nullptr, double* f2w = nullptr) {
     const int M = p.M, tid = threadIdx.x;
     const int4 ch = k.ch;
     __syncthreads();
-    if (tid >= kGmHalo && tid < ch.w - kGmHalo) sw[tid] = gm_spline_s2(p.taps, xw, tid);
+    if (tid >= kGmHalo && tid < ch.w - kGmHalo) {
+        sw[tid] = gm_spline_s2(p.taps, xw, tid);
+        if (fw) f2w[tid] = gm_spline_s2(p.taps, fw, tid);
+    }
     __syncthreads();
     if (tid >= ch.y - ch.x) return;
     const int ks[4] = {k.arm.x, k.arm.y, k.arm.z, k.arm.w};
@@ -613,11 +617,13 @@ __device__ inline void gm_corr_finish(const DevPlan& p, const GmCorr& k, const d
         const double P = w * y0 + u * y1 + (w * w * w - w) * s0 * sixth + (u * u * u - u) * s1 * sixth;
         const double P1 = (y1 - y0) - (3.0 * w * w - 1.0) * s0 * sixth + (3.0 * u * u - 1.0) * s1 * sixth;
         const double P2 = w * s0 + u * s1;
-        // the jumps, as jumps_at computes them with [F] = 0
+        const double F = fw ? w * fw[l] + u * fw[l + 1] + (w * w * w - w) * f2w[l] * sixth + (u * u * u - u) * f2w[l + 1] * sixth
+                            : 0.0;
+        // the jumps, as jumps_at computes them
         const double Ps = P1 * g.a1;
         double jv, gv, hh;
         if (p.normal_jump) {
-            const double vtt = g.curv * P, vtn = Ps, vnn = 0.0 - vtt;
+            const double vtt = g.curv * P, vtn = Ps, vnn = F - vtt;
             jv = 0.0;
             if (k.axs[a]) {
                 gv = P * g.ny;
@@ -628,7 +634,7 @@ __device__ inline void gm_corr_finish(const DevPlan& p, const GmCorr& k, const d
             }
         } else {
             const double Pss = P2 * g.a2 - P1 * g.a3;
-            const double vtt = Pss, vtn = -g.curv * Ps, vnn = 0.0 + p.kappa * P - vtt;
+            const double vtt = Pss, vtn = -g.curv * Ps, vnn = F + p.kappa * P - vtt;
             jv = P;
             if (k.axs[a]) {
                 gv = Ps * g.ty;
@@ -697,6 +703,34 @@ __device__ inline void gm_density(const DevPlan& p, const double* __restrict__ y
     }
     __syncthreads();
     if (tid >= kGmHalo && tid < kGmHalo + kGmOwnSpline && at < M) s2[e] = gm_spline_s2(p.taps, win, tid);
+}
+
+// gm_density for an interface solve: the density y and f on Gamma (either null: zero).
+__device__ inline void gm_density_f(const DevPlan& p, const double* __restrict__ y, const double* __restrict__ f,
+                                    double* __restrict__ s2, double* __restrict__ f2, double* __restrict__ corr_il, int gc) {
+    __shared__ double win[kGmChunk], sw[kGmChunk], fw[kGmChunk], f2w[kGmChunk];
+    const int tid = threadIdx.x, c = blockIdx.x, M = p.M;
+    if (c >= gc) {
+        GmCorr k = gm_corr_loads(p, c - gc);
+        if (tid < k.ch.w) {
+            const int e = (k.ch.z + tid) % M;
+            win[tid] = y ? y[e] : 0.0;
+            fw[tid] = f ? f[e] : 0.0;
+        }
+        gm_corr_geometry(p, k);
+        gm_corr_finish(p, k, win, sw, corr_il, fw, f2w);
+        return;
+    }
+    const int at = c * kGmOwnSpline - kGmHalo + tid;
+    int e = at % M;
+    if (e < 0) e += M;
+    win[tid] = y ? y[e] : 0.0;
+    fw[tid] = f ? f[e] : 0.0;
+    __syncthreads();
+    if (tid >= kGmHalo && tid < kGmHalo + kGmOwnSpline && at < M) {
+        if (y) s2[e] = gm_spline_s2(p.taps, win, tid);
+        if (f) f2[e] = gm_spline_s2(p.taps, fw, tid);
+    }
 }
 
 // ---------------------------------------------------------------- start of a run

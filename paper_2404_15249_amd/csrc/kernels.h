@@ -78,6 +78,7 @@ struct DevPlan {
                               // d_n v+ for a plan that extracts the normal derivative)
     const unsigned char* cp_out;   // 6 M
     const unsigned char* inside;   // (n+1)^2
+    const unsigned char* mask8;    // (n+1) n / 8: the same for interior nodes as bits, byte j (n/8) + (i-1)/8, bit (i-1)%8
     const double* sinq;       // N/2 + 1: sin(pi k / N)
     const ModeConst* modes;   // N (index l = 1..N-1 used)
     const double* taps;       // 2 K + 3 spline filter taps
@@ -226,11 +227,22 @@ struct DensityCheck {
 // layout; with check (may be null) also the check.
 hipError_t launch_density(const DevPlan& p, const double* y, double* s2, double* corr_il, const int* skip,
                           const DensityCheck* check, hipStream_t s);
+// The same for an interface solve (no check): the density y and f on Gamma (either
+// null: zero), their spline second derivatives into s2 and f2.
+hipError_t launch_density_f(const DevPlan& p, const double* y, const double* f, double* s2, double* f2, double* corr_il,
+                            hipStream_t s);
+// The row solves of an interface solve (k_modes_dense): rows, the transformed
+// right-hand side on the whole grid (added to the corrections' sums when `load`),
+// becomes the transformed solution when `store`; with partial (may be null) the
+// samples' partial sums as launch_modes, with w2 also those with the weights w2.
+hipError_t launch_modes_dense(const DevPlan& p, const double* corr, double* rows, bool load, bool store, int R,
+                              double* partial, const double* w2, double* partial2, hipStream_t s);
 hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const int* skip, hipStream_t s);
 // with gm non-null (a GMRES step) the output goes to gm->w, the launch is skipped
-// once GMRES is done, and it also makes its part of the GMRES step (gmres.h)
+// once GMRES is done, and it also makes its part of the GMRES step (gmres.h); with
+// `from` (gm null) out = from - the result
 hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* partial, int G, double* out,
-                                const int* skip, const GmresBufs* gm, hipStream_t s);
+                                const int* skip, const GmresBufs* gm, hipStream_t s, const double* from = nullptr);
 hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* R, double* out, hipStream_t s);
 hipError_t launch_fill_rhs(const DevPlan& p, const double* f, bool mask, double* R, hipStream_t s);
 // column sine transforms (dst.hip): FP64, and FP32 arithmetic reading an FP64
@@ -239,6 +251,12 @@ hipError_t launch_fill_rhs(const DevPlan& p, const double* f, bool mask, double*
 // B: columns per workgroup (4, 8 or 16; 32 or 64 with FP64 pairs; see dst_tile_ok)
 hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, bool acc, int B,
                            hipStream_t s);
+// The same (FP64, alpha = 1) reading the user's grid f, zero outside Omega with mask;
+// and writing the user's grid u (the box's rows and columns zero), zero outside Omega
+// with mask.
+hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, double* out, int B, hipStream_t s);
+hipError_t launch_dst_to_grid(const DevPlan& p, const double* in, double* u, double alpha, bool mask, int B,
+                              hipStream_t s);
 hipError_t launch_dst_cols_f32(const DevPlan& p, const double* in, float* out, double alpha, int B, hipStream_t s);
 hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, bool acc, int B,
                                     hipStream_t s);

@@ -58,7 +58,25 @@ __global__ __launch_bounds__(kModeWaves * 64) void k_modes(DevPlan p, const doub
     extern __shared__ double smem[];
     const ModesLds L = modes_lds<C>(smem);
     double* row = partial + (size_t)blockIdx.x * p.M;
-    modes_round<C, R, true>(p, corr, blockIdx.x, L, [&](int cp, double v) { row[cp] = v; }, skip);
+    modes_round<C, R, true, false>(p, corr, blockIdx.x, L, [&](int, int cp, double v) { row[cp] = v; }, skip);
+}
+
+// The same with the whole grid's transformed right-hand side (see ModesDense): the
+// row solves of an interface solve, its corrections and its samples in one launch.
+// What bounds it is what bounds k_modes, then the grid's rows (read once, written
+// once): 15 us at 2048^2 where only the samples are wanted and 19 with the rows
+// stored, against 13.4 (the row solves alone) + 5.7 (corrections on the grid) + 4.5
+// (interpolation), and an inverse transform of 23 where only the samples are wanted;
+// at 1024^2 7 and 9, at 4096^2 108 (of which the corrections' sums make half).
+template <int C, int R>
+__global__ __launch_bounds__(kModeWaves * 64) void k_modes_dense(DevPlan p, const double* __restrict__ corr,
+                                                                ModesDense dn, double* __restrict__ partial,
+                                                                double* __restrict__ partial2) {
+    extern __shared__ double smem[];
+    const ModesLds L = modes_lds<C>(smem);
+    const size_t at = (size_t)blockIdx.x * p.M;
+    modes_round<C, R, true, true>(
+        p, corr, blockIdx.x, L, [&](int set, int cp, double v) { (set ? partial2 : partial)[at + cp] = v; }, nullptr, dn);
 }
 
 // ---------------------------------------------------------------- spline of a density
@@ -74,9 +92,10 @@ __global__ __launch_bounds__(256) void k_spline(DevPlan p, const double* __restr
 
 // 64 samples per workgroup of 16 wavefronts (reduce_samples64).
 __global__ __launch_bounds__(1024) void k_reduce_interp(DevPlan p, JumpSrc js, const double* __restrict__ partial,
-                                                        int G, double* __restrict__ out, const int* __restrict__ skip) {
+                                                        int G, double* __restrict__ out, const int* __restrict__ skip,
+                                                        const double* __restrict__ from) {
     __shared__ double red[16 * 64];
-    reduce_samples64(p, js, partial, G, blockIdx.x * 64, out, red, skip);
+    reduce_samples64(p, js, partial, G, blockIdx.x * 64, out, red, skip, from);
 }
 
 // Interpolation from a full grid solution (dense path): R in the padded interior layout.
@@ -247,28 +266,55 @@ __global__ __launch_bounds__(kGmChunk) void k_density(DevPlan p, const double* _
     gm_density(p, y, s2, corr_il, gc, flag, flag_next, bad, number);
 }
 
+// The same for an interface solve: the density y and f on Gamma (either null: zero).
+__global__ __launch_bounds__(kGmChunk) void k_density_f(DevPlan p, const double* __restrict__ y,
+                                                        const double* __restrict__ f, double* __restrict__ s2,
+                                                        double* __restrict__ f2, double* __restrict__ corr_il, int gc) {
+    gm_density_f(p, y, f, s2, f2, corr_il, gc);
+}
+
+// One launch of the sparse fast solve: the apply's (dn null) or an interface solve's.
+struct ModesArgs {
+    const double* corr;
+    double *partial, *partial2;
+    const int* skip;
+    const ModesDense* dn;
+};
+
 template <int C, int R>
-hipError_t modes_launch(const DevPlan& p, const double* corr, double* partial, const int* skip, hipStream_t s) {
+hipError_t modes_launch(const DevPlan& p, const ModesArgs& a, hipStream_t s) {
     constexpr size_t lds = sizeof(double) * modes_lds_len<C, R>();
     if constexpr (lds > 160 * 1024) {
         return hipErrorInvalidValue;                  // never fits the local data share
     } else {
-        if (hipError_t e = hipFuncSetAttribute((const void*)k_modes<C, R>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds))
-            return e;
-        const int groups = (p.n + R - 1) / R;
-        return klaunch(&k_modes<C, R>, dim3(groups), dim3(kModeWaves * 64), lds, s, p, corr, partial, skip);
+        const void* f = a.dn ? (const void*)k_modes_dense<C, R> : (const void*)k_modes<C, R>;
+        if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) return e;
+        const dim3 groups((p.n + R - 1) / R), t(kModeWaves * 64);
+        if (a.dn) return klaunch(&k_modes_dense<C, R>, groups, t, lds, s, p, a.corr, *a.dn, a.partial, a.partial2);
+        return klaunch(&k_modes<C, R>, groups, t, lds, s, p, a.corr, a.partial, a.skip);
     }
 }
 
 template <int C>
-hipError_t modes_dispatch_r(const DevPlan& p, const double* corr, double* partial, int R, const int* skip,
-                            hipStream_t s) {
+hipError_t modes_dispatch_r(const DevPlan& p, int R, const ModesArgs& a, hipStream_t s) {
     switch (R) {
-        case 1: return modes_launch<C, 1>(p, corr, partial, skip, s);
-        case 2: return modes_launch<C, 2>(p, corr, partial, skip, s);
-        case 4: return modes_launch<C, 4>(p, corr, partial, skip, s);
-        case 8: return modes_launch<C, 8>(p, corr, partial, skip, s);
+        case 1: return modes_launch<C, 1>(p, a, s);
+        case 2: return modes_launch<C, 2>(p, a, s);
+        case 4: return modes_launch<C, 4>(p, a, s);
+        case 8: return modes_launch<C, 8>(p, a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t modes_dispatch(const DevPlan& p, int R, const ModesArgs& a, hipStream_t s) {
+    switch (p.N) {
+        case 64: return modes_dispatch_r<1>(p, R, a, s);
+        case 128: return modes_dispatch_r<2>(p, R, a, s);
+        case 256: return modes_dispatch_r<4>(p, R, a, s);
+        case 512: return modes_dispatch_r<8>(p, R, a, s);
+        case 1024: return modes_dispatch_r<16>(p, R, a, s);
+        case 2048: return modes_dispatch_r<32>(p, R, a, s);
+        case 4096: return modes_dispatch_r<64>(p, R, a, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -324,16 +370,13 @@ hipError_t launch_correct(const DevPlan& p, JumpSrc js, double* corr, double* co
 
 hipError_t launch_modes(const DevPlan& p, const double* corr, double* partial, int R, const int* skip,
                         hipStream_t s) {
-    switch (p.N) {
-        case 64: return modes_dispatch_r<1>(p, corr, partial, R, skip, s);
-        case 128: return modes_dispatch_r<2>(p, corr, partial, R, skip, s);
-        case 256: return modes_dispatch_r<4>(p, corr, partial, R, skip, s);
-        case 512: return modes_dispatch_r<8>(p, corr, partial, R, skip, s);
-        case 1024: return modes_dispatch_r<16>(p, corr, partial, R, skip, s);
-        case 2048: return modes_dispatch_r<32>(p, corr, partial, R, skip, s);
-        case 4096: return modes_dispatch_r<64>(p, corr, partial, R, skip, s);
-        default: return hipErrorInvalidValue;
-    }
+    return modes_dispatch(p, R, ModesArgs{corr, partial, nullptr, skip, nullptr}, s);
+}
+
+hipError_t launch_modes_dense(const DevPlan& p, const double* corr, double* rows, bool load, bool store, int R,
+                              double* partial, const double* w2, double* partial2, hipStream_t s) {
+    const ModesDense dn{rows, load, store, partial != nullptr, w2};
+    return modes_dispatch(p, R, ModesArgs{corr, partial, partial2, nullptr, &dn}, s);
 }
 
 hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const int* skip, hipStream_t s) {
@@ -349,10 +392,16 @@ hipError_t launch_density(const DevPlan& p, const double* y, double* s2, double*
                    k.bad, k.number);
 }
 
+hipError_t launch_density_f(const DevPlan& p, const double* y, const double* f, double* s2, double* f2, double* corr_il,
+                            hipStream_t s) {
+    const int gc = gm_chunks(p.M, true);
+    return klaunch(&k_density_f, dim3(gc + p.n_cc), dim3(kGmChunk), 0, s, p, y, f, s2, f2, corr_il, gc);
+}
+
 hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* partial, int G, double* out,
-                                const int* skip, const GmresBufs* gm, hipStream_t s) {
+                                const int* skip, const GmresBufs* gm, hipStream_t s, const double* from) {
     if (gm) return klaunch(&k_reduce_gm, dim3(gm->gc64 + 1), dim3(1024), 0, s, p, js, partial, G, *gm);
-    if (hipError_t e_ = klaunch(&k_reduce_interp, dim3((p.M + 63) / 64), dim3(1024), 0, s, p, js, partial, G, out, skip)) return e_;
+    if (hipError_t e_ = klaunch(&k_reduce_interp, dim3((p.M + 63) / 64), dim3(1024), 0, s, p, js, partial, G, out, skip, from)) return e_;
     return hipGetLastError();
 }
 
