@@ -1,8 +1,8 @@
 // Column sine transforms of the dense path (the fast solver's y-direction
 // passes, Alg. 4 on the full grid).
 //
-// out[l-1][c] = alpha * sum_{j=1}^{N-1} sin(pi j l / N) in[j-1][c] (+ out[l-1][c]
-// when accumulating), for every column c of an N x N row-major array whose last
+// out[l-1][c] = alpha * sum_{j=1}^{N-1} sin(pi j l / N) in[j-1][c] (+ add[l-1][c]
+// with add), for every column c of an N x N row-major array whose last
 // row is the zero pad of node N.  One workgroup owns B adjacent columns: it
 // loads the N x B tile once (B-wide row segments), transforms it in LDS and
 // writes it back in place of the same tile, so no transpose is needed.
@@ -242,7 +242,7 @@ __device__ __forceinline__ void radix2_step(const cpx<double>* sq, int tw, int N
 // (several independent N-row arrays, as the planes of a 3D grid).
 template <class T, class Tin, class Tout, int B, int IO>
 __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, const double* __restrict__ sinq,
-                                                          const Tin* in, Tout* out, double alpha, int accumulate,
+                                                          const Tin* in, Tout* out, double alpha, const Tout* add,
                                                           int ld, size_t slice, const int* __restrict__ skip,
                                                           const unsigned char* __restrict__ mask8) {
     if (skip && *skip) return;
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
     }
     __syncthreads();
     // write: X_l to row l-1 (odd l from slot (l-1)/2, even l from slot N - l/2); row N-1 is the pad
-    // (every thread reads LDS and, when accumulating, loads the old values at a
+    // (every thread reads LDS and, with add, loads its values at a
     // valid place: clamped past the tile's last element, only the stores are
     // guarded, so the reads of a batch issue together)
     for (int base = 0; base < N * P; base += NTH * kLoadBatch) {
@@ -553,13 +553,13 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
             vx[u] = l < N ? alpha * (double)ev[u].x : 0.0;
             vy[u] = l < N ? alpha * (double)ev[u].y : 0.0;
         }
-        if (accumulate) {
+        if (add) {
             Vout old[kLoadBatch];
 #pragma unroll
             for (int u = 0; u < kLoadBatch; ++u) {
                 const int idx = min(base + u * NTH + tid, N * P - 1);
                 const int r = idx >> LP, p = idx & (P - 1);
-                old[u] = *reinterpret_cast<const Vout*>(out + (size_t)r * ld + col0 + 2 * p);
+                old[u] = *reinterpret_cast<const Vout*>(add + (size_t)r * ld + col0 + 2 * p);
             }
 #pragma unroll
             for (int u = 0; u < kLoadBatch; ++u) {
@@ -634,8 +634,8 @@ constexpr int kShortThreads = 256;   // four pairs (eight columns) per workgroup
 
 template <int NP, int IO>
 __global__ __launch_bounds__(kShortThreads) void k_dst_short(const double* __restrict__ sinq, const double* in,
-                                                             double* out, double alpha, int accumulate, int ld,
-                                                             size_t slice, const int* __restrict__ skip,
+                                                             double* out, double alpha, int ld, size_t slice,
+                                                             const int* __restrict__ skip,
                                                              const unsigned char* __restrict__ mask8) {
     constexpr int N = 64 * NP;
     constexpr int LOG2N = NP == 1 ? 6 : NP == 2 ? 7 : 8;
@@ -754,14 +754,7 @@ __global__ __launch_bounds__(kShortThreads) void k_dst_short(const double* __res
             grid_put(out, mask8, N, row + 1, col, alpha * a, alpha * b);
             return;
         }
-        double2* o = reinterpret_cast<double2*>(out + (size_t)row * ld + col);
-        double2 val = make_double2(alpha * a, alpha * b);
-        if (accumulate) {
-            const double2 old = *o;
-            val.x += old.x;
-            val.y += old.y;
-        }
-        *o = val;
+        *reinterpret_cast<double2*>(out + (size_t)row * ld + col) = make_double2(alpha * a, alpha * b);
     };
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
@@ -791,43 +784,43 @@ struct Lines {
 };
 
 template <class T, class Tin, class Tout, int B, int IO>
-hipError_t dst_launch(const Lines& g, const Tin* in, Tout* out, double alpha, bool acc, hipStream_t s) {
+hipError_t dst_launch(const Lines& g, const Tin* in, Tout* out, double alpha, const Tout* add, hipStream_t s) {
     const size_t lds = dst_lds_bytes(g.N, B, sizeof(cpx<T>));
     if (hipError_t e = hipFuncSetAttribute((const void*)k_dst_cols<T, Tin, Tout, B, IO>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))
         return e;
     if (hipError_t e_ = klaunch(&k_dst_cols<T, Tin, Tout, B, IO>, dim3(g.ld / B, g.slices), dim3(kDstThreads), lds, s,
-                                g.N, g.log2N, g.sinq, in, out, alpha, acc ? 1 : 0, g.ld, g.slice, g.skip, g.mask8))
+                                g.N, g.log2N, g.sinq, in, out, alpha, add, g.ld, g.slice, g.skip, g.mask8))
         return e_;
     return hipGetLastError();
 }
 
 template <int NP, int IO>
-hipError_t short_launch(const Lines& g, const double* in, double* out, double alpha, bool acc, hipStream_t s) {
+hipError_t short_launch(const Lines& g, const double* in, double* out, double alpha, hipStream_t s) {
     constexpr int cols = 2 * (kShortThreads / 64);
     if (hipError_t e_ = klaunch(&k_dst_short<NP, IO>, dim3(g.ld / cols, g.slices), dim3(kShortThreads), 0, s, g.sinq,
-                                in, out, alpha, acc ? 1 : 0, g.ld, g.slice, g.skip, g.mask8))
+                                in, out, alpha, g.ld, g.slice, g.skip, g.mask8))
         return e_;
     return hipGetLastError();
 }
 
 template <class T, class Tin, class Tout, int IO = kPadded>
-hipError_t dst_dispatch(const Lines& g, const Tin* in, Tout* out, double alpha, bool acc, int B, hipStream_t s) {
+hipError_t dst_dispatch(const Lines& g, const Tin* in, Tout* out, double alpha, const Tout* add, int B, hipStream_t s) {
     // FP64 columns of 64 rows: one wavefront per column pair (4.6 against 7.2
     // us for the 64^3 grid's transform along z; at 128 and 256 rows the tiled
     // kernel is the faster one: 12.0 against 15.5 us, 75 against 93 us)
     if constexpr (sizeof(T) == 8 && sizeof(Tin) == 8 && sizeof(Tout) == 8) {
-        if (g.ld % 8 == 0 && g.N == 64) return short_launch<1, IO>(g, in, out, alpha, acc, s);
+        if (g.ld % 8 == 0 && g.N == 64) return short_launch<1, IO>(g, in, out, alpha, s);
     }
     if (!dst_tile_ok(g.N, B, sizeof(cpx<T>), ~(size_t)0) || g.ld % B != 0) return hipErrorInvalidValue;
     switch (B) {
-        case 4: return dst_launch<T, Tin, Tout, 4, IO>(g, in, out, alpha, acc, s);
-        case 8: return dst_launch<T, Tin, Tout, 8, IO>(g, in, out, alpha, acc, s);
-        case 16: return dst_launch<T, Tin, Tout, 16, IO>(g, in, out, alpha, acc, s);
+        case 4: return dst_launch<T, Tin, Tout, 4, IO>(g, in, out, alpha, add, s);
+        case 8: return dst_launch<T, Tin, Tout, 8, IO>(g, in, out, alpha, add, s);
+        case 16: return dst_launch<T, Tin, Tout, 16, IO>(g, in, out, alpha, add, s);
         default:
             if constexpr (sizeof(T) == 8) {                  // wide tiles: 16-byte pairs only
-                if (B == 32) return dst_launch<T, Tin, Tout, 32, IO>(g, in, out, alpha, acc, s);
-                return dst_launch<T, Tin, Tout, 64, IO>(g, in, out, alpha, acc, s);
+                if (B == 32) return dst_launch<T, Tin, Tout, 32, IO>(g, in, out, alpha, add, s);
+                return dst_launch<T, Tin, Tout, 64, IO>(g, in, out, alpha, add, s);
             }
             return hipErrorInvalidValue;
     }
@@ -866,36 +859,45 @@ int dst_default_tile(int N, size_t cpx_bytes, size_t lds_max, long lines, int mi
     return 0;
 }
 
-hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, bool acc, int B,
-                           hipStream_t s) {
-    return dst_dispatch<double>(grid2(p), in, out, alpha, acc, B, s);
+hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, int B, hipStream_t s) {
+    return dst_dispatch<double, double, double>(grid2(p), in, out, alpha, nullptr, B, s);
 }
 
 hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, double* out, int B, hipStream_t s) {
     Lines g = grid2(p);
     g.mask8 = mask ? p.mask8 : nullptr;
-    return dst_dispatch<double, double, double, kFromGrid>(g, f, out, 1.0, false, B, s);
+    return dst_dispatch<double, double, double, kFromGrid>(g, f, out, 1.0, nullptr, B, s);
 }
 
 hipError_t launch_dst_to_grid(const DevPlan& p, const double* in, double* u, double alpha, bool mask, int B,
                               hipStream_t s) {
     Lines g = grid2(p);
     g.mask8 = mask ? p.mask8 : nullptr;
-    return dst_dispatch<double, double, double, kToGrid>(g, in, u, alpha, false, B, s);
+    return dst_dispatch<double, double, double, kToGrid>(g, in, u, alpha, nullptr, B, s);
 }
 
 hipError_t launch_dst_cols_f32(const DevPlan& p, const double* in, float* out, double alpha, int B, hipStream_t s) {
-    return dst_dispatch<float>(grid2(p), in, out, alpha, false, B, s);
+    return dst_dispatch<float, double, float>(grid2(p), in, out, alpha, nullptr, B, s);
 }
 
-hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, bool acc, int B,
-                                    hipStream_t s) {
-    return dst_dispatch<float>(grid2(p), in, out, alpha, acc, B, s);
+hipError_t launch_dst_from_grid_f32(const DevPlan& p, const double* f, float* out, int B, hipStream_t s) {
+    return dst_dispatch<float, double, float, kFromGrid>(grid2(p), f, out, 1.0, nullptr, B, s);
+}
+
+hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, const double* add,
+                                    int B, hipStream_t s) {
+    return dst_dispatch<float, float, double>(grid2(p), in, out, alpha, add, B, s);
+}
+
+hipError_t launch_dst_f32_to_grid(const DevPlan& p, const float* in, double* u, double alpha, const double* add, int B,
+                                  hipStream_t s) {
+    return dst_dispatch<float, float, double, kToGrid>(grid2(p), in, u, alpha, add, B, s);
 }
 
 hipError_t launch_dst_lines(int N, int log2N, const double* sinq, double* a, double alpha, int B, int ld, int slices,
                             size_t slice, const int* skip, hipStream_t s) {
-    return dst_dispatch<double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr}, a, a, alpha, false, B, s);
+    return dst_dispatch<double, double, double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr}, a, a, alpha, nullptr, B,
+                                                s);
 }
 
 }  // namespace kfbi

@@ -247,10 +247,9 @@ hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* R, dou
 hipError_t launch_fill_rhs(const DevPlan& p, const double* f, bool mask, double* R, hipStream_t s);
 // column sine transforms (dst.hip): FP64, and FP32 arithmetic reading an FP64
 // grid into FP32 storage or reading FP32 storage into an FP64 grid (written or
-// accumulated)
+// added to add, padded as well)
 // B: columns per workgroup (4, 8 or 16; 32 or 64 with FP64 pairs; see dst_tile_ok)
-hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, bool acc, int B,
-                           hipStream_t s);
+hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, int B, hipStream_t s);
 // The same (FP64, alpha = 1) reading the user's grid f, zero outside Omega with mask;
 // and writing the user's grid u (the box's rows and columns zero), zero outside Omega
 // with mask.
@@ -258,8 +257,12 @@ hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, do
 hipError_t launch_dst_to_grid(const DevPlan& p, const double* in, double* u, double alpha, bool mask, int B,
                               hipStream_t s);
 hipError_t launch_dst_cols_f32(const DevPlan& p, const double* in, float* out, double alpha, int B, hipStream_t s);
-hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, bool acc, int B,
-                                    hipStream_t s);
+hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, const double* add,
+                                    int B, hipStream_t s);
+// The same reading the user's grid f, and writing the user's grid u.
+hipError_t launch_dst_from_grid_f32(const DevPlan& p, const double* f, float* out, int B, hipStream_t s);
+hipError_t launch_dst_f32_to_grid(const DevPlan& p, const float* in, double* u, double alpha, const double* add, int B,
+                                  hipStream_t s);
 // In-place FP64 transforms of `slices` N-row arrays (rows ld elements apart,
 // ld columns, arrays `slice` elements apart): the column transforms of the
 // planes of a 3D grid.  Skipped while *skip is nonzero (skip may be null).
@@ -275,9 +278,10 @@ int dst_default_tile(int N, size_t cpx_bytes, size_t lds_max, long lines, int mi
 // tridiagonal solves along x of every sine mode (FP64 arithmetic; FP64 or FP32 storage)
 hipError_t launch_rows_solve(const DevPlan& p, double* A, hipStream_t s);
 hipError_t launch_rows_solve_f32(const DevPlan& p, float* A, hipStream_t s);
-// R <- R - (L_h - kappa) V on the interior nodes (FP64): the refinement
-// residual; with A non-null also A <- A + V (V a correction being applied)
-hipError_t launch_residual(const DevPlan& p, const double* V, double* R, double* A, hipStream_t s);
+// R <- R - (L_h - kappa) V on the interior nodes (FP64), the refinement residual;
+// with the user's grid f R <- f - (L_h - kappa) V and R's pad zero; with A non-null
+// also A <- A + V (V a correction being applied)
+hipError_t launch_residual(const DevPlan& p, const double* V, const double* f, double* R, double* A, hipStream_t s);
 hipError_t launch_grid_out(const DevPlan& p, const double* V, bool mask, double* u, hipStream_t s);
 hipError_t launch_axpby(int n, double a, const double* x, double b, const double* y, double* z,
                         hipStream_t s);

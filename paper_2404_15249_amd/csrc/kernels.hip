@@ -171,19 +171,24 @@ __global__ __launch_bounds__(64 * rows_per_group<C>()) void k_rows_solve(DevPlan
 
 // R <- R - ((V_E + V_W + V_N + V_S - 4 V) / h^2 - kappa V) at the interior nodes
 // (V = 0 on the box), all in the padded interior layout; with A, also A <- A + V.
-__global__ __launch_bounds__(256) void k_residual(DevPlan p, const double* __restrict__ V, double* __restrict__ R,
+__global__ __launch_bounds__(256) void k_residual(DevPlan p, const double* __restrict__ V,
+                                                  const double* __restrict__ f, double* __restrict__ R,
                                                   double* __restrict__ A) {
     const int N = p.N;
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (size_t)N * N) return;
     const int i = (int)(idx % N) + 1, j = (int)(idx / N) + 1;
-    if (i >= N || j >= N) return;
+    if (i >= N || j >= N) {
+        if (f) R[idx] = 0.0;
+        return;
+    }
+    const double r = f ? f[(size_t)j * (N + 1) + i] : R[idx];
     const double v = V[idx];
     const double vw = i > 1 ? V[idx - 1] : 0.0;
     const double ve = i < N - 1 ? V[idx + 1] : 0.0;
     const double vs = j > 1 ? V[idx - N] : 0.0;
     const double vn = j < N - 1 ? V[idx + N] : 0.0;
-    R[idx] -= (vw + ve + vs + vn - 4.0 * v) * p.inv_h2 - p.kappa * v;
+    R[idx] = r - ((vw + ve + vs + vn - 4.0 * v) * p.inv_h2 - p.kappa * v);
     if (A) A[idx] += v;
 }
 
@@ -420,9 +425,9 @@ hipError_t launch_rows_solve(const DevPlan& p, double* A, hipStream_t s) { retur
 
 hipError_t launch_rows_solve_f32(const DevPlan& p, float* A, hipStream_t s) { return rows_solve_any(p, A, s); }
 
-hipError_t launch_residual(const DevPlan& p, const double* V, double* R, double* A, hipStream_t s) {
+hipError_t launch_residual(const DevPlan& p, const double* V, const double* f, double* R, double* A, hipStream_t s) {
     const size_t tot = (size_t)p.N * p.N;
-    if (hipError_t e_ = klaunch(&k_residual, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, p, V, R, A)) return e_;
+    if (hipError_t e_ = klaunch(&k_residual, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, p, V, f, R, A)) return e_;
     return hipGetLastError();
 }
 

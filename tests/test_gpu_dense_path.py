@@ -61,10 +61,11 @@ def test_tiles_and_outputs_match_oracle(n, m):
             assert relerr(gd, dn) < 1e-12 * n, (rm, cols)
 
 
+@pytest.mark.parametrize("precision,refine", [("fp64", 0), ("fp32", 0), ("fp32", 1), ("fp32", 3)])
 @pytest.mark.parametrize("n", [64, 512, 2048])
-def test_fast_solve_in_place(n):
+def test_fast_solve_in_place(n, precision, refine):
     from paper_2404_15249_amd import kfbi
-    prob = kfbi.Problem(kfbi.Context(0), synth.circle_points(n, 0.8), n, 1.0)
+    prob = kfbi.Problem(kfbi.Context(0), synth.circle_points(n, 0.8), n, 1.0, precision=precision, refine_steps=refine)
     rhs = dev(np.random.default_rng(n).standard_normal((n + 1, n + 1)))
     want = prob.fast_solve(rhs)
     assert not want[0].any() and not want[-1].any() and not want[:, 0].any() and not want[:, -1].any()
