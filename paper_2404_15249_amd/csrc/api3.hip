@@ -26,11 +26,14 @@ struct kfbi_prob3 {
     std::vector<void*> allocs;
     size_t bytes = 0;
     double* G = nullptr;        // N^3 grid, interior layout
-    double* J = nullptr;        // 10 M jumps
+    double2* S = nullptr;       // M: jumps along the crossings' axes
+    double* far = nullptr;      // M: far-side jump terms of the interpolation
+    double* corr = nullptr;     // corrections by folded column (N <= kSlabMax)
+    double* val = nullptr;      // solution at the stencils' nodes (N <= kSlabMax)
     double* tmpM = nullptr;     // M
     double* zeroM = nullptr;    // M zeros (the density of Y f)
-    int* d_flag = nullptr;      // 1: the density checked by kfbi3_apply holds a NaN or Inf
-    int h_flag = 0;
+    int* d_flag = nullptr;      // 2: whether the density checked by kfbi3_apply holds a NaN or Inf, by turns
+    unsigned n_apply = 0;       // number of the last such check
     int dstB = 16;
     GmresBufs gm{};
     GmresHost host;              // what the device tells of a run (gm.pub)
@@ -72,30 +75,46 @@ void free3(kfbi_prob3* p) {
     delete p;
 }
 
+// K_D phi: v+ at the control points of the interface solve with no right-hand side,
+// into vz or (gm) the GMRES step.  Up to kSlabMax the solve goes from the corrections
+// to the stencils' nodes by half planes in LDS (at 128^3 26 us against 82 by way of the
+// whole grid); above, a half plane does not fit and the whole grid is transformed.
+kfbi_status apply3(kfbi_prob3* p, const double* phi, double* vz, const GmresBufs* gm, const int* skip, hipStream_t s,
+                   const DensityCheck* check = nullptr) {
+    HIP_TRY(launch_surface3(p->dp, phi, nullptr, p->S, p->far, check ? nullptr : skip, check, s));
+    if (p->N <= kSlabMax) {
+        HIP_TRY(launch_correct3(p->dp, phi, p->S, nullptr, p->corr, skip, s));
+        HIP_TRY(launch_solve3_sparse(p->dp, p->corr, p->G, p->val, skip, s));
+        HIP_TRY(launch_interp3(p->dp, p->val, p->dp.st_pos, p->far, vz, skip, gm, s));
+        return KFBI_OK;
+    }
+    HIP_TRY(launch_fill3(p->dp, nullptr, p->G, skip, s));
+    HIP_TRY(launch_correct3(p->dp, phi, p->S, p->G, nullptr, skip, s));
+    HIP_TRY(launch_solve3(p->dp, p->G, p->dstB, skip, s));
+    HIP_TRY(launch_interp3(p->dp, p->G, p->dp.st_node, p->far, vz, skip, gm, s));
+    return KFBI_OK;
+}
+
 // one interface solve: jumps from (phi, fgam), the masked base right-hand side
 // f (null: zero), correction, fast solve; v+ at the control points into vz
 // (null: skipped), the grid solution into vgrid (null: skipped)
 kfbi_status interface3(kfbi_prob3* p, const double* phi, const double* f, const double* fgam, double* vgrid,
                        bool mask, double* vz) {
     hipStream_t s = p->ctx->stream;
-    HIP_TRY(launch_jumps3(p->dp, phi ? phi : p->zeroM, fgam, p->J, nullptr, s));
+    if (!phi) phi = p->zeroM;
+    HIP_TRY(launch_surface3(p->dp, phi, fgam, p->S, p->far, nullptr, nullptr, s));
     HIP_TRY(launch_fill3(p->dp, f, p->G, nullptr, s));
-    HIP_TRY(launch_correct3(p->dp, p->J, p->G, nullptr, s));
+    HIP_TRY(launch_correct3(p->dp, phi, p->S, p->G, nullptr, nullptr, s));
     HIP_TRY(launch_solve3(p->dp, p->G, p->dstB, nullptr, s));
-    if (vz) HIP_TRY(launch_interp3(p->dp, p->G, p->J, vz, nullptr, s));
+    if (vz) HIP_TRY(launch_interp3(p->dp, p->G, p->dp.st_node, p->far, vz, nullptr, nullptr, s));
     if (vgrid) HIP_TRY(launch_grid_out3(p->dp, p->G, mask, vgrid, s));
     return KFBI_OK;
 }
 
 kfbi_status enqueue_steps3(kfbi_prob3* p, int nsteps, hipStream_t s) {
     GmresBufs b = p->gm;
-    const int* skip = &b.st->converged;
     for (int k = 0; k < nsteps; ++k) {
-        HIP_TRY(launch_jumps3(p->dp, b.xcur, nullptr, p->J, skip, s));
-        HIP_TRY(launch_fill3(p->dp, nullptr, p->G, skip, s));
-        HIP_TRY(launch_correct3(p->dp, p->J, p->G, skip, s));
-        HIP_TRY(launch_solve3(p->dp, p->G, p->dstB, skip, s));
-        HIP_TRY(launch_interp3(p->dp, p->G, p->J, nullptr, &b, s));
+        if (kfbi_status e = apply3(p, b.xcur, nullptr, &b, &b.st->converged, s)) return e;
         HIP_TRY(launch_gmres_step(nullptr, p->M, b, s));
     }
     return KFBI_OK;
@@ -200,20 +219,36 @@ kfbi_status kfbi3_prob_create(kfbi_ctx* ctx, const kfbi_desc3* d, kfbi_prob3** o
                 row_solve_constants(P.h * P.h * p->kappa + 4.0 * sl * sl + 4.0 * sm * sm, N);
         }
     }
+    Apply3Host A;
+    try {
+        A = build_apply3(P);
+    } catch (const std::bad_alloc&) {
+        return fail(set_err(KFBI_ERR_OOM, "host allocation failed in the plan"));
+    }
+    dp.E = (int)P.fit_idx.size();
+    dp.y_first = A.y_first;
     kfbi_status st;
+    if ((st = upload3(p, &dp.fit, A.fit)) || (st = upload3(p, &dp.point, A.point)) ||
+        (st = upload3(p, &dp.sp_wave, A.sp_wave)) || (st = upload3(p, &dp.sp_piece, A.sp_piece)) || (st = upload3(p, &dp.irr_pos, A.irr_pos)) ||
+        (st = upload3(p, &dp.zg_off, A.zg_off)) || (st = upload3(p, &dp.zg_code, A.zg_code)) ||
+        (st = upload3(p, &dp.st_pos, A.st_pos)) || (st = alloc3(p, &p->corr, 4 * A.sp_piece.size())) ||
+        (st = alloc3(p, &p->val, 4 * A.zg_code.size())))
+        return fail(st);
+    if (!A.sp_piece.empty() && hipMemset(p->corr, 0, 4 * A.sp_piece.size() * sizeof(double)) != hipSuccess)   // the padding's
+        return fail(set_err(KFBI_ERR_DEVICE, "hipMemset failed"));
     if ((st = upload3(p, &dp.sinq, sinq)) || (st = upload3(p, &dp.modes, modes)) ||
         (st = upload3(p, &dp.geo, P.geo)) || (st = upload3(p, &dp.fit_off, P.fit_off)) ||
         (st = upload3(p, &dp.fit_idx, P.fit_idx)) || (st = upload3(p, &dp.fit_w, P.fit_w)) ||
         (st = upload3(p, &dp.irr_node, P.irr_node)) || (st = upload3(p, &dp.irr_sign, P.irr_sign)) ||
         (st = upload3(p, &dp.arm_off, P.arm_off)) || (st = upload3(p, &dp.arm_q, P.arm_q)) ||
-        (st = upload3(p, &dp.arm_d, P.arm_d)) || (st = upload3(p, &dp.q_axis, P.axis)) ||
-        (st = upload3(p, &dp.st_node, P.st_node)) || (st = upload3(p, &dp.st_w, P.st_w)) ||
-        (st = upload3(p, &dp.st_t, P.st_t)) || (st = upload3(p, &dp.inside, P.inside)))
+        (st = upload3(p, &dp.arm_d, P.arm_d)) ||
+        (st = upload3(p, &dp.st_node, A.st_node)) || (st = upload3(p, &dp.st_w, A.st_w)) ||
+        (st = upload3(p, &dp.inside, P.inside)))
         return fail(st);
     const int m = p->restart;
     GmresBufs& b = p->gm;
-    if ((st = alloc3(p, &p->G, (size_t)N * N * N)) || (st = alloc3(p, &p->J, (size_t)kJump3 * M)) ||
-        (st = alloc3(p, &p->tmpM, M)) || (st = alloc3(p, &p->zeroM, M)) || (st = alloc3(p, &p->d_flag, 1)) ||
+    if ((st = alloc3(p, &p->G, (size_t)N * N * N)) || (st = alloc3(p, &p->S, M)) || (st = alloc3(p, &p->far, M)) ||
+        (st = alloc3(p, &p->tmpM, M)) || (st = alloc3(p, &p->zeroM, M)) || (st = alloc3(p, &p->d_flag, 2)) ||
         (st = alloc3(p, &b.V, (size_t)(m + 1) * M)) || (st = alloc3(p, &b.H, (size_t)(m + 1) * m)) ||
         (st = alloc3(p, &b.cs, m)) || (st = alloc3(p, &b.sn, m)) || (st = alloc3(p, &b.g, m + 1)) ||
         (st = alloc3(p, &b.ghat, M)) || (st = alloc3(p, &b.phi, M)) || (st = alloc3(p, &b.xcur, M)) ||
@@ -227,7 +262,7 @@ kfbi_status kfbi3_prob_create(kfbi_ctx* ctx, const kfbi_desc3* d, kfbi_prob3** o
     b.m = m;
     b.gc = gm_chunks(M, false);
     b.gc64 = gm_chunks64(M);
-    if (hipMemset(p->zeroM, 0, M * sizeof(double)) != hipSuccess)
+    if (hipMemset(p->zeroM, 0, M * sizeof(double)) != hipSuccess || hipMemset(p->d_flag, 0, 2 * sizeof(int)) != hipSuccess)
         return fail(set_err(KFBI_ERR_DEVICE, "hipMemset failed"));
     p->dstB = dst_default_tile(N, 2 * sizeof(double), ctx->lds_max, (long)N * N, ctx->num_cu);
     if (p->dstB == 0) return fail(set_err(KFBI_ERR_UNSUPPORTED, "no column-transform tile fits this grid"));
@@ -275,7 +310,7 @@ kfbi_status kfbi3_jumps(kfbi_prob3* p, const double* phi, const double* f_gamma,
     if (kfbi_status s = check_ptr(phi, "phi")) return s;
     if (kfbi_status s = check_ptr(J, "J")) return s;
     HIP_TRY(hipSetDevice(p->ctx->device));
-    HIP_TRY(launch_jumps3(p->dp, phi, f_gamma, J, nullptr, p->ctx->stream));
+    HIP_TRY(launch_jumps3(p->dp, phi, f_gamma, J, p->ctx->stream));
     return KFBI_OK;
 }
 
@@ -284,13 +319,16 @@ kfbi_status kfbi3_apply(kfbi_prob3* p, const double* phi, double* out) {
     if (kfbi_status s = check_ptr(phi, "phi")) return s;
     if (kfbi_status s = check_ptr(out, "out")) return s;
     HIP_TRY(hipSetDevice(p->ctx->device));
-    // the density is checked first; with a NaN or Inf nothing is enqueued
+    // the first launch checks the density: with a NaN or Inf the others skip, so
+    // nothing is written
     hipStream_t s = p->ctx->stream;
-    HIP_TRY(launch_nonfinite(p->M, phi, p->d_flag, s));
-    HIP_TRY(hipMemcpyAsync(&p->h_flag, p->d_flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    const unsigned number = p->n_apply = p->n_apply + 1 ? p->n_apply + 1 : 2;   // never 0; parity alternates
+    const DensityCheck check{p->d_flag + (number & 1), p->d_flag + (~number & 1), &p->host.pub->bad, number};
+    if (kfbi_status e = apply3(p, phi, out, nullptr, check.flag, s, &check)) return e;
     HIP_TRY(hipStreamSynchronize(s));
-    if (p->h_flag) return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in the density");
-    return interface3(p, phi, nullptr, nullptr, nullptr, false, out);
+    if (__atomic_load_n(check.bad, __ATOMIC_ACQUIRE) == number)
+        return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in the density");
+    return KFBI_OK;
 }
 
 kfbi_status kfbi3_interface_solve(kfbi_prob3* p, const double* phi, const double* f_grid, const double* f_gamma,

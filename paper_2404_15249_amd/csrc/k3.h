@@ -24,31 +24,51 @@ struct DevPlan3 {
     const double* fit_w;        // 5 per neighbour
     const int* irr_node;        // I
     const double* irr_sign;     // I
+    // the apply's tables (Apply3Host)
+    int E;                      // fit neighbours in all
+    const double* fit;          // 3 E
+    const double* point;        // 3 M
+    const int* sp_wave;         // N <= kSlabMax, as all below
+    const int* sp_piece;
+    int y_first;
+    const int* irr_pos;         // I
+    const int* zg_off;
+    const int* zg_code;
+    const int* st_pos;          // 10 M
     const int* arm_off;         // I + 1
     const int* arm_q;
     const double* arm_d;
-    const int* q_axis;          // M
-    const int* st_node;         // 10 M (-1: a node on the box)
-    const double* st_w;         // 10 M
-    const double* st_t;         // 10 M
+    const int* st_node;         // 10 M (-1: a node on the box), node s of point m at s M + m
+    const double* st_w;         // 10 M, the same order
     const unsigned char* inside;   // (N+1)^3
 };
 
 // J <- Cartesian jumps at every control point for [v] = phi, [F] = fgam (null:
 // zero), [d_n v] = 0.
-hipError_t launch_jumps3(const DevPlan3& p, const double* phi, const double* fgam, double* J, const int* skip,
-                         hipStream_t s);
+hipError_t launch_jumps3(const DevPlan3& p, const double* phi, const double* fgam, double* J, hipStream_t s);
+// The jumps an apply uses: S[m] <- ([v_a], [v_aa]) along the crossing's own axis a and
+// far[m] <- the jump terms of its interpolation, for [v] = phi, [F] = fgam (null: zero);
+// with check (may be null) also the density's check.
+hipError_t launch_surface3(const DevPlan3& p, const double* phi, const double* fgam, double2* S, double* far,
+                           const int* skip, const DensityCheck* check, hipStream_t s);
 // G <- f masked to Omega (f on the (N+1)^3 grid; null: zero), in the interior layout
 hipError_t launch_fill3(const DevPlan3& p, const double* f, double* G, const int* skip, hipStream_t s);
-// G[node] += correction at every irregular node (Alg. 2 along the three axes)
-hipError_t launch_correct3(const DevPlan3& p, const double* J, double* G, const int* skip, hipStream_t s);
+// The correction at every irregular node (Alg. 2 along the three axes): added to G, or
+// (G null) put in its place in corr.
+hipError_t launch_correct3(const DevPlan3& p, const double* phi, const double2* S, double* G, double* corr,
+                           const int* skip, hipStream_t s);
 // G <- (L_h - kappa)^-1 G: sine transforms along z and y, tridiagonal solves
 // along x, inverse transforms (Alg. 4 in three dimensions); B: transform tile
 hipError_t launch_solve3(const DevPlan3& p, double* G, int B, const int* skip, hipStream_t s);
-// out[m] <- v+ at control point m (Alg. 3, ten-node stencil); with gm non-null
-// (a GMRES step) the result goes to gm->w and the first Gram-Schmidt pass follows
-hipError_t launch_interp3(const DevPlan3& p, const double* G, const double* J, double* out, const GmresBufs* gm,
-                          hipStream_t s);
+// The same for a right-hand side of corrections alone, in their places in corr, and the
+// stencils' nodes alone, into val (N <= kSlabMax; W: scratch, (N-1) N^2).
+hipError_t launch_solve3_sparse(const DevPlan3& p, const double* corr, double* W, double* val, const int* skip,
+                                hipStream_t s);
+// out[m] <- v+ at control point m (Alg. 3, ten-node stencil) from the nodes' values v at
+// node (st_node or st_pos); with gm non-null (a GMRES step) the reduce part of the step
+// follows instead
+hipError_t launch_interp3(const DevPlan3& p, const double* v, const int* node, const double* far, double* out,
+                          const int* skip, const GmresBufs* gm, hipStream_t s);
 // u <- the grid solution on the (N+1)^3 grid, zero outside Omega when mask
 hipError_t launch_grid_out3(const DevPlan3& p, const double* G, bool mask, double* u, hipStream_t s);
 

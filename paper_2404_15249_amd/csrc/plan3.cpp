@@ -287,4 +287,150 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
     return P;
 }
 
+Apply3Host build_apply3(const Plan3Host& P) {
+    Apply3Host A;
+    const int M = P.M(), N = P.N, H = N / 2;
+    const size_t E = P.fit_idx.size();
+    A.fit.resize(3 * E);
+    A.point.resize(3 * (size_t)M);
+    A.st_node.resize((size_t)kStencil3 * M);
+    A.st_w.resize((size_t)kStencil3 * M);
+    for (int m = 0; m < M; ++m) {
+        const double *g = &P.geo[12 * (size_t)m], *n = g, *t1 = g + 3, *t2 = g + 6;
+        const double s11 = g[9], s12 = g[10], s22 = g[11];
+        const double* t = &P.st_t[(size_t)kJump3 * m];
+        // the jump [v_ij] in the tangent derivatives d0..d4 of the fit and in
+        // [v_nn] + d2 + d4 (which is [F] + kappa [v])
+        struct Lin {
+            double d[5], nn;
+        };
+        auto hess = [&](int i, int j) {
+            const double a = t1[i] * n[j] + n[i] * t1[j], b = t2[i] * n[j] + n[i] * t2[j];
+            return Lin{{-(s11 * a + s12 * b), -(s12 * a + s22 * b), t1[i] * t1[j] - n[i] * n[j],
+                        t1[i] * t2[j] + t2[i] * t1[j], t2[i] * t2[j] - n[i] * n[j]},
+                       n[i] * n[j]};
+        };
+        const int ax = P.axis[m];
+        const Lin grad{{t1[ax], t2[ax], 0.0, 0.0, 0.0}, 0.0}, second = hess(ax, ax);
+        Lin far{{0.0, 0.0, 0.0, 0.0, 0.0}, 0.0};
+        for (int c = 0; c < 3; ++c) {
+            far.d[0] += t[1 + c] * t1[c];
+            far.d[1] += t[1 + c] * t2[c];
+        }
+        static const int ij[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {0, 2}, {1, 2}};
+        for (int c = 0; c < 6; ++c) {
+            const Lin h = hess(ij[c][0], ij[c][1]);
+            for (int q = 0; q < 5; ++q) far.d[q] += t[4 + c] * h.d[q];
+            far.nn += t[4 + c] * h.nn;
+        }
+        A.point[m] = second.nn;
+        A.point[(size_t)M + m] = far.nn;
+        A.point[(size_t)2 * M + m] = t[0];
+        for (int e = P.fit_off[m]; e < P.fit_off[m + 1]; ++e) {
+            const double* w = &P.fit_w[5 * (size_t)e];
+            const Lin* of[3] = {&grad, &second, &far};
+            for (int k = 0; k < 3; ++k) {
+                double v = 0.0;
+                for (int q = 0; q < 5; ++q) v += of[k]->d[q] * w[q];
+                A.fit[k * E + e] = v;
+            }
+        }
+        for (int s = 0; s < kStencil3; ++s) {
+            A.st_node[(size_t)s * M + m] = P.st_node[(size_t)kStencil3 * m + s];
+            A.st_w[(size_t)s * M + m] = P.st_w[(size_t)kStencil3 * m + s];
+        }
+    }
+    if (N > kSlabMax) return A;
+    // a node's folded column (y' - 1) N + x - 1, its z and its side
+    struct Fold {
+        int col, z, side;
+    };
+    auto fold = [&](int node) {
+        const int x = node % N, y = node / N % N + 1, z = node / (N * N) + 1, side = y > H;
+        return Fold{((side ? N - y : y) - 1) * N + x, z, side};
+    };
+    // the pieces' heights of every folded column
+    std::vector<std::vector<int>> column((size_t)H * N);
+    for (int node : P.irr_node) {
+        const Fold f = fold(node);
+        column[f.col].push_back(std::min(f.z, N - f.z));
+    }
+    std::vector<int> order;
+    for (int c = 0; c < H * N; ++c) {
+        auto& z = column[c];
+        std::sort(z.begin(), z.end());
+        z.erase(std::unique(z.begin(), z.end()), z.end());
+        if (!z.empty()) order.push_back(c);
+    }
+    A.y_first = order.empty() ? 0 : order[0] / N;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return column[a].size() > column[b].size(); });
+    // groups of 64 columns, longest first, each to the wavefront with the fewest rows yet
+    const int waves = N / 8;
+    std::vector<std::vector<size_t>> of(waves);
+    std::vector<size_t> rows(waves, 0);
+    for (size_t g = 0; g < order.size(); g += 64) {
+        const size_t w = std::min_element(rows.begin(), rows.end()) - rows.begin();
+        of[w].push_back(g);
+        rows[w] += column[order[g]].size();
+    }
+    std::vector<size_t> first((size_t)H * N, 0);             // a column's first piece
+    A.sp_wave.assign(1, 0);
+    for (int w = 0; w < waves; ++w) {
+        for (size_t g : of[w]) {
+            const size_t at = A.sp_piece.size();
+            A.sp_piece.resize(at + 64 * column[order[g]].size(), -1);
+            for (size_t lane = 0; lane < 64 && g + lane < order.size(); ++lane) {
+                const int c = order[g + lane];
+                first[c] = at + lane;
+                for (size_t t = 0; t < column[c].size(); ++t)
+                    A.sp_piece[at + 64 * t + lane] = c % N | (c / N) << 8 | column[c][t] << 16;
+            }
+        }
+        A.sp_wave.push_back((int)(A.sp_piece.size() / 64));
+    }
+    A.irr_pos.resize(P.I());
+    for (int r = 0; r < P.I(); ++r) {
+        const Fold f = fold(P.irr_node[r]);
+        const auto& z = column[f.col];
+        const size_t t = std::lower_bound(z.begin(), z.end(), std::min(f.z, N - f.z)) - z.begin();
+        A.irr_pos[r] = (int)(4 * (first[f.col] + 64 * t)) + 2 * f.side + (f.z > H);
+    }
+    // the stencils' nodes by tile; keys (column, side, z') in order, each once
+    std::vector<std::vector<int>> tile((size_t)H * (N / 32));
+    auto key = [&](const Fold& f) { return (f.col % 32 << 1 | f.side) << 8 | std::min(f.z, N - f.z); };
+    for (int node : A.st_node)
+        if (node >= 0) {
+            const Fold f = fold(node);
+            tile[f.col / N * (N / 32) + f.col % N / 32].push_back(key(f));
+            A.y_first = std::min(A.y_first, f.col / N);
+        }
+    A.zg_off.assign(1, 0);
+    for (auto& keys : tile) {
+        std::sort(keys.begin(), keys.end());
+        keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
+        for (size_t k = 0; k < keys.size();) {
+            const int a = keys[k], column_side = a >> 8;
+            const bool two = k + 1 < keys.size() && keys[k + 1] >> 8 == column_side;
+            const int b = two ? keys[k + 1] : a;
+            A.zg_code.push_back((a & 255) | (b & 255) << 8 | (column_side >> 1) << 16 | (column_side & 1) << 24);
+            k += two ? 2 : 1;
+        }
+        A.zg_off.push_back((int)A.zg_code.size());
+    }
+    A.st_pos.resize(A.st_node.size());
+    for (size_t k = 0; k < A.st_node.size(); ++k) {
+        A.st_pos[k] = -1;
+        if (A.st_node[k] < 0) continue;
+        const Fold f = fold(A.st_node[k]);
+        const int t = f.col / N * (N / 32) + f.col % N / 32, want = key(f);
+        // the entries of a tile are in the order of their first keys
+        const auto begin = A.zg_code.begin() + A.zg_off[t], end = A.zg_code.begin() + A.zg_off[t + 1];
+        auto first = [](int c) { return ((c >> 16 & 31) << 1 | c >> 24) << 8 | (c & 255); };
+        const auto at = std::upper_bound(begin, end, want, [&](int v, int c) { return v < first(c); }) - 1;
+        const int e = (int)(at - A.zg_code.begin());
+        A.st_pos[k] = 4 * e + ((*at & 255) == (want & 255) ? 0 : 2) + (f.z > H);
+    }
+    return A;
+}
+
 }  // namespace kfbi

@@ -55,6 +55,36 @@ struct Plan3Host {
     int I() const { return (int)irr_node.size(); }
 };
 
+// What the GPU's apply reads instead of the plan's own tables.
+struct Apply3Host {
+    // the three sums a crossing needs of its fit neighbours (dv the density there minus
+    // that at the point): along its own axis a the jumps of v_a and v_aa, and the
+    // far-side jump terms of its interpolation; 3 per neighbour (weight w of neighbour e
+    // at w E + e, E neighbours in all) and 3 per point: the parts of [v_aa] and of the
+    // far-side terms in [v_nn], and of the latter in [v]
+    std::vector<double> fit;        // 3 E
+    std::vector<double> point;      // 3 M: n_a^2, coefficient of [v_nn], coefficient of [v]
+    std::vector<int> st_node;       // 10 M, node s of point m at s M + m
+    std::vector<double> st_w;       // 10 M, the same order
+    // N <= kSlabMax: the irregular nodes in pieces, one for each folded column (x, y' =
+    // min(y, N - y)) and height z' = min(z, N - z): node (y, z) is number 2 (y > N / 2) +
+    // (z > N / 2) of its piece.  Row r holds 64 pieces (one a lane), wavefront w of a half
+    // plane's workgroup (N / 8 of them) adds rows sp_wave[w] to sp_wave[w + 1], and the
+    // pieces of a column follow each other in one lane
+    std::vector<int> sp_wave;       // N / 8 + 1
+    std::vector<int> sp_piece;      // 64 per row: x - 1 | (y' - 1) << 8 | z' << 16, -1: none
+    std::vector<int> irr_pos;       // I: place of the irregular node's correction, 4 piece + number
+    int y_first = 0;                // the least y' - 1 of a piece or a stencil's node
+    // and the stencils' nodes by tile of 32 folded columns, tile (y' - 1) (N / 32) + (x - 1) / 32,
+    // as entries of two folded heights z1, z2 (z' = min(z, N - z)) of one column on one
+    // side: entry e makes the nodes z1, N - z1, z2, N - z2 in this order, at 4 e
+    std::vector<int> zg_off;        // tiles + 1
+    std::vector<int> zg_code;       // z1 | z2 << 8 | (x - 1) % 32 << 16 | side << 24
+    std::vector<int> st_pos;        // 10 M, as st_node: the node's place there
+};
+constexpr int kSlabMax = 128;       // the largest N whose half plane fits a workgroup's LDS
+Apply3Host build_apply3(const Plan3Host& P);
+
 // Throws GeometryError when the ellipsoid is not strictly inside the box or
 // the grid is not supported.
 Plan3Host build_plan3(int N, double lo, double hi, const double axes[3]);

@@ -589,7 +589,7 @@ class Problem3:
     def apply(self, phi, out=None):
         if out is None:
             out = torch.empty_like(phi)
-        with self.ctx:
+        with self.ctx.waiting:
             _check(_lib.kfbi3_apply(self._h, _dptr(phi, "phi", self.M), _dptr(out, "out", self.M)))
         return out
 

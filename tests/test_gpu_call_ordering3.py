@@ -1,5 +1,4 @@
-"""The three-dimensional apply returns before its work has run: what the caller
-enqueues next is ordered after it by events."""
+"""What the caller enqueues after a three-dimensional apply sees its result."""
 import numpy as np
 import pytest
 import torch
