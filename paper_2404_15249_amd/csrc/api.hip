@@ -1541,15 +1541,12 @@ struct kfbi_batch {
     std::vector<kfbi_prob*> slot;
     std::vector<size_t> slot_bytes;
     std::vector<SlotDev> h_slots;
-    SlotDev* d_slots = nullptr;
-    int* d_counts = nullptr;
-    int2* d_mode = nullptr;
-    int2* d_cp = nullptr;
-    int2* d_gm = nullptr;
-    int cap_mode = 0, cap_cp = 0, cap_gm = 0;
-    std::vector<int2> h_mode, h_cp, h_gm;
+    char* d_work = nullptr;           // counts, slots and work lists (batch_work)
+    size_t cap_work = 0;
+    std::vector<int2> h_items;
     int live = 0;
-    int h_counts[kBatchCounts] = {0, 0, 0};
+    GmresState* d_states = nullptr;   // max_slots: the poll's
+    GmresState* h_states = nullptr;   // the same in pinned memory
     // pinned staging of the uploads, reused once the event says the stream has
     // consumed the previous upload
     char* stage = nullptr;
@@ -1562,63 +1559,61 @@ struct kfbi_batch {
 
 namespace {
 
-void batch_free_lists(kfbi_batch* B) {
-    for (void* q : {(void*)B->d_mode, (void*)B->d_cp, (void*)B->d_gm})
-        if (q) hipFree(q);
-    B->d_mode = nullptr;
-    B->d_cp = nullptr;
-    B->d_gm = nullptr;
-    B->cap_mode = B->cap_cp = B->cap_gm = 0;
-}
+constexpr size_t kBatchHead = 64;    // bytes of the counts, before the slots
 
-kfbi_status batch_grow(hipStream_t s, int2** d, int* cap, size_t need) {
-    if ((size_t)*cap >= need) return KFBI_OK;
-    size_t nc = std::max<size_t>(need, 2 * (size_t)*cap);
-    if (*d) {
-        HIP_TRY(hipStreamSynchronize(s));   // queued launches may still read the old list
-        hipFree(*d);
-    }
-    *d = nullptr;
-    if (hipMalloc((void**)d, nc * sizeof(int2)) != hipSuccess) {
-        hipGetLastError();
-        *cap = 0;
-        return set_err(KFBI_ERR_OOM, "batch work list allocation failed");
-    }
-    *cap = (int)nc;
-    return KFBI_OK;
+BatchWork batch_work(const kfbi_batch* B) {
+    BatchWork w;
+    w.counts = reinterpret_cast<const int*>(B->d_work);
+    w.slots = reinterpret_cast<const SlotDev*>(B->d_work + kBatchHead);
+    w.items = reinterpret_cast<const int2*>(B->d_work + kBatchHead + sizeof(SlotDev) * B->max_slots);
+    return w;
 }
 
 // Rebuild the work lists of the live slots and upload them (stream ordered).
 kfbi_status batch_rebuild(kfbi_batch* B) {
-    B->h_mode.clear();
-    B->h_cp.clear();
-    B->h_gm.clear();
-    B->live = 0;
-    for (int s = 0; s < B->max_slots; ++s) {
-        kfbi_prob* p = B->slot[s];
-        if (!p) continue;
-        B->live += 1;
-        for (int b = 0; b < p->Gs; ++b) B->h_mode.push_back(make_int2(s, b));
-        B->h_cp.push_back(make_int2(s, -1));             // the commit, the longest of the slot's items, first
-        for (int c = 0; c < p->M; c += 64) B->h_cp.push_back(make_int2(s, c));
-        for (int c = 0; c < p->gm.gc + p->dp.n_cc; ++c) B->h_gm.push_back(make_int2(s, c));
+    static_assert(sizeof(int) * (kBatchLists + 1) <= kBatchHead && sizeof(SlotDev) % alignof(int2) == 0, "layout");
+    int counts[kBatchLists + 1] = {0, 0, 0, 0};
+    B->h_items.clear();
+    std::vector<int> order;
+    for (int s = 0; s < B->max_slots; ++s)
+        if (B->slot[s]) order.push_back(s);
+    B->live = (int)order.size();
+    // the modes' items of the largest grids first: the longest, one a workgroup before
+    // the shorter ones fill up
+    std::vector<int> by_size = order;
+    std::stable_sort(by_size.begin(), by_size.end(), [&](int a, int b) { return B->slot[a]->N > B->slot[b]->N; });
+    for (int s : by_size)
+        for (int b = 0; b < B->slot[s]->Gs; ++b) B->h_items.push_back(make_int2(s, b));
+    counts[kBatchReduce] = (int)B->h_items.size();
+    for (int s : order) {
+        B->h_items.push_back(make_int2(s, -1));          // the commit, the longest of the slot's items, first
+        for (int c = 0; c < B->slot[s]->M; c += 64) B->h_items.push_back(make_int2(s, c));
     }
-    const int2* old[3] = {B->d_mode, B->d_cp, B->d_gm};
-    hipStream_t gs = B->ctx->stream;
-    if (kfbi_status e = batch_grow(gs, &B->d_mode, &B->cap_mode, std::max<size_t>(B->h_mode.size(), 1))) return e;
-    if (kfbi_status e = batch_grow(gs, &B->d_cp, &B->cap_cp, std::max<size_t>(B->h_cp.size(), 1))) return e;
-    if (kfbi_status e = batch_grow(gs, &B->d_gm, &B->cap_gm, std::max<size_t>(B->h_gm.size(), 1))) return e;
-    if (old[0] != B->d_mode || old[1] != B->d_cp || old[2] != B->d_gm) {
-        // the captured graph holds the old list addresses
+    counts[kBatchSteps] = (int)B->h_items.size();
+    for (int s : order)
+        for (int c = 0; c < B->slot[s]->gm.gc + B->slot[s]->dp.n_cc; ++c) B->h_items.push_back(make_int2(s, c));
+    counts[kBatchLists] = (int)B->h_items.size();
+    for (int s = 0; s < B->max_slots; ++s) B->h_slots[s].live = B->slot[s] != nullptr;
+    hipStream_t s = B->ctx->stream;
+    const size_t slots = sizeof(SlotDev) * B->max_slots, items = sizeof(int2) * B->h_items.size();
+    const size_t nb = kBatchHead + slots + items;
+    if (nb > B->cap_work) {
+        const size_t cap = std::max(nb, kBatchHead + slots + 2 * (B->cap_work ? B->cap_work - kBatchHead - slots : 0));
+        if (B->d_work) {
+            HIP_TRY(hipStreamSynchronize(s));            // queued launches may still read the old lists
+            hipFree(B->d_work);
+        }
+        B->d_work = nullptr;
+        B->cap_work = 0;
+        // the recorded graph holds the old address
         if (B->gexec) hipGraphExecDestroy(B->gexec);
         B->gexec = nullptr;
+        if (hipMalloc((void**)&B->d_work, cap) != hipSuccess) {
+            hipGetLastError();
+            return set_err(KFBI_ERR_OOM, "batch work list allocation failed");
+        }
+        B->cap_work = cap;
     }
-    hipStream_t s = B->ctx->stream;
-    B->h_counts[0] = (int)B->h_mode.size();
-    B->h_counts[1] = (int)B->h_cp.size();
-    B->h_counts[2] = (int)B->h_gm.size();
-    const size_t nb = sizeof(int2) * (B->h_mode.size() + B->h_cp.size() + B->h_gm.size()) +
-                      sizeof(int) * kBatchCounts + sizeof(SlotDev) * B->max_slots;
     HIP_TRY(hipEventSynchronize(B->up_ev));
     if (nb > B->stage_cap) {
         if (B->stage) hipHostFree(B->stage);
@@ -1628,37 +1623,17 @@ kfbi_status batch_rebuild(kfbi_batch* B) {
         B->stage_cap = 2 * nb;
     }
     // upload, ordered on the stream after the work that used the previous lists
-    char* q = B->stage;
-    auto put = [&](void* dst, const void* src, size_t bytes) -> kfbi_status {
-        if (!bytes) return KFBI_OK;
-        std::memcpy(q, src, bytes);
-        HIP_TRY(hipMemcpyAsync(dst, q, bytes, hipMemcpyHostToDevice, s));
-        q += bytes;
-        return KFBI_OK;
-    };
-    kfbi_status e = KFBI_OK;
-    if ((e = put(B->d_mode, B->h_mode.data(), B->h_mode.size() * sizeof(int2))) ||
-        (e = put(B->d_cp, B->h_cp.data(), B->h_cp.size() * sizeof(int2))) ||
-        (e = put(B->d_gm, B->h_gm.data(), B->h_gm.size() * sizeof(int2))) ||
-        (e = put(B->d_counts, B->h_counts, sizeof B->h_counts)) ||
-        (e = put(B->d_slots, B->h_slots.data(), sizeof(SlotDev) * B->max_slots)))
-        return e;
+    std::memcpy(B->stage, counts, sizeof counts);
+    std::memcpy(B->stage + kBatchHead, B->h_slots.data(), slots);
+    if (items) std::memcpy(B->stage + kBatchHead + slots, B->h_items.data(), items);
+    HIP_TRY(hipMemcpyAsync(B->d_work, B->stage, nb, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(B->up_ev, s));
     return KFBI_OK;
 }
 
-BatchWork batch_work(const kfbi_batch* B) {
-    BatchWork w;
-    w.counts = B->d_counts;
-    w.mode_items = B->d_mode;
-    w.cp_items = B->d_cp;
-    w.gm_items = B->d_gm;
-    return w;
-}
-
 kfbi_status batch_enqueue_steps(kfbi_batch* B, int nsteps, hipStream_t s) {
     for (int k = 0; k < nsteps; ++k)
-        HIP_TRY(launch_batch_step(B->d_slots, batch_work(B), B->ctx->num_cu, s));
+        HIP_TRY(launch_batch_step(batch_work(B), B->ctx->num_cu, s));
     return KFBI_OK;
 }
 
@@ -1713,8 +1688,8 @@ kfbi_status kfbi_batch_create(kfbi_ctx* ctx, int max_slots, int m_max, size_t bu
     B->slot_bytes.assign(max_slots, 0);
     B->h_slots.resize(max_slots);
     bool ok = hipEventCreateWithFlags(&B->up_ev, hipEventDisableTiming) == hipSuccess &&
-              hipMalloc((void**)&B->d_slots, sizeof(SlotDev) * max_slots) == hipSuccess &&
-              hipMalloc((void**)&B->d_counts, sizeof(int) * kBatchCounts) == hipSuccess;
+              hipMalloc((void**)&B->d_states, sizeof(GmresState) * max_slots) == hipSuccess &&
+              hipHostMalloc((void**)&B->h_states, sizeof(GmresState) * max_slots) == hipSuccess;
     if (!ok) {
         hipGetLastError();
         kfbi_batch_destroy(B);
@@ -1733,9 +1708,9 @@ kfbi_status kfbi_batch_destroy(kfbi_batch* B) {
     hipSetDevice(B->ctx->device);
     hipStreamSynchronize(B->ctx->stream);
     if (B->gexec) hipGraphExecDestroy(B->gexec);
-    batch_free_lists(B);
-    for (void* q : {(void*)B->d_slots, (void*)B->d_counts})
+    for (void* q : {(void*)B->d_work, (void*)B->d_states})
         if (q) hipFree(q);
+    if (B->h_states) hipHostFree(B->h_states);
     if (B->stage) hipHostFree(B->stage);
     if (B->up_ev) hipEventDestroy(B->up_ev);
     delete B;
@@ -1779,7 +1754,6 @@ kfbi_status kfbi_batch_admit(kfbi_batch* B, kfbi_prob* p, const double* f_grid, 
     S.corr_il = p->corr_il;
     S.partial = p->partial_b;
     S.Gs = p->Gs;
-    S.pad = 0;
     p->b_modes = p->modes_of;
     p->b_fgrid = f_grid;
     p->b_fgam = f_gamma;
@@ -1811,10 +1785,13 @@ kfbi_status kfbi_batch_poll(kfbi_batch* B, int* state, int* iters, double* rel_r
     if (!B) return set_err(KFBI_ERR_ARG, "batch is NULL");
     HIP_TRY(hipSetDevice(B->ctx->device));
     hipStream_t s = B->ctx->stream;
-    for (int k = 0; k < B->max_slots; ++k)
-        if (B->slot[k]) HIP_TRY(hipMemcpyAsync(&B->slot[k]->st_host, B->slot[k]->gm.st, sizeof(GmresState),
-                                               hipMemcpyDeviceToHost, s));
+    if (B->live) {
+        HIP_TRY(launch_batch_states(batch_work(B), B->max_slots, B->d_states, s));
+        HIP_TRY(hipMemcpyAsync(B->h_states, B->d_states, sizeof(GmresState) * B->max_slots, hipMemcpyDeviceToHost, s));
+    }
     HIP_TRY(hipStreamSynchronize(s));
+    for (int k = 0; k < B->max_slots; ++k)
+        if (B->slot[k]) B->slot[k]->st_host = B->h_states[k];
     for (int k = 0; k < B->max_slots; ++k) {
         const kfbi_prob* p = B->slot[k];
         if (state) state[k] = !p ? -2 : p->st_host.converged == kGmNonfinite ? -3 : p->st_host.converged;

@@ -28,21 +28,29 @@ struct SlotDev {
     double* corr_il;   // interleaved corrections (T x 64)
     double* partial;   // Gs x M partial sums, one row per mode block
     int Gs;            // mode blocks: ceil((n-1) / batch_modes_per_group(N))
-    int pad;
+    int live;          // the slot holds a problem
 };
 
-// Work lists of the batched launches, rebuilt on the host when a slot is
-// admitted or released.  counts = {mode items, reduce items, step items}; items
-// are (slot, first index) pairs.
-struct BatchWork {
-    const int* counts;
-    const int2* mode_items;   // mode blocks of batch_modes_per_group(N) modes
-    const int2* cp_items;     // blocks of 64 samples, and (slot, -1) the commit
-    const int2* gm_items;     // (slot, chunk): vector chunks, then correction chunks
+// Work lists of the batched launches, rebuilt on the host when a slot is admitted or
+// released: (slot, first index) pairs, one list after the other in items, list k from
+// counts[k] up to counts[k + 1]:
+enum BatchList {
+    kBatchModes = 0,    // mode blocks of batch_modes_per_group(N) modes, the largest grids first
+    kBatchReduce = 1,   // blocks of 64 samples, and (slot, -1) the commit
+    kBatchSteps = 2,    // (slot, chunk): vector chunks, then correction chunks
+    kBatchLists = 3
 };
-constexpr int kBatchCounts = 3;
+// The counts, the slots and the items are one allocation and one upload: an admission
+// or a release copied five arrays before, 3 us of the stream each.
+struct BatchWork {
+    const int* counts;        // kBatchLists + 1
+    const SlotDev* slots;
+    const int2* items;
+};
 
 size_t modes_b_lds_bytes();
-hipError_t launch_batch_step(const SlotDev* slots, BatchWork w, int n_cu, hipStream_t s);
+hipError_t launch_batch_step(BatchWork w, int n_cu, hipStream_t s);
+// out[k] <- the GMRES state of slot k, live slots only
+hipError_t launch_batch_states(BatchWork w, int max_slots, GmresState* out, hipStream_t s);
 
 }  // namespace kfbi

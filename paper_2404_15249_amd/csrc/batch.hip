@@ -30,9 +30,10 @@ __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __re
     ModesLds L;
     L.sq = smem;
     L.xs = smem + kBatchTable;
-    const int n_items = w.counts[0];
+    static_assert(kBatchModes == 0, "the first list");
+    const int n_items = w.counts[1];
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const int2 item = w.mode_items[it];
+        const int2 item = w.items[it];
         const SlotDev& S = slots[item.x];
         if (slot_done(S)) continue;
         const DevPlan& p = S.p;
@@ -49,12 +50,12 @@ __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __re
 }
 
 // A slot's reduce items: 64 samples from item.y on, or (item.y < 0) its commit.
-__global__ __launch_bounds__(1024) void k_reduce_b(const SlotDev* __restrict__ slots, BatchWork w) {
+__global__ __launch_bounds__(1024) void k_reduce_b(BatchWork w) {
     __shared__ double red[16 * 64];
-    const int n_items = w.counts[1];
-    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const int2 item = w.cp_items[it];
-        const SlotDev& S = slots[item.x];
+    const int n_items = w.counts[kBatchReduce + 1];
+    for (int it = w.counts[kBatchReduce] + blockIdx.x; it < n_items; it += gridDim.x) {
+        const int2 item = w.items[it];
+        const SlotDev& S = w.slots[item.x];
         if (item.y < 0) {
             gm_commit(S.b, S.p.M);
         } else if (!slot_done(S)) {
@@ -70,11 +71,11 @@ __global__ __launch_bounds__(1024) void k_reduce_b(const SlotDev* __restrict__ s
 
 // GMRES (gmres.h): the step launch walks (slot, chunk) items, the vector's chunks
 // and then the correction chunks of each slot.
-__global__ __launch_bounds__(kGmChunk) void k_gm_step_b(const SlotDev* __restrict__ slots, BatchWork w) {
-    const int n_items = w.counts[2];
-    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const int2 item = w.gm_items[it];
-        const SlotDev& S = slots[item.x];
+__global__ __launch_bounds__(kGmChunk) void k_gm_step_b(BatchWork w) {
+    const int n_items = w.counts[kBatchSteps + 1];
+    for (int it = w.counts[kBatchSteps] + blockIdx.x; it < n_items; it += gridDim.x) {
+        const int2 item = w.items[it];
+        const SlotDev& S = w.slots[item.x];
         if (item.y < S.b.gc) {
             gm_step(S.p.taps, S.b, S.p.M, item.y);
         } else {
@@ -84,6 +85,12 @@ __global__ __launch_bounds__(kGmChunk) void k_gm_step_b(const SlotDev* __restric
     }
 }
 
+// The poll's states, together: a copy for each slot took 3 us of the stream and more of
+// the host (twelve of them four times were a fifth of a batch of 12).
+__global__ __launch_bounds__(64) void k_states_b(BatchWork w, int max_slots, GmresState* __restrict__ out) {
+    const int k = blockIdx.x * 64 + threadIdx.x;
+    if (k < max_slots && w.slots[k].live) out[k] = *w.slots[k].b.st;
+}
 
 }  // namespace
 
@@ -91,13 +98,17 @@ size_t modes_b_lds_bytes() {
     return sizeof(double) * ((size_t)kBatchTable + (size_t)kBatchXs);
 }
 
-hipError_t launch_batch_step(const SlotDev* slots, BatchWork w, int n_cu, hipStream_t s) {
+hipError_t launch_batch_step(BatchWork w, int n_cu, hipStream_t s) {
     const size_t lds = modes_b_lds_bytes();
     if (hipError_t e = hipFuncSetAttribute((const void*)k_modes_b, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))
         return e;
-    if (hipError_t e = klaunch(&k_modes_b, dim3(n_cu), dim3(kModeWaves * 64), lds, s, slots, w)) return e;
-    if (hipError_t e = klaunch(&k_reduce_b, dim3(n_cu), dim3(1024), 0, s, slots, w)) return e;
-    return klaunch(&k_gm_step_b, dim3(n_cu), dim3(kGmChunk), 0, s, slots, w);
+    if (hipError_t e = klaunch(&k_modes_b, dim3(n_cu), dim3(kModeWaves * 64), lds, s, w.slots, w)) return e;
+    if (hipError_t e = klaunch(&k_reduce_b, dim3(n_cu), dim3(1024), 0, s, w)) return e;
+    return klaunch(&k_gm_step_b, dim3(n_cu), dim3(kGmChunk), 0, s, w);
+}
+
+hipError_t launch_batch_states(BatchWork w, int max_slots, GmresState* out, hipStream_t s) {
+    return klaunch(&k_states_b, dim3((max_slots + 63) / 64), dim3(64), 0, s, w, max_slots, out);
 }
 
 }  // namespace kfbi
