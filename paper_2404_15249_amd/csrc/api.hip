@@ -1543,7 +1543,7 @@ struct kfbi_batch {
     std::vector<SlotDev> h_slots;
     char* d_work = nullptr;           // counts, slots and work lists (batch_work)
     size_t cap_work = 0;
-    std::vector<int2> h_items;
+    bool stale = false;               // the slots changed since the last upload
     int live = 0;
     GmresState* d_states = nullptr;   // max_slots: the poll's
     GmresState* h_states = nullptr;   // the same in pinned memory
@@ -1569,36 +1569,25 @@ BatchWork batch_work(const kfbi_batch* B) {
     return w;
 }
 
-// Rebuild the work lists of the live slots and upload them (stream ordered).
-kfbi_status batch_rebuild(kfbi_batch* B) {
+// The slots have changed: room for their work lists on the device and in the staging
+// buffer, which batch_upload fills before the next launch that reads them (one upload
+// for a run of admissions or releases).
+kfbi_status batch_changed(kfbi_batch* B) {
     static_assert(sizeof(int) * (kBatchLists + 1) <= kBatchHead && sizeof(SlotDev) % alignof(int2) == 0, "layout");
-    int counts[kBatchLists + 1] = {0, 0, 0, 0};
-    B->h_items.clear();
-    std::vector<int> order;
-    for (int s = 0; s < B->max_slots; ++s)
-        if (B->slot[s]) order.push_back(s);
-    B->live = (int)order.size();
-    // the modes' items of the largest grids first: the longest, one a workgroup before
-    // the shorter ones fill up
-    std::vector<int> by_size = order;
-    std::stable_sort(by_size.begin(), by_size.end(), [&](int a, int b) { return B->slot[a]->N > B->slot[b]->N; });
-    for (int s : by_size)
-        for (int b = 0; b < B->slot[s]->Gs; ++b) B->h_items.push_back(make_int2(s, b));
-    counts[kBatchReduce] = (int)B->h_items.size();
-    for (int s : order) {
-        B->h_items.push_back(make_int2(s, -1));          // the commit, the longest of the slot's items, first
-        for (int c = 0; c < B->slot[s]->M; c += 64) B->h_items.push_back(make_int2(s, c));
+    size_t n_items = 0;
+    B->live = 0;
+    B->stale = true;
+    for (int s = 0; s < B->max_slots; ++s) {
+        const kfbi_prob* p = B->slot[s];
+        B->h_slots[s].live = p != nullptr;
+        if (!p) continue;
+        B->live += 1;
+        n_items += p->Gs + 1 + (p->M + 63) / 64 + p->gm.gc + p->dp.n_cc;
     }
-    counts[kBatchSteps] = (int)B->h_items.size();
-    for (int s : order)
-        for (int c = 0; c < B->slot[s]->gm.gc + B->slot[s]->dp.n_cc; ++c) B->h_items.push_back(make_int2(s, c));
-    counts[kBatchLists] = (int)B->h_items.size();
-    for (int s = 0; s < B->max_slots; ++s) B->h_slots[s].live = B->slot[s] != nullptr;
     hipStream_t s = B->ctx->stream;
-    const size_t slots = sizeof(SlotDev) * B->max_slots, items = sizeof(int2) * B->h_items.size();
-    const size_t nb = kBatchHead + slots + items;
+    const size_t fixed = kBatchHead + sizeof(SlotDev) * B->max_slots, nb = fixed + sizeof(int2) * n_items;
     if (nb > B->cap_work) {
-        const size_t cap = std::max(nb, kBatchHead + slots + 2 * (B->cap_work ? B->cap_work - kBatchHead - slots : 0));
+        const size_t cap = std::max(nb, fixed + 2 * (B->cap_work ? B->cap_work - fixed : 0));
         if (B->d_work) {
             HIP_TRY(hipStreamSynchronize(s));            // queued launches may still read the old lists
             hipFree(B->d_work);
@@ -1614,20 +1603,53 @@ kfbi_status batch_rebuild(kfbi_batch* B) {
         }
         B->cap_work = cap;
     }
-    HIP_TRY(hipEventSynchronize(B->up_ev));
     if (nb > B->stage_cap) {
+        HIP_TRY(hipEventSynchronize(B->up_ev));
         if (B->stage) hipHostFree(B->stage);
         B->stage = nullptr;
         B->stage_cap = 0;
         HIP_TRY(hipHostMalloc((void**)&B->stage, 2 * nb));
         B->stage_cap = 2 * nb;
     }
-    // upload, ordered on the stream after the work that used the previous lists
-    std::memcpy(B->stage, counts, sizeof counts);
+    return KFBI_OK;
+}
+
+// The work lists of the live slots, uploaded if the slots changed since the last time
+// (ordered on the stream after the work that used the previous ones).
+kfbi_status batch_upload(kfbi_batch* B) {
+    if (!B->stale) return KFBI_OK;
+    if (!B->d_work || !B->stage) {                       // an allocation failed before
+        if (kfbi_status e = batch_changed(B)) return e;
+    }
+    HIP_TRY(hipEventSynchronize(B->up_ev));
+    const size_t slots = sizeof(SlotDev) * B->max_slots;
+    int* counts = reinterpret_cast<int*>(B->stage);
+    int2* items = reinterpret_cast<int2*>(B->stage + kBatchHead + slots);
+    int n = 0;
+    counts[kBatchModes] = 0;
+    std::vector<int> order;
+    for (int s = 0; s < B->max_slots; ++s)
+        if (B->slot[s]) order.push_back(s);
+    // the modes' items of the largest grids first: the longest, one a workgroup before
+    // the shorter ones fill up
+    std::vector<int> by_size = order;
+    std::stable_sort(by_size.begin(), by_size.end(), [&](int a, int b) { return B->slot[a]->N > B->slot[b]->N; });
+    for (int s : by_size)
+        for (int b = 0; b < B->slot[s]->Gs; ++b) items[n++] = make_int2(s, b);
+    counts[kBatchReduce] = n;
+    for (int s : order) {
+        items[n++] = make_int2(s, -1);                   // the commit, the longest of the slot's items, first
+        for (int c = 0; c < B->slot[s]->M; c += 64) items[n++] = make_int2(s, c);
+    }
+    counts[kBatchSteps] = n;
+    for (int s : order)
+        for (int c = 0; c < B->slot[s]->gm.gc + B->slot[s]->dp.n_cc; ++c) items[n++] = make_int2(s, c);
+    counts[kBatchLists] = n;
     std::memcpy(B->stage + kBatchHead, B->h_slots.data(), slots);
-    if (items) std::memcpy(B->stage + kBatchHead + slots, B->h_items.data(), items);
-    HIP_TRY(hipMemcpyAsync(B->d_work, B->stage, nb, hipMemcpyHostToDevice, s));
+    hipStream_t s = B->ctx->stream;
+    HIP_TRY(hipMemcpyAsync(B->d_work, B->stage, kBatchHead + slots + sizeof(int2) * n, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(B->up_ev, s));
+    B->stale = false;
     return KFBI_OK;
 }
 
@@ -1695,7 +1717,7 @@ kfbi_status kfbi_batch_create(kfbi_ctx* ctx, int max_slots, int m_max, size_t bu
         kfbi_batch_destroy(B);
         return set_err(KFBI_ERR_OOM, "batch allocation failed");
     }
-    if (kfbi_status e = batch_rebuild(B)) {
+    if (kfbi_status e = batch_changed(B)) {
         kfbi_batch_destroy(B);
         return e;
     }
@@ -1760,7 +1782,7 @@ kfbi_status kfbi_batch_admit(kfbi_batch* B, kfbi_prob* p, const double* f_grid, 
     B->slot[free_slot] = p;
     B->slot_bytes[free_slot] = p->bytes;
     B->used += p->bytes;
-    if (kfbi_status e = batch_rebuild(B)) return e;
+    if (kfbi_status e = batch_changed(B)) return e;
     *slot = free_slot;
     return KFBI_OK;
 }
@@ -1769,6 +1791,7 @@ kfbi_status kfbi_batch_step(kfbi_batch* B, int nsteps) {
     if (!B || nsteps < 0) return set_err(KFBI_ERR_ARG, "bad arguments");
     if (B->live == 0 || nsteps == 0) return KFBI_OK;
     HIP_TRY(hipSetDevice(B->ctx->device));
+    if (kfbi_status e = batch_upload(B)) return e;
     batch_ensure_graph(B);
     const int K = kfbi_batch::kGraphSteps;
     for (int done = 0; done < nsteps; done += K) {
@@ -1786,6 +1809,7 @@ kfbi_status kfbi_batch_poll(kfbi_batch* B, int* state, int* iters, double* rel_r
     HIP_TRY(hipSetDevice(B->ctx->device));
     hipStream_t s = B->ctx->stream;
     if (B->live) {
+        if (kfbi_status e = batch_upload(B)) return e;
         HIP_TRY(launch_batch_states(batch_work(B), B->max_slots, B->d_states, s));
         HIP_TRY(hipMemcpyAsync(B->h_states, B->d_states, sizeof(GmresState) * B->max_slots, hipMemcpyDeviceToHost, s));
     }
@@ -1819,7 +1843,7 @@ kfbi_status kfbi_batch_finish(kfbi_batch* B, int slot, double* u_grid, double* u
     B->slot[slot] = nullptr;
     B->slot_bytes[slot] = 0;
     p->b_fgrid = p->b_fgam = nullptr;
-    if (kfbi_status e = batch_rebuild(B)) return e;
+    if (kfbi_status e = batch_changed(B)) return e;
     return bad ? set_err(KFBI_ERR_NONFINITE, "NaN or Inf in the slot's f, f_gamma or g") : KFBI_OK;
 }
 
