@@ -243,7 +243,9 @@ hipError_t launch_spline(const DevPlan& p, const double* y, double* s2, const in
 // `from` (gm null) out = from - the result
 hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* partial, int G, double* out,
                                 const int* skip, const GmresBufs* gm, hipStream_t s, const double* from = nullptr);
-hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* R, double* out, hipStream_t s);
+// v+ (or d_n v+) at the samples from a grid solution V in the padded layout, or (user)
+// on the caller's grid
+hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* V, bool user, double* out, hipStream_t s);
 hipError_t launch_fill_rhs(const DevPlan& p, const double* f, bool mask, double* R, hipStream_t s);
 // column sine transforms (dst.hip): FP64, and FP32 arithmetic reading an FP64
 // grid into FP32 storage or reading FP32 storage into an FP64 grid (written or

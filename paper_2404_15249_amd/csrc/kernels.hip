@@ -98,8 +98,9 @@ __global__ __launch_bounds__(1024) void k_reduce_interp(DevPlan p, JumpSrc js, c
     reduce_samples64(p, js, partial, G, blockIdx.x * 64, out, red, skip, from);
 }
 
-// Interpolation from a full grid solution (dense path): R in the padded interior layout.
-__global__ __launch_bounds__(256) void k_interp_grid(DevPlan p, JumpSrc js, const double* __restrict__ R,
+// Interpolation from a full grid solution (dense path): V in the padded interior
+// layout, or (user) the caller's grid.
+__global__ __launch_bounds__(256) void k_interp_grid(DevPlan p, JumpSrc js, const double* __restrict__ V, int user,
                                                      double* __restrict__ out) {
     const int cp = blockIdx.x * blockDim.x + threadIdx.x;
     if (cp >= p.M) return;
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256) void k_interp_grid(DevPlan p, JumpSrc js, cons
     stencil_nodes(p, cp, ni, nj);
     const double* w = p.cp_w + cp;
     double s = 0.0;
-    for (int k = 0; k < 6; ++k) s += w[(size_t)k * p.M] * R[(size_t)(nj[k] - 1) * p.N + (ni[k] - 1)];
+    for (int k = 0; k < 6; ++k) s += w[(size_t)k * p.M] * (user ? V[(size_t)nj[k] * (p.N + 1) + ni[k]] : V[(size_t)(nj[k] - 1) * p.N + (ni[k] - 1)]);
     out[cp] = s + outside_terms(p, js, cp, ni, nj, w, p.M);
 }
 
@@ -410,8 +411,8 @@ hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* part
     return hipGetLastError();
 }
 
-hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* R, double* out, hipStream_t s) {
-    if (hipError_t e_ = klaunch(&k_interp_grid, dim3((p.M + 255) / 256), dim3(256), 0, s, p, js, R, out)) return e_;
+hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* V, bool user, double* out, hipStream_t s) {
+    if (hipError_t e_ = klaunch(&k_interp_grid, dim3((p.M + 255) / 256), dim3(256), 0, s, p, js, V, user ? 1 : 0, out)) return e_;
     return hipGetLastError();
 }
 
