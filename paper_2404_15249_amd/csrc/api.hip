@@ -92,7 +92,6 @@ struct kfbi_prob {
     double* A = nullptr;         // N N
     int precision = KFBI_FP64, refine = 0;
     float* X32 = nullptr;        // N N: FP32 transform storage (KFBI_FP32_REFINED)
-    double* D = nullptr;         // N N: a refinement correction (refine_steps >= 2)
     int dstB = 8;                // columns per workgroup of the column transforms
     int Gcap = 1;                // workgroups the partial buffer has room for
     double* tmpM = nullptr;      // M
@@ -205,27 +204,23 @@ size_t cpx_bytes(int precision) { return precision == KFBI_FP64 ? 2 * sizeof(dou
 
 
 // Alg. 4 on the full grid with FP32 transforms (KFBI_FP32_REFINED): solve
-// (L_h - kappa) V = R (R in the padded interior layout, consumed) into A: an FP32 solve
-// (FP32 column transforms around the FP64 row solves) of R, then per refine step
-// R <- R - (L_h - kappa) d for the last correction d (FP64), and the FP32 solve of R as
-// the next correction; A is the sum of them.  With the user's grids f and v instead
-// the first transform and the first residual read f and the last transform writes v:
-// at 2048^2 a copy into R and one out of A were 28 of a fast solve's 172 us.
+// (L_h - kappa) A = R (R in the padded interior layout): an FP32 solve (FP32 column
+// transforms around the FP64 row solves) of R into A, then per refine step the FP32 solve
+// of the residual R - (L_h - kappa) A (FP64, formed by the transform that reads it), which
+// the last transform adds to A.  With the user's grids f and v instead f is read there
+// and the last transform of all writes v: at 2048^2 a copy into R and one out of A were
+// 28 of a fast solve's 172 us.
 kfbi_status grid_solve_f32(kfbi_prob* p, const double* f = nullptr, double* v = nullptr) {
     hipStream_t s = p->ctx->stream;
     const double inv = 2.0 / p->N;
-    // corrections: the first lands in A; middle ones in D (then added to A while
-    // forming the next residual); the last is added to A by its transform
     for (int k = 0; k <= p->refine; ++k) {
-        if (k == 1) HIP_TRY(launch_residual(p->dp, p->A, f, p->R, nullptr, s));
-        if (k >= 2) HIP_TRY(launch_residual(p->dp, p->D, nullptr, p->R, p->A, s));
-        if (f && k == 0) HIP_TRY(launch_dst_from_grid_f32(p->dp, f, p->X32, p->dstB, s));
+        if (k > 0) HIP_TRY(launch_dst_residual_f32(p->dp, f ? f : p->R, f != nullptr, p->A, p->X32, p->dstB, s));
+        else if (f) HIP_TRY(launch_dst_from_grid_f32(p->dp, f, p->X32, p->dstB, s));
         else HIP_TRY(launch_dst_cols_f32(p->dp, p->R, p->X32, 1.0, p->dstB, s));
         HIP_TRY(launch_rows_solve_f32(p->dp, p->X32, s));
-        const bool last = k == p->refine, middle = k > 0 && !last;
-        const double* add = k > 0 && last ? p->A : nullptr;
-        if (v && last) HIP_TRY(launch_dst_f32_to_grid(p->dp, p->X32, v, inv, add, p->dstB, s));
-        else HIP_TRY(launch_dst_cols_f32_to64(p->dp, p->X32, middle ? p->D : p->A, inv, add, p->dstB, s));
+        const double* add = k > 0 ? p->A : nullptr;
+        if (v && k == p->refine) HIP_TRY(launch_dst_f32_to_grid(p->dp, p->X32, v, inv, add, p->dstB, s));
+        else HIP_TRY(launch_dst_cols_f32_to64(p->dp, p->X32, p->A, inv, add, p->dstB, s));
     }
     return KFBI_OK;
 }
@@ -1069,7 +1064,6 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     if ((st = p->host.alloc())) return fail(st);
     p->gm.pub = p->host.pub;
     if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
-    if (p->refine >= 2 && (st = dev_alloc(p, &p->D, (size_t)n * n))) return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
     HIP_TRY(hipMemset(p->corr_d, 0, sizeof(double) * (size_t)dp.T * 64));

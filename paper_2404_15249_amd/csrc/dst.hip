@@ -123,7 +123,15 @@ struct pair_of<float> {
 // are read and written as zero.  So the right-hand side needs no copy into the padded
 // layout and the solution none out of it (two passes over the grid each, 13 + 13 us
 // at 2048^2 beside transforms of 23).
-enum DstIo { kPadded = 0, kFromGrid = 1, kToGrid = 2 };
+// The residual's forms (FP32 transforms) read a right-hand side R (padded, or the user's
+// grid) and a solution V (padded) and transform R - (L_h - kappa) V: 38 us at 2048^2,
+// where the launch that formed it took 23 and the transform that read it 20 more (the
+// rows above and below come from L2 again; half the loads in flight of the plain form).
+enum DstIo { kPadded = 0, kFromGrid = 1, kToGrid = 2, kResidual = 3, kResidualGrid = 4 };
+struct DstResidual {
+    const double* v;
+    double inv_h2, kappa;
+};
 struct alignas(8) GridPair {
     double x, y;
 };
@@ -139,6 +147,33 @@ __device__ __forceinline__ double2 grid_pair(const double* f, const unsigned cha
 __device__ __forceinline__ void grid_put(double* u, const unsigned char* mask8, int N, int j, int col, double x, double y) {
     const unsigned m = j < N ? mask_bits(mask8, N, j, col) : 0u;
     *reinterpret_cast<GridPair*>(u + (size_t)j * (N + 1) + col + 1) = GridPair{(m & 1) ? x : 0.0, (m & 2) ? y : 0.0};
+}
+
+// columns col, col + 1 of row j - 1 of the residual
+struct ResidualLoads {
+    double2 r, mid, up, down;
+    double left, right;
+};
+template <int IO>
+__device__ __forceinline__ ResidualLoads residual_loads(const double* r, const DstResidual& q, int N, int j, int col) {
+    ResidualLoads a;
+    const double* v = q.v + (size_t)(j - 1) * N + col;
+    a.r = IO == kResidualGrid ? grid_pair(r, nullptr, N, j, col)
+                              : *reinterpret_cast<const double2*>(r + (size_t)(j - 1) * N + col);
+    a.mid = *reinterpret_cast<const double2*>(v);
+    a.left = v[col > 0 ? -1 : 0];
+    a.right = v[col + 2 < N ? 2 : 1];
+    a.up = *reinterpret_cast<const double2*>(v + (j < N - 1 ? N : 0));
+    a.down = *reinterpret_cast<const double2*>(v - (j > 1 ? N : 0));
+    return a;
+}
+__device__ __forceinline__ double2 residual_of(const ResidualLoads& a, const DstResidual& q, int N, int j, int col) {
+    const double east = col + 2 < N ? a.mid.y : 0.0;         // column N - 1 is the pad
+    const double l = col > 0 ? a.left : 0.0, r = col + 3 < N ? a.right : 0.0;
+    const bool top = j == N - 1, low = j == 1;
+    const double ux = top ? 0.0 : a.up.x, uy = top ? 0.0 : a.up.y, dx = low ? 0.0 : a.down.x, dy = low ? 0.0 : a.down.y;
+    return make_double2(a.r.x - ((l + east + dx + ux - 4.0 * a.mid.x) * q.inv_h2 - q.kappa * a.mid.x),
+                        col + 2 < N ? a.r.y - ((a.mid.x + r + dy + uy - 4.0 * a.mid.y) * q.inv_h2 - q.kappa * a.mid.y) : 0.0);
 }
 
 constexpr int kDstThreads = 1024;   // 16 wavefronts per workgroup: the LDS tile limits a CU to one
@@ -244,7 +279,7 @@ template <class T, class Tin, class Tout, int B, int IO>
 __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, const double* __restrict__ sinq,
                                                           const Tin* in, Tout* out, double alpha, const Tout* add,
                                                           int ld, size_t slice, const int* __restrict__ skip,
-                                                          const unsigned char* __restrict__ mask8) {
+                                                          const unsigned char* __restrict__ mask8, DstResidual res) {
     if (skip && *skip) return;
     in += blockIdx.y * slice;
     out += blockIdx.y * slice;
@@ -282,7 +317,8 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
     // place 1 twice; threads past the last item redo it (the same values to
     // the same places).
     const int lh = log2N - 1;                                // log2 (N/2)
-    constexpr int LB = kLoadBatch / 2;
+    constexpr bool RES = IO == kResidual || IO == kResidualGrid;
+    constexpr int LB = RES ? 2 : kLoadBatch / 2;
     const int items = P << lh;
     auto place = [&](int q, int& lo) {
         const int r = N / 2 - q;                             // 1 .. N/2
@@ -291,6 +327,7 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
     };
     for (int base = 0; base < items; base += NTH * LB) {
         Vin va[LB], vb[LB];
+        ResidualLoads qa[RES ? LB : 1], qb[RES ? LB : 1];
         double sv[LB];
 #pragma unroll
         for (int u = 0; u < LB; ++u) {
@@ -299,7 +336,10 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
             int lo;
             const int i = place(idx >> LP, lo);
             const int j = bitrev(i, log2N);
-            if constexpr (IO == kFromGrid) {
+            if constexpr (RES) {
+                qa[u] = residual_loads<IO>(in, res, N, j, col0 + 2 * p);
+                qb[u] = residual_loads<IO>(in, res, N, N - j, col0 + 2 * p);
+            } else if constexpr (IO == kFromGrid) {
                 va[u] = grid_pair(in, mask8, N, j, col0 + 2 * p);
                 vb[u] = grid_pair(in, mask8, N, N - j, col0 + 2 * p);
             } else {
@@ -315,6 +355,11 @@ __global__ __launch_bounds__(kDstThreads) void k_dst_cols(int N, int log2N, cons
             int lo;
             const int i = place(idx >> LP, lo);
             cpx<T>* zp = z + p * NS;
+            if constexpr (RES) {
+                const int j = bitrev(i, log2N);
+                va[u] = residual_of(qa[u], res, N, j, col0 + 2 * p);
+                vb[u] = residual_of(qb[u], res, N, N - j, col0 + 2 * p);
+            }
             const T ax = (T)va[u].x, ay = (T)va[u].y;
             const T bx = (T)vb[u].x, by = (T)vb[u].y;
             const T sj = (T)sv[u];
@@ -781,6 +826,7 @@ struct Lines {
     size_t slice;
     const int* skip;
     const unsigned char* mask8;
+    DstResidual res;
 };
 
 template <class T, class Tin, class Tout, int B, int IO>
@@ -790,7 +836,7 @@ hipError_t dst_launch(const Lines& g, const Tin* in, Tout* out, double alpha, co
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))
         return e;
     if (hipError_t e_ = klaunch(&k_dst_cols<T, Tin, Tout, B, IO>, dim3(g.ld / B, g.slices), dim3(kDstThreads), lds, s,
-                                g.N, g.log2N, g.sinq, in, out, alpha, add, g.ld, g.slice, g.skip, g.mask8))
+                                g.N, g.log2N, g.sinq, in, out, alpha, add, g.ld, g.slice, g.skip, g.mask8, g.res))
         return e_;
     return hipGetLastError();
 }
@@ -826,7 +872,7 @@ hipError_t dst_dispatch(const Lines& g, const Tin* in, Tout* out, double alpha, 
     }
 }
 
-Lines grid2(const DevPlan& p) { return Lines{p.N, p.log2N, p.sinq, p.N, 1, 0, nullptr, nullptr}; }
+Lines grid2(const DevPlan& p) { return Lines{p.N, p.log2N, p.sinq, p.N, 1, 0, nullptr, nullptr, {}}; }
 
 }  // namespace
 
@@ -884,6 +930,14 @@ hipError_t launch_dst_from_grid_f32(const DevPlan& p, const double* f, float* ou
     return dst_dispatch<float, double, float, kFromGrid>(grid2(p), f, out, 1.0, nullptr, B, s);
 }
 
+hipError_t launch_dst_residual_f32(const DevPlan& p, const double* r, bool user, const double* v, float* out, int B,
+                                   hipStream_t s) {
+    Lines g = grid2(p);
+    g.res = DstResidual{v, p.inv_h2, p.kappa};
+    if (user) return dst_dispatch<float, double, float, kResidualGrid>(g, r, out, 1.0, nullptr, B, s);
+    return dst_dispatch<float, double, float, kResidual>(g, r, out, 1.0, nullptr, B, s);
+}
+
 hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, const double* add,
                                     int B, hipStream_t s) {
     return dst_dispatch<float, float, double>(grid2(p), in, out, alpha, add, B, s);
@@ -896,7 +950,7 @@ hipError_t launch_dst_f32_to_grid(const DevPlan& p, const float* in, double* u, 
 
 hipError_t launch_dst_lines(int N, int log2N, const double* sinq, double* a, double alpha, int B, int ld, int slices,
                             size_t slice, const int* skip, hipStream_t s) {
-    return dst_dispatch<double, double, double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr}, a, a, alpha, nullptr, B,
+    return dst_dispatch<double, double, double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr, {}}, a, a, alpha, nullptr, B,
                                                 s);
 }
 

@@ -261,6 +261,10 @@ hipError_t launch_dst_to_grid(const DevPlan& p, const double* in, double* u, dou
 hipError_t launch_dst_cols_f32(const DevPlan& p, const double* in, float* out, double alpha, int B, hipStream_t s);
 hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, const double* add,
                                     int B, hipStream_t s);
+// The FP32 transform of the FP64 residual r - (L_h - kappa) v, r in the padded layout or
+// (user) the user's grid.
+hipError_t launch_dst_residual_f32(const DevPlan& p, const double* r, bool user, const double* v, float* out, int B,
+                                   hipStream_t s);
 // The same reading the user's grid f, and writing the user's grid u.
 hipError_t launch_dst_from_grid_f32(const DevPlan& p, const double* f, float* out, int B, hipStream_t s);
 hipError_t launch_dst_f32_to_grid(const DevPlan& p, const float* in, double* u, double alpha, const double* add, int B,
@@ -280,10 +284,6 @@ int dst_default_tile(int N, size_t cpx_bytes, size_t lds_max, long lines, int mi
 // tridiagonal solves along x of every sine mode (FP64 arithmetic; FP64 or FP32 storage)
 hipError_t launch_rows_solve(const DevPlan& p, double* A, hipStream_t s);
 hipError_t launch_rows_solve_f32(const DevPlan& p, float* A, hipStream_t s);
-// R <- R - (L_h - kappa) V on the interior nodes (FP64), the refinement residual;
-// with the user's grid f R <- f - (L_h - kappa) V and R's pad zero; with A non-null
-// also A <- A + V (V a correction being applied)
-hipError_t launch_residual(const DevPlan& p, const double* V, const double* f, double* R, double* A, hipStream_t s);
 hipError_t launch_grid_out(const DevPlan& p, const double* V, bool mask, double* u, hipStream_t s);
 hipError_t launch_axpby(int n, double a, const double* x, double b, const double* y, double* z,
                         hipStream_t s);

@@ -23,8 +23,7 @@
 // GMRES the step launch of gmres.h does it for the next input).
 // The dense solve (volume potential, final solution) uses the same tridiagonal
 // solver on full rows (k_rows_solve), between two column sine transforms
-// (dst.hip); in the FP32 mode the transforms and the stored rows are FP32 and
-// k_residual forms the FP64 residual of the refinement step.
+// (dst.hip); in the FP32 mode the transforms and the stored rows are FP32.
 #include <hip/hip_runtime.h>
 
 #include "device.h"
@@ -168,29 +167,6 @@ __global__ __launch_bounds__(64 * rows_per_group<C>()) void k_rows_solve(DevPlan
 #pragma unroll 8
         for (int c = 0; c < C; ++c) row[c * 64 + lane] = (T)r[pad(c * 64 + lane)];
     }
-}
-
-// R <- R - ((V_E + V_W + V_N + V_S - 4 V) / h^2 - kappa V) at the interior nodes
-// (V = 0 on the box), all in the padded interior layout; with A, also A <- A + V.
-__global__ __launch_bounds__(256) void k_residual(DevPlan p, const double* __restrict__ V,
-                                                  const double* __restrict__ f, double* __restrict__ R,
-                                                  double* __restrict__ A) {
-    const int N = p.N;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)N * N) return;
-    const int i = (int)(idx % N) + 1, j = (int)(idx / N) + 1;
-    if (i >= N || j >= N) {
-        if (f) R[idx] = 0.0;
-        return;
-    }
-    const double r = f ? f[(size_t)j * (N + 1) + i] : R[idx];
-    const double v = V[idx];
-    const double vw = i > 1 ? V[idx - 1] : 0.0;
-    const double ve = i < N - 1 ? V[idx + 1] : 0.0;
-    const double vs = j > 1 ? V[idx - N] : 0.0;
-    const double vn = j < N - 1 ? V[idx + N] : 0.0;
-    R[idx] = r - ((vw + ve + vs + vn - 4.0 * v) * p.inv_h2 - p.kappa * v);
-    if (A) A[idx] += v;
 }
 
 __global__ __launch_bounds__(256) void k_grid_out(DevPlan p, const double* __restrict__ R, int mask,
@@ -425,12 +401,6 @@ hipError_t launch_fill_rhs(const DevPlan& p, const double* f, bool mask, double*
 hipError_t launch_rows_solve(const DevPlan& p, double* A, hipStream_t s) { return rows_solve_any(p, A, s); }
 
 hipError_t launch_rows_solve_f32(const DevPlan& p, float* A, hipStream_t s) { return rows_solve_any(p, A, s); }
-
-hipError_t launch_residual(const DevPlan& p, const double* V, const double* f, double* R, double* A, hipStream_t s) {
-    const size_t tot = (size_t)p.N * p.N;
-    if (hipError_t e_ = klaunch(&k_residual, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, p, V, f, R, A)) return e_;
-    return hipGetLastError();
-}
 
 hipError_t launch_grid_out(const DevPlan& p, const double* R, bool mask, double* u, hipStream_t s) {
     const size_t tot = (size_t)(p.N + 1) * (p.N + 1);
