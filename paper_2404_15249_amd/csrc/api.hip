@@ -125,8 +125,6 @@ struct kfbi_prob {
     // Richardson and BiCGSTAB (Table 2's alternatives): vectors, state, and a
     // graph of a batch of iterations for each
     IterBufs ib{};
-    hipGraphExec_t iexec[2] = {nullptr, nullptr};
-    bool iexec_failed[2] = {false, false};
 };
 
 namespace {
@@ -168,10 +166,6 @@ void free_prob(kfbi_prob* p) {
             if (g) hipGraphExecDestroy(g);
             g = nullptr;
         }
-    for (auto& g : p->iexec) {
-        if (g) hipGraphExecDestroy(g);
-        g = nullptr;
-    }
 }
 
 // Per-mode constants of the x-direction tridiagonal systems (Alg. 4), FP64.
@@ -548,7 +542,6 @@ kfbi_status gmres_call(kfbi_prob* p, int op, const double* rhs, double* x, doubl
 // ---------------------------------------------------------------- Richardson and BiCGSTAB
 
 enum IterMethod { kRich = 0, kBicg = 1 };
-constexpr int kIterBatch[2] = {8, 4};   // iterations per replayed batch (8 applies each)
 
 // One K_D apply of `in` into ib.w (spline and corrections, sparse solve, reduction),
 // skipped once the run is done.
@@ -557,29 +550,20 @@ kfbi_status iter_apply(kfbi_prob* p, const double* in, const int* skip, hipStrea
     return sparse_apply(p, kOpD, in, p->ib.s2, p->ib.w, skip, nullptr, s, true);
 }
 
-kfbi_status enqueue_iters(kfbi_prob* p, int method, int n, hipStream_t s) {
+// Slot k of a run: an update of Richardson, half an iteration of BiCGSTAB.
+kfbi_status enqueue_iter_slot(kfbi_prob* p, int method, int k, hipStream_t s) {
     const IterBufs& B = p->ib;
-    const int* skip = &B.st->done;
-    for (int k = 0; k < n; ++k) {
-        if (method == kRich) {
-            if (kfbi_status e = iter_apply(p, B.x, skip, s)) return e;
-            HIP_TRY(launch_iter_step(kIterRich, B, s));
-        } else {
-            if (kfbi_status e = iter_apply(p, B.q, skip, s)) return e;
-            HIP_TRY(launch_iter_step(kIterBicgHalf, B, s));
-            if (kfbi_status e = iter_apply(p, B.q, skip, s)) return e;
-            HIP_TRY(launch_iter_step(kIterBicgFull, B, s));
-        }
-    }
+    if (kfbi_status e = iter_apply(p, method == kRich ? B.x : B.q, &B.st->done, s)) return e;
+    HIP_TRY(launch_iter_step(method == kRich ? kIterRich : k % 2 ? kIterBicgFull : kIterBicgHalf, B, s));
     return KFBI_OK;
 }
 
 // Richardson (x <- x + gamma (b - K_D x)) or BiCGSTAB on K_D x = rhs from the
 // initial guess in x; same stopping rule as GMRES (relative to the initial
-// residual).  Batches of iterations are replayed from a graph; the host polls
-// the device state between batches.
+// residual).  The slots are launched as the run goes (GmresDriver).  With wait = false
+// the caller waits for the stream, then finds the final state in p->host.pub->iter.
 kfbi_status run_iters(kfbi_prob* p, int method, const double* rhs, double* x, double gamma, double tol, int max_iter,
-                      IterState* out) {
+                      IterState* out, bool wait = true) {
     if (!p) return set_err(KFBI_ERR_ARG, "prob is NULL");
     if (kfbi_status e = check_ptr(rhs, "rhs")) return e;
     if (kfbi_status e = check_ptr(x, "x")) return e;
@@ -595,45 +579,35 @@ kfbi_status run_iters(kfbi_prob* p, int method, const double* rhs, double* x, do
         bool t;
         ~Restore() { p->timing = t; }
     } restore{p, timing};
-    HIP_TRY(hipMemcpyAsync(B.b, rhs, M * sizeof(double), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipMemcpyAsync(B.x, x, M * sizeof(double), hipMemcpyDeviceToDevice, s));
-    static thread_local IterState st0;
-    st0 = IterState{};
+    IterState st0{};
     st0.max_iter = max_iter;
     st0.tol = tol;
     st0.gamma = gamma;
-    HIP_TRY(hipMemcpyAsync(B.st, &st0, sizeof st0, hipMemcpyHostToDevice, s));
+    st0.epoch = p->host.next_epoch();
+    HIP_TRY(launch_iter_start(B, rhs, x, st0, s));
     if (method == kBicg) {                  // r0 = b - K x0, r^ = p = r0
         if (kfbi_status e = iter_apply(p, B.x, &B.st->done, s)) return e;
         HIP_TRY(launch_iter_step(kIterBicgInit, B, s));
     }
-    if (!p->iexec[method] && !p->iexec_failed[method])
-        p->iexec_failed[method] = !record_graph(s, &p->iexec[method], [&](hipStream_t gs) {
-            return enqueue_iters(p, method, kIterBatch[method], gs);
-        });
-    const int nb = kIterBatch[method];
-    const int batches = (max_iter + 1) / nb + 2;
-    IterState st{};
-    for (int b = 0; b < batches; ++b) {
-        if (p->iexec[method]) {
-            HIP_TRY(hipGraphLaunch(p->iexec[method], s));
-        } else if (kfbi_status e = enqueue_iters(p, method, nb, s)) {
+    GmresDriver drv;
+    drv.host = &p->host;
+    drv.stream = s;
+    drv.most = 2 * max_iter + 4;
+    for (bool over = false; !over;)
+        if (kfbi_status e = drv.drive([&](hipStream_t st) { return enqueue_iter_slot(p, method, drv.launched - 1, st); },
+                                      &over))
             return e;
-        }
-        HIP_TRY(hipMemcpyAsync(&st0, B.st, sizeof st0, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        st = st0;
-        if (st.done) break;
-    }
+    const IterState& st = p->host.pub->iter;
     if (st.done == kIterNonfinite) return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in rhs or the initial guess");
+    *out = st;
     if (method == kBicg) {                  // the true residual of the final iterate
         if (kfbi_status e = iter_apply(p, B.x, nullptr, s)) return e;
         HIP_TRY(launch_iter_step(kIterTrueRes, B, s));
-        HIP_TRY(hipMemcpyAsync(&st0, B.st, sizeof st0, hipMemcpyDeviceToHost, s));
     }
     HIP_TRY(hipMemcpyAsync(x, B.x, M * sizeof(double), hipMemcpyDeviceToDevice, s));
+    if (!wait) return KFBI_OK;
     HIP_TRY(hipStreamSynchronize(s));
-    *out = st0;
+    *out = st;
     return KFBI_OK;
 }
 
@@ -1062,7 +1036,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     }
     HIP_TRY(hipMemset(p->d_flag, 0, 2 * sizeof(int)));
     if ((st = p->host.alloc())) return fail(st);
-    p->gm.pub = p->host.pub;
+    p->gm.pub = p->ib.pub = p->host.pub;
     if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
@@ -1311,10 +1285,11 @@ kfbi_status kfbi_solve_method(kfbi_prob* p, int method, double relax, const doub
     if (kfbi_status e = dirichlet_prepare(p, f_grid, f_gamma, g, p->tmpM)) return e;
     IterState st{};
     if (kfbi_status e = run_iters(p, method == KFBI_BICGSTAB ? kBicg : kRich, p->tmpM, phi, relax, p->tol,
-                                  p->max_iter, &st))
+                                  p->max_iter, &st, false))
         return e;
     if (kfbi_status e = dirichlet_finish(p, phi, f_grid, f_gamma, u_grid, u_gamma, p->modes_of)) return e;
     HIP_TRY(hipStreamSynchronize(s));
+    st = p->host.pub->iter;
     if (iters) *iters = st.it;
     if (rel_res) *rel_res = st.relres;
     if (st.done == 1) return KFBI_OK;

@@ -142,6 +142,23 @@ struct GmresState {
     int slot;        // slots whose commit has run
 };
 
+constexpr int kIterNonfinite = -2;
+
+// State of a Richardson or BiCGSTAB run (krylov.hip), in device memory.
+struct IterState {
+    int it;          // Richardson: updates made; BiCGSTAB: iterations begun
+    int done;        // 0 running, 1 converged, -1 iteration cap or breakdown, -2 (kIterNonfinite)
+                     // a NaN or Inf met (launches skip while nonzero)
+    int max_iter;
+    int started;     // 1 once r0 is known
+    int half;        // BiCGSTAB: 1 if it stopped half way through an iteration (one apply short)
+    int slot;        // slots whose step has run: Richardson's updates, BiCGSTAB's half iterations
+    double tol, r0, relres;
+    double rho, alpha, omega;
+    double gamma;    // Richardson relaxation
+    unsigned epoch;  // the run's number, for the host (GmresPub)
+};
+
 // What a run tells the host while it goes on (pinned, coherent host memory the
 // device writes; the host reads it without waiting for the stream).  prog: epoch in
 // the upper half; then kGmLastSlot when the commit found that the run ends at the
@@ -152,6 +169,7 @@ struct GmresPub {
     unsigned done;             // the run's epoch once it is over
     unsigned again;            // residuals that did not end a run (any run's)
     unsigned bad;              // number of the last apply whose density held a NaN or Inf
+    IterState iter;            // a Richardson or BiCGSTAB run's final state, likewise
 };
 constexpr unsigned kGmLastSlot = 0x80000000u;
 
@@ -177,32 +195,20 @@ struct GmresBufs {
     int gc64;        // chunks of 64 samples (the reduce launch)
 };
 
-constexpr int kIterNonfinite = -2;
-
-// State of a Richardson or BiCGSTAB run (krylov.hip), in device memory.
-struct IterState {
-    int it;          // Richardson: updates made; BiCGSTAB: iterations begun
-    int done;        // 0 running, 1 converged, -1 iteration cap or breakdown, -2 (kIterNonfinite)
-                     // a NaN or Inf met (launches skip while nonzero)
-    int max_iter;
-    int started;     // 1 once r0 is known
-    int half;        // BiCGSTAB: 1 if it stopped half way through an iteration (one apply short)
-    int pad;
-    double tol, r0, relres;
-    double rho, alpha, omega;
-    double gamma;    // Richardson relaxation
-};
 
 // Vectors of a Richardson or BiCGSTAB run (M doubles each).  The apply reads q
 // (BiCGSTAB) or x (Richardson) and writes w.
 struct IterBufs {
     double *b, *x, *r, *rhat, *p, *v, *s, *q, *w, *s2;
     IterState* st;
+    GmresPub* pub;
     int M;
 };
 
 constexpr int kIterRich = 0, kIterBicgInit = 1, kIterBicgHalf = 2, kIterBicgFull = 3, kIterTrueRes = 4;
 
+// The start of a run: b <- rhs, x <- the initial guess, the state.
+hipError_t launch_iter_start(const IterBufs& B, const double* rhs, const double* x, const IterState& st, hipStream_t s);
 // One single-workgroup step of the iterations (krylov.hip): which = kIter*.
 hipError_t launch_iter_step(int which, const IterBufs& B, hipStream_t s);
 

@@ -5,9 +5,11 @@
 // hold at most kMaxSamples values, so 1024 threads cover them in at most 12
 // strided passes, and every dot product is a fixed-order block sum (the same
 // result on every run).  The scalars and the stop decision live in device
-// memory (IterState), so a batch of iterations is one replayed graph and the
-// host only polls between batches; once the state says done, every later
-// launch of the batch returns at once.
+// memory (IterState); each step tells the host that its slot has run (GmresPub), and
+// the host launches the slots as the run goes, one ahead: replayed graphs of four
+// iterations polled in between ran up to three of them, and the poll, for nothing
+// (a solve of five iterations at 512^2: 500 -> 389 us).  Once the state says done, every later launch
+// returns at once.
 #include <hip/hip_runtime.h>
 
 #include "graph.h"
@@ -39,6 +41,30 @@ __device__ inline void block_sums(double (&v)[K], double* red) {
         v[k] = s;
     }
     __syncthreads();
+}
+
+// The step's end, by one thread: its slot has run (counts = false: none), or the run
+// is over.
+__device__ __forceinline__ void iter_publish(const IterBufs& B, bool counts = true) {
+    IterState* st = B.st;
+    if (counts) st->slot += 1;
+    if (st->done) {
+        B.pub->iter = *st;
+        __hip_atomic_store(&B.pub->done, st->epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (counts) {
+        __hip_atomic_store(&B.pub->prog, (unsigned long long)st->epoch << 32 | (unsigned)st->slot, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_iter_start(IterBufs B, const double* __restrict__ rhs,
+                                                    const double* __restrict__ x, IterState st) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < B.M) {
+        B.b[i] = rhs[i];
+        B.x[i] = x[i];
+    }
+    if (i == 0) *B.st = st;
 }
 
 // Richardson, after w = K x: r = b - w and its norm; the first call sets r0.
@@ -76,6 +102,7 @@ __global__ __launch_bounds__(kIterThreads) void k_rich_step(IterBufs B) {
         st->relres = rel;
         if (!done) st->it = it + 1;
         st->done = done;
+        iter_publish(B);
     }
 }
 
@@ -103,6 +130,7 @@ __global__ __launch_bounds__(kIterThreads) void k_bicg_init(IterBufs B) {
         st->relres = nr[0] > 0.0 ? 1.0 : 0.0;
         if (!isfinite(nr[0])) st->done = kIterNonfinite;
         else if (nr[0] == 0.0) st->done = 1;
+        iter_publish(B, false);
     }
 }
 
@@ -122,7 +150,10 @@ __global__ __launch_bounds__(kIterThreads) void k_bicg_half(IterBufs B) {
     block_sums(d, red);
     if (!isfinite(d[0]) || d[0] == 0.0) {               // NaN/Inf, or breakdown: r^ orthogonal to v
         __syncthreads();
-        if (threadIdx.x == 0) st->done = isfinite(d[0]) ? -1 : kIterNonfinite;
+        if (threadIdx.x == 0) {
+            st->done = isfinite(d[0]) ? -1 : kIterNonfinite;
+            iter_publish(B);
+        }
         return;
     }
     const double alpha = st->rho / d[0];
@@ -147,6 +178,7 @@ __global__ __launch_bounds__(kIterThreads) void k_bicg_half(IterBufs B) {
             st->half = 1;
             st->done = 1;
         }
+        iter_publish(B);
     }
 }
 
@@ -168,7 +200,10 @@ __global__ __launch_bounds__(kIterThreads) void k_bicg_full(IterBufs B) {
     const bool fin = isfinite(d[0]) && isfinite(d[1]);
     if (!fin || d[1] == 0.0 || d[0] == 0.0) {           // NaN/Inf, or breakdown: t = 0 or t orthogonal to s
         __syncthreads();
-        if (threadIdx.x == 0) st->done = fin ? -1 : kIterNonfinite;
+        if (threadIdx.x == 0) {
+            st->done = fin ? -1 : kIterNonfinite;
+            iter_publish(B);
+        }
         return;
     }
     const double omega = d[0] / d[1], alpha = st->alpha;
@@ -200,6 +235,7 @@ __global__ __launch_bounds__(kIterThreads) void k_bicg_full(IterBufs B) {
         st->relres = rel;
         st->done = done;
         if (!done) st->rho = e[1];
+        iter_publish(B);
     }
 }
 
@@ -215,10 +251,15 @@ __global__ __launch_bounds__(kIterThreads) void k_iter_true_res(IterBufs B) {
     if (threadIdx.x == 0) {
         const double r0 = B.st->r0;
         B.st->relres = r0 > 0.0 ? sqrt(nr[0]) / r0 : 0.0;
+        B.pub->iter = *B.st;
     }
 }
 
 }  // namespace
+
+hipError_t launch_iter_start(const IterBufs& B, const double* rhs, const double* x, const IterState& st, hipStream_t s) {
+    return klaunch(&k_iter_start, dim3((B.M + 255) / 256), dim3(256), 0, s, B, rhs, x, st);
+}
 
 hipError_t launch_iter_step(int which, const IterBufs& B, hipStream_t s) {
     void (*k)(IterBufs) = which == kIterRich ? k_rich_step
