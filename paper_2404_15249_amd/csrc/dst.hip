@@ -850,14 +850,15 @@ hipError_t short_launch(const Lines& g, const double* in, double* out, double al
     return hipGetLastError();
 }
 
-// Transforms of 128 and 256 rows as products with the sine matrix, on the FP64 matrix
+// Transforms of 128 to 512 rows as products with the sine matrix, on the FP64 matrix
 // cores: a workgroup folds 16 columns for one parity of the modes (x_y +- x_{N-y}: half
-// the products) in LDS, and each of its wavefronts makes 16 modes of them, element
-// (m, y) of the matrix being entry m y mod 2N of a sine table.  What bounds it: latency
-// (one load, one barrier, H / 4 matrix instructions in four chains, one store): 6.7 us at
-// 256^2, where the passes, scans and barriers of k_dst_cols took 11.
+// the products) in LDS, and two of its wavefronts, half of the rows each, make 16 modes of
+// them, element (m, y) of the matrix being entry m y mod 2N of a sine table.  What bounds
+// it: latency (one load, three barriers, H / 8 matrix instructions in four chains, one
+// store): at 256^2 5.2 us (6.7 with one wavefront for all rows) where the passes, scans
+// and barriers of k_dst_cols took 11, at 512^2 8.5 against 12.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int kMmThreads = 256, kMmCols = 16;
+constexpr int kMmThreads = 512, kMmCols = 16;
 template <int C, int IO>
 __global__ __launch_bounds__(kMmThreads) void k_dst_mm(const double* __restrict__ sinq, const double* __restrict__ in,
                                                        double* __restrict__ out, double alpha,
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(kMmThreads) void k_dst_mm(const double* __restrict_
     constexpr int N = 64 * C, H = N / 2, NT = kMmThreads;
     auto slot = [](int k) { return k + (k >> 5); };          // of sin(pi k / N): a power of two times the lane spreads
     __shared__ double tab[2 * N + N / 16];
-    __shared__ double F[H * kMmCols];
+    __shared__ __attribute__((aligned(32))) double F[H * kMmCols];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // neighbouring column tiles on one XCD, as in k_dst_cols: a tile's workgroups too
     constexpr int per_tile = 2 * (H / 64), G = N / kMmCols * per_tile;
@@ -897,20 +898,27 @@ __global__ __launch_bounds__(kMmThreads) void k_dst_mm(const double* __restrict_
         *reinterpret_cast<double2*>(F + 2 * idx) = make_double2(s * a[u].x + t * b[u].x, s * a[u].y + t * b[u].y);
     }
     __syncthreads();
-    const int ar = lane & 15, ak = lane >> 4, row0 = (4 * chunk + wave) * 16;
+    const int ar = lane & 15, ak = lane >> 4, row0 = (4 * chunk + (wave & 3)) * 16, half = wave >> 2;
     const int m = 2 * (row0 + ar) + 1 + even;                // the even modes' last, m = N, is the pad: zero
     f64x4 acc[4] = {};
 #pragma unroll 4
-    for (int k = ak; k < H; k += 16)
+    for (int k = half * (H / 2) + ak; k < (half + 1) * (H / 2); k += 16)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(tab[slot((m * (k + 4 * q + 1)) & (2 * N - 1))],
                                                           F[(k + 4 * q) * kMmCols + ar], acc[q], 0, 0, 0);
+    f64x4 sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    __syncthreads();
+    f64x4* other = reinterpret_cast<f64x4*>(F) + (wave & 3) * 64 + lane;
+    if (half) *other = sum;
+    __syncthreads();
+    if (!half) sum += *other;
     const int c = col0 + ar;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+        if (half) break;
         const int l = 2 * (row0 + 4 * r + ak) + 1 + even;
-        const double v = l < N ? alpha * ((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r])) : 0.0;
+        const double v = l < N ? alpha * sum[r] : 0.0;
         if constexpr (IO == kToGrid) {
             const bool in_omega = mask8 ? (mask8[(size_t)l * (N >> 3) + (c >> 3)] >> (c & 7)) & 1 : c + 1 < N;
             out[(size_t)l * (N + 1) + c + 1] = in_omega ? v : 0.0;
@@ -932,7 +940,8 @@ hipError_t mm_launch(const Lines& g, const double* in, double* out, double alpha
     const dim3 grid(g.N / kMmCols * 2 * (g.N / 128)), t(kMmThreads);
     switch (g.N) {
         case 128: return klaunch(&k_dst_mm<2, IO>, grid, t, 0, s, g.sinq, in, out, alpha, g.mask8);
-        default: return klaunch(&k_dst_mm<4, IO>, grid, t, 0, s, g.sinq, in, out, alpha, g.mask8);
+        case 256: return klaunch(&k_dst_mm<4, IO>, grid, t, 0, s, g.sinq, in, out, alpha, g.mask8);
+        default: return klaunch(&k_dst_mm<8, IO>, grid, t, 0, s, g.sinq, in, out, alpha, g.mask8);
     }
 }
 
@@ -944,11 +953,11 @@ hipError_t dst_dispatch(const Lines& g, const Tin* in, Tout* out, double alpha, 
     if constexpr (sizeof(T) == 8 && sizeof(Tin) == 8 && sizeof(Tout) == 8) {
         if (g.ld % 8 == 0 && g.N == 64) return short_launch<1, IO>(g, in, out, alpha, s);
     }
-    // 128 and 256 rows to and from the user's grid: k_dst_mm, at 256^2 6.7 us against 11.5
-    // (from) and 10.3 (to); at 512^2 the matrix's four times as many products take longer
-    // (13 and 11.1 against 13 and 11.5, beside another stream's work 15.6 against 13)
+    // 128 to 512 rows to and from the user's grid: k_dst_mm, at 512^2 8.7 us against 13.0
+    // (from) and 8.2 against 11.1 (to); at 1024^2 the products alone would take 15, the
+    // whole tiled transform 15 to 18
     if constexpr (sizeof(T) == 8 && (IO == kFromGrid || IO == kToGrid)) {
-        if (g.N == 128 || g.N == 256) return mm_launch<IO>(g, in, out, alpha, s);
+        if (g.N >= 128 && g.N <= 512) return mm_launch<IO>(g, in, out, alpha, s);
     }
     if (!dst_tile_ok(g.N, B, sizeof(cpx<T>), ~(size_t)0) || g.ld % B != 0) return hipErrorInvalidValue;
     switch (B) {
