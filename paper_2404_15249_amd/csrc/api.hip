@@ -332,7 +332,7 @@ kfbi_status dirichlet_finish(kfbi_prob* p, const double* phi, const double* f, c
 
 // K_D phi or K_N phi (op) without the dense grid (correction, sparse fast
 // solve, reduction and interpolation).  With corr_ready the corrections are
-// already in corr_il (made by the previous GMRES step's emit launch) and the
+// already in corr_il (made by the previous GMRES step's launch) and the
 // correction launch is skipped.
 kfbi_status sparse_apply(kfbi_prob* p, int op, const double* phi, const double* phi_s2, double* out, const int* skip,
                          const GmresBufs* gm, hipStream_t s, bool corr_ready = false) {
