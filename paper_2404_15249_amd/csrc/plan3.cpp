@@ -395,26 +395,37 @@ Apply3Host build_apply3(const Plan3Host& P) {
         const size_t t = std::lower_bound(z.begin(), z.end(), std::min(f.z, N - f.z)) - z.begin();
         A.irr_pos[r] = (int)(4 * (first[f.col] + 64 * t)) + 2 * f.side + (f.z > H);
     }
-    // the stencils' nodes by tile; keys (column, side, z') in order, each once
-    std::vector<std::vector<int>> tile((size_t)H * (N / 32));
-    auto key = [&](const Fold& f) { return (f.col % 32 << 1 | f.side) << 8 | std::min(f.z, N - f.z); };
+    // the stencils' nodes by tile: place[column, side, z'] is first a mark, then the place
+    // of the node at z' in the entries
+    const size_t per = H + 1;
+    std::vector<int> place((size_t)H * N * 2 * per, -1);
+    auto at = [&](const Fold& f) { return ((size_t)f.col * 2 + f.side) * per + std::min(f.z, N - f.z); };
     for (int node : A.st_node)
         if (node >= 0) {
             const Fold f = fold(node);
-            tile[f.col / N * (N / 32) + f.col % N / 32].push_back(key(f));
+            place[at(f)] = 0;
             A.y_first = std::min(A.y_first, f.col / N);
         }
     A.zg_off.assign(1, 0);
-    for (auto& keys : tile) {
-        std::sort(keys.begin(), keys.end());
-        keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
-        for (size_t k = 0; k < keys.size();) {
-            const int a = keys[k], column_side = a >> 8;
-            const bool two = k + 1 < keys.size() && keys[k + 1] >> 8 == column_side;
-            const int b = two ? keys[k + 1] : a;
-            A.zg_code.push_back((a & 255) | (b & 255) << 8 | (column_side >> 1) << 16 | (column_side & 1) << 24);
-            k += two ? 2 : 1;
-        }
+    for (int t = 0; t < H * (N / 32); ++t) {
+        for (int x = 0; x < 32; ++x)
+            for (int side = 0; side < 2; ++side) {
+                const int col = t / (N / 32) * N + t % (N / 32) * 32 + x;
+                int* p = &place[((size_t)col * 2 + side) * per];
+                int waiting = 0;                             // a height without a second one yet
+                for (int z = 1; z <= H; ++z) {
+                    if (p[z] < 0) continue;
+                    if (waiting) {
+                        A.zg_code.back() = waiting | z << 8 | x << 16 | side << 24;
+                        p[z] = 4 * (int)A.zg_code.size() - 2;
+                        waiting = 0;
+                    } else {
+                        A.zg_code.push_back(z | z << 8 | x << 16 | side << 24);
+                        p[z] = 4 * (int)A.zg_code.size() - 4;
+                        waiting = z;
+                    }
+                }
+            }
         A.zg_off.push_back((int)A.zg_code.size());
     }
     A.st_pos.resize(A.st_node.size());
@@ -422,13 +433,7 @@ Apply3Host build_apply3(const Plan3Host& P) {
         A.st_pos[k] = -1;
         if (A.st_node[k] < 0) continue;
         const Fold f = fold(A.st_node[k]);
-        const int t = f.col / N * (N / 32) + f.col % N / 32, want = key(f);
-        // the entries of a tile are in the order of their first keys
-        const auto begin = A.zg_code.begin() + A.zg_off[t], end = A.zg_code.begin() + A.zg_off[t + 1];
-        auto first = [](int c) { return ((c >> 16 & 31) << 1 | c >> 24) << 8 | (c & 255); };
-        const auto at = std::upper_bound(begin, end, want, [&](int v, int c) { return v < first(c); }) - 1;
-        const int e = (int)(at - A.zg_code.begin());
-        A.st_pos[k] = 4 * e + ((*at & 255) == (want & 255) ? 0 : 2) + (f.z > H);
+        A.st_pos[k] = place[at(f)] + (f.z > H);
     }
     return A;
 }
