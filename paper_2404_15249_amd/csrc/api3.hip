@@ -247,13 +247,14 @@ kfbi_status kfbi3_prob_create(kfbi_ctx* ctx, const kfbi_desc3* d, kfbi_prob3** o
         return fail(st);
     const int m = p->restart;
     GmresBufs& b = p->gm;
+    const int reduce_groups = (gm_chunks64(M) + reduce3_chunks(M) - 1) / reduce3_chunks(M);
     if ((st = alloc3(p, &p->G, (size_t)N * N * N)) || (st = alloc3(p, &p->S, M)) || (st = alloc3(p, &p->far, M)) ||
         (st = alloc3(p, &p->tmpM, M)) || (st = alloc3(p, &p->zeroM, M)) || (st = alloc3(p, &p->d_flag, 2)) ||
         (st = alloc3(p, &b.V, (size_t)(m + 1) * M)) || (st = alloc3(p, &b.H, (size_t)(m + 1) * m)) ||
         (st = alloc3(p, &b.cs, m)) || (st = alloc3(p, &b.sn, m)) || (st = alloc3(p, &b.g, m + 1)) ||
         (st = alloc3(p, &b.ghat, M)) || (st = alloc3(p, &b.phi, M)) || (st = alloc3(p, &b.xcur, M)) ||
         (st = alloc3(p, &b.w, M)) || (st = alloc3(p, &b.z, M)) ||
-        (st = alloc3(p, &b.part, gm_part_size(m, gm_chunks(M, false), gm_chunks64(M)))) ||
+        (st = alloc3(p, &b.part, gm_part_size(m, gm_chunks(M, false), reduce_groups))) ||
         (st = alloc3(p, &b.y, m + 1)) || (st = alloc3(p, &b.h, m + 1)) || (st = alloc3(p, &b.st, 1)))
         return fail(st);
     if ((st = p->host.alloc())) return fail(st);
@@ -261,7 +262,7 @@ kfbi_status kfbi3_prob_create(kfbi_ctx* ctx, const kfbi_desc3* d, kfbi_prob3** o
     b.s2cur = nullptr;
     b.m = m;
     b.gc = gm_chunks(M, false);
-    b.gc64 = gm_chunks64(M);
+    b.gc64 = reduce_groups;
     if (hipMemset(p->zeroM, 0, M * sizeof(double)) != hipSuccess || hipMemset(p->d_flag, 0, 2 * sizeof(int)) != hipSuccess)
         return fail(set_err(KFBI_ERR_DEVICE, "hipMemset failed"));
     p->dstB = dst_default_tile(N, 2 * sizeof(double), ctx->lds_max, (long)N * N, ctx->num_cu);

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(1024) void k_reduce_b(BatchWork w) {
         if (item.y < 0) {
             gm_commit(S.b, S.p.M);
         } else if (!slot_done(S)) {
-            const GmPre pre = gm_reduce_prefetch(S.b, S.p.M, item.y / 64);
+            const GmPre<1> pre = gm_reduce_prefetch(S.b, S.p.M, item.y / 64);
             const GmPh ph{S.b.st->ph, S.b.st->j, S.b.st->second, S.b.st->reorth};
             const JumpSrc js{S.b.xcur, S.b.s2cur, nullptr, nullptr, nullptr, nullptr};
             reduce_samples64(S.p, js, S.partial, S.Gs, item.y, nullptr, red);

@@ -112,23 +112,29 @@ __device__ __forceinline__ bool gm_cancelled(double zz, double ww, double reorth
 // reduction so that the latencies overlap: V_i at the lane's sample for
 // i = wave, wave + 16, ... (kMaxRestart <= 64; every row that can be in use, none
 // waits for the state), the apply's input, ghat, and the lane's share of the norm
-// partials.
+// partials.  NC chunks of 64 samples a workgroup.
+template <int NC>
 struct GmPre {
-    double v[4];
-    double xc, gh, zz, ww;
+    double v[NC][4];
+    double xc[NC], gh[NC], zz, ww;
 };
-__device__ __forceinline__ GmPre gm_reduce_prefetch(const GmresBufs& b, int M, int c64) {
+template <int NC = 1>
+__device__ __forceinline__ GmPre<NC> gm_reduce_prefetch(const GmresBufs& b, int M, int c64) {
     static_assert(kMaxRestart <= 64, "four basis values per lane");
-    GmPre pre;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cp = c64 * 64 + lane;
+    GmPre<NC> pre;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const GmPart q = gm_part(b);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int i = wave + 16 * k;
-        pre.v[k] = (i < b.m && cp < M) ? b.V[(size_t)i * M + cp] : 0.0;
+    for (int h = 0; h < NC; ++h) {
+        const int cp = (c64 * NC + h) * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = wave + 16 * k;
+            pre.v[h][k] = (i < b.m && cp < M) ? b.V[(size_t)i * M + cp] : 0.0;
+        }
+        pre.xc[h] = cp < M ? b.xcur[cp] : 0.0;
+        pre.gh[h] = wave == 0 && cp < M ? b.ghat[cp] : 0.0;
     }
-    pre.xc = cp < M ? b.xcur[cp] : 0.0;
-    pre.gh = wave == 0 && cp < M ? b.ghat[cp] : 0.0;
     pre.zz = gm_lane_share(q.nrm, b.gc);
     pre.ww = gm_lane_share(q.nrmw, b.gc);
     return pre;
@@ -140,44 +146,60 @@ struct GmPh {
     double reorth;
 };
 
-// Samples c64 * 64 .. + 63 by a workgroup of 16 wavefronts right after the apply's
-// output there (wv[lane] in LDS).
-__device__ inline void gm_reduce64(const GmresBufs& b, int M, int c64, const double* wv, const GmPre& pre, GmPh ph) {
+// Samples 64 NC c64 .. + 64 NC - 1 by a workgroup of 16 wavefronts right after the
+// apply's output there (wv[64 h + lane] in LDS).
+template <int NC>
+__device__ inline void gm_reduce64(const GmresBufs& b, int M, int c64, const double* wv, const GmPre<NC>& pre, GmPh ph) {
     if (ph.phase == kGmOver) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cp = c64 * 64 + lane;
+    const int cp0 = c64 * NC * 64 + lane;
     const GmPart q = gm_part(b);
     if (ph.phase == kGmResidualPh) {                       // the apply was given the iterate
         if (wave != 0) return;
-        double r = 0.0;
-        if (cp < M) {
-            b.phi[cp] = pre.xc;
-            r = pre.gh - wv[lane];
+        double s = 0.0;
+#pragma unroll
+        for (int h = 0; h < NC; ++h) {
+            const int cp = cp0 + 64 * h;
+            if (cp >= M) continue;
+            b.phi[cp] = pre.xc[h];
+            const double r = pre.gh[h] - wv[64 * h + lane];
             b.z[cp] = r;
+            s = fma(r, r, s);
         }
-        const double s = wave_sum(r * r);
+        s = wave_sum(s);
         if (lane == 0) q.nrm0[c64] = s;
         return;
     }
     const double zz = wave_sum(pre.zz), ww = wave_sum(pre.ww);
     const bool second = ph.j > 0 && !ph.second && gm_cancelled(zz, ww, ph.reorth);
     const double hn = sqrt(zz), sc = hn > 0.0 ? 1.0 / hn : 0.0;
-    const double vj = pre.xc * sc;                         // the new basis vector
-    const double x = second ? pre.xc : cp < M ? wv[lane] * sc : 0.0;
-    if (wave == 0 && cp < M) {
-        b.w[cp] = x;
-        if (!second) b.V[(size_t)ph.j * M + cp] = vj;
+    double vj[NC], x[NC];                                  // the new basis vector, its product
+#pragma unroll
+    for (int h = 0; h < NC; ++h) {
+        const int cp = cp0 + 64 * h;
+        vj[h] = pre.xc[h] * sc;
+        x[h] = second ? pre.xc[h] : cp < M ? wv[64 * h + lane] * sc : 0.0;
+        if (wave == 0 && cp < M) {
+            b.w[cp] = x[h];
+            if (!second) b.V[(size_t)ph.j * M + cp] = vj[h];
+        }
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int i = wave + 16 * k;
         if (i < ph.j) {
-            const double s = wave_sum(pre.v[k] * x);
+            double s = pre.v[0][k] * x[0];
+#pragma unroll
+            for (int h = 1; h < NC; ++h) s = fma(pre.v[h][k], x[h], s);
+            s = wave_sum(s);
             if (lane == 0) q.d1[(size_t)i * b.gc64 + c64] = s;
         }
     }
     if (!second && wave == (ph.j & 15)) {
-        const double s = wave_sum(vj * x);
+        double s = vj[0] * x[0];
+#pragma unroll
+        for (int h = 1; h < NC; ++h) s = fma(vj[h], x[h], s);
+        s = wave_sum(s);
         if (lane == 0) q.d1[(size_t)ph.j * b.gc64 + c64] = s;
     }
 }

@@ -13,6 +13,13 @@
 
 namespace kfbi {
 
+// Chunks of 64 samples a workgroup of a GMRES step's reduce launch takes: four where one
+// would make more workgroups than compute units.  At 128^3 one leaves 399 partial sums a
+// dot for every workgroup of the step launch to add (11.9 us, five rounds of loads) and
+// four 100 (7.4 us), and the reduce launch takes as long (9.4 and 9.3); at 64^3 (100
+// chunks) four in 25 workgroups make the reduce launch 8.8 us, one in 100 5.6.
+inline int reduce3_chunks(int M) { return (M + 63) / 64 > 256 ? 4 : 1; }
+
 struct DevPlan3 {
     int N, log2N, M, I;
     double h, h2, kappa;

@@ -441,37 +441,44 @@ __global__ __launch_bounds__(256) void k_interp3(DevPlan3 p, const double* __res
     out[m] = s + far[m];
 }
 
-// inside GMRES: v+ at 64 control points (a wavefront for each of the ten nodes, one for
-// the far-side terms), then the reduce part of the step; the last workgroup commits the
-// previous column
+// inside GMRES: v+ at 64 NC control points (a wavefront for each of the ten nodes,
+// one for the far-side terms), then the reduce part of the step; the last workgroup
+// commits the previous column
+template <int NC>
 __global__ __launch_bounds__(1024) void k_interp3_gm(DevPlan3 p, const double* __restrict__ v,
                                                      const int* __restrict__ node, const double* __restrict__ far,
                                                      GmresBufs b) {
-    __shared__ double red[kStencil3 + 1][64];
+    __shared__ double red[kStencil3 + 1][64 * NC];
     if ((int)blockIdx.x == b.gc64) {
         gm_commit(b, p.M);
         return;
     }
     if (b.st->converged) return;
-    const GmPre pre = gm_reduce_prefetch(b, p.M, blockIdx.x);
+    const GmPre<NC> pre = gm_reduce_prefetch<NC>(b, p.M, blockIdx.x);
     const GmPh ph{b.st->ph, b.st->j, b.st->second, b.st->reorth};
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = min((int)(blockIdx.x * 64) + lane, p.M - 1);
-    if (wave < kStencil3) {
-        const int at = node[(size_t)wave * p.M + m];
-        red[wave][lane] = at >= 0 ? p.st_w[(size_t)wave * p.M + m] * v[at] : 0.0;
-    } else if (wave == kStencil3) {
-        red[wave][lane] = far[m];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.x * 64 * NC + lane;
+    if (wave <= kStencil3) {
+        int at[NC];
+        double w[NC];
+#pragma unroll
+        for (int h = 0; h < NC; ++h) {
+            const int m = min(m0 + 64 * h, p.M - 1);
+            at[h] = wave < kStencil3 ? node[(size_t)wave * p.M + m] : m;
+            w[h] = wave < kStencil3 ? p.st_w[(size_t)wave * p.M + m] : 1.0;
+        }
+        const double* from = wave < kStencil3 ? v : far;
+#pragma unroll
+        for (int h = 0; h < NC; ++h) red[wave][64 * h + lane] = at[h] >= 0 ? w[h] * from[at[h]] : 0.0;
     }
     __syncthreads();
-    if (wave == 0) {
+    if (wave < NC) {
         double s = 0.0;
 #pragma unroll
-        for (int k = 0; k <= kStencil3; ++k) s += red[k][lane];
-        red[0][lane] = blockIdx.x * 64 + lane < p.M ? s : 0.0;
+        for (int k = 0; k <= kStencil3; ++k) s += red[k][64 * wave + lane];
+        red[0][64 * wave + lane] = m0 + 64 * wave < p.M ? s : 0.0;
     }
     __syncthreads();
-    gm_reduce64(b, p.M, blockIdx.x, red[0], pre, ph);
+    gm_reduce64<NC>(b, p.M, blockIdx.x, red[0], pre, ph);
 }
 
 __global__ __launch_bounds__(256) void k_grid_out3(DevPlan3 p, const double* __restrict__ G, int mask,
@@ -563,7 +570,9 @@ hipError_t launch_solve3(const DevPlan3& p, double* G, int B, const int* skip, h
 
 hipError_t launch_interp3(const DevPlan3& p, const double* v, const int* node, const double* far, double* out,
                           const int* skip, const GmresBufs* gm, hipStream_t s) {
-    if (gm) return klaunch(&k_interp3_gm, dim3(gm->gc64 + 1), dim3(1024), 0, s, p, v, node, far, *gm);
+    if (gm && reduce3_chunks(p.M) == 4)
+        return klaunch(&k_interp3_gm<4>, dim3(gm->gc64 + 1), dim3(1024), 0, s, p, v, node, far, *gm);
+    if (gm) return klaunch(&k_interp3_gm<1>, dim3(gm->gc64 + 1), dim3(1024), 0, s, p, v, node, far, *gm);
     return klaunch(&k_interp3, dim3((p.M + 255) / 256), dim3(256), 0, s, p, v, node, far, out, skip);
 }
 

@@ -192,7 +192,7 @@ struct GmresBufs {
     GmresPub* pub;   // what the host sees of the run (may be null)
     int m;
     int gc;          // chunks of the step launch (gm_chunks)
-    int gc64;        // chunks of 64 samples (the reduce launch)
+    int gc64;        // workgroups of the reduce launch: chunks of 64 samples (3D: of 64 reduce3_chunks(M))
 };
 
 

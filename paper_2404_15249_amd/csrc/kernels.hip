@@ -216,7 +216,7 @@ __global__ __launch_bounds__(1024) void k_reduce_gm(DevPlan p, JumpSrc js, const
         gm_commit(b, p.M);
         return;
     }
-    const GmPre pre = gm_reduce_prefetch(b, p.M, blockIdx.x);
+    const GmPre<1> pre = gm_reduce_prefetch(b, p.M, blockIdx.x);
     const GmPh ph{load_flag_late(&b.st->ph), load_flag_late(&b.st->j), load_flag_late(&b.st->second),
                   load_real_late(&b.st->reorth)};       // waited for where used
     if (!reduce_samples64(p, js, partial, G, blockIdx.x * 64, nullptr, red, &b.st->converged)) return;
