@@ -83,8 +83,12 @@ struct kfbi_prob {
     size_t bytes = 0;
     // work buffers
     double* corr = nullptr;      // I
-    double* corr_il = nullptr;   // T x 64: corrections in the interleaved layout of the sparse sums
-    double* corr_d = nullptr;    // the same for an interface solve (corr_il may hold an admitted request's next ones)
+    // corrections in the interleaved layout of the sparse sums, T x 64 each: the next
+    // apply's of a GMRES run, which an admitted request's batch reads at its next step
+    // whatever the problem is used for meanwhile; and those of the other calls, made and
+    // used within one apply or interface solve
+    double* corr_il = nullptr;
+    double* corr_call = nullptr;
     double* partial = nullptr;   // G M
     double* R = nullptr;         // N N: right-hand side, modes or their solution (padded layout)
     unsigned modes_of = 0;       // number of the dense solve whose right-hand side's modes R holds (0: none; FP64)
@@ -265,11 +269,11 @@ kfbi_status dense_interface_solve(kfbi_prob* p, DenseArgs a) {
     if (a.js.phi) a.js.phi_s2 = p->s2a;
     if (a.js.fgam) a.js.fgam_s2 = p->s2b;
     if (f64 && !a.js.jq) {
-        HIP_TRY(launch_density_f(dv, a.js.phi, a.js.fgam, p->s2a, p->s2b, p->corr_d, s));
+        HIP_TRY(launch_density_f(dv, a.js.phi, a.js.fgam, p->s2a, p->s2b, p->corr_call, s));
     } else {
         if (a.js.phi) HIP_TRY(launch_spline(p->dp, a.js.phi, p->s2a, nullptr, s));
         if (a.js.fgam) HIP_TRY(launch_spline(p->dp, a.js.fgam, p->s2b, nullptr, s));
-        if (f64) HIP_TRY(launch_correct(dv, a.js, nullptr, p->corr_d, nullptr, nullptr, s));
+        if (f64) HIP_TRY(launch_correct(dv, a.js, nullptr, p->corr_call, nullptr, nullptr, s));
     }
     const bool held = a.modes && a.modes == p->modes_of;
     p->modes_of = 0;
@@ -279,7 +283,7 @@ kfbi_status dense_interface_solve(kfbi_prob* p, DenseArgs a) {
     // there: at 4096^2 the row solves take 77 us without the gather and the loads 8, with
     // it 108 and the partial sums' reduction 20
     if (a.vgrid && !a.mask_out) {
-        HIP_TRY(launch_modes_dense(dv, p->corr_d, p->R, a.f != nullptr, true, p->Rm, nullptr, nullptr, nullptr, s));
+        HIP_TRY(launch_modes_dense(dv, p->corr_call, p->R, a.f != nullptr, true, p->Rm, nullptr, nullptr, nullptr, s));
         HIP_TRY(launch_dst_to_grid(p->dp, p->R, a.vgrid, 2.0 / p->N, false, p->dstB, s));
         if (a.vz) HIP_TRY(launch_interp_grid(dv, a.js, a.vgrid, true, a.vz, s));
         if (a.dnz) HIP_TRY(launch_interp_grid(plan_view(p, a.normal_jump, true), a.js, a.vgrid, true, a.dnz, s));
@@ -291,7 +295,7 @@ kfbi_status dense_interface_solve(kfbi_prob* p, DenseArgs a) {
     const bool both = a.vz && a.dnz;
     const int Rm = both && 2 * p->G > p->Gcap ? 2 * p->Rm : p->Rm, G = (p->n + Rm - 1) / Rm;
     double* second = both ? p->partial + (size_t)G * p->M : nullptr;
-    HIP_TRY(launch_modes_dense(dw, p->corr_d, p->R, a.f != nullptr, a.vgrid != nullptr, Rm,
+    HIP_TRY(launch_modes_dense(dw, p->corr_call, p->R, a.f != nullptr, a.vgrid != nullptr, Rm,
                                a.vz || a.dnz ? p->partial : nullptr, both ? dn.cp_w : nullptr, second, s));
     if (a.vz || a.dnz)
         HIP_TRY(launch_reduce_interp(dw, a.js, p->partial, G, a.vz ? a.vz : a.dnz, nullptr, nullptr, s, a.from));
@@ -331,11 +335,11 @@ kfbi_status dirichlet_finish(kfbi_prob* p, const double* phi, const double* f, c
 }
 
 // K_D phi or K_N phi (op) without the dense grid (correction, sparse fast
-// solve, reduction and interpolation).  With corr_ready the corrections are
-// already in corr_il (made by the previous GMRES step's launch) and the
-// correction launch is skipped.
-kfbi_status sparse_apply(kfbi_prob* p, int op, const double* phi, const double* phi_s2, double* out, const int* skip,
-                         const GmresBufs* gm, hipStream_t s, bool corr_ready = false) {
+// solve, reduction and interpolation), its corrections in corr.  With corr_ready
+// they are there already (made by the launch of the density, or by the previous
+// GMRES step's) and the correction launch is skipped.
+kfbi_status sparse_apply(kfbi_prob* p, int op, const double* phi, const double* phi_s2, double* corr, double* out,
+                         const int* skip, const GmresBufs* gm, hipStream_t s, bool corr_ready = false) {
     JumpSrc js{phi, phi_s2, nullptr, nullptr, nullptr, nullptr};
     const DevPlan d = op_view(p, op);
     hipEvent_t* ev = nullptr;
@@ -352,14 +356,14 @@ kfbi_status sparse_apply(kfbi_prob* p, int op, const double* phi, const double* 
         if (ev) launch_events() = LaunchEvents{ev[2 * q], ev[2 * q + 1]};
     };
     stage(0);
-    if (!corr_ready) HIP_TRY(launch_correct(d, js, nullptr, p->corr_il, nullptr, skip, s));
+    if (!corr_ready) HIP_TRY(launch_correct(d, js, nullptr, corr, nullptr, skip, s));
     if (ev && launch_events().start) {            // nothing was launched
         launch_events() = LaunchEvents{};
         HIP_TRY(hipEventRecord(ev[0], s));
         HIP_TRY(hipEventRecord(ev[1], s));
     }
     stage(1);
-    HIP_TRY(launch_modes(d, p->corr_il, p->partial, p->Rm, skip, s));
+    HIP_TRY(launch_modes(d, corr, p->partial, p->Rm, skip, s));
     stage(2);
     HIP_TRY(launch_reduce_interp(d, js, p->partial, p->G, out, skip, gm, s));
     launch_events() = LaunchEvents{};
@@ -374,8 +378,8 @@ kfbi_status checked_apply(kfbi_prob* p, int op, const double* phi, double* out) 
     const unsigned number = p->n_apply = p->n_apply + 1 ? p->n_apply + 1 : 2;   // never 0; parity alternates
     const DensityCheck check{p->d_flag + (number & 1), p->d_flag + (~number & 1), &p->host.pub->bad, number};
     const bool ready = !p->timing;                          // timed: the corrections are a launch of their own
-    HIP_TRY(launch_density(op_view(p, op), phi, p->s2a, p->corr_il, nullptr, &check, s));
-    if (kfbi_status e = sparse_apply(p, op, phi, p->s2a, out, check.flag, nullptr, s, ready)) return e;
+    HIP_TRY(launch_density(op_view(p, op), phi, p->s2a, p->corr_call, nullptr, &check, s));
+    if (kfbi_status e = sparse_apply(p, op, phi, p->s2a, p->corr_call, out, check.flag, nullptr, s, ready)) return e;
     HIP_TRY(hipStreamSynchronize(s));
     if (__atomic_load_n(check.bad, __ATOMIC_ACQUIRE) == number)
         return set_err(KFBI_ERR_NONFINITE, "NaN or Inf in the density");
@@ -394,7 +398,7 @@ kfbi_status enqueue_steps(kfbi_prob* p, int op, int nsteps, hipStream_t s) {
     const int* skip = &b.st->converged;
     const bool fused = !p->timing;
     for (int k = 0; k < nsteps; ++k) {
-        if (kfbi_status e = sparse_apply(p, op, b.xcur, b.s2cur, b.w, skip, &p->gm, s, fused)) return e;
+        if (kfbi_status e = sparse_apply(p, op, b.xcur, b.s2cur, p->corr_il, b.w, skip, &p->gm, s, fused)) return e;
         if (fused) {
             HIP_TRY(launch_gmres_step_corr(op_view(p, op), b, p->corr_il, s));
         } else {
@@ -546,8 +550,8 @@ enum IterMethod { kRich = 0, kBicg = 1 };
 // One K_D apply of `in` into ib.w (spline and corrections, sparse solve, reduction),
 // skipped once the run is done.
 kfbi_status iter_apply(kfbi_prob* p, const double* in, const int* skip, hipStream_t s) {
-    HIP_TRY(launch_density(p->dp, in, p->ib.s2, p->corr_il, skip, nullptr, s));
-    return sparse_apply(p, kOpD, in, p->ib.s2, p->ib.w, skip, nullptr, s, true);
+    HIP_TRY(launch_density(p->dp, in, p->ib.s2, p->corr_call, skip, nullptr, s));
+    return sparse_apply(p, kOpD, in, p->ib.s2, p->corr_call, p->ib.w, skip, nullptr, s, true);
 }
 
 // Slot k of a run: an update of Richardson, half an iteration of BiCGSTAB.
@@ -1013,7 +1017,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     for (int w = 0; w <= kModeWaves; ++w) dp.sub_offv[w] = sub_off[w];
     const int M = p->M, m = p->restart;
     if ((st = dev_alloc(p, &p->corr, p->I)) || (st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) ||
-        (st = dev_alloc(p, &p->corr_d, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
+        (st = dev_alloc(p, &p->corr_call, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
         (st = dev_alloc(p, &p->R, (size_t)n * n)) || (st = dev_alloc(p, &p->A, (size_t)n * n)) ||
         (st = dev_alloc(p, &p->tmpM, M)) || (st = dev_alloc(p, &p->s2a, M)) || (st = dev_alloc(p, &p->s2b, M)) ||
         (st = dev_alloc(p, &p->d_flag, 2)) ||
@@ -1040,7 +1044,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
-    HIP_TRY(hipMemset(p->corr_d, 0, sizeof(double) * (size_t)dp.T * 64));
+    HIP_TRY(hipMemset(p->corr_call, 0, sizeof(double) * (size_t)dp.T * 64));
     p->gm.m = m;
     p->gm.gc = gm_chunks(M, true);
     p->gm.gc64 = gm_chunks64(M);
@@ -1468,7 +1472,7 @@ kfbi_status kfbi_prob_autotune(kfbi_prob* p, int reps, kfbi_tiles* out) {
         p->G = (p->n + Rm - 1) / Rm;
         double us = 0;
         if (kfbi_status e = time_us(s, reps, &us,
-                                    [&] { return sparse_apply(p, kOpD, p->tmpM, p->s2a, p->s2b, nullptr, nullptr, s); })) {
+                                    [&] { return sparse_apply(p, kOpD, p->tmpM, p->s2a, p->corr_call, p->s2b, nullptr, nullptr, s); })) {
             p->Rm = r0;
             p->G = (p->n + r0 - 1) / r0;
             return e;
