@@ -104,6 +104,8 @@ typedef struct {
  * enqueue on (NULL: the library creates its own stream with default flags and
  * priority).  The caller keeps ownership of a stream it passes in. */
 kfbi_status kfbi_ctx_create(int device, void* hip_stream, kfbi_ctx** out);
+/* Gives the context up.  Problems, batches and time steppers made in it stay usable (a
+ * stream passed in has to outlive them); the context itself goes with the last of them. */
 kfbi_status kfbi_ctx_destroy(kfbi_ctx* ctx);
 /* Block until all work enqueued on the context stream has finished. */
 kfbi_status kfbi_ctx_sync(kfbi_ctx* ctx);

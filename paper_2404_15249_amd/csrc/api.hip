@@ -70,7 +70,7 @@ kfbi_status scratch_on(int device, void** out) {
 }  // namespace
 
 struct kfbi_prob {
-    kfbi_ctx* ctx = nullptr;
+    CtxRef ctx;
     Plan plan;
     double kappa = 0, tol = 1e-10;
     int restart = 50, max_iter = 500;
@@ -733,9 +733,7 @@ kfbi_status kfbi_ctx_create(int device, void* hip_stream, kfbi_ctx** out) {
 }
 
 kfbi_status kfbi_ctx_destroy(kfbi_ctx* ctx) {
-    if (!ctx) return KFBI_OK;
-    if (ctx->own_stream) hipStreamDestroy(ctx->stream);
-    delete ctx;
+    ctx_release(ctx);
     return KFBI_OK;
 }
 

@@ -17,7 +17,7 @@
 using namespace kfbi;
 
 struct kfbi_prob3 {
-    kfbi_ctx* ctx = nullptr;
+    CtxRef ctx;
     Plan3Host plan;
     double kappa = 0, tol = 1e-10;
     int restart = 50, max_iter = 500;

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <string>
 
 #include <cmath>
@@ -199,4 +200,35 @@ struct kfbi_ctx {
     bool own_stream = false;
     size_t lds_max = 65536;
     int num_cu = 256;
+    std::atomic<int> users{1};          // its creator, and every object made in it
 };
+
+namespace kfbi {
+
+inline void ctx_release(kfbi_ctx* c) {
+    if (!c || --c->users) return;
+    if (c->own_stream) hipStreamDestroy(c->stream);
+    delete c;
+}
+
+// An object's hold on its context: a caller (a garbage collector that finalises a
+// cycle in any order) may destroy the context first.
+class CtxRef {
+public:
+    CtxRef() = default;
+    CtxRef(const CtxRef&) = delete;
+    CtxRef& operator=(const CtxRef&) = delete;
+    ~CtxRef() { ctx_release(c_); }
+    void operator=(kfbi_ctx* c) {
+        if (c) ++c->users;
+        ctx_release(c_);
+        c_ = c;
+    }
+    kfbi_ctx* operator->() const { return c_; }
+    operator kfbi_ctx*() const { return c_; }
+
+private:
+    kfbi_ctx* c_ = nullptr;
+};
+
+}  // namespace kfbi

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void k_gs_post(GsState S, const double* __rest
 }  // namespace
 
 struct kfbi_gs {
-    kfbi_ctx* ctx = nullptr;     // the caller's context: stream A (state, pointwise kernels, u)
+    CtxRef ctx;                  // the caller's context: stream A (state, pointwise kernels, u)
     kfbi_ctx* ctx2 = nullptr;    // the second stream (v's solve)
     hipEvent_t ev_pre = nullptr, ev_solved = nullptr;
     kfbi_prob* pu = nullptr;     // kappa_u = 2/(eps1 dt)
