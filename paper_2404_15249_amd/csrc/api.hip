@@ -427,7 +427,7 @@ void ensure_graph(kfbi_prob* p, int op, int k) {
 struct GmresRun {
     kfbi_prob* p = nullptr;
     int op = kOpD;
-    int max_steps = 0;           // slots of a run without second passes
+    long long max_steps = 0;     // slots of a run without second passes
     GmresDriver drv;
     bool finished = false;
 };
@@ -449,7 +449,7 @@ kfbi_status gmres_start(kfbi_prob* p, int op, const double* rhs, const double* p
     *r = GmresRun{};
     r->p = p;
     r->op = op;
-    r->max_steps = max_iter + 2 * ((max_iter + m - 1) / m);
+    r->max_steps = max_iter + 2 * (((long long)max_iter + m - 1) / m);
     r->drv.host = &p->host;
     r->drv.stream = s;
     r->drv.most = 2 * r->max_steps + 2;
@@ -463,7 +463,7 @@ kfbi_status gmres_drive(GmresRun& r) {
 
 // The slots of a run of fixed length, from replayed graphs of up to 32 (launched
 // directly while per-launch timing is on).
-kfbi_status gmres_fixed(GmresRun& r, int slots) {
+kfbi_status gmres_fixed(GmresRun& r, long long slots) {
     kfbi_prob* p = r.p;
     hipStream_t s = p->ctx->stream;
     while (slots > 0) {
@@ -496,7 +496,7 @@ kfbi_status run_gmres(kfbi_prob* p, int op, const double* rhs, const double* phi
     } else {
         if (!p->timing)                                     // recorded at the first run, not inside a later one
             for (int k = 0; k < kfbi_prob::kGraphSizes; ++k) ensure_graph(p, op, k);
-        for (int slots = r.max_steps, launched = 0, more = 1;; slots = more, more *= 2) {
+        for (long long slots = r.max_steps, launched = 0, more = 1;; slots = more, more *= 2) {
             if (launched >= r.drv.most) return set_err(KFBI_ERR_DEVICE, "a GMRES run did not end");
             if (kfbi_status e = gmres_fixed(r, slots)) return e;
             launched += slots;
@@ -555,7 +555,7 @@ kfbi_status iter_apply(kfbi_prob* p, const double* in, const int* skip, hipStrea
 }
 
 // Slot k of a run: an update of Richardson, half an iteration of BiCGSTAB.
-kfbi_status enqueue_iter_slot(kfbi_prob* p, int method, int k, hipStream_t s) {
+kfbi_status enqueue_iter_slot(kfbi_prob* p, int method, long long k, hipStream_t s) {
     const IterBufs& B = p->ib;
     if (kfbi_status e = iter_apply(p, method == kRich ? B.x : B.q, &B.st->done, s)) return e;
     HIP_TRY(launch_iter_step(method == kRich ? kIterRich : k % 2 ? kIterBicgFull : kIterBicgHalf, B, s));
@@ -596,7 +596,7 @@ kfbi_status run_iters(kfbi_prob* p, int method, const double* rhs, double* x, do
     GmresDriver drv;
     drv.host = &p->host;
     drv.stream = s;
-    drv.most = 2 * max_iter + 4;
+    drv.most = 2LL * max_iter + 4;
     for (bool over = false; !over;)
         if (kfbi_status e = drv.drive([&](hipStream_t st) { return enqueue_iter_slot(p, method, drv.launched - 1, st); },
                                       &over))

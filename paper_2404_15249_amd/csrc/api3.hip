@@ -131,7 +131,8 @@ kfbi_status run_gmres3(kfbi_prob3* p, const double* phi_in, double tol, int max_
                                nullptr, p->host.next_epoch(), s));
     // a slot per Arnoldi step and two per cycle (its end is found in one, the
     // residual takes the other); a nonzero guess and second Gram-Schmidt passes take more
-    const int m = std::max(1, p->restart), max_steps = max_iter + 2 * ((max_iter + m - 1) / m), most = 2 * max_steps + 2;
+    const int m = std::max(1, p->restart);
+    const long long max_steps = max_iter + 2 * (((long long)max_iter + m - 1) / m), most = 2 * max_steps + 2;
     if (tol > 0) {
         GmresDriver drv;
         drv.host = &p->host;
@@ -143,13 +144,13 @@ kfbi_status run_gmres3(kfbi_prob3* p, const double* phi_in, double tol, int max_
         const int B = kfbi_prob3::kGraphSteps;
         if (!p->gexec && !p->graph_failed)
             p->graph_failed = !record_graph(s, &p->gexec, [&](hipStream_t st) { return enqueue_steps3(p, B, st); });
-        for (int slots = max_steps, launched = 0, more = 1;; slots = more, more *= 2) {
+        for (long long slots = max_steps, launched = 0, more = 1;; slots = more, more *= 2) {
             if (launched >= most) return set_err(KFBI_ERR_DEVICE, "a GMRES run did not end");
             launched += slots;
             for (; slots > 0; slots -= B) {
                 if (p->gexec && slots >= B) {
                     HIP_TRY(hipGraphLaunch(p->gexec, s));
-                } else if (kfbi_status e = enqueue_steps3(p, std::min(B, slots), s)) {
+                } else if (kfbi_status e = enqueue_steps3(p, (int)std::min<long long>(B, slots), s)) {
                     return e;
                 }
             }

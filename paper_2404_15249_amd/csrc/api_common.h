@@ -70,15 +70,16 @@ struct GmresHost {
     unsigned next_epoch() { return epoch = epoch + 1 ? epoch + 1 : 1; }
     bool over() const { return __atomic_load_n(&pub->done, __ATOMIC_ACQUIRE) == epoch; }
     unsigned again() const { return __atomic_load_n(&pub->again, __ATOMIC_RELAXED); }
-    // slots of this run whose commit has run; *last: the next one is expected to end it
-    int committed(bool* last) const {
+    // slots of this run whose commit has run, of `launched`; *last: the next one is
+    // expected to end it
+    long long committed(long long launched, bool* last) const {
         const unsigned long long v = __atomic_load_n(&pub->prog, __ATOMIC_RELAXED);
         if ((unsigned)(v >> 32) != epoch) {
             *last = false;
             return 0;
         }
         *last = ((unsigned)v & kGmLastSlot) != 0;
-        return (int)((unsigned)v & (kGmLastSlot - 1));
+        return launched - (((unsigned)launched - (unsigned)v) & (kGmLastSlot - 1));
     }
 };
 
@@ -93,8 +94,9 @@ struct GmresHost {
 struct GmresDriver {
     GmresHost* host = nullptr;
     hipStream_t stream = nullptr;
-    int launched = 0, most = 0;                              // most: a bound no run reaches
-    int held = 0;                                            // the commit that announced the end (0: none)
+    // 64 bits: a cap of 2^30 iterations ("no cap") is a bound of more slots than an int holds
+    long long launched = 0, most = 0;                        // most: a bound no run reaches
+    long long held = 0;                                      // the commit that announced the end (0: none)
     unsigned again = 0;                                      // residuals seen before that
     unsigned spins = 0;
     bool idle = false;                                       // the stream was seen empty after the last launch
@@ -105,7 +107,7 @@ struct GmresDriver {
         if (*over) return KFBI_OK;
         bool last = false;
         const unsigned seen = host->again();                 // before the commit: a residual in between counts as new
-        int done = host->committed(&last);
+        long long done = host->committed(launched, &last);
         if (idle) {                                          // everything launched has run
             done = launched;
             held = 0;

@@ -77,7 +77,7 @@ __device__ inline void gm_publish_end(const GmresBufs& b) {
 // A slot's commit, told to the host; `last`: the next slot's residual is expected to
 // end the run.
 __device__ __forceinline__ void gm_publish_slot(const GmresBufs& b, bool last) {
-    const unsigned slot = (unsigned)(b.st->slot += 1);
+    const unsigned slot = (b.st->slot += 1) & (kGmLastSlot - 1);
     if (!b.pub) return;
     __hip_atomic_store(&b.pub->prog, (unsigned long long)b.st->epoch << 32 | (last ? kGmLastSlot : 0u) | slot,
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

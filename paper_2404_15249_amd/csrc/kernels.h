@@ -139,7 +139,7 @@ struct GmresState {
     double reorth;   // second Gram-Schmidt pass when |z| < reorth |w| (0: never, 1: always)
     double* xout;    // where the step launch that ends the run copies the iterate (null: nowhere)
     unsigned epoch;  // the run's number, for the host (GmresPub)
-    int slot;        // slots whose commit has run
+    unsigned slot;   // slots whose commit has run
 };
 
 constexpr int kIterNonfinite = -2;
@@ -152,7 +152,7 @@ struct IterState {
     int max_iter;
     int started;     // 1 once r0 is known
     int half;        // BiCGSTAB: 1 if it stopped half way through an iteration (one apply short)
-    int slot;        // slots whose step has run: Richardson's updates, BiCGSTAB's half iterations
+    unsigned slot;   // slots whose step has run: Richardson's updates, BiCGSTAB's half iterations
     double tol, r0, relres;
     double rho, alpha, omega;
     double gamma;    // Richardson relaxation
@@ -162,7 +162,7 @@ struct IterState {
 // What a run tells the host while it goes on (pinned, coherent host memory the
 // device writes; the host reads it without waiting for the stream).  prog: epoch in
 // the upper half; then kGmLastSlot when the commit found that the run ends at the
-// next slot's residual if that confirms it; slots committed in the low bits.
+// next slot's residual if that confirms it; slots committed in the 31 bits below (modulo).
 struct GmresPub {
     GmresState st;             // the final state, written before `done`
     unsigned long long prog;

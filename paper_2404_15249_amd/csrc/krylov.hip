@@ -52,8 +52,8 @@ __device__ __forceinline__ void iter_publish(const IterBufs& B, bool counts = tr
         B.pub->iter = *st;
         __hip_atomic_store(&B.pub->done, st->epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     } else if (counts) {
-        __hip_atomic_store(&B.pub->prog, (unsigned long long)st->epoch << 32 | (unsigned)st->slot, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&B.pub->prog, (unsigned long long)st->epoch << 32 | (st->slot & (kGmLastSlot - 1)),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
