@@ -427,7 +427,7 @@ void ensure_graph(kfbi_prob* p, int op, int k) {
 struct GmresRun {
     kfbi_prob* p = nullptr;
     int op = kOpD;
-    long long max_steps = 0;     // slots of a run without second passes
+    long long max_steps = 0;     // slots of a run of full cycles without second passes
     GmresDriver drv;
     bool finished = false;
 };
@@ -435,10 +435,10 @@ struct GmresRun {
 // Set up GMRES on K phi = ghat (K_D or K_N by op) from phi_in: ghat <- rhs
 // (null: already in p->gm.ghat), the state, and the first K input with its
 // spline and corrections, in one launch (gm_begin); xout (may be null)
-// receives the final iterate from the device.  The run takes a slot for each of at
-// most max_iter Arnoldi steps and two per cycle: the one in which the cycle's end is
-// found and the residual's.  A nonzero guess takes one residual slot more, at the
-// start, and every second Gram-Schmidt pass takes one.
+// receives the final iterate from the device.  A run of full cycles takes a slot for
+// each of at most max_iter Arnoldi steps and two per cycle (gmres_slot_bound); a nonzero
+// guess takes one residual slot more, at the start, and every second Gram-Schmidt pass
+// takes one.
 kfbi_status gmres_start(kfbi_prob* p, int op, const double* rhs, const double* phi_in, double tol, int max_iter,
                         double* xout, GmresRun* r) {
     hipStream_t s = p->ctx->stream;
@@ -452,7 +452,7 @@ kfbi_status gmres_start(kfbi_prob* p, int op, const double* rhs, const double* p
     r->max_steps = max_iter + 2 * (((long long)max_iter + m - 1) / m);
     r->drv.host = &p->host;
     r->drv.stream = s;
-    r->drv.most = 2 * r->max_steps + 2;
+    r->drv.most = gmres_slot_bound(max_iter);
     return KFBI_OK;
 }
 

@@ -132,7 +132,7 @@ kfbi_status run_gmres3(kfbi_prob3* p, const double* phi_in, double tol, int max_
     // a slot per Arnoldi step and two per cycle (its end is found in one, the
     // residual takes the other); a nonzero guess and second Gram-Schmidt passes take more
     const int m = std::max(1, p->restart);
-    const long long max_steps = max_iter + 2 * (((long long)max_iter + m - 1) / m), most = 2 * max_steps + 2;
+    const long long max_steps = max_iter + 2 * (((long long)max_iter + m - 1) / m), most = gmres_slot_bound(max_iter);
     if (tol > 0) {
         GmresDriver drv;
         drv.host = &p->host;

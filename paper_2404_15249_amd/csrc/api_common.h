@@ -83,6 +83,12 @@ struct GmresHost {
     }
 };
 
+// A bound of a GMRES run's slots.  A step takes one and its second Gram-Schmidt pass
+// another; a cycle takes two more, the one in which its end is found and the
+// residual's, and a cycle can be one step long: its estimate passes the tolerance where
+// the true residual, held up by rounding, does not.  Besides, the first residual.
+inline long long gmres_slot_bound(int max_iter) { return 4LL * max_iter + 8; }
+
 // Runs the slots of a run that may stop early: `enqueue` launches one slot on the
 // stream.  A slot is launched while the one before it runs, as soon as the commit
 // before that is known, and none beyond the one expected to end the run; so the
@@ -95,7 +101,7 @@ struct GmresDriver {
     GmresHost* host = nullptr;
     hipStream_t stream = nullptr;
     // 64 bits: a cap of 2^30 iterations ("no cap") is a bound of more slots than an int holds
-    long long launched = 0, most = 0;                        // most: a bound no run reaches
+    long long launched = 0, most = 0;                        // most: see gmres_slot_bound
     long long held = 0;                                      // the commit that announced the end (0: none)
     unsigned again = 0;                                      // residuals seen before that
     unsigned spins = 0;
