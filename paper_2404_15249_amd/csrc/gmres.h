@@ -25,7 +25,10 @@
 // Partial sums are added in a fixed order, so results do not depend on timing.
 // The state's two halves alternate: the step launch writes what the apply's
 // launches read (ph, converged, r0), the reduce launch what the step launch reads
-// (act); no launch reads what it writes, but for the commit's own counters.
+// (act); no launch reads what it writes, but for the commit's own counters.  So the
+// end of a run, which makes the other launches return, is written by the step launch
+// alone, also when the commit meets a NaN: a workgroup whose wavefronts read the flag
+// before and after the commit's write would part at the next barrier.
 #pragma once
 
 #include "device.h"
@@ -37,7 +40,7 @@ constexpr int kGmHalo = kSplineK + 1;    // reach of the spline filter on each s
 constexpr int kGmOwnSpline = kGmChunk - 2 * kGmHalo;   // places a step workgroup owns beside its halos
 
 enum GmPhase { kGmResidualPh = 0, kGmArnoldi = 1, kGmOver = 2 };
-enum GmAct { kGmNextVector = 0, kGmSecondPass = 1, kGmCycleEnd = 2, kGmResidual = 3, kGmDone = 4 };
+enum GmAct { kGmNextVector = 0, kGmSecondPass = 1, kGmCycleEnd = 2, kGmResidual = 3, kGmDone = 4, kGmFailed = 5 };
 
 // GmresState::converged when a norm of the iteration came out NaN or Inf
 constexpr int kGmNonfinite = -2;
@@ -286,9 +289,7 @@ __device__ inline void gm_commit(const GmresBufs& b, int M) {
         for (int i = 0; i < j; ++i) col[i] = rot[i];
         const double den = hypot(a, hn), gj = b.g[j];
         if (!isfinite(den) || !isfinite(gj)) {             // NaN or Inf in the data: stop here
-            st->converged = kGmNonfinite;
-            st->act = kGmDone;
-            gm_publish_end(b);
+            st->act = kGmFailed;
             s_end = -1;
         } else {
             const double c = den > 0.0 ? a / den : 1.0;
@@ -412,7 +413,7 @@ __device__ __forceinline__ GmStepIn gm_step_loads(const GmresBufs& b, int M, int
 // What a step does, the same in every workgroup of the launch.
 struct GmTodo {
     int act, j;              // act_j
-    bool done;               // the run has ended (with kGmResidual, or kGmDone)
+    bool done;               // the run has ended (with kGmResidual or kGmFailed), or had (kGmDone)
     int converged;           // then
     double rel, r0;
 };
@@ -420,6 +421,10 @@ __device__ __forceinline__ GmTodo gm_todo(const GmresBufs& b, const GmStepIn& u)
     const GmresState* st = b.st;
     GmTodo t{st->act, st->act_j, false, 0, 0.0, 0.0};
     if (t.act == kGmDone) t.done = true;
+    if (t.act == kGmFailed) {
+        t.done = true;
+        t.converged = kGmNonfinite;
+    }
     if (t.act != kGmResidual) return t;
     const double beta = sqrt(wave_sum(u.rr));
     if (!isfinite(beta)) {                                 // NaN or Inf in the data: stop here
@@ -483,6 +488,10 @@ __device__ __forceinline__ void gm_advance(const GmresBufs& b, const GmTodo& t) 
         st->second = t.act == kGmSecondPass;
     } else if (t.act == kGmCycleEnd) {
         st->ph = kGmResidualPh;
+    } else if (t.act == kGmFailed) {
+        st->converged = t.converged;
+        st->ph = kGmOver;
+        gm_publish_end(b);
     } else if (t.act == kGmResidual) {
         if (t.converged != kGmNonfinite) {
             st->res_applies += 1;
