@@ -114,7 +114,7 @@ kfbi_status interface3(kfbi_prob3* p, const double* phi, const double* f, const 
 kfbi_status enqueue_steps3(kfbi_prob3* p, int nsteps, hipStream_t s) {
     GmresBufs b = p->gm;
     for (int k = 0; k < nsteps; ++k) {
-        if (kfbi_status e = apply3(p, b.xcur, nullptr, &b, &b.st->converged, s)) return e;
+        if (kfbi_status e = apply3(p, b.xcur, nullptr, &b, &b.st->skip, s)) return e;
         HIP_TRY(launch_gmres_step(nullptr, p->M, b, s));
     }
     return KFBI_OK;

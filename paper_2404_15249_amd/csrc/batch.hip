@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kModeWaves * 64) void k_modes_b(const SlotDev* __re
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 item = w.items[it];
         const SlotDev& S = slots[item.x];
-        if (slot_done(S)) continue;
+        if (S.b.st->skip) continue;
         const DevPlan& p = S.p;
         switch (p.N) {
             case 64: modes_item<1>(p, S.corr_il, item.y, L, S.partial); break;

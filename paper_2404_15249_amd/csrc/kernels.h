@@ -129,6 +129,7 @@ struct GmresState {
     int it;          // K_D applications made by the Arnoldi process
     int first;       // 1 until r0 is known
     int converged;   // 1 converged, -1 iteration cap, -2 a NaN or Inf met (kGmNonfinite), 0 running
+    int skip;        // 1: the next apply is not used (the run is over, or see gm_advance in gmres.h)
     int cycles;
     double r0;
     double relres;
