@@ -349,7 +349,8 @@ kfbi_status kfbi_interface_solve_jumps(kfbi_prob* prob, const double* jq, const 
 typedef struct {
     int modes_per_group;  /* sparse fast solve: sine modes per workgroup, 1/2/4/8/16 */
     int modes_groups;     /* sparse fast solve: workgroups, ceil((n-1) / modes_per_group) (output only) */
-    int dst_cols;         /* column sine transforms: columns per workgroup, 4/8/16 (32/64 in FP64) */
+    int dst_cols;         /* column sine transforms: columns per workgroup, 4/8/16 (32/64 in FP64);
+                             FP64 transforms of grids up to 512^2 do not use it */
     double apply_us;      /* autotune output: mean K_D apply time with this shape */
     double grid_solve_us; /* autotune output: mean dense grid solve time (transforms + row solves) */
 } kfbi_tiles;
@@ -358,7 +359,8 @@ typedef struct {
  * candidate `reps` times, after one warm-up, with HIP events on the context
  * stream), keep the fastest and return it in *out.  Candidates: half, the same
  * and twice the default modes per workgroup (where the local data share holds
- * them); every valid column tile.  Overwrites the problem's scratch vectors
+ * them); column tiles of 4, 8 and 16 where they are valid and used (else the one in
+ * use stays).  FP64 needs memory for one grid meanwhile.  Overwrites the problem's scratch vectors
  * (not its results).  Synchronises.  reps <= 0: 10. */
 kfbi_status kfbi_prob_autotune(kfbi_prob* prob, int reps, kfbi_tiles* out);
 /* The shapes in use (the times are those of the last autotune, else 0). */

@@ -201,6 +201,15 @@ DevPlan op_view(const kfbi_prob* p, int op) { return plan_view(p, op == kOpN, op
 size_t cpx_bytes(int precision) { return precision == KFBI_FP64 ? 2 * sizeof(double) : 2 * sizeof(float); }
 
 
+// Alg. 4 on the full grid in FP64, from the user's grid f to the user's grid v.
+kfbi_status grid_solve_f64(kfbi_prob* p, const double* f, double* v) {
+    hipStream_t s = p->ctx->stream;
+    HIP_TRY(launch_dst_from_grid(p->dp, f, false, p->R, p->dstB, s));
+    HIP_TRY(launch_rows_solve(p->dp, p->R, s));
+    HIP_TRY(launch_dst_to_grid(p->dp, p->R, v, 2.0 / p->N, false, p->dstB, s));
+    return KFBI_OK;
+}
+
 // Alg. 4 on the full grid with FP32 transforms (KFBI_FP32_REFINED): solve
 // (L_h - kappa) A = R (R in the padded interior layout): an FP32 solve (FP32 column
 // transforms around the FP64 row solves) of R into A, then per refine step the FP32 solve
@@ -1178,15 +1187,8 @@ kfbi_status kfbi_fast_solve(kfbi_prob* p, const double* rhs, double* v) {
     if (kfbi_status s = check_ptr(rhs, "rhs")) return s;
     if (kfbi_status s = check_ptr(v, "v")) return s;
     HIP_TRY(hipSetDevice(p->ctx->device));
-    hipStream_t s = p->ctx->stream;
     p->modes_of = 0;
-    if (p->precision == KFBI_FP64) {
-        HIP_TRY(launch_dst_from_grid(p->dp, rhs, false, p->R, p->dstB, s));
-        HIP_TRY(launch_rows_solve(p->dp, p->R, s));
-        HIP_TRY(launch_dst_to_grid(p->dp, p->R, v, 2.0 / p->N, false, p->dstB, s));
-        return KFBI_OK;
-    }
-    return grid_solve_f32(p, rhs, v);
+    return p->precision == KFBI_FP64 ? grid_solve_f64(p, rhs, v) : grid_solve_f32(p, rhs, v);
 }
 
 kfbi_status kfbi_interface_solve(kfbi_prob* p, const double* phi, const double* ftilde, const double* f_gamma,
@@ -1458,9 +1460,8 @@ kfbi_status kfbi_prob_autotune(kfbi_prob* p, int reps, kfbi_tiles* out) {
     hipStream_t s = p->ctx->stream;
     HIP_TRY(hipStreamSynchronize(s));
     drop_graph(p);
-    // a zero density in tmpM with its spline in s2a: the values do not change the work
+    // a zero density in tmpM: the values do not change the work
     HIP_TRY(hipMemsetAsync(p->tmpM, 0, sizeof(double) * p->M, s));
-    HIP_TRY(hipMemsetAsync(p->s2a, 0, sizeof(double) * p->M, s));
     double best = 1e300;
     const int r0 = p->Rm;
     int br = r0;
@@ -1469,8 +1470,10 @@ kfbi_status kfbi_prob_autotune(kfbi_prob* p, int reps, kfbi_tiles* out) {
         p->Rm = Rm;
         p->G = (p->n + Rm - 1) / Rm;
         double us = 0;
-        if (kfbi_status e = time_us(s, reps, &us,
-                                    [&] { return sparse_apply(p, kOpD, p->tmpM, p->s2a, p->corr_call, p->s2b, nullptr, nullptr, s); })) {
+        if (kfbi_status e = time_us(s, reps, &us, [&] {                    // kfbi_apply's launches
+                HIP_TRY(launch_density(p->dp, p->tmpM, p->s2a, p->corr_call, nullptr, nullptr, s));
+                return sparse_apply(p, kOpD, p->tmpM, p->s2a, p->corr_call, p->s2b, nullptr, nullptr, s, true);
+            })) {
             p->Rm = r0;
             p->G = (p->n + r0 - 1) / r0;
             return e;
@@ -1483,20 +1486,37 @@ kfbi_status kfbi_prob_autotune(kfbi_prob* p, int reps, kfbi_tiles* out) {
     p->Rm = br;
     p->G = (p->n + br - 1) / br;
     p->tuned_apply_us = best;
+    // kfbi_fast_solve's launches, in place on a grid of zeros as a caller's (FP32: an
+    // interface solve's, in the problem's own); FP64 up to 512^2 no launch reads the tile,
+    // so the one in use stays
     double bestg = 1e300;
     int bb = p->dstB;
     p->modes_of = 0;
-    for (int B : {4, 8, 16}) {
+    const bool f64 = p->precision == KFBI_FP64;
+    const size_t grid_bytes = sizeof(double) * (p->N + 1) * (p->N + 1);
+    struct Grid {
+        double* v = nullptr;
+        ~Grid() {
+            if (v) hipFree(v);
+        }
+    } grid;
+    if (f64) {
+        if (hipMalloc((void**)&grid.v, grid_bytes) != hipSuccess) {
+            hipGetLastError();
+            return set_err(KFBI_ERR_OOM, "no memory for the autotuner's grid");
+        }
+        HIP_TRY(hipMemsetAsync(grid.v, 0, grid_bytes, s));
+    }
+    const bool sweep = !f64 || dst_grid_tiled(p->N);
+    for (int B : {4, 8, 16}) {                               // wider ones are valid up to 512^2 only
+        if (!sweep) B = p->dstB;
         if (!tiles_valid(p, p->Rm, B)) continue;
         p->dstB = B;
         double us = 0;
         if (kfbi_status e = time_us(s, reps, &us, [&] {
+                if (f64) return grid_solve_f64(p, grid.v, grid.v);
                 HIP_TRY(launch_fill_rhs(p->dp, nullptr, false, p->R, s));
-                if (p->precision != KFBI_FP64) return grid_solve_f32(p);
-                HIP_TRY(launch_dst_cols(p->dp, p->R, p->R, 1.0, p->dstB, s));
-                HIP_TRY(launch_rows_solve(p->dp, p->R, s));
-                HIP_TRY(launch_dst_cols(p->dp, p->R, p->R, 2.0 / p->N, p->dstB, s));
-                return KFBI_OK;
+                return grid_solve_f32(p);
             })) {
             p->dstB = bb;
             return e;
@@ -1505,6 +1525,7 @@ kfbi_status kfbi_prob_autotune(kfbi_prob* p, int reps, kfbi_tiles* out) {
             bestg = us;
             bb = B;
         }
+        if (!sweep) break;
     }
     p->dstB = bb;
     p->tuned_grid_us = bestg;

@@ -859,6 +859,7 @@ hipError_t short_launch(const Lines& g, const double* in, double* out, double al
 // and barriers of k_dst_cols took 11, at 512^2 8.5 against 12.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMmThreads = 512, kMmCols = 16;
+constexpr int kMmMax = 512;                                  // the most rows (see dst_dispatch)
 template <int C, int IO>
 __global__ __launch_bounds__(kMmThreads) void k_dst_mm(const double* __restrict__ sinq, const double* __restrict__ in,
                                                        double* __restrict__ out, double alpha,
@@ -957,7 +958,7 @@ hipError_t dst_dispatch(const Lines& g, const Tin* in, Tout* out, double alpha, 
     // (from) and 8.2 against 11.1 (to); at 1024^2 the products alone would take 15, the
     // whole tiled transform 15 to 18
     if constexpr (sizeof(T) == 8 && (IO == kFromGrid || IO == kToGrid)) {
-        if (g.N >= 128 && g.N <= 512) return mm_launch<IO>(g, in, out, alpha, s);
+        if (g.N >= 128 && g.N <= kMmMax) return mm_launch<IO>(g, in, out, alpha, s);
     }
     if (!dst_tile_ok(g.N, B, sizeof(cpx<T>), ~(size_t)0) || g.ld % B != 0) return hipErrorInvalidValue;
     switch (B) {
@@ -1006,9 +1007,7 @@ int dst_default_tile(int N, size_t cpx_bytes, size_t lds_max, long lines, int mi
     return 0;
 }
 
-hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, int B, hipStream_t s) {
-    return dst_dispatch<double, double, double>(grid2(p), in, out, alpha, nullptr, B, s);
-}
+bool dst_grid_tiled(int N) { return N > kMmMax; }
 
 hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, double* out, int B, hipStream_t s) {
     Lines g = grid2(p);

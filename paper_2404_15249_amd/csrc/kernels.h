@@ -254,17 +254,18 @@ hipError_t launch_reduce_interp(const DevPlan& p, JumpSrc js, const double* part
 // on the caller's grid
 hipError_t launch_interp_grid(const DevPlan& p, JumpSrc js, const double* V, bool user, double* out, hipStream_t s);
 hipError_t launch_fill_rhs(const DevPlan& p, const double* f, bool mask, double* R, hipStream_t s);
-// column sine transforms (dst.hip): FP64, and FP32 arithmetic reading an FP64
-// grid into FP32 storage or reading FP32 storage into an FP64 grid (written or
-// added to add, padded as well)
+// column sine transforms (dst.hip)
 // B: columns per workgroup (4, 8 or 16; 32 or 64 with FP64 pairs; see dst_tile_ok)
-hipError_t launch_dst_cols(const DevPlan& p, const double* in, double* out, double alpha, int B, hipStream_t s);
-// The same (FP64, alpha = 1) reading the user's grid f, zero outside Omega with mask;
-// and writing the user's grid u (the box's rows and columns zero), zero outside Omega
-// with mask.
+// FP64 (alpha = 1) reading the user's grid f, zero outside Omega with mask, into the
+// padded layout; and from there writing the user's grid u (the box's rows and columns
+// zero), zero outside Omega with mask.
 hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, double* out, int B, hipStream_t s);
 hipError_t launch_dst_to_grid(const DevPlan& p, const double* in, double* u, double alpha, bool mask, int B,
                               hipStream_t s);
+// whether the two above read B (up to 512 rows they do not)
+bool dst_grid_tiled(int N);
+// FP32 arithmetic reading an FP64 grid into FP32 storage, or FP32 storage into an FP64
+// grid (written, or added to add, padded as well)
 hipError_t launch_dst_cols_f32(const DevPlan& p, const double* in, float* out, double alpha, int B, hipStream_t s);
 hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* out, double alpha, const double* add,
                                     int B, hipStream_t s);
@@ -272,7 +273,7 @@ hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* o
 // (user) the user's grid.
 hipError_t launch_dst_residual_f32(const DevPlan& p, const double* r, bool user, const double* v, float* out, int B,
                                    hipStream_t s);
-// The same reading the user's grid f, and writing the user's grid u.
+// The FP32 transforms reading the user's grid f, and writing the user's grid u.
 hipError_t launch_dst_from_grid_f32(const DevPlan& p, const double* f, float* out, int B, hipStream_t s);
 hipError_t launch_dst_f32_to_grid(const DevPlan& p, const float* in, double* u, double alpha, const double* add, int B,
                                   hipStream_t s);
