@@ -82,7 +82,6 @@ struct kfbi_prob {
     std::vector<void*> allocs;
     size_t bytes = 0;
     // work buffers
-    double* corr = nullptr;      // I
     // corrections in the interleaved layout of the sparse sums, T x 64 each: the next
     // apply's of a GMRES run, which an admitted request's batch reads at its next step
     // whatever the problem is used for meanwhile; and those of the other calls, made and
@@ -93,7 +92,7 @@ struct kfbi_prob {
     double* R = nullptr;         // N N: right-hand side, modes or their solution (padded layout)
     unsigned modes_of = 0;       // number of the dense solve whose right-hand side's modes R holds (0: none; FP64)
     unsigned modes_number = 0;   // the last such number given
-    double* A = nullptr;         // N N
+    double* A = nullptr;         // N N: the solution (KFBI_FP32_REFINED)
     int precision = KFBI_FP64, refine = 0;
     float* X32 = nullptr;        // N N: FP32 transform storage (KFBI_FP32_REFINED)
     int dstB = 8;                // columns per workgroup of the column transforms
@@ -1023,9 +1022,9 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
         return fail(st);
     for (int w = 0; w <= kModeWaves; ++w) dp.sub_offv[w] = sub_off[w];
     const int M = p->M, m = p->restart;
-    if ((st = dev_alloc(p, &p->corr, p->I)) || (st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) ||
+    if ((st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) ||
         (st = dev_alloc(p, &p->corr_call, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
-        (st = dev_alloc(p, &p->R, (size_t)n * n)) || (st = dev_alloc(p, &p->A, (size_t)n * n)) ||
+        (st = dev_alloc(p, &p->R, (size_t)n * n)) ||
         (st = dev_alloc(p, &p->tmpM, M)) || (st = dev_alloc(p, &p->s2a, M)) || (st = dev_alloc(p, &p->s2b, M)) ||
         (st = dev_alloc(p, &p->d_flag, 2)) ||
         (st = dev_alloc(p, &p->gm.s2cur, M)) || (st = dev_alloc(p, &p->gm.V, (size_t)(m + 1) * M)) ||
@@ -1048,7 +1047,9 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     HIP_TRY(hipMemset(p->d_flag, 0, 2 * sizeof(int)));
     if ((st = p->host.alloc())) return fail(st);
     p->gm.pub = p->ib.pub = p->host.pub;
-    if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
+    if (p->precision == KFBI_FP32_REFINED &&
+        ((st = dev_alloc(p, &p->A, (size_t)n * n)) || (st = dev_alloc(p, &p->X32, (size_t)n * n))))
+        return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
     HIP_TRY(hipMemset(p->corr_call, 0, sizeof(double) * (size_t)dp.T * 64));
