@@ -60,16 +60,33 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
     for (int k = 0; k < S; ++k) c[k] = lo + (double)k * h;
     auto lin = [S](int i, int j, int k) { return ((size_t)k * S + j) * S + i; };
     P.inside.assign((size_t)S * S * S, 0);
+    // each coordinate's term once (three divisions a node took a tenth of the plan)
+    std::vector<double> tx(S), ty(S), tz(S);
+    for (int k = 0; k < S; ++k) {
+        tx[k] = c[k] * c[k] / a2;
+        ty[k] = c[k] * c[k] / b2;
+        tz[k] = c[k] * c[k] / c2;
+    }
     for (int k = 0; k < S; ++k)
         for (int j = 0; j < S; ++j)
+            for (int i = 0; i < S; ++i) P.inside[lin(i, j, k)] = tx[i] + ty[j] + tz[k] - 1.0 < 0.0 ? 1 : 0;
+    // whether a grid line along axis a has a node inside: line[a][t_hi * S + t_lo] (below)
+    std::vector<unsigned char> line[3];
+    for (auto& l : line) l.assign((size_t)S * S, 0);
+    for (int k = 0; k < S; ++k)
+        for (int j = 0; j < S; ++j) {
+            unsigned char any = 0;
             for (int i = 0; i < S; ++i) {
-                const double x = c[i], y = c[j], z = c[k];
-                const double F = x * x / a2 + y * y / b2 + z * z / c2 - 1.0;
-                P.inside[lin(i, j, k)] = F < 0.0 ? 1 : 0;
+                const unsigned char in = P.inside[lin(i, j, k)];
+                any |= in;
+                line[1][(size_t)k * S + i] |= in;
+                line[2][(size_t)j * S + i] |= in;
             }
+            line[0][(size_t)k * S + j] = any;
+        }
     for (int k = 0; k < S; ++k)
         for (int j = 0; j < S; ++j)
-            for (int i = 0; i < S; ++i)
+            for (int i = 0; line[0][(size_t)k * S + j] && i < S; ++i)
                 if (P.inside[lin(i, j, k)] && (i < 2 || j < 2 || k < 2 || i > N - 2 || j > N - 2 || k > N - 2))
                     fail3("the ellipsoid must keep two grid cells away from the box");
 
@@ -81,7 +98,7 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
         const double A = P.axes[ax];
         for (int t_hi = 0; t_hi < S; ++t_hi)
             for (int t_lo = 0; t_lo < S; ++t_lo)
-                for (int s = 0; s < N; ++s) {
+                for (int s = 0; line[ax][(size_t)t_hi * S + t_lo] && s < N; ++s) {
                     int ia[3], ib[3];
                     ia[ax] = s;
                     ia[o0] = t_lo;
@@ -149,14 +166,20 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
     // size 2.5 h (a point's neighbours lie in its cell and the 26 around it)
     const double rad = 0.5 * kFitRadiusNum * h;
     const int nc = (int)std::ceil((hi - lo) / rad) + 1;
-    std::unordered_map<long long, std::vector<int>> cells;
     auto cell_of = [&](const double* p, int a) { return (int)std::floor((p[a] - lo) / rad); };
-    auto cell_key = [&](int x, int y, int z) { return ((long long)z * nc + y) * nc + x; };
-    for (int m = 0; m < M; ++m)
-        cells[cell_key(cell_of(&P.pos[3 * m], 0), cell_of(&P.pos[3 * m], 1), cell_of(&P.pos[3 * m], 2))].push_back(m);
+    auto cell_key = [&](int x, int y, int z) { return ((size_t)z * nc + y) * nc + x; };
+    auto cell_at = [&](int m) {
+        return cell_key(cell_of(&P.pos[3 * m], 0), cell_of(&P.pos[3 * m], 1), cell_of(&P.pos[3 * m], 2));
+    };
+    // cell c's points, in order: cells[cell_first[c]] up to cells[cell_first[c + 1]]
+    // (counted into place: a hash map's 27 look-ups a point took a twelfth of the plan)
+    std::vector<int> cell_first((size_t)nc * nc * nc + 2, 0), cells(M);
+    for (int m = 0; m < M; ++m) cell_first[cell_at(m) + 2] += 1;
+    for (size_t k = 2; k < cell_first.size(); ++k) cell_first[k] += cell_first[k - 1];
+    for (int m = 0; m < M; ++m) cells[cell_first[cell_at(m) + 1]++] = m;
     P.fit_off.assign(1, 0);
     std::vector<int> near;
-    std::vector<double> dist;
+    std::vector<double> A, wts, B;
     for (int m = 0; m < M; ++m) {
         const double* pm = &P.pos[3 * m];
         auto dist_to = [&](int k) {
@@ -168,10 +191,10 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
         for (int z = cz - 1; z <= cz + 1; ++z)
             for (int y = cy - 1; y <= cy + 1; ++y)
                 for (int x = cx - 1; x <= cx + 1; ++x) {
-                    auto it = cells.find(cell_key(x, y, z));
-                    if (it == cells.end()) continue;
-                    for (int k : it->second)
-                        if (k != m && dist_to(k) <= rad) near.push_back(k);
+                    if (std::min({x, y, z}) < 0 || std::max({x, y, z}) >= nc) continue;
+                    const size_t cell = cell_key(x, y, z);
+                    for (int at = cell_first[cell]; at < cell_first[cell + 1]; ++at)
+                        if (cells[at] != m && dist_to(cells[at]) <= rad) near.push_back(cells[at]);
                 }
         if ((int)near.size() < kFitMin) {           // the nearest kFitMin, ties by index
             std::vector<int> all;
@@ -183,7 +206,9 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
         std::sort(near.begin(), near.end());
         const int K = (int)near.size();
         const double* G = &P.geo[(size_t)12 * m];
-        std::vector<double> A((size_t)K * 5), wts(K);
+        A.resize((size_t)K * 5);
+        wts.resize(K);
+        B.resize((size_t)5 * K);
         for (int e = 0; e < K; ++e) {
             const int k = near[e];
             const double rel[3] = {P.pos[3 * k] - pm[0], P.pos[3 * k + 1] - pm[1], P.pos[3 * k + 2] - pm[2]};
@@ -194,7 +219,7 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
             const double d = dist_to(k) / h;
             wts[e] = 1.0 / (1.0 + d * d);
         }
-        std::vector<double> Gm(25, 0.0), B((size_t)5 * K);
+        std::vector<double> Gm(25, 0.0);
         for (int a = 0; a < 5; ++a) {
             for (int b = 0; b < 5; ++b) {
                 double s = 0.0;
@@ -217,7 +242,10 @@ Plan3Host build_plan3(int N, double lo, double hi, const double axes_in[3]) {
     for (int k = 1; k < N; ++k)
         for (int j = 1; j < N; ++j)
             for (int i = 1; i < N; ++i) {
-                const unsigned char here = P.inside[lin(i, j, k)];
+                const unsigned char* at = &P.inside[lin(i, j, k)];
+                const unsigned char here = *at;
+                const size_t sy = S, sz = (size_t)S * S;
+                if (*(at - 1) + at[1] + *(at - sy) + at[sy] + *(at - sz) + at[sz] == 6 * here) continue;   // no arm
                 const int before = (int)P.arm_q.size();
                 for (int ax = 0; ax < 3; ++ax)
                     for (int step = -1; step <= 1; step += 2) {
