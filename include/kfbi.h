@@ -154,7 +154,7 @@ kfbi_status kfbi_apply(kfbi_prob* prob, const double* phi, double* out);
  * graph capture, tight serving loops, harnesses that forbid allocation): the
  * same kernels and the same result, with the apply's scratch (spline second
  * derivatives, corrections, partial sums: 256 + 8 M + 512 T + 8 G M bytes,
- * rounded up to 256-byte blocks) taken from a 32 MiB array of static device
+ * rounded up to 256-byte blocks) taken from an array of 32 MiB and 64 KiB of static device
  * memory that each GPU holds for the life of the process, in place of the
  * problem's workspace.  Allocates nothing and enqueues only: it does not wait,
  * so a NaN or Inf in phi leaves out untouched but is not reported (kfbi_apply

@@ -43,7 +43,9 @@ std::string& kfbi::last_error() {
 // holds its own copy for the life of the process; host code uses the address
 // hipGetSymbolAddress gives for it on that device (resolved once per device,
 // when a context is created there), never the array's name.
-constexpr size_t kNoAllocBytes = size_t(32) << 20;
+// 32 MiB, and what sixteen sub-tables of nodes may take beyond eight (up to 3 rows of 64
+// values each, and longer steps): at 4096^2 the partial sums of 4076 samples leave 2 KiB.
+constexpr size_t kNoAllocBytes = (size_t(32) << 20) + (size_t(64) << 10);
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
