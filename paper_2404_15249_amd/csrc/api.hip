@@ -110,7 +110,7 @@ struct kfbi_prob {
     int* d_flag = nullptr;       // 2: 1 when the density checked by a kfbi_apply call holds a NaN or Inf (calls in turn)
     unsigned n_apply = 0;        // kfbi_apply and kfbi_apply_neumann calls so far
     GmresBufs gm{};
-    GmresState st_host{};        // host copy of the GMRES state (stable address for async copies)
+    GmresState st_host{};        // an admitted request's state at the last poll
     GmresHost host;              // what the device tells of a run (gm.pub)
     // timing: a start and an end event for each of an apply's three launches,
     // read back by kfbi_apply_timing
@@ -119,16 +119,14 @@ struct kfbi_prob {
     std::vector<hipEvent_t> ev;
     int t_count = 0;
     double tuned_apply_us = 0, tuned_grid_us = 0;
-    // a captured batch of GMRES steps (apply + Arnoldi update) per operator
-    // (kOpD, kOpN), replayed per batch
-    // graphs of 32, 16, 8, 4, 2 and 1 steps (index k: kGraphSteps >> k
-    // steps), so a run launches exactly the steps it has left, in few graphs
+    // graphs of 32, 16, 8, 4, 2 and 1 GMRES slots (apply + step launch; index k:
+    // kGraphSteps >> k) per operator (kOpD, kOpN), so a run of fixed length launches
+    // exactly its slots, in few graphs
     static constexpr int kGraphSteps = 32;
     static constexpr int kGraphSizes = 6;
     hipGraphExec_t gexec[2][kGraphSizes] = {};
     bool graph_failed[2][kGraphSizes] = {};
-    // Richardson and BiCGSTAB (Table 2's alternatives): vectors, state, and a
-    // graph of a batch of iterations for each
+    // Richardson and BiCGSTAB (Table 2's alternatives): vectors and state
     IterBufs ib{};
 };
 
@@ -396,9 +394,6 @@ kfbi_status checked_apply(kfbi_prob* p, int op, const double* phi, double* out) 
     return KFBI_OK;
 }
 
-// Restarted GMRES on K_D phi = ghat (ghat already in p->gm.ghat).  Steps are
-// enqueued in batches; with tol > 0 the host polls the device state after each
-// batch, with tol <= 0 the work is fixed and the host waits once at the end.
 // One GMRES step slot is the apply and the step launch (gmres.h).  Outside timing
 // mode the step launch also makes the next apply's corrections, so the apply starts
 // from them; run_gmres makes the first slot's.  With timing on the corrections get

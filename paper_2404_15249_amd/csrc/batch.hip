@@ -1,7 +1,7 @@
 // Batched KFBI steps: many problems of uneven size advance through one launch
 // per stage of a GMRES iteration.  Every launch is persistent: a fixed grid
 // walks a device-resident work list of (slot, block) items, so the same
-// captured graph serves any mix of live slots, and a slot that has converged
+// recorded graph serves any mix of live slots, and a slot that has converged
 // turns its items into no-ops.  Each slot's arithmetic is split into the same
 // blocks whatever else is in the batch (one workgroup partial per mode block,
 // fixed reduction order), so its result does not depend on the mix.

@@ -106,8 +106,8 @@ constexpr int kMaxModesPerGroup = 8;
 constexpr int kMaxExtra = 126;      // extra pieces of long column halves (per pair of modes): what the LDS has room for at 2048
 // a node table entry: bit 31 j > N/2; 16-30 dest; 4-15 modes_row_place(min(j, N - j)); 1 last row of a step
 constexpr int kIlRow = 0xfff0, kIlLast = 2;
-constexpr int kMaxRestart = 64;
-constexpr int kMaxSamples = 12288; // boundary samples per problem (the GMRES step keeps one M-vector in LDS)   // GMRES restart length cap (LDS-resident Hessenberg)
+constexpr int kMaxRestart = 64;    // GMRES restart length cap (LDS-resident Hessenberg)
+constexpr int kMaxSamples = 12288; // boundary samples per problem (the one-workgroup steps of krylov.hip: twelve a thread)
 
 // Source of the interface jumps: either computed from densities on the
 // spline (phi, fgam may be null) or given directly (jq / jz, 6 per point).

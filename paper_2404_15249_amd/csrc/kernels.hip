@@ -1,10 +1,12 @@
 // HIP kernels of the KFBI hot path for gfx950 (MI355X), FP64.
 //
 // One K_D apply (Sec. 3, Alg. 1 steps 4-6) is three launches:
-//   k_correct  one thread per irregular node: jumps at the crossings on its
-//              arms (Alg. 2 line 4) and the correction of its right-hand side
-//              (Alg. 2 line 5).  For the double-layer apply F = 0, so the
-//              right-hand side of the corrected system is nonzero only here.
+//   k_density  the density's check and spline and, one thread per irregular
+//              node, the jumps at the crossings on its arms (Alg. 2 line 4) and
+//              the correction of its right-hand side (Alg. 2 line 5).  For the
+//              double-layer apply F = 0, so the right-hand side of the corrected
+//              system is nonzero only here.  Inside GMRES the step launch of
+//              gmres.h makes them for the next input.
 //   k_modes    the fast solver (Alg. 4) restricted to what the interpolation
 //              reads, R sine modes per workgroup.  Along y the right-hand side
 //              is expanded in sines; for a sparse right-hand side each
@@ -16,14 +18,15 @@
 //              the six stencil nodes of each boundary sample, already weighted
 //              by the interpolation weights, and written as the workgroup's row
 //              of partial sums.
-//   k_reduce_interp  one wavefront per sample: the partials summed in a fixed
-//              order plus the jump terms of the stencil nodes outside Omega
-//              (Alg. 3).
-// k_spline precomputes the spline second derivatives of the density (inside
-// GMRES the step launch of gmres.h does it for the next input).
-// The dense solve (volume potential, final solution) uses the same tridiagonal
-// solver on full rows (k_rows_solve), between two column sine transforms
-// (dst.hip); in the FP32 mode the transforms and the stored rows are FP32.
+//   k_reduce_interp  64 samples per workgroup of sixteen wavefronts: the partials
+//              summed in a fixed order plus the jump terms of the stencil nodes
+//              outside Omega (Alg. 3); inside GMRES k_reduce_gm, with the dots.
+// k_correct and k_spline are launches of their own where only one of them is
+// wanted (given jumps, the FP32 interface solves, timed applies).
+// The dense solve (volume potential, final solution) stands between two column
+// sine transforms (dst.hip): k_modes_dense, which adds the corrections' sums and
+// makes the samples' partials, or the rows' tridiagonal solves alone
+// (k_rows_solve; in the FP32 mode on FP32 rows).
 #include <hip/hip_runtime.h>
 
 #include "device.h"
