@@ -1022,6 +1022,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     if ((st = dev_alloc(p, &p->corr_il, (size_t)dp.T * 64)) ||
         (st = dev_alloc(p, &p->corr_call, (size_t)dp.T * 64)) || (st = dev_alloc(p, &p->partial, (size_t)p->Gcap * M)) ||
         (st = dev_alloc(p, &p->R, (size_t)n * n)) ||
+        (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->A, (size_t)n * n))) ||
         (st = dev_alloc(p, &p->tmpM, M)) || (st = dev_alloc(p, &p->s2a, M)) || (st = dev_alloc(p, &p->s2b, M)) ||
         (st = dev_alloc(p, &p->d_flag, 2)) ||
         (st = dev_alloc(p, &p->gm.s2cur, M)) || (st = dev_alloc(p, &p->gm.V, (size_t)(m + 1) * M)) ||
@@ -1044,9 +1045,7 @@ kfbi_status kfbi_prob_create(kfbi_ctx* ctx, const kfbi_desc* d, kfbi_prob** out)
     HIP_TRY(hipMemset(p->d_flag, 0, 2 * sizeof(int)));
     if ((st = p->host.alloc())) return fail(st);
     p->gm.pub = p->ib.pub = p->host.pub;
-    if (p->precision == KFBI_FP32_REFINED &&
-        ((st = dev_alloc(p, &p->A, (size_t)n * n)) || (st = dev_alloc(p, &p->X32, (size_t)n * n))))
-        return fail(st);
+    if (p->precision == KFBI_FP32_REFINED && (st = dev_alloc(p, &p->X32, (size_t)n * n))) return fail(st);
     // pad slots of the interleaved corrections stay zero for the life of the problem
     HIP_TRY(hipMemset(p->corr_il, 0, sizeof(double) * (size_t)dp.T * 64));
     HIP_TRY(hipMemset(p->corr_call, 0, sizeof(double) * (size_t)dp.T * 64));

@@ -1009,6 +1009,15 @@ int dst_default_tile(int N, size_t cpx_bytes, size_t lds_max, long lines, int mi
 
 bool dst_grid_tiled(int N) { return N > kMmMax; }
 
+// First of the launchers: their order is that of the kernels' code, and with the padded
+// FP64 forms behind the others an FP32 solve with one refinement at 2048^2 took 120.5 us in
+// place of 119.4.
+hipError_t launch_dst_lines(int N, int log2N, const double* sinq, double* a, double alpha, int B, int ld, int slices,
+                            size_t slice, const int* skip, hipStream_t s) {
+    return dst_dispatch<double, double, double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr, {}}, a, a, alpha, nullptr, B,
+                                                s);
+}
+
 hipError_t launch_dst_from_grid(const DevPlan& p, const double* f, bool mask, double* out, int B, hipStream_t s) {
     Lines g = grid2(p);
     g.mask8 = mask ? p.mask8 : nullptr;
@@ -1046,12 +1055,6 @@ hipError_t launch_dst_cols_f32_to64(const DevPlan& p, const float* in, double* o
 hipError_t launch_dst_f32_to_grid(const DevPlan& p, const float* in, double* u, double alpha, const double* add, int B,
                                   hipStream_t s) {
     return dst_dispatch<float, float, double, kToGrid>(grid2(p), in, u, alpha, add, B, s);
-}
-
-hipError_t launch_dst_lines(int N, int log2N, const double* sinq, double* a, double alpha, int B, int ld, int slices,
-                            size_t slice, const int* skip, hipStream_t s) {
-    return dst_dispatch<double, double, double>(Lines{N, log2N, sinq, ld, slices, slice, skip, nullptr, {}}, a, a, alpha, nullptr, B,
-                                                s);
 }
 
 }  // namespace kfbi
