@@ -487,8 +487,8 @@ __device__ __forceinline__ double gm_spline_s2(const double* __restrict__ taps, 
 // The state for the next slot, by thread 0 of the step launch's first workgroup.  The
 // next apply is not used (skip) when its input ends the cycle, by the restart length or
 // the iteration cap, or is to have a second pass first; the reduce launch only commits
-// it then.  At 4096^2 twelve steps in cycles of one went from 3.25 to 2.65 ms so, and
-// with reorth = 1 in one cycle from 2.58 to 1.98.
+// it then.  At 4096^2 twelve steps in cycles of one went from 3.25 to 2.63 ms so, and
+// with reorth = 1 in one cycle from 2.58 to 1.93.
 __device__ __forceinline__ void gm_advance(const GmresBufs& b, const GmTodo& t) {
     GmresState* st = b.st;
     if (t.act == kGmNextVector || t.act == kGmSecondPass) {
