@@ -400,8 +400,9 @@ kfbi_status checked_apply(kfbi_prob* p, int op, const double* phi, double* out) 
 // their own launch, timed as a stage of the apply.
 kfbi_status enqueue_steps(kfbi_prob* p, int op, int nsteps, hipStream_t s) {
     GmresBufs b = p->gm;
-    const int* skip = &b.st->skip;
     const bool fused = !p->timing;
+    // timed, an apply that is not used runs all the same: the averages are of whole launches
+    const int* skip = fused ? &b.st->skip : &b.st->converged;
     for (int k = 0; k < nsteps; ++k) {
         if (kfbi_status e = sparse_apply(p, op, b.xcur, b.s2cur, p->corr_il, b.w, skip, &p->gm, s, fused)) return e;
         if (fused) {
