@@ -1541,6 +1541,7 @@ struct kfbi_batch {
     std::vector<kfbi_prob*> slot;
     std::vector<size_t> slot_bytes;
     std::vector<SlotDev> h_slots;
+    std::vector<int> order;           // the live slots (batch_upload)
     char* d_work = nullptr;           // counts, slots and work lists (batch_work)
     size_t cap_work = 0;
     bool stale = false;               // the slots changed since the last upload
@@ -1627,15 +1628,16 @@ kfbi_status batch_upload(kfbi_batch* B) {
     int2* items = reinterpret_cast<int2*>(B->stage + kBatchHead + slots);
     int n = 0;
     counts[kBatchModes] = 0;
-    std::vector<int> order;
+    // room made at creation: a step or a poll allocates nothing on the host
+    std::vector<int>& order = B->order;
+    order.clear();
     for (int s = 0; s < B->max_slots; ++s)
         if (B->slot[s]) order.push_back(s);
     // the modes' items of the largest grids first: the longest, one a workgroup before
     // the shorter ones fill up
-    std::vector<int> by_size = order;
-    std::stable_sort(by_size.begin(), by_size.end(), [&](int a, int b) { return B->slot[a]->N > B->slot[b]->N; });
-    for (int s : by_size)
-        for (int b = 0; b < B->slot[s]->Gs; ++b) items[n++] = make_int2(s, b);
+    for (int N = kBatchNmax; N >= 64; N /= 2)
+        for (int s : order)
+            for (int b = 0; B->slot[s]->N == N && b < B->slot[s]->Gs; ++b) items[n++] = make_int2(s, b);
     counts[kBatchReduce] = n;
     for (int s : order) {
         items[n++] = make_int2(s, -1);                   // the commit, the longest of the slot's items, first
@@ -1709,6 +1711,7 @@ kfbi_status kfbi_batch_create(kfbi_ctx* ctx, int max_slots, int m_max, size_t bu
     B->slot.assign(max_slots, nullptr);
     B->slot_bytes.assign(max_slots, 0);
     B->h_slots.resize(max_slots);
+    B->order.reserve(max_slots);
     bool ok = hipEventCreateWithFlags(&B->up_ev, hipEventDisableTiming) == hipSuccess &&
               hipMalloc((void**)&B->d_states, sizeof(GmresState) * max_slots) == hipSuccess &&
               hipHostMalloc((void**)&B->h_states, sizeof(GmresState) * max_slots) == hipSuccess;
