@@ -649,11 +649,10 @@ __device__ inline void gm_corr_finish(const DevPlan& p, const GmCorr& k, const d
         if (ks[a] < 0) continue;
         const double d = ds[a];
         const PointGeom& g = k.gs[a];
-        // the segment's first knot in the window; a window longer than M holds
-        // some knots twice, and the copy inside the filter's reach of the
-        // window's ends has no second derivative: take the other
-        int l = ((g.seg - ch.z) % M + M) % M;
-        if (l < kGmHalo) l += M;
+        // the segment's first knot in the window: the first copy past the filter's reach
+        // of its start (a window longer than M holds knots several times, and those
+        // inside the reach of its ends have no second derivative)
+        const int l = kGmHalo + ((g.seg - ch.z - kGmHalo) % M + M) % M;
         // the spline on the segment, as spline_at computes it
         const double s0 = sw[l], s1 = sw[l + 1];
         const double y0 = xw[l], y1 = xw[l + 1], u = g.u, w = 1.0 - u;
